@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcachefocus.so")
-SOURCES = ["cf_api.hip", "cf_reposition.hip", "cf_attn_generic.hip", "cf_attn_mfma.hip", "cf_attn_reduce.hip", "cf_select.hip", "cf_calibrate.hip"]
+SOURCES = ["cf_api.hip", "cf_reposition.hip", "cf_attn_generic.hip", "cf_attn_mfma.hip", "cf_attn_plain.hip", "cf_attn_reduce.hip", "cf_select.hip", "cf_calibrate.hip"]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hidden",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -24,7 +24,7 @@ FLAGS = [
 RESOURCES = os.path.join(HERE, "kernel_resources.json")
 # kernels on the hot path that must keep everything in registers: a spill to scratch memory there
 # (a few lines of source can tip the register allocator over) costs far more than any tuning gains
-NO_SCRATCH = ("attn_tile_kernel", "attn_pipe_kernel", "attn_combine_kernel", "layer_epilogue_kernel", "reposition_kernel",
+NO_SCRATCH = ("attn_tile_kernel", "attn_plain_kernel", "attn_pipe_kernel", "attn_combine_kernel", "layer_epilogue_kernel", "reposition_kernel",
               "assemble_kernel")
 
 

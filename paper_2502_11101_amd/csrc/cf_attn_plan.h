@@ -361,5 +361,9 @@ void launch_pending_masses(const AttnArgs& a, const attn::Plan& p, hipStream_t s
 // The fused epilogue keeps every per-document row and the slot partials of a query in LDS: whether they fit.
 bool epilogue_fits(const attn::Plan& p, const cf_prune_step* prune);
 void launch_epilogue(const AttnArgs& a, const attn::Plan& p, const cf_prune_step* prune, hipStream_t s);
+// the same with slot partials in double (the path of cf_attn_plain.hip, which defers nothing)
+void launch_mass_f64(const AttnArgs& a, const attn::Plan& p, hipStream_t s);
+bool epilogue_fits_f64(const attn::Plan& p, const cf_prune_step* prune);
+void launch_epilogue_f64(const AttnArgs& a, const attn::Plan& p, const cf_prune_step* prune, hipStream_t s);
 
 }  // namespace cf

@@ -165,10 +165,11 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
 // column in groups of eight, each group from zero, then the group sums from zero.
 // Sum of n <= 8 values `pitch` floats apart, added in order from zero.  A full group's loads all go out
 // before the first add (a loop with a run-time bound would wait for each in turn).
-__device__ __forceinline__ float group_sum(const float* x, int pitch, int n) {
-    float gs = 0.f;
+template <class T>
+__device__ __forceinline__ T group_sum(const T* x, int pitch, int n) {
+    T gs = 0;
     if (n == 8) {
-        float v[8];
+        T v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = x[i * pitch];
 #pragma unroll
@@ -179,8 +180,9 @@ __device__ __forceinline__ float group_sum(const float* x, int pitch, int n) {
     return gs;
 }
 
+template <class T>
 struct MassScratch {
-    float colsum[kMaxSegs + 2 * kMaxSplit];
+    T colsum[kMaxSegs + 2 * kMaxSplit];
     int32_t sub_begin[2 * kMaxSplit + 1];
     float seg_mass[kMaxSegs];               // every entry's mass, for the per-document sums
 };
@@ -242,9 +244,9 @@ __device__ __forceinline__ void add_doc_scores_wave(int doc, float m, int n, int
 }
 constexpr int kMassStage = 4096;            // floats of partials staged per round by the stand-alone mass kernel
 
-template <class F>
-__device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTable& tbl, float* parts, float* stage,
-                                                     MassScratch* ms, F on_mass) {
+template <class T, class F>
+__device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTable& tbl, T* parts, T* stage,
+                                                     MassScratch<T>* ms, F on_mass) {
     const int tid = threadIdx.x, nthr = blockDim.x;
     const unsigned total = (unsigned)tbl.tile0[tbl.n];
     const unsigned nsub = (unsigned)(p.nsplit * p.groups);
@@ -254,18 +256,18 @@ __device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTab
         const int ngroups = (nparts + kGroup - 1) / kGroup;
         for (int idx = tid; idx < ngroups * p.slots; idx += nthr) {
             const int g = (int)div_exact((unsigned)idx, (unsigned)p.slots), k = idx - g * p.slots;
-            const float gs = group_sum(parts + g * kGroup * p.slots + k, p.slots, min(kGroup, nparts - g * kGroup));
+            const T gs = group_sum(parts + g * kGroup * p.slots + k, p.slots, min(kGroup, nparts - g * kGroup));
             parts[g * kGroup * p.slots + k] = gs;
         }
         __syncthreads();
         for (int k = tid; k < p.slots; k += nthr) {
-            float c = 0.f;
+            T c = 0;
             for (int g = 0; g < ngroups; ++g) c += parts[g * kGroup * p.slots + k];
             ms->colsum[k] = c;
         }
     } else {                                         // partials in memory: whole rows through LDS, many loads in flight
         const int rows = kMassStage / p.slots / kGroup * kGroup;   // slots <= kMassStage / kGroup: whole groups per round
-        float c[2] = {0.f, 0.f};                     // this thread's columns tid, tid + nthr (slots <= 2 * nthr)
+        T c[2] = {0, 0};                             // this thread's columns tid, tid + nthr (slots <= 2 * nthr)
         for (int r0 = 0; r0 < nparts; r0 += rows) {
             const int nr = min(rows, nparts - r0);
             __syncthreads();
@@ -286,13 +288,13 @@ __device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTab
     __syncthreads();
     for (int s = tid; s < tbl.n; s += nthr) {
         const int ts = tbl.tile0[s], te = tbl.tile0[s + 1];
-        float m = 0.f;
+        T m = 0;
         if (te > ts) {
             const int s0 = split_of(total, nsub, ts), s1 = split_of(total, nsub, te - 1);
             for (int sp = s0; sp <= s1; ++sp)
                 if (ms->sub_begin[sp] < ms->sub_begin[sp + 1]) m += ms->colsum[s + sp];
         }
-        on_mass(s, m);
+        on_mass(s, (float)m);
     }
 }
 
@@ -301,25 +303,25 @@ __device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTab
 // Returns lane s's segment mass (0 for lanes past the table).
 // BATCHED: a column of at most 40 parts is requested in one batch (clamped, unconditional loads) before the first
 // add, instead of a round trip — to memory or to LDS — per group of eight.
-template <bool BATCHED = false>
-__device__ __forceinline__ float segment_masses_wave(const Plan& p, const RegSegTable& t, const float* parts, int lane) {
+template <bool BATCHED = false, class T = float>
+__device__ __forceinline__ float segment_masses_wave(const Plan& p, const RegSegTable& t, const T* parts, int lane) {
     const unsigned total = (unsigned)t.total;
     const unsigned nsub = (unsigned)(p.nsplit * p.groups);
     const int nparts = p.units_per_b * p.nrb;
     constexpr int kGroup = 8;
-    float c[2] = {0.f, 0.f};                         // columns lane, lane + 64
+    T c[2] = {0, 0};                                 // columns lane, lane + 64
     int first_looped = 0;
     if constexpr (BATCHED) {
         constexpr int kBatch = 40;
         if (nparts <= kBatch) {
-            float v[kBatch];
-            const float* col = parts + min(lane, p.slots - 1);
+            T v[kBatch];
+            const T* col = parts + min(lane, p.slots - 1);
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) v[i] = col[min(i, nparts - 1) * p.slots];
             if (lane < p.slots) {
 #pragma unroll
                 for (int g0 = 0; g0 < kBatch; g0 += kGroup) {
-                    float gs = 0.f;                  // the same sums in the same order as group_sum
+                    T gs = 0;                        // the same sums in the same order as group_sum
 #pragma unroll
                     for (int i = 0; i < kGroup; ++i)
                         if (g0 + i < nparts) gs += v[g0 + i];
@@ -340,34 +342,36 @@ __device__ __forceinline__ float segment_masses_wave(const Plan& p, const RegSeg
     int s0 = 0, s1 = -1;
     if (has_tiles) { s0 = split_of(total, nsub, t.t0); s1 = split_of(total, nsub, t.t1 - 1); }
     const int span = wave_max_i32(s1 - s0);
-    float m = 0.f;
+    T m = 0;
     for (int d = 0; d <= span; ++d) {
         const int sp = s0 + d;
         const int slot = lane + sp;                                  // slot = segment + sub-split, < 128
-        const float c_lo = __shfl(c[0], slot & (kWave - 1)), c_hi = __shfl(c[1], slot & (kWave - 1));
+        const T c_lo = __shfl(c[0], slot & (kWave - 1)), c_hi = __shfl(c[1], slot & (kWave - 1));
         if (has_tiles && sp <= s1 && ((owns_mask >> sp) & 1)) m += slot < kWave ? c_lo : c_hi;
     }
-    return lane < t.n ? m : 0.f;
+    return lane < t.n ? (float)m : 0.f;
 }
 
 // Third kernel: per-segment attention mass, one workgroup per query; then S += mass.
 // Takes parts 0 .. n_parts - 1 of the ledger in order; the last one's masses go to `mass` when `write_mass` is set
 // (it is not when only layers that deferred their scores are taken in, ahead of the fused epilogue).
+// T: the type of the slot partials (double on the path that keeps fp32 precision throughout).
+template <class T>
 __global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a, Plan p, int n_parts, int write_mass) {
     __shared__ SegTable tbl;
-    __shared__ MassScratch ms;
-    __shared__ float stage[kMassStage];
+    __shared__ MassScratch<T> ms;
+    __shared__ T stage[kMassStage];
     const char* ws = static_cast<const char*>(a.workspace);
     const int b = __builtin_amdgcn_readfirstlane(blockIdx.x);
     const int tid = threadIdx.x;
     const int n_part_floats = p.units_per_b * p.nrb * p.slots;
     // part j of the ledger: the slot partials of the j-th layer still pending (the last one is this call's)
-    auto part = [&](int j) { return reinterpret_cast<const float*>(ws + p.off_masspart + (size_t)j * p.masspart_bytes) + (int64_t)b * n_part_floats; };
+    auto part = [&](int j) { return reinterpret_cast<const T*>(ws + p.off_masspart + (size_t)j * p.masspart_bytes) + (int64_t)b * n_part_floats; };
     if (p.slots <= 2 * kWave && a.seg_stride <= kWave && n_part_floats <= kMassStage) {
         // small query: the partials go to LDS in one batch (requested before the query's scalars are waited for),
         // then one wavefront finishes alone from a table in its registers — the same sums in the same order
-        float r_part[kMassStage / kThreads];
-        const float* mp0 = part(0);
+        T r_part[kMassStage / kThreads];
+        const T* mp0 = part(0);
 #pragma unroll
         for (int i = 0; i < kMassStage / kThreads; ++i) r_part[i] = mp0[min(tid + i * kThreads, n_part_floats - 1)];   // unconditional
         const QueryHead qh = load_query_head(a, b, tid & (kWave - 1));
@@ -380,12 +384,12 @@ __global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a, Plan p,
         for (int j = 0; j < n_parts; ++j) {
             if (j > 0) {
                 __syncthreads();                     // the staged part has been read
-                const float* mp = part(j);
+                const T* mp = part(j);
                 for (int i = tid; i < n_part_floats; i += kThreads) stage[i] = mp[i];
                 __syncthreads();
             }
             if (tid < kWave) {
-                const float m = segment_masses_wave(p, rtbl, stage, tid);
+                const float m = segment_masses_wave<false>(p, rtbl, stage, tid);
                 if (write_mass && j == n_parts - 1 && tid < rtbl.n) a.mass[(int64_t)b * a.seg_stride + tid] = m;
                 if (a.score_accum)                   // qh.seg is this lane's entry
                     add_doc_scores_wave(qh.seg.doc, m, rtbl.n, tid, a.score_accum + (int64_t)b * a.score_stride, a.score_stride);
@@ -397,7 +401,7 @@ __global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a, Plan p,
     build_table(a, qh, &tbl, p.tile);
     for (int j = 0; j < n_parts; ++j) {
         const bool last = write_mass && j == n_parts - 1;
-        segment_masses_block(p, tbl, const_cast<float*>(part(j)), stage, &ms, [&](int s, float m) {
+        segment_masses_block(p, tbl, const_cast<T*>(part(j)), stage, &ms, [&](int s, float m) {
             if (last) a.mass[(int64_t)b * a.seg_stride + s] = m;
             ms.seg_mass[s] = m;
         });
@@ -489,11 +493,12 @@ struct PruneArgs {
 // partial masses are fetched into LDS in one batch at the start: the ranking, the allocation and the
 // table rebuild then run out of LDS with workgroup barriers between them instead of a round trip
 // through memory per stage, and the results are written back at the end.
-// Dynamic LDS: 44*stride + 4*parts*slots bytes; larger problems take the stand-alone kernels.
+// Dynamic LDS: 44*stride + sizeof(T)*parts*slots bytes; larger problems take the stand-alone kernels.
+template <class T>
 __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a, Plan p, PruneArgs pr) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
     __shared__ SegTable tbl;
-    __shared__ MassScratch ms;
+    __shared__ MassScratch<T> ms;
     __shared__ int s_int[6];
     __shared__ uint4 s_bcast[kWave];
 
@@ -507,7 +512,7 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     int32_t* l_keep = l_cand + stride;
     int32_t* l_start = l_keep + stride;
     int32_t* l_order = l_start + stride;
-    float* l_part = reinterpret_cast<float*>(l_order + stride);
+    T* l_part = reinterpret_cast<T*>(dyn_smem + (((size_t)44 * stride + 7) & ~(size_t)7));
 
     const char* ws = static_cast<const char*>(a.workspace);
     const int b = __builtin_amdgcn_readfirstlane(blockIdx.x);
@@ -515,7 +520,7 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     const int nparts = p.units_per_b * p.nrb;
     // this call's own slot partials are part n_pending of the ledger (earlier parts, of layers that deferred their
     // scores, have been taken in by the mass kernel before this one)
-    const float* mp_b = reinterpret_cast<const float*>(ws + p.off_masspart + (size_t)a.n_pending * p.masspart_bytes) + (int64_t)b * nparts * p.slots;
+    const T* mp_b = reinterpret_cast<const T*>(ws + p.off_masspart + (size_t)a.n_pending * p.masspart_bytes) + (int64_t)b * nparts * p.slots;
     // The first batch of row loads, the slot partials and the query's scalars all go out before anything is waited
     // for; every load is unconditional (a clamped, in-bounds index: threads past the end re-read the last element and
     // drop it), since a load inside a branch is waited for before the branch ends.
@@ -527,7 +532,7 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     const int32_t r_start = pr.new_start[off + row_i], r_order = pr.order[off + row_i];
     constexpr int kPartRegs = 4;                     // slot partials per thread fetched with the first batch
     const int n_part_floats = nparts * p.slots;
-    float r_part[kPartRegs];
+    T r_part[kPartRegs];
 #pragma unroll
     for (int i = 0; i < kPartRegs; ++i) r_part[i] = mp_b[min(tid + i * kEpiThreads, n_part_floats - 1)];
     const int n_cand = pr.n_cand[b];
@@ -559,13 +564,13 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
         __syncthreads();                             // publishes the rows above
         if (tid >= kWave) return;
         const RegSegTable rtbl = build_reg_table(a, qh, tid, p.tile);
-        const float m = segment_masses_wave(p, rtbl, l_part, tid);
+        const float m = segment_masses_wave<false>(p, rtbl, l_part, tid);
         if (tid < rtbl.n) a.mass[(int64_t)b * a.seg_stride + tid] = m;
         add_doc_scores_wave(qh.seg.doc, m, rtbl.n, tid, l_score, stride);       // qh.seg is this lane's entry
         __syncthreads();
     } else {
         build_table(a, qh, &tbl, p.tile);            // its barriers also publish the rows above
-        segment_masses_block(p, tbl, l_part, nullptr, &ms, [&](int s, float m) {
+        segment_masses_block<T>(p, tbl, l_part, nullptr, &ms, [&](int s, float m) {
             a.mass[(int64_t)b * a.seg_stride + s] = m;
             ms.seg_mass[s] = m;
         });
@@ -624,20 +629,25 @@ static void launch_masses(const AttnArgs& a, const Plan& p, int n_parts, int wri
     if (n_parts > 1 && pending_fit_combine(a, p))
         hipLaunchKernelGGL(pending_masses_kernel, dim3((unsigned)a.batch), dim3(kWave * n_parts), 0, s, a, p, n_parts, write_mass);
     else
-        hipLaunchKernelGGL(attn_mass_kernel, dim3((unsigned)a.batch), dim3(kThreads), 0, s, a, p, n_parts, write_mass);
+        hipLaunchKernelGGL(attn_mass_kernel<float>, dim3((unsigned)a.batch), dim3(kThreads), 0, s, a, p, n_parts, write_mass);
 }
 
 void launch_mass(const AttnArgs& a, const Plan& p, hipStream_t s) { launch_masses(a, p, a.n_pending + 1, 1, s); }
 
 void launch_pending_masses(const AttnArgs& a, const Plan& p, hipStream_t s) { launch_masses(a, p, a.n_pending, 0, s); }
 
-static size_t epilogue_lds_bytes(const Plan& p, const cf_prune_step* prune) {
-    return (size_t)44 * prune->stride + (size_t)4 * p.units_per_b * p.nrb * p.slots;
+void launch_mass_f64(const AttnArgs& a, const Plan& p, hipStream_t s) {
+    hipLaunchKernelGGL(attn_mass_kernel<double>, dim3((unsigned)a.batch), dim3(kThreads), 0, s, a, p, 1, 1);
 }
 
-bool epilogue_fits(const Plan& p, const cf_prune_step* prune) { return epilogue_lds_bytes(p, prune) <= 60 * 1024; }
+static size_t epilogue_lds_bytes(const Plan& p, const cf_prune_step* prune, size_t elem) {
+    return (((size_t)44 * prune->stride + 7) & ~(size_t)7) + elem * p.units_per_b * p.nrb * p.slots;
+}
 
-void launch_epilogue(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
+bool epilogue_fits(const Plan& p, const cf_prune_step* prune) { return epilogue_lds_bytes(p, prune, sizeof(float)) <= 60 * 1024; }
+bool epilogue_fits_f64(const Plan& p, const cf_prune_step* prune) { return epilogue_lds_bytes(p, prune, sizeof(double)) <= 60 * 1024; }
+
+static PruneArgs prune_args(const cf_prune_step* prune) {
     PruneArgs pr;
     pr.enabled = 1; pr.keep = prune->keep; pr.strategy = prune->strategy; pr.force_n_reuse = prune->force_n_reuse;
     pr.normalise_by_len = prune->normalise_by_len; pr.stride = prune->stride; pr.pos_begin = prune->pos_begin;
@@ -646,7 +656,17 @@ void launch_epilogue(const AttnArgs& a, const Plan& p, const cf_prune_step* prun
     pr.n_cand = prune->n_cand; pr.keep_idx = prune->keep_idx; pr.n_keep = prune->n_keep;
     pr.new_start = prune->new_start; pr.q_start = prune->q_start; pr.n_reuse = prune->n_reuse;
     pr.order = prune->order; pr.next_segs = prune->next_segs; pr.next_n_seg = prune->next_n_seg;
-    hipLaunchKernelGGL(layer_epilogue_kernel, dim3(a.batch), dim3(kEpiThreads), epilogue_lds_bytes(p, prune), s, a, p, pr);
+    return pr;
+}
+
+void launch_epilogue(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
+    hipLaunchKernelGGL(layer_epilogue_kernel<float>, dim3(a.batch), dim3(kEpiThreads), epilogue_lds_bytes(p, prune, sizeof(float)), s, a, p,
+                       prune_args(prune));
+}
+
+void launch_epilogue_f64(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
+    hipLaunchKernelGGL(layer_epilogue_kernel<double>, dim3(a.batch), dim3(kEpiThreads), epilogue_lds_bytes(p, prune, sizeof(double)), s, a,
+                       p, prune_args(prune));
 }
 
 }  // namespace cf
