@@ -1,9 +1,11 @@
-"""ctypes binding of libcachefocus.so: one Python function per C entry point, same names.
+"""Binding of libcachefocus.so: one Python function per C entry point, same names.
 
 Argument marshalling only: tensors are torch CUDA tensors (PyTorch is used for device
 memory and streams, nothing else), pointers are taken with ``data_ptr()``, the current
-torch stream is passed unless one is given.  There is no fallback: if the shared library
-has not been built, loading raises.
+torch stream is passed unless one is given.  The calls made once per layer or token go through
+_cfcall.so (csrc/cf_pycall.cpp), which does the marshalling in native code; the others, and the handle that
+``load()`` returns, through ctypes.  There is no fallback: if the shared libraries
+have not been built, loading raises.
 """
 
 from __future__ import annotations
@@ -64,6 +66,17 @@ class CacheFocusError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def _call():
+    """The native marshalling module; raises if the libraries have not been built."""
+    global _native
+    if _native is None:
+        load()
+        from . import _cfcall
+        _native = _cfcall
+    return _native
 
 
 def load() -> C.CDLL:
@@ -196,8 +209,10 @@ def cf_last_error() -> str:
 
 def cf_reposition_keys(desc, k_in, k_out, segs, n_seg: int, n_store_tokens: int, max_seg_len: int,
                        dev_flag=None, stream=None) -> None:
-    _check(load().cf_reposition_keys(C.byref(desc), _ptr(k_in), _ptr(k_out), _ptr(segs), n_seg, n_store_tokens,
-                                     max_seg_len, _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).reposition_keys(
+        desc, k_in, k_out, segs, n_seg, n_store_tokens, max_seg_len, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_prefill_workspace_bytes(desc, batch: int, max_tq: int, seg_stride: int, max_kv_tokens: int) -> int:
@@ -208,21 +223,24 @@ def cf_prefill_attention(desc, q, q_off, q_stored_start: int, q_new_start, k_sto
                          k_self, v_self, segs, n_seg, seg_stride: int, batch: int, max_tq: int,
                          max_kv_tokens: int, out, mass, score_accum, score_stride: int, workspace,
                          workspace_bytes: int, dev_flag=None, stream=None) -> None:
-    _check(load().cf_prefill_attention(
-        C.byref(desc), _ptr(q), _ptr(q_off), q_stored_start, _ptr(q_new_start), _ptr(k_store), _ptr(v_store),
-        n_store_tokens, _ptr(k_self), _ptr(v_self), _ptr(segs), _ptr(n_seg), seg_stride, batch, max_tq,
-        max_kv_tokens, _ptr(out), _ptr(mass), _ptr(score_accum), score_stride, _ptr(workspace), workspace_bytes,
-        _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).prefill_attention(
+        desc, q, q_off, q_stored_start, q_new_start, k_store, v_store, n_store_tokens, k_self, v_self,
+        segs, n_seg, seg_stride, batch, max_tq, max_kv_tokens, out, mass, score_accum, score_stride, workspace,
+        workspace_bytes, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_prefill_attention_static(desc, q, q_off, q_stored_start: int, q_new_start, k_store, v_store, n_store_tokens: int,
                                 k_self, v_self, segs, n_seg, seg_stride: int, batch: int, max_tq: int,
                                 max_kv_tokens: int, out, mass, score_accum, score_stride: int, dev_flag=None,
                                 stream=None) -> None:
-    _check(load().cf_prefill_attention_static(
-        C.byref(desc), _ptr(q), _ptr(q_off), q_stored_start, _ptr(q_new_start), _ptr(k_store), _ptr(v_store),
-        n_store_tokens, _ptr(k_self), _ptr(v_self), _ptr(segs), _ptr(n_seg), seg_stride, batch, max_tq,
-        max_kv_tokens, _ptr(out), _ptr(mass), _ptr(score_accum), score_stride, _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).prefill_attention_static(
+        desc, q, q_off, q_stored_start, q_new_start, k_store, v_store, n_store_tokens, k_self, v_self,
+        segs, n_seg, seg_stride, batch, max_tq, max_kv_tokens, out, mass, score_accum, score_stride, dev_flag,
+        stream)
+    if status:
+        _check(status)
 
 
 def make_prune_step(keep: int, strategy: int, force_n_reuse: int, normalise_by_len: bool, stride: int, pos_begin: int,
@@ -239,41 +257,48 @@ def cf_prefill_layer(desc, q, q_off, q_stored_start: int, q_new_start, k_store, 
                      mass, score_accum, score_stride: int, workspace, workspace_bytes: int,
                      prune: Optional[cf_prune_step] = None, dev_flag=None, stream=None, n_pending: int = 0,
                      defer: bool = False) -> None:
-    _check(load().cf_prefill_layer(
-        C.byref(desc), _ptr(q), _ptr(q_off), q_stored_start, _ptr(q_new_start), _ptr(k_store), _ptr(v_store),
-        n_store_tokens, _ptr(k_self), _ptr(v_self), _ptr(segs), _ptr(n_seg), seg_stride, batch, max_tq,
-        max_kv_tokens, _ptr(out), _ptr(mass), _ptr(score_accum), score_stride, _ptr(workspace), workspace_bytes,
-        C.byref(prune) if prune is not None else None, n_pending, 1 if defer else 0, _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).prefill_layer(
+        desc, q, q_off, q_stored_start, q_new_start, k_store, v_store, n_store_tokens, k_self, v_self,
+        segs, n_seg, seg_stride, batch, max_tq, max_kv_tokens, out, mass, score_accum, score_stride, workspace,
+        workspace_bytes, prune, n_pending, 1 if defer else 0, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_assemble_cache(desc, k_store, v_store, n_store_tokens: int, k_self, v_self, q_off, segs, n_seg, seg_stride: int,
                       batch: int, max_tq: int, max_seg_len: int, final_off, final_capacity: int, final_token_stride: int,
                       final_head_stride: int, k_final, v_final, final_len, final_pos=None, dev_flag=None,
                       stream=None) -> None:
-    _check(load().cf_assemble_cache(
-        C.byref(desc), _ptr(k_store), _ptr(v_store), n_store_tokens, _ptr(k_self), _ptr(v_self), _ptr(q_off), _ptr(segs),
-        _ptr(n_seg), seg_stride, batch, max_tq, max_seg_len, _ptr(final_off), final_capacity, final_token_stride,
-        final_head_stride, _ptr(k_final), _ptr(v_final), _ptr(final_len), _ptr(final_pos), _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).assemble_cache(
+        desc, k_store, v_store, n_store_tokens, k_self, v_self, q_off, segs, n_seg, seg_stride, batch, max_tq, max_seg_len,
+        final_off, final_capacity, final_token_stride, final_head_stride, k_final, v_final, final_len, final_pos, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_prune_topk(score, len_, cand, n_cand, keep: int, batch: int, stride: int, keep_idx, n_keep,
                   dev_flag=None, stream=None) -> None:
-    _check(load().cf_prune_topk(_ptr(score), _ptr(len_), _ptr(cand), _ptr(n_cand), keep, batch, stride,
-                                _ptr(keep_idx), _ptr(n_keep), _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).prune_topk(
+        score, len_, cand, n_cand, keep, batch, stride, keep_idx, n_keep, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_assign_positions(len_, ranked, n_ranked, batch: int, stride: int, pos_begin: int, pos_end: int,
                         strategy: int, force_n_reuse: int, new_start, q_start, n_reuse, order,
                         dev_flag=None, stream=None) -> None:
-    _check(load().cf_assign_positions(_ptr(len_), _ptr(ranked), _ptr(n_ranked), batch, stride, pos_begin, pos_end,
-                                      strategy, force_n_reuse, _ptr(new_start), _ptr(q_start), _ptr(n_reuse),
-                                      _ptr(order), _ptr(dev_flag), _stream(stream)))
+    status = (_native or _call()).assign_positions(
+        len_, ranked, n_ranked, batch, stride, pos_begin, pos_end, strategy, force_n_reuse, new_start, q_start, n_reuse,
+        order, dev_flag, stream)
+    if status:
+        _check(status)
 
 
 def cf_gather_segments(doc_tok_offset, len_, order, n_order, new_start, q_start, q_off, batch: int, stride: int,
                        prefix_len: int, doc_stored_start: int, q_stored_start: int, segs, n_seg, seg_stride: int,
                        dev_flag=None, stream=None) -> None:
-    _check(load().cf_gather_segments(_ptr(doc_tok_offset), _ptr(len_), _ptr(order), _ptr(n_order), _ptr(new_start),
-                                     _ptr(q_start), _ptr(q_off), batch, stride, prefix_len, doc_stored_start,
-                                     q_stored_start, _ptr(segs), _ptr(n_seg), seg_stride, _ptr(dev_flag),
-                                     _stream(stream)))
+    status = (_native or _call()).gather_segments(
+        doc_tok_offset, len_, order, n_order, new_start, q_start, q_off, batch, stride, prefix_len, doc_stored_start,
+        q_stored_start, segs, n_seg, seg_stride, dev_flag, stream)
+    if status:
+        _check(status)

@@ -1,4 +1,4 @@
-"""Builds libcachefocus.so in-tree with hipcc for gfx950.
+"""Builds libcachefocus.so in-tree with hipcc for gfx950, and _cfcall.so, the native half of binding.py, beside it.
 
 Usage: python -m paper_2502_11101_amd.build
 """
@@ -10,11 +10,13 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcachefocus.so")
+PYCALL = os.path.join(HERE, "_cfcall.so")
 SOURCES = ["cf_api.hip", "cf_reposition.hip", "cf_attn_generic.hip", "cf_attn_mfma.hip", "cf_attn_plain.hip", "cf_attn_reduce.hip", "cf_select.hip", "cf_calibrate.hip"]
 FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fvisibility=hidden",
@@ -48,6 +50,12 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
             _wait(procs, verbose, usage)
     _wait(procs, verbose, usage)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "cf_pycall.cpp"), "-L", HERE, "-l:libcachefocus.so",
+           "-Wl,-rpath,$ORIGIN", "-o", PYCALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

@@ -665,7 +665,11 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
     // the attention kernel's launch carries the profiling aid's start/stop events (null when it is off)
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     profile_kernel_pair(&ev_start, &ev_stop);
-#define CF_LAUNCH_TIMED(KERNEL, GRID, BLOCK) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p)
+#define CF_LAUNCH_TIMED(KERNEL, GRID, BLOCK)                                                          \
+    do {                                                                                              \
+        if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
+        else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
+    } while (0)
 #define CF_LAUNCH_DT(DT)                                                                                                       \
     if (p.producers == 0) {                                                                                                    \
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, true>), grid3, dim3(2 * kThreads));                            \

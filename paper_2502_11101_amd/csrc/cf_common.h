@@ -35,7 +35,7 @@ void set_error(const char* fmt, ...);
 // the start/stop events of the attention kernel's next launch while cf_profile_kernel_events is on (else both null)
 void profile_kernel_pair(hipEvent_t* start, hipEvent_t* stop);
 cf_status check_desc(const cf_layer_desc* d);
-void fill_rope_freq(const cf_layer_desc* d, RopeFreq* f);
+const RopeFreq& rope_freq(const cf_layer_desc* d);
 size_t elem_size(int32_t dtype);
 
 #define CF_REQUIRE(cond, status, ...)      \
