@@ -145,9 +145,11 @@ template <int U> struct Walk {
     }
 };
 
-// grid = (n_seg, pieces of a segment); block = 256 threads, U items each.  Bound by HBM, one read and one write of
-// K; every load of a piece is requested before the cos/sin table is worked out, which hides behind them.
-template <int DT, int PAIRING, int U>
+// grid = (n_seg, pieces of a segment); block = 256 threads, an item each.  Bound by HBM, one read and one write of K;
+// a block's loads are requested before the cos/sin table is worked out, which hides behind them.  One item per thread:
+// two or four were slower at every size (30 documents x 160 tokens of 32 heads, bf16: 13.8 us against 14.5 and 14.3, 5.7 TB/s
+// read and written; 16 fp32 documents of 50-79 tokens 8.8 against 9.5 and 10.0).
+template <int DT, int PAIRING>
 __global__ __launch_bounds__(kThreads) void reposition_kernel(
     const void* k_in, void* k_out, const cf_segment* __restrict__ segs,
     int64_t n_store_tokens, int n_kv_heads, int head_dim, int64_t tok_stride, int64_t head_stride, RopeFreq freq,
@@ -165,67 +167,46 @@ __global__ __launch_bounds__(kThreads) void reposition_kernel(
     }
     const int items_per_head = half / 8;                 // head_dim % 16 == 0 checked on the host
     const bool by_head = head_stride > tok_stride;
-    Walk<U> walk(seg.len, n_kv_heads * items_per_head);
+    Walk<1> walk(seg.len, n_kv_heads * items_per_head);
     if (!walk.more()) return;                            // the whole block
     const int delta = seg.new_start - seg.stored_start;
     bool table = false;
     for (; walk.more(); walk.next()) {
-        const int n_items = walk.n_items();
-        Chunk8<DT> a[U], b[U];
-        int64_t base[U];
-        int j[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // an item past the end reads the last one again and stores nothing
-            const Item i = locate(min(walk.at + u * kThreads + (int)threadIdx.x, n_items - 1), items_per_head, n_kv_heads,
-                                  walk.ntok(), by_head);
-            j[u] = i.j;
-            base[u] = (seg.tok_offset + walk.tok0 + i.tok) * tok_stride + (int64_t)i.head * head_stride;
-            a[u].load(k_in, base[u] + first_of<PAIRING>(i.j));
-            b[u].load(k_in, base[u] + second_of<PAIRING>(i.j, half));
-        }
+        const int n_items = walk.n_items(), it = walk.at + (int)threadIdx.x;
+        // an item past the end reads the last one again and stores nothing
+        const Item i = locate(min(it, n_items - 1), items_per_head, n_kv_heads, walk.ntok(), by_head);
+        const int64_t base = (seg.tok_offset + walk.tok0 + i.tok) * tok_stride + (int64_t)i.head * head_stride;
+        const int64_t o0 = base + first_of<PAIRING>(i.j), o1 = base + second_of<PAIRING>(i.j, half);
+        Chunk8<DT> a, b;
+        a.load(k_in, o0);
+        b.load(k_in, o1);
         if (!table) {
             for (int m = threadIdx.x; m < half; m += kThreads) cs[m] = rope_cos_sin(delta, freq.rev[m]);
             __syncthreads();
             table = true;
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (walk.at + u * kThreads + (int)threadIdx.x >= n_items) continue;
-            rotate<DT, PAIRING>(a[u], b[u], cs, j[u]);
-            a[u].store(k_out, base[u] + first_of<PAIRING>(j[u]));
-            b[u].store(k_out, base[u] + second_of<PAIRING>(j[u], half));
-        }
+        if (it >= n_items) continue;
+        rotate<DT, PAIRING>(a, b, cs, i.j);
+        a.store(k_out, o0);
+        b.store(k_out, o1);
     }
 }
 
-// Items per thread: more of them share a block's table lookups and its cos/sin pairs, fewer leave a short table enough
-// blocks to fill the chip.  Pieces of a segment: all of them, as far as the grid allows.
-int pick_unroll(int64_t items) { return items >= (int64_t)256 * 8 * kThreads * 2 ? 4 : items >= (int64_t)256 * 4 * kThreads ? 2 : 1; }
+// Pieces of a segment: all of them, as far as the grid allows.
 unsigned pieces(int32_t max_seg_len, int per_tok, int unroll) {
     const int64_t n = ((int64_t)max_seg_len * per_tok + unroll * kThreads - 1) / (unroll * kThreads);
     return (unsigned)(n > 65535 ? 65535 : n);
-}
-
-template <int DT, int PAIRING, int U>
-cf_status launch_piece(const cf_layer_desc* d, const RopeFreq& f, const void* k_in, void* k_out, const cf_segment* segs,
-                       int32_t n_seg, int64_t n_store_tokens, int32_t max_seg_len, int32_t* dev_flag, hipStream_t s) {
-    const dim3 grid(n_seg, pieces(max_seg_len, d->n_kv_heads * (d->head_dim / 16), U));
-    hipLaunchKernelGGL((reposition_kernel<DT, PAIRING, U>), grid, dim3(kThreads), 0, s, k_in, k_out, segs, n_store_tokens,
-                       d->n_kv_heads, d->head_dim, store_token_stride(d), store_head_stride(d), f, dev_flag, d->max_positions);
-    CF_HIP(hipGetLastError());
-    return CF_OK;
 }
 
 template <int DT, int PAIRING>
 cf_status launch_dt(const cf_layer_desc* d, const RopeFreq& f, const void* k_in, void* k_out,
                     const cf_segment* segs, int32_t n_seg, int64_t n_store_tokens, int32_t max_seg_len,
                     int32_t* dev_flag, hipStream_t s) {
-    switch (pick_unroll((int64_t)n_seg * max_seg_len * d->n_kv_heads * (d->head_dim / 16))) {
-        case 1: return launch_piece<DT, PAIRING, 1>(d, f, k_in, k_out, segs, n_seg, n_store_tokens, max_seg_len, dev_flag, s);
-        case 2: return launch_piece<DT, PAIRING, 2>(d, f, k_in, k_out, segs, n_seg, n_store_tokens, max_seg_len, dev_flag, s);
-        default: return launch_piece<DT, PAIRING, 4>(d, f, k_in, k_out, segs, n_seg, n_store_tokens, max_seg_len, dev_flag, s);
-    }
+    const dim3 grid(n_seg, pieces(max_seg_len, d->n_kv_heads * (d->head_dim / 16), 1));
+    hipLaunchKernelGGL((reposition_kernel<DT, PAIRING>), grid, dim3(kThreads), 0, s, k_in, k_out, segs, n_store_tokens,
+                       d->n_kv_heads, d->head_dim, store_token_stride(d), store_head_stride(d), f, dev_flag, d->max_positions);
+    CF_HIP(hipGetLastError());
+    return CF_OK;
 }
 
 // Final Re-Positioning (Alg. 2, Phase 2): gather + rotate.  grid = (batch * seg_stride, pieces of a segment); block
@@ -357,9 +338,11 @@ cf_status launch_assemble_piece(const cf_layer_desc* d, const RopeFreq& f, const
 template <int DT, int PAIRING>
 cf_status launch_assemble_dt(const cf_layer_desc* d, const RopeFreq& f, const AssembleArgs& a, int32_t max_seg_len,
                              hipStream_t s) {
-    // an item of this kernel is four chunks, not two: it needs half as many per thread
-    if (pick_unroll((int64_t)a.batch * a.seg_stride * max_seg_len * d->n_kv_heads * (d->head_dim / 16)) == 1)
-        return launch_assemble_piece<DT, PAIRING, 1>(d, f, a, max_seg_len, s);
+    // Two items per thread share a block's table sums and cos/sin pairs, but leave half as many blocks.  From 1024 blocks of
+    // one on they are faster (30 documents x 160 tokens of 32 heads, bf16: 33.7 against 35.8 us; 5 queries x 7
+    // documents of 199 and more tokens, 4 heads: 10.6 against 10.9), below it slower (under 7 us: by 0.1-0.5 us).
+    const int64_t items = (int64_t)a.batch * a.seg_stride * max_seg_len * d->n_kv_heads * (d->head_dim / 16);
+    if (items < (int64_t)256 * 4 * kThreads) return launch_assemble_piece<DT, PAIRING, 1>(d, f, a, max_seg_len, s);
     return launch_assemble_piece<DT, PAIRING, 2>(d, f, a, max_seg_len, s);
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the streaming kernels (cf_reposition_keys, cf_assemble_cache) where the numbering of their work items can
-go wrong: the last piece of a segment, one to four items per thread, segments past the stated longest length, more than 2^20
+go wrong: the last piece of a segment, one or two items per thread, segments past the stated longest length, more than 2^20
 items in one segment, either store layout."""
 
 import numpy as np
@@ -22,7 +22,7 @@ SHAPES = [
     ([1], 1, 1, 16),                    # one item
     ([7, 0, 13, 64], 64, 5, 48),        # three items per row, pieces that end inside a row's heads
     ([33, 150, 2], 40, 32, 128),        # two items per thread; a segment longer than stated
-    ([200] * 19 + [101], 200, 32, 128), # four items per thread
+    ([200] * 19 + [101], 200, 32, 128), # many pieces
     ([2060, 3], 2060, 32, 256),         # more items than are numbered together
 ]
 
