@@ -73,9 +73,15 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     p.units_per_b = n_kv_heads * p.n_rg;
     p.units = batch * p.units_per_b;
     const int64_t est_tiles = max_kv_tokens / p.tile + seg_stride;
-    // One workgroup per CU and launch wave.  A CU holds one attn_pipe_kernel workgroup at a time, so there the
-    // count stays within the 256 CUs; two of the small kernel's fit, and a few more than 256 do no harm.
-    int64_t ns = p.producers ? 256 / p.units : (256 + p.units - 1) / p.units;
+    // One launch wave: a CU holds one workgroup of either kernel at a time (8 wavefronts of about 190 and 250 registers), so a
+    // grid a little past the 256 CUs runs two rounds, the second nearly empty, each with its prologue and tail.  Rounded down and
+    // not up, attn_tile_kernel's calls that 256 does not divide measured: 6 decode queries x 32 heads over 1017-1573 tokens (192
+    // units, two splits against one) 37.6 -> 26.5 us, 17 x 4 heads over 1355-1704 (68 units, four against three) 26.3 -> 19.0,
+    // 28 x 2 heads over 723 (56 units) 18.6 -> 13.1, 3 layer queries x 32 heads, 7 short documents (96 units) 28.0 -> 22.2.
+    // The exception is a long batch that would leave over a quarter of the CUs idle: its halves even out unequal lengths (36 decode
+    // queries x 4 heads over 1000-5000 tokens, 144 units: 67 us with two splits, 73 with one; 50 queries, 200 units: 85 and 77).
+    const bool halves = !p.producers && p.units > 128 && p.units < 192 && est_tiles > 128;
+    int64_t ns = halves ? 2 : 256 / p.units;
     const int64_t cap = est_tiles / (2 * p.groups) > 1 ? est_tiles / (2 * p.groups) : 1;
     if (ns > cap) ns = cap;
     if (ns > kMaxSplit) ns = kMaxSplit;
