@@ -95,7 +95,6 @@ class PrefillBatch:
         self.n_alive = self.stride
         self.n_pending = 0          # layers whose scores are still pending in the workspace (layer(defer=True))
         self._cache = None          # device addresses and the prune-step structs of the current tables (layer())
-        self._caches = {}           # the same for the two arrangements that advance() swaps between
 
     # -- Alg. 2 init: every document is a candidate, placement order = retriever order
     def allocate_initial(self, force_n_reuse: int = 0) -> None:
@@ -142,13 +141,18 @@ class PrefillBatch:
         # the tables' addresses only change in advance(): marshal them once, not per call
         c = self._cache
         if c is None:
-            c = self._cache = self._marshalled()
+            c = self._cache = dict(
+                steps={}, q_off=self.q_off.data_ptr(), q_start=self.q_start.data_ptr(), segs=self.segs.data_ptr(),
+                n_seg=self.n_seg.data_ptr(), mass=self.mass.data_ptr(), score=self.score.data_ptr(),
+                workspace=self.workspace.data_ptr(), dev_flag=self.dev_flag.data_ptr())
         step = None
         if keep is not None:
             if strategy == cf.CF_ALLOC_KEEP:
                 self.next_new_start.copy_(self.new_start)
                 self.next_q_start.copy_(self.q_start)
-            key = (keep, strategy, force_n_reuse, normalise_by_len, self.pos_begin, self.pos_end)
+            # every scalar of the struct: a caller may change any of them between two layers
+            key = (keep, strategy, force_n_reuse, normalise_by_len, self.stride, self.pos_begin, self.pos_end,
+                   self.prefix_len, self.doc_stored_start)
             step = c["steps"].get(key)
             if step is None:
                 step = c["steps"][key] = cf.make_prune_step(
@@ -163,23 +167,6 @@ class PrefillBatch:
                             c["mass"], c["score"], self.stride, c["workspace"], self.ws_bytes, step, c["dev_flag"],
                             None, self.n_pending, defer)
         self.n_pending = self.n_pending + 1 if defer else 0
-
-    # Addresses of the tables as they stand.  advance() swaps pairs of them, so a stack comes back to the same two
-    # arrangements: an entry is found again by the tensors themselves (which it holds, so that no other can take their place).
-    def _marshalled(self) -> dict:
-        held = (self.q_off, self.q_start, self.segs, self.n_seg, self.mass, self.score, self.workspace, self.dev_flag,
-                self.doc_tok_offset, self.doc_len, self.cand, self.n_cand, self.keep_idx, self.n_keep, self.next_new_start,
-                self.next_q_start, self.n_reuse, self.order, self.next_segs, self.next_n_seg)
-        key = tuple(map(id, held))
-        c = self._caches.get(key)
-        if c is None:
-            if len(self._caches) >= 4:
-                self._caches.clear()
-            c = self._caches[key] = dict(
-                held=held, steps={}, q_off=self.q_off.data_ptr(), q_start=self.q_start.data_ptr(), segs=self.segs.data_ptr(),
-                n_seg=self.n_seg.data_ptr(), mass=self.mass.data_ptr(), score=self.score.data_ptr(),
-                workspace=self.workspace.data_ptr(), dev_flag=self.dev_flag.data_ptr())
-        return c
 
     # -- the survivors, in placement order, become the candidates of the following layers
     def advance(self) -> None:
