@@ -190,7 +190,9 @@ CF_API cf_status cf_prefill_attention(const cf_layer_desc* desc,
  * holds until the process ends.  The call itself allocates nothing (no hipMalloc / hipFree, no
  * allocating library routine).
  *   - Shapes whose workspace (cf_prefill_workspace_bytes) exceeds CF_STATIC_SCRATCH_BYTES are
- *     rejected with CF_ERR_WORKSPACE before anything is launched.
+ *     rejected with CF_ERR_WORKSPACE before anything is launched.  One exception: shapes outside the 16-bit kernels'
+ *     (fp32, head_dim other than 128, interleaved pairs) whose batch * max_tq * n_q_heads * (seg_stride + 1) * 8 bytes
+ *     fit are served by the row-by-row kernel, slower and with results that agree to fp32 rounding instead.
  *   - The first call on a device looks the array's address up (hipGetSymbolAddress, once per device,
  *     with that device current); make that call outside stream capture.
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

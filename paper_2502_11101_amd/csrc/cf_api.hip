@@ -206,7 +206,7 @@ static cf_status prefill_impl(const cf_layer_desc* desc, const void* q, const in
                                int32_t seg_stride, int32_t batch, int32_t max_tq, int64_t max_kv_tokens,
                                void* out, float* mass, float* score_accum, int32_t score_stride,
                                void* workspace, size_t workspace_bytes, const cf_prune_step* prune,
-                               int32_t n_pending, int32_t defer, int32_t* dev_flag, void* stream) {
+                               int32_t n_pending, int32_t defer, int32_t* dev_flag, void* stream, bool row_by_row = false) {
     cf_status st = check_desc(desc);
     if (st != CF_OK) return st;
     CF_REQUIRE(batch >= 0, CF_ERR_INVALID_ARG, "batch is negative");
@@ -237,7 +237,8 @@ static cf_status prefill_impl(const cf_layer_desc* desc, const void* q, const in
                CF_ERR_INVALID_ARG, "tensor base pointers must be 16-byte aligned");
     CF_REQUIRE(q_stored_start >= 0 && q_stored_start < desc->max_positions, CF_ERR_RANGE,
                "q_stored_start outside [0, max_positions)");
-    const size_t need = cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+    const size_t need = row_by_row ? generic_workspace_bytes(desc, batch, max_tq, seg_stride)
+                                   : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
     CF_REQUIRE(workspace != nullptr && workspace_bytes >= need, CF_ERR_WORKSPACE,
                "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
     CF_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, CF_ERR_WORKSPACE,
@@ -263,7 +264,7 @@ static cf_status prefill_impl(const cf_layer_desc* desc, const void* q, const in
     const RopeFreq& f = rope_freq(desc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (mfma_path_supported(desc)) return launch_attention_mfma(a, f, s, prune);
-    if (plain_path_supported(desc, batch, max_tq, seg_stride)) return launch_attention_plain(desc, a, f, s, prune);
+    if (!row_by_row && plain_path_supported(desc, batch, max_tq, seg_stride)) return launch_attention_plain(desc, a, f, s, prune);
     st = launch_attention_generic(a, f, s);
     if (st != CF_OK || !prune) return st;
     return launch_prune_step(a, prune, s);
@@ -320,7 +321,12 @@ cf_status cf_prefill_attention_static(const cf_layer_desc* desc, const void* q, 
     CF_REQUIRE(batch >= 0 && max_tq >= 1 && seg_stride >= 1 && max_kv_tokens >= 0, CF_ERR_INVALID_ARG,
                "batch, max_tq, seg_stride or max_kv_tokens out of range");
     if (batch == 0) return CF_OK;
-    const size_t need = cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+    size_t need = cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+    // Outside the 16-bit kernels' shapes a plan may need more than the row-by-row kernel, which keeps (slots x rows) statistics only:
+    // by the partial rows of its splits and the slots' sums.  What that kernel can serve from the buffer is served by it.
+    const bool row_by_row = need > CF_STATIC_SCRATCH_BYTES && !mfma_path_supported(desc) &&
+                            generic_workspace_bytes(desc, batch, max_tq, seg_stride) <= CF_STATIC_SCRATCH_BYTES;
+    if (row_by_row) need = generic_workspace_bytes(desc, batch, max_tq, seg_stride);
     CF_REQUIRE(need <= CF_STATIC_SCRATCH_BYTES, CF_ERR_WORKSPACE,
                "this shape needs %zu bytes of scratch, the library-owned buffer holds %zu: use cf_prefill_attention with a workspace",
                need, (size_t)CF_STATIC_SCRATCH_BYTES);
@@ -329,7 +335,7 @@ cf_status cf_prefill_attention_static(const cf_layer_desc* desc, const void* q, 
     if (st != CF_OK) return st;
     return prefill_impl(desc, q, q_off, q_stored_start, q_new_start, k_store, v_store, n_store_tokens, k_self, v_self,
                         segs, n_seg, seg_stride, batch, max_tq, max_kv_tokens, out, mass, score_accum, score_stride,
-                        scratch, CF_STATIC_SCRATCH_BYTES, nullptr, 0, 0, dev_flag, stream);
+                        scratch, CF_STATIC_SCRATCH_BYTES, nullptr, 0, 0, dev_flag, stream, row_by_row);
 }
 
 cf_status cf_prefill_layer(const cf_layer_desc* desc, const void* q, const int32_t* q_off, int32_t q_stored_start,

@@ -377,11 +377,13 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
 
     char* ws = static_cast<char*>(a.workspace);
     const int rows = 16 * RB;
-    float2* massml = reinterpret_cast<float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * rows;
+    // slot statistics: [query, kv head][slot][row], for the rows there are and not for those a block is padded to
+    const int rows_kv = group * a.max_tq;
+    float2* massml = reinterpret_cast<float2*>(ws + p.off_massml) + ((int64_t)b * a.n_kv_heads + hkv) * p.slots * rows_kv + row_base;
     auto emit = [&](int slot) __attribute__((always_inline)) {                              // (reference, sum) of the segment per row
         float tot = seg_l + __shfl_xor(seg_l, 16);
         tot += __shfl_xor(tot, 32);
-        if (lg == 0) massml[(int64_t)slot * rows + wave * 16 + li] = make_float2(m_run, tot);
+        if (lg == 0 && row_ok) massml[(int64_t)slot * rows_kv + wave * 16 + li] = make_float2(m_run, tot);
     };
 
     Tile nxt;
@@ -485,7 +487,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
         double* part = reinterpret_cast<double*>(ws + p.off_masspart) + (int64_t)unit * p.slots;
         const float2 st = lane < rows ? ml_lds[0][lane] : make_float2(0.f, 0.f);
         for (int k = wave_all; k < p.slots; k += kWaves) {
-            const float2 v = lane < rows ? massml[(int64_t)k * rows + lane] : make_float2(0.f, 0.f);
+            const float2 v = lane < row_limit - row_base ? massml[(int64_t)k * rows_kv + lane] : make_float2(0.f, 0.f);
             const double c = wave_sum_f64(st.y > 0.f && v.y > 0.f ? (double)(v.y * exp2f(v.x - st.x)) * (double)st.y : 0.0);
             if (lane == 0) part[k] = c;
         }
@@ -507,7 +509,6 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
     char* ws = static_cast<char*>(a.workspace);
     const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * rows;
     const f32x4* opart = reinterpret_cast<const f32x4*>(ws + p.off_opart) + (int64_t)unit * p.nsplit * rbs * blocks * kWave;
-    const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * rows;
 
     const int item = blockIdx.x * kWaves + wave;             // row block, channel block
     const bool item_ok = item < rbs * blocks;
@@ -562,9 +563,11 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
     }
     if (a.mass != nullptr) {
         double* part = reinterpret_cast<double*>(ws + p.off_masspart) + (int64_t)unit * p.slots;
+        const int rows_kv = p.group * a.max_tq;
+        const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + ((int64_t)b * a.n_kv_heads + hkv) * p.slots * rows_kv + row_base;
         const float2 st = lane < rows ? stat[lane] : make_float2(0.f, 0.f);
         for (int k = item; k < p.slots; k += (int)gridDim.x * kWaves) {
-            const float2 v = lane < rows ? massml[(int64_t)k * rows + lane] : make_float2(0.f, 0.f);
+            const float2 v = lane < rows_here ? massml[(int64_t)k * rows_kv + lane] : make_float2(0.f, 0.f);
             const double c = wave_sum_f64(st.y > 0.f && v.y > 0.f ? (double)(v.y * exp2f(v.x - st.x)) * (double)st.y : 0.0);
             if (lane == 0) part[k] = c;
         }
@@ -604,7 +607,7 @@ Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stri
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     p.off_ml = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
     p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * dp * sizeof(float));
-    p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
+    p.off_massml = take((size_t)batch * d.n_kv_heads * p.slots * p.group * max_tq * sizeof(float2));
     p.masspart_bytes = ((size_t)p.units * p.slots * sizeof(double) + 255) & ~(size_t)255;
     p.off_masspart = take(p.masspart_bytes);
     p.total = off;
