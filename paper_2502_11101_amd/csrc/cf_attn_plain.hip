@@ -640,10 +640,10 @@ void launch_plain(const AttnArgs& a, const RopeFreq& f, const Plan& p, hipStream
 
 }  // namespace
 
-// Tables past kMaxSegs entries, and grids past the hardware's, stay with the row-by-row kernel.
+// Tables past kMaxSegs entries, grids past the hardware's and counts past the plan's 32 bits stay with the row-by-row kernel.
 bool plain_path_supported(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride) {
-    const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * max_tq;
-    return seg_stride <= kMaxSegs && batch <= 65535 && rows < (1 << 20) && d->n_kv_heads * ((rows + 63) / 64 + 1) <= 65535;
+    const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * max_tq, units_per_b = d->n_kv_heads * ((rows + 63) / 64 + 1);
+    return seg_stride <= kMaxSegs && batch <= 65535 && rows < (1 << 20) && units_per_b <= 65535 && batch * units_per_b <= 0x7fffffff;
 }
 
 size_t plain_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens) {

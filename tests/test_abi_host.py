@@ -226,3 +226,9 @@ def test_bench_refuses_more_than_one_gpu():
 
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_workspace_sizes_of_calls_past_the_plans_counts():
+    """Units past 2^31 (3.2 G here) stay with the row-by-row kernel: its workspace, not a wrapped product."""
+    d = _desc(n_q_heads=16383, n_kv_heads=16383, head_dim=16, dtype="f32")
+    assert cf.cf_prefill_workspace_bytes(d, 65535, 192, 4, 1000) == -(-65535 * 192 * 16383 * 5 * 8 // 256) * 256
