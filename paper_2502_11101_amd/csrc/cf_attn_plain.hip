@@ -101,6 +101,11 @@ __device__ __forceinline__ void turn_chunks(float (&x)[8], float (&y)[8], const 
     }
 }
 
+// A row's weight on a slot: (reference, sum) of the slot against those of the row, divided in double.
+__device__ __forceinline__ double slot_share(float2 v, float2 row) {
+    return row.y > 0.f && v.y > 0.f ? (double)(v.y * exp2f(v.x - row.x)) / (double)row.y : 0.0;
+}
+
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -482,13 +487,13 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
     // ---- one split: the rows' statistics are final, so the slots are reduced here (else by the merge kernel)
     if (p.direct_out && a.mass != nullptr) {
         __syncthreads();                                     // publishes the slots (and everybody has read ml_lds)
-        if (grp == 0 && lg == 0) ml_lds[0][wave * 16 + li] = make_float2(m_run, row_ok ? inv : 0.f);
+        if (grp == 0 && lg == 0) ml_lds[0][wave * 16 + li] = make_float2(m_run, row_ok ? l_row : 0.f);
         __syncthreads();
         double* part = reinterpret_cast<double*>(ws + p.off_masspart) + (int64_t)unit * p.slots;
         const float2 st = lane < rows ? ml_lds[0][lane] : make_float2(0.f, 0.f);
         for (int k = wave_all; k < p.slots; k += kWaves) {
             const float2 v = lane < row_limit - row_base ? massml[(int64_t)k * rows_kv + lane] : make_float2(0.f, 0.f);
-            const double c = wave_sum_f64(st.y > 0.f && v.y > 0.f ? (double)(v.y * exp2f(v.x - st.x)) * (double)st.y : 0.0);
+            const double c = wave_sum_f64(slot_share(v, st));
             if (lane == 0) part[k] = c;
         }
     }
@@ -499,7 +504,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
 template <int DT>
 __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Plan p, int blocks) {
     __shared__ float2 mlw[kMaxSplit * 64];                   // (m, l) per split and row, then the split's weight in .x
-    __shared__ float2 stat[64];                              // row maximum, 1 / row sum
+    __shared__ float2 stat[64];                              // row maximum, row sum (0: no such row)
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int li = lane & 15, lg = lane >> 4;
     const int b = blockIdx.z, unit = b * p.units_per_b + (int)blockIdx.y;
@@ -537,7 +542,7 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
             mlw[s * rows + tid].x = w;
             z += w;
         }
-        stat[tid] = make_float2(m, tid < rows_here && z > 0.f ? 1.f / z : 0.f);
+        stat[tid] = make_float2(m, tid < rows_here ? z : 0.f);
     }
     __syncthreads();
     if (item_ok) {
@@ -547,7 +552,8 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
         for (int s = 0; s < kPre; ++s)
             if (s < p.nsplit) o += pre[s] * mlw[s * rows + row].x;
         for (int s = kPre; s < p.nsplit; ++s) o += src[s * stride] * mlw[s * rows + row].x;
-        o *= stat[row].y;
+        const float z = stat[row].y;
+        o *= z > 0.f ? 1.f / z : 0.f;
         if (row < rows_here && 16 * db < a.head_dim) {
             const int m2 = row_base + row;
             const int gi = (int)div_exact((unsigned)m2, (unsigned)tq), t = m2 - gi * tq;
@@ -568,7 +574,7 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
         const float2 st = lane < rows ? stat[lane] : make_float2(0.f, 0.f);
         for (int k = item; k < p.slots; k += (int)gridDim.x * kWaves) {
             const float2 v = lane < rows_here ? massml[(int64_t)k * rows_kv + lane] : make_float2(0.f, 0.f);
-            const double c = wave_sum_f64(st.y > 0.f && v.y > 0.f ? (double)(v.y * exp2f(v.x - st.x)) * (double)st.y : 0.0);
+            const double c = wave_sum_f64(slot_share(v, st));
             if (lane == 0) part[k] = c;
         }
     }
