@@ -10,8 +10,8 @@
 // relative shift once per segment, in fp32, and keys and values go to LDS as they are: no arithmetic per cached token.
 //   * fp32: S^T = K Q^T and O^T += V^T P^T on v_mfma_f32_16x16x4f32.
 //   * bf16 / fp16: keys and values are exact MFMA operands; the turned query and the probabilities are fp32 numbers handed
-//     over as sums of two or three 16-bit parts (bf16: 8 + 8 + 8 significant bits; fp16: 11 + 11 (+ 11), the parts of the
-//     query scaled up by 2^11 each so that none underflows, with an accumulator per part).  Products of parts are exact
+//     over as sums of three 16-bit parts (bf16: 8 + 8 + 8 significant bits; fp16: 11 + 11 + 11, each part scaled up by 2^11
+//     against the one before it so that none underflows, with an accumulator per part).  Products of parts are exact
 //     in the fp32 accumulators, so the result has fp32 precision at a third of the 16-bit matrix rate: 2048 -> 384 matrix cycles
 //     per 16 rows x 32 tokens x 128 channels and product, against v_mfma_f32_16x16x4f32.
 //
@@ -45,11 +45,11 @@ template <int DT, int DP> struct PlainShape {
     static constexpr int kBlocks = DP / 16;                  // 16-channel blocks of the output
     static constexpr int kBuf = kTile * (kKRow + kVRow);
     static constexpr int kQParts = kF32 ? 1 : 3;
-    static constexpr int kPParts = DT == CF_BF16 ? 3 : 2;    // 16-bit parts of a probability
+    static constexpr int kPParts = 3;                        // 16-bit parts of a probability
 };
 
-// fp16 probabilities live in (0, 2^15]: the reference stays 2^7 below the row maximum it was taken from, so that two fp16 parts
-// resolve 2^-32 of the largest probability
+// fp16 probabilities live in (0, 2^15]: the reference stays 2^7 below the row maximum it was taken from.  Three parts, the second
+// and third scaled up by 2^11 and 2^22, hold all 24 bits of a probability down to 2^-30 of the largest, and 2^-53 of that at worst
 template <int DT> constexpr float kRefBelow = DT == CF_F16 ? 7.f : 0.f;
 template <int DT> constexpr float kPlainLimit = DT == CF_F16 ? 32768.f : kProbLimit;
 
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
         } else {
             uint4 pp[S::kPParts];
 #pragma unroll
-            for (int n = 0; n < S::kPParts; ++n) pp[n] = split_part<DT>(reinterpret_cast<float (&)[8]>(pv), 1.f);
+            for (int n = 0; n < S::kPParts; ++n) pp[n] = split_part<DT>(reinterpret_cast<float (&)[8]>(pv), DT == CF_F16 ? 2048.f : 1.f);
             const unsigned char* vb = v_lds + (4 * lg + (li >> 2)) * S::kVRow + 8 * (li & 3);
 #pragma unroll
             for (int db = 0; db < S::kBlocks; ++db) {
@@ -374,8 +374,14 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
                 const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(vb + 32 * db + 16 * S::kVRow));
                 const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
                 const uint4 va = make_uint4(l2.x, l2.y, h2.x, h2.y);
+                if constexpr (DT == CF_F16) {                // the scaled parts: their sum joins the first's
+                    f32x4 t = Mma<CF_F16>::run(va, pp[2], f32x4{0.f, 0.f, 0.f, 0.f});
+                    t = Mma<CF_F16>::run(va, pp[1], t * 0x1p-11f);
+                    acc[db] = Mma<CF_F16>::run(va, pp[0], acc[db] + t * 0x1p-11f);
+                } else {
 #pragma unroll
-                for (int n = S::kPParts - 1; n >= 0; --n) acc[db] = Mma<DT == CF_F32 ? CF_BF16 : DT>::run(va, pp[n], acc[db]);
+                    for (int n = S::kPParts - 1; n >= 0; --n) acc[db] = Mma<CF_BF16>::run(va, pp[n], acc[db]);
+                }
             }
         }
     };

@@ -53,3 +53,26 @@ def test_the_mass_of_all_a_row_sees_is_one(dtype, far):
     _, mass = _attend(dtype, q, ks, vs, [13, far] if far else [13])
     assert np.array_equal(mass[:, 0], np.ones(64, np.float32))
     assert np.all(mass[:, 1:] == 0.0)
+
+
+@pytest.mark.parametrize("small", [20, 28, 33, 36])
+@pytest.mark.parametrize("far", [0, 700])          # without and with splits to merge
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_small_probabilities_keep_their_bits(dtype, far, small):
+    """A token with 2^-small of the largest probability carries the only values there are: the outputs are its products alone,
+    and as exact as the type they are stored in."""
+    print(f"small {dtype} far={far} 2^-{small}", flush=True)
+    n, tokens = 16, 13 + far
+    q, ks, vs = np.zeros((n, 1, D), np.float32), np.zeros((tokens, 1, D), np.float32), np.zeros((tokens, 1, D), np.float32)
+    q[:, 0, 0] = 1.0 + np.arange(n) / 128.0         # exact in every type
+    ks[5, 0, 0] = -np.float32(np.round(small * np.log(2.0) * np.sqrt(D)))
+    ks[13:, 0, 0] = -1200.0
+    vs[5] = np.where(np.arange(D) % 2, 1.0, -1.5) * 2.0 ** 15
+    out, _ = _attend(dtype, q, ks, vs, [13, far] if far else [13])
+    s = np.float64(q[:, 0, 0])[:, None] * np.float64(ks[:, 0, 0])[None] / np.sqrt(D)
+    p = np.exp(s - s.max(axis=1, keepdims=True))
+    ref = (p / p.sum(axis=1, keepdims=True)) @ np.float64(vs[:, 0])
+    # scores up to 2^40 apart in fp32 (two roundings of a number below 64), and one rounding of the result (fp16: to multiples of 2^-24
+    # below 2^-14)
+    bound = np.abs(ref) * ({"f32": 0.0, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] + 64 * 2.0 ** -23) + (2.0 ** -25 if dtype == "f16" else 0.0)
+    assert np.all(np.abs(out[:, 0] - ref) <= bound)
