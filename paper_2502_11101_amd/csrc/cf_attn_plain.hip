@@ -397,6 +397,73 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
         if (lg == 0 && row_ok) massml[(int64_t)slot * rows_kv + wave * 16 + li] = make_float2(m_run, tot);
     };
 
+    // Row rr of the wavefront's block over all the tokens of the workgroup, as the row-by-row kernel goes over them: only what the row
+    // sees is read, keys are turned and products summed in fp32.  Same records as emit.
+    auto redo_row = [&](int rr, float (&o)[4], float& m, float& l) {
+        using E = Elem<DT>;
+        using T = typename E::type;
+        const int half = d >> 1, row = row_base + wave * 16 + rr;
+        const int head = (int)div_exact((unsigned)row, (unsigned)tq), t = row - head * tq;
+        const T* qp = static_cast<const T*>(a.q) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + head) * d;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = 0.f;
+        auto lane_of = [](float x, int from) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), from)); };
+        m = -INFINITY;
+        l = 0.f;
+        for (int g = 0; g < kGroups; ++g) {
+            const int sub = split * kGroups + g;
+            TileWalk<S::kTile> from(split_begin(total, nsub, sub), split_begin(total, nsub, sub + 1));
+            int seg = -1;
+            float sum = 0.f;
+            float2 cs_lo = {}, cs_hi = {};                   // slices lane, lane + 64
+            for (;;) {
+                const Tile c = reg_table ? from.next(rtbl, lane) : from.next(tbl, lane);
+                if (c.ntok == 0 || c.seg != seg) {
+                    if (seg >= 0 && lane == 0) massml[(int64_t)(seg + sub) * rows_kv + wave * 16 + rr] = make_float2(m, sum);
+                    if (c.ntok == 0) break;
+                    seg = c.seg;
+                    sum = 0.f;
+                    cs_lo = rope_cos_sin(c.delta, freq.rev[min(lane, half - 1)]);
+                    if (half > kWave) cs_hi = rope_cos_sin(c.delta, freq.rev[min(lane + kWave, half - 1)]);
+                }
+                const int vis = c.self ? min(c.ntok, t + 1 - c.tok0) : c.ntok;
+                if (vis <= 0) continue;
+                const int64_t ts = c.self ? (int64_t)a.n_kv_heads * d : a.store_ts;
+                const int64_t base = (from.c_tok + c.tok0) * ts + (int64_t)hkv * (c.self ? d : a.store_hs);
+                const T* kp = static_cast<const T*>(c.self ? a.k_self : a.k_store) + base + min(lane, vis - 1) * ts;
+                const T* vp = static_cast<const T*>(c.self ? a.v_self : a.v_store) + base;
+                float sc = 0.f;
+                for (int n = 0; n < half; ++n) {             // (every lane, past the visible tokens too: lane reads are not for branches)
+                    const int c0 = a.pairing == CF_ROPE_HALF ? n : 2 * n, c1 = a.pairing == CF_ROPE_HALF ? n + half : 2 * n + 1;
+                    float x = E::load(kp + c0), y = E::load(kp + c1);
+                    if (c.delta != 0) {
+                        const float2 w = n < kWave ? cs_lo : cs_hi;
+                        const float2 u = make_float2(lane_of(w.x, n & (kWave - 1)), lane_of(w.y, n & (kWave - 1)));
+                        const float nx = x * u.x - y * u.y;
+                        y = x * u.y + y * u.x;
+                        x = nx;
+                    }
+                    sc += E::load(qp + c0) * x + E::load(qp + c1) * y;
+                }
+                sc = lane < vis ? sc * a.scale_log2e : -INFINITY;
+                const float m_new = fmaxf(m, wave_max(sc)), m_ref = m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = exp2f(m - m_ref), pr = lane < vis ? exp2f(sc - m_ref) : 0.f;
+                const float add = wave_sum(pr);
+                l = l * alpha + add;
+                sum = sum * alpha + add;
+                m = m_new;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] *= alpha;
+                for (int j = 0; j < vis; ++j) {
+                    const float pj = lane_of(pr, j);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (lane + kWave * i < d) o[i] += pj * E::load(vp + j * ts + lane + kWave * i);
+                }
+            }
+        }
+    };
+
     Tile nxt;
     fetch(nxt, regs);
     int cs_slot = 0, cur_seg = -1;
@@ -464,6 +531,29 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
                 for (int db = 0; db < S::kBlocks; ++db) acc[db] += red[(((g - 1) * RB + wave) * S::kBlocks + db) * kWave + lane] * f;
             }
             m_run = m;
+        }
+    }
+    // ---- rows that did not stay finite: a tile's product multiplies tokens a row does not see by zero, and the parts of a number
+    // do not add up to infinities, so these rows go over the workgroup's tokens once more, one by one
+    if (grp == 0 && has_rows) {
+        float zero = l_row * 0.f;
+#pragma unroll
+        for (int db = 0; db < S::kBlocks; ++db)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) zero = fmaf(acc[db][e], 0.f, zero);
+        const unsigned long long lost = __ballot(row_ok && !(zero == 0.f));
+        for (unsigned left = (unsigned)(lost | lost >> 16 | lost >> 32 | lost >> 48) & 0xffffu; left != 0; left &= left - 1) {
+            const int rr = __builtin_ctz(left);
+            float o[4], m, l;                                // channels lane, lane + 64, ...
+            redo_row(rr, o, m, l);
+            if (li == rr) { m_run = m; l_row = l; }
+#pragma unroll
+            for (int db = 0; db < S::kBlocks; ++db)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = __shfl(o[db / 4], (16 * db + 4 * lg + e) & (kWave - 1));
+                    if (li == rr) acc[db][e] = x;
+                }
         }
     }
     const float inv = l_row > 0.f ? 1.f / l_row : 0.f;

@@ -7,10 +7,13 @@ import torch
 
 from paper_2502_11101_amd import binding as cf
 from paper_2502_11101_amd import pipeline as pl
+from paper_2502_11101_amd import workloads as wl
+from tests import gpu_harness as G
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 
-INTER = cf.CF_ROPE_INTERLEAVED
+HALF, INTER = cf.CF_ROPE_HALF, cf.CF_ROPE_INTERLEAVED
 I32 = dict(dtype=torch.int32, device="cuda")
 D = 64
 
@@ -76,3 +79,84 @@ def test_small_probabilities_keep_their_bits(dtype, far, small):
     # below 2^-14)
     bound = np.abs(ref) * ({"f32": 0.0, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] + 64 * 2.0 ** -23) + (2.0 ** -25 if dtype == "f16" else 0.0)
     assert np.all(np.abs(out[:, 0] - ref) <= bound)
+
+
+def _reference(q, ks, vs, own, tq):
+    """The same in 64 bits: a row's products with the tokens it sees, and no others.  Outputs, and masses of the store and the own block."""
+    out, mass = np.zeros((len(q), D)), np.zeros((len(q) // tq, 2))
+    for row in range(len(q)):
+        b, t = divmod(row, tq)
+        k, v = (np.concatenate([x[:, 0], y[b * tq:b * tq + t + 1, 0]]).astype(np.float64) for x, y in ((ks, own[0]), (vs, own[1])))
+        with np.errstate(invalid="ignore", over="ignore"):
+            s = (k * q[row, 0].astype(np.float64)).sum(axis=1) / np.sqrt(D)
+            p = np.exp(s - s.max())
+            p /= p.sum()
+            out[row] = (p[:, None] * v).sum(axis=0)
+        mass[b] += [p[:len(ks)].sum(), p[len(ks):].sum()]
+    return out, mass
+
+
+@pytest.mark.parametrize("store", [9, 700])        # without and with splits to merge
+@pytest.mark.parametrize("tq", [3, 20, 60])        # one, two and four row blocks
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("what", ["own value NaN", "own value Inf", "own key NaN", "value Inf", "value NaN", "key weight zero"])
+def test_infinities_and_nan_reach_the_rows_that_see_them(what, dtype, tq, store):
+    """A row's result does not depend on tokens it does not see, whatever they hold; an infinite value it sees gives an infinite
+    channel and a NaN a NaN one; a key whose score is minus infinity has no weight."""
+    print(f"non-finite {what}: {dtype} tq={tq} store={store}", flush=True)
+    rng = np.random.default_rng(tq + store)
+    rows = 2 * tq
+    normal = lambda n: torch.from_numpy(rng.standard_normal((n, 1, D), dtype=np.float32)).to(pl.TORCH_DTYPE[dtype]).float().numpy()
+    q, k1, v1, ks, vs = normal(rows), normal(rows), normal(rows), normal(store), normal(store)
+    at = tq + tq // 2                              # a token of the second query's own block
+    if what == "own value NaN": v1[at, 0, 5] = np.nan
+    elif what == "own value Inf": v1[at, 0, 62] = -np.inf
+    elif what == "own key NaN": k1[at, 0, 7] = np.nan
+    elif what == "value Inf": vs[4, 0, 1:4] = np.inf
+    elif what == "value NaN": vs[store - 1, 0, 33] = np.nan
+    else: q[:, 0, 9], ks[2, 0, 9] = 2.0, -np.inf
+    out, mass = _attend(dtype, q, ks, vs, [store], (k1, v1), tq)
+    ref, ref_mass = _reference(q, ks, vs, (k1, v1), tq)
+    out = out[:, 0].astype(np.float64)
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(kind(out), kind(ref))
+    ok = np.isfinite(ref)
+    assert np.all(np.abs(out[ok] - ref[ok]) <= {"f32": 1e-5, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype] * np.maximum(np.abs(ref[ok]), 1e-2) + 1e-5)
+    seen = np.isfinite(ref_mass).all(axis=1)       # (a row that sees a NaN key has no masses)
+    assert np.allclose(mass[seen], ref_mass[seen], rtol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,pairing,d,hq,hkv,tq,docs,lens,layout", [
+    ("f32", HALF, 208, 4, 2, 11, 6, (20, 90), "head_padded"),      # padded to 256; several splits
+    ("bf16", INTER, 256, 2, 1, 35, 4, (20, 70), "token"),          # four row blocks
+    ("f16", HALF, 80, 6, 3, 3, 5, (31, 33), "head"),
+    ("f32", INTER, 64, 2, 1, 33, 100, (1, 9), "token"),            # table in LDS, two row groups
+    ("bf16", INTER, 128, 2, 2, 1, 40, (60, 160), "head_padded"),   # a single row
+])
+def test_rows_with_an_infinite_value_keep_their_other_channels(dtype, pairing, d, hq, hkv, tq, docs, lens, layout):
+    """One infinite value in a re-positioned document: its channel is infinite in every row of the query heads on that kv head, all
+    else is as without it, against the oracle."""
+    print(f"infinite channel: {dtype} d={d} tq={tq}", flush=True)
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name=f"inf_{dtype}_{d}", geometry=wl.Geometry(hq, hkv, d, dtype, 1.0e4, 8192),
+                    n_store_docs=docs, docs_per_query=docs, batch=1, doc_len_range=lens, tq=tq, prefix_len=4, doc_stored_start=7, n_planted=1)
+    st = wl.build_structure(cfg, seed=d)
+    t = wl.build_layer(cfg, st, seed=d + 1)
+    segs, q_start, _ = H.initial_segments(cfg, st, 0)
+    ref_out, ref_mass = H.oracle_query(cfg, st, t, 0, segs, q_start, pairing="half" if pairing == HALF else "interleaved")
+    at = next(s for s in segs if s.kind == cf.CF_SEG_DOC).tok_offset
+    t["v_store"] = np.array(t["v_store"])
+    t["v_store"][at, hkv - 1, 3] = np.inf
+    pb = G.make_batch(cfg, st, pairing, layout)
+    dev = G.upload_layer(cfg, t, layout)
+    out = torch.empty_like(dev["q"])
+    pb.allocate_initial()
+    pb.workspace.fill_(0xFF)
+    pb.attention(dev["q"], dev["k_self"], dev["v_self"], dev["k_store"], dev["v_store"], out)
+    torch.cuda.synchronize()
+    assert pb.flags() == 0
+    got = out.float().cpu().numpy()
+    hit = np.zeros(got.shape, bool)
+    hit[:, (hkv - 1) * (hq // hkv):, 3] = True
+    assert np.all(np.isposinf(got[hit]))
+    assert G.row_error(np.where(hit, 0.0, got), np.where(hit, 0.0, ref_out)) <= G.OUT_TOL[dtype]
+    assert G.rel_error(pb.mass.cpu().numpy()[0, :len(segs)], ref_mass) <= 1e-5
