@@ -402,9 +402,13 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
     auto redo_row = [&](int rr, float (&o)[4], float& m, float& l) {
         using E = Elem<DT>;
         using T = typename E::type;
+        // (the kernel's first argument read anew: kept in registers for this, its fields would crowd those of the main loop)
+        uint64_t kernarg = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(kernarg));
+        const auto* ka = reinterpret_cast<const __attribute__((address_space(4))) AttnArgs*>(kernarg);
         const int half = d >> 1, row = row_base + wave * 16 + rr;
         const int head = (int)div_exact((unsigned)row, (unsigned)tq), t = row - head * tq;
-        const T* qp = static_cast<const T*>(a.q) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + head) * d;
+        const T* qp = static_cast<const T*>(ka->q) + (((int64_t)qh.q0 + t) * ka->n_q_heads + hkv * group + head) * d;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = 0.f;
         auto lane_of = [](float x, int from) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), from)); };
@@ -428,13 +432,13 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
                 }
                 const int vis = c.self ? min(c.ntok, t + 1 - c.tok0) : c.ntok;
                 if (vis <= 0) continue;
-                const int64_t ts = c.self ? (int64_t)a.n_kv_heads * d : a.store_ts;
-                const int64_t base = (from.c_tok + c.tok0) * ts + (int64_t)hkv * (c.self ? d : a.store_hs);
-                const T* kp = static_cast<const T*>(c.self ? a.k_self : a.k_store) + base + min(lane, vis - 1) * ts;
-                const T* vp = static_cast<const T*>(c.self ? a.v_self : a.v_store) + base;
+                const int64_t ts = c.self ? (int64_t)ka->n_kv_heads * d : ka->store_ts;
+                const int64_t base = (from.c_tok + c.tok0) * ts + (int64_t)hkv * (c.self ? d : ka->store_hs);
+                const T* kp = static_cast<const T*>(c.self ? ka->k_self : ka->k_store) + base + min(lane, vis - 1) * ts;
+                const T* vp = static_cast<const T*>(c.self ? ka->v_self : ka->v_store) + base;
                 float sc = 0.f;
                 for (int n = 0; n < half; ++n) {             // (every lane, past the visible tokens too: lane reads are not for branches)
-                    const int c0 = a.pairing == CF_ROPE_HALF ? n : 2 * n, c1 = a.pairing == CF_ROPE_HALF ? n + half : 2 * n + 1;
+                    const int c0 = ka->pairing == CF_ROPE_HALF ? n : 2 * n, c1 = ka->pairing == CF_ROPE_HALF ? n + half : 2 * n + 1;
                     float x = E::load(kp + c0), y = E::load(kp + c1);
                     if (c.delta != 0) {
                         const float2 w = n < kWave ? cs_lo : cs_hi;
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
                     }
                     sc += E::load(qp + c0) * x + E::load(qp + c1) * y;
                 }
-                sc = lane < vis ? sc * a.scale_log2e : -INFINITY;
+                sc = lane < vis ? sc * ka->scale_log2e : -INFINITY;
                 const float m_new = fmaxf(m, wave_max(sc)), m_ref = m_new == -INFINITY ? 0.f : m_new;
                 const float alpha = exp2f(m - m_ref), pr = lane < vis ? exp2f(sc - m_ref) : 0.f;
                 const float add = wave_sum(pr);
@@ -542,7 +546,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
 #pragma unroll
             for (int e = 0; e < 4; ++e) zero = fmaf(acc[db][e], 0.f, zero);
         const unsigned long long lost = __ballot(row_ok && !(zero == 0.f));
-        for (unsigned left = (unsigned)(lost | lost >> 16 | lost >> 32 | lost >> 48) & 0xffffu; left != 0; left &= left - 1) {
+        if (__builtin_expect(lost != 0, 0)) for (unsigned left = (unsigned)(lost | lost >> 16 | lost >> 32 | lost >> 48) & 0xffffu; left != 0; left &= left - 1) {
             const int rr = __builtin_ctz(left);
             float o[4], m, l;                                // channels lane, lane + 64, ...
             redo_row(rr, o, m, l);
