@@ -21,9 +21,12 @@ TOL = {"f32": 2e-6, "bf16": 2.0 ** -8, "f16": 2.0 ** -10}      # one rounding of
 SHAPES = [
     ([1], 1, 1, 16),                    # one item
     ([7, 0, 13, 64], 64, 5, 48),        # three items per row, pieces that end inside a row's heads
-    ([33, 150, 2], 40, 32, 128),        # two items per thread; a segment longer than stated
+    ([33, 150, 2], 40, 32, 128),        # a segment longer than stated
     ([200] * 19 + [101], 200, 32, 128), # many pieces
     ([2060, 3], 2060, 32, 256),         # more items than are numbered together
+    ([150] * 30 + [2], 40, 32, 128),    # two items per thread in the assembly, segments longer than stated
+    ([33, 150, 2], 100000, 32, 128),    # stated far too long: fewer pieces than that would take
+    ([1, 2, 3] * 3000 + [500], 500, 2, 32),   # more segments than a launch has blocks for pieces: one each, in rounds
 ]
 
 
@@ -74,3 +77,39 @@ def test_moves(lens, longest, hkv, d, dtype, pairing, layout):
     assert np.all(got_k[0] == 3.0) and np.all(got_v[0] == 3.0) and np.all(got_k[1 + total:] == 3.0) and np.all(got_v[1 + total:] == 3.0)
     want = np.concatenate([np.arange(s.new_start, s.new_start + s.len) for s in segs])
     assert pos[rows].cpu().numpy().tolist() == want.tolist()
+
+
+def test_a_loose_stated_length_costs_little():
+    """The stated longest length only sizes the launch: a bound 200 times too large may not cost a multiple of the call."""
+    n_seg, length, hkv, d = 30, 160, 32, 128
+    n = n_seg * length
+    ts, hs = pl.store_strides(n, hkv, d, "head")
+    desc = cf.make_desc(hkv, hkv, d, "bf16", 1.0e4, 8192, HALF, store_token_stride=ts, store_head_stride=hs)
+    table = cf.segments_to_device(cf.segments_array([(i * length, length, 5, 9 * i, cf.CF_SEG_DOC, i) for i in range(n_seg)]))
+    k = torch.randn(n * hkv * d, device="cuda").to(torch.bfloat16)
+    k_out, v_out, flag = torch.empty_like(k), torch.empty_like(k), torch.zeros(1, **I32)
+    q_off, count, final_off, final_len = torch.zeros(2, **I32), torch.full((1,), n_seg, **I32), torch.zeros(1, dtype=torch.int64, device="cuda"), torch.zeros(1, **I32)
+
+    def moved(longest):
+        cf.cf_reposition_keys(desc, k, k_out, table, n_seg, n, longest, flag)
+
+    def assembled(longest):
+        cf.cf_assemble_cache(desc, k, k, n, None, None, q_off, table, count, n_seg, 1, 1, longest, final_off, n, ts, hs, k_out, v_out, final_len, None, flag)
+
+    def us(call, longest):
+        times = []
+        for _ in range(9):
+            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            e0.record()
+            for _ in range(20):
+                call(longest)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1) * 50)
+        return sorted(times)[4]
+
+    for call in (moved, assembled):
+        fits, loose = us(call, length), us(call, 200 * length)
+        print(f"{call.__name__}: {fits:.1f} us, stated 200 times longer {loose:.1f} us", flush=True)
+        assert loose <= 3 * fits             # (without a limit on the launch: over 20 times)
+    assert flag.item() == 0
