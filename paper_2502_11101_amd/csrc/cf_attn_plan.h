@@ -78,8 +78,11 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     // not up, attn_tile_kernel's calls that 256 does not divide measured: 6 decode queries x 32 heads over 1017-1573 tokens (192
     // units, two splits against one) 37.6 -> 26.5 us, 17 x 4 heads over 1355-1704 (68 units, four against three) 26.3 -> 19.0,
     // 28 x 2 heads over 723 (56 units) 18.6 -> 13.1, 3 layer queries x 32 heads, 7 short documents (96 units) 28.0 -> 22.2.
-    // The exception is a long batch that would leave over a quarter of the CUs idle: its halves even out unequal lengths (36 decode
-    // queries x 4 heads over 1000-5000 tokens, 144 units: 67 us with two splits, 73 with one; 50 queries, 200 units: 85 and 77).
+    // The exception is a long batch that would leave over a quarter of the CUs idle: its halves even out unequal lengths, which the host
+    // does not know, and cost less where the lengths are equal than they save where they are not.  Decode queries x 4 heads, one
+    // split against two: up to 4096 tokens, lengths a fifth of that and more: 144 units 78 -> 64 us, 160 78 -> 62, 176 80 -> 74; up to
+    // 12000: 198 -> 154, 204 -> 186, 207 -> 175; all of 4096: 82 -> 95, 82 -> 97, 83 -> 100.  At 192 units and more one is the better
+    // (50 queries of 1000-5000 tokens, 200 units: 77 against 85), and for shorter lists (1024 tokens, 160 units: 31 against 35 and 39).
     const bool halves = !p.producers && p.units > 128 && p.units < 192 && est_tiles > 128;
     int64_t ns = halves ? 2 : 256 / p.units;
     const int64_t cap = est_tiles / (2 * p.groups) > 1 ? est_tiles / (2 * p.groups) : 1;
