@@ -404,7 +404,9 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
         using T = typename E::type;
         // (the kernel's first argument read anew: kept in registers for this, its fields would crowd those of the main loop)
         uint64_t kernarg = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(kernarg));
+        uint32_t lo = (uint32_t)kernarg, hi = (uint32_t)(kernarg >> 32);
+        asm volatile("" : "+v"(lo), "+v"(hi));
+        kernarg = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)hi) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
         const auto* ka = reinterpret_cast<const __attribute__((address_space(4))) AttnArgs*>(kernarg);
         const int half = d >> 1, row = row_base + wave * 16 + rr;
         const int head = (int)div_exact((unsigned)row, (unsigned)tq), t = row - head * tq;
