@@ -167,7 +167,7 @@ size_t cf_prefill_workspace_bytes(const cf_layer_desc* desc, int32_t batch, int3
     if (check_desc(desc) != CF_OK) return 0;
     if (batch <= 0 || max_tq <= 0 || seg_stride <= 0 || max_kv_tokens < 0) return 0;
     size_t n = mfma_path_supported(desc) ? mfma_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens)
-               : plain_path_supported(desc, batch, max_tq, seg_stride)
+               : plain_path_supported(desc, batch, max_tq, seg_stride, max_kv_tokens)
                    ? plain_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens)
                    : generic_workspace_bytes(desc, batch, max_tq, seg_stride);
     return (n + 255) & ~(size_t)255;
@@ -264,7 +264,7 @@ static cf_status prefill_impl(const cf_layer_desc* desc, const void* q, const in
     const RopeFreq& f = rope_freq(desc);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (mfma_path_supported(desc)) return launch_attention_mfma(a, f, s, prune);
-    if (!row_by_row && plain_path_supported(desc, batch, max_tq, seg_stride)) return launch_attention_plain(desc, a, f, s, prune);
+    if (!row_by_row && plain_path_supported(desc, batch, max_tq, seg_stride, max_kv_tokens)) return launch_attention_plain(desc, a, f, s, prune);
     st = launch_attention_generic(a, f, s);
     if (st != CF_OK || !prune) return st;
     return launch_prune_step(a, prune, s);

@@ -748,9 +748,17 @@ void launch_plain(const AttnArgs& a, const RopeFreq& f, const Plan& p, hipStream
 
 }  // namespace
 
-// Tables past kMaxSegs entries, grids past the hardware's and counts past the plan's 32 bits stay with the row-by-row kernel.
-bool plain_path_supported(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride) {
+// Tables past kMaxSegs entries, grids past the hardware's and counts past the plan's 32 bits stay with the row-by-row kernel, and so
+// do many queries of a row or two over a few tokens: a workgroup takes the 10 us of its round trips (23 at 256 channels) whatever
+// it holds, a CU has one or two of them, and a wavefront per row is through such a row in a fraction of that.  A row there costs about
+// as much as 45 tokens.  256 queries x 32 heads, row by row against this kernel: fp32, d = 64, 1 row over 21 tokens 64 and 157 us, over 61
+// 102 and 161, over 201 322 and 267; 3 rows over 23 162 and 159; bf16, d = 128 (one workgroup per CU), 1 row over 61 161 and 367, over
+// 201 500 and 466; fp16, d = 256, 1 row over 21 163 and 740.  64 queries x 32 heads: fp32 25 and 45, 46 and 49, 101 and 71; 16 x 32: 25
+// and 18, 31 and 17.
+bool plain_path_supported(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens) {
     const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * max_tq, units_per_b = d->n_kv_heads * ((rows + 63) / 64 + 1);
+    const int64_t few = plain_per_cu(d->dtype == CF_F32, padded_dim(d->head_dim), 1) == 1 ? 160 : 110;
+    if ((int64_t)batch * d->n_kv_heads >= 2048 && rows <= 3 && max_kv_tokens <= few && rows * (max_kv_tokens + 45) <= few) return false;
     return seg_stride <= kMaxSegs && batch <= 65535 && rows < (1 << 20) && units_per_b <= 65535 && batch * units_per_b <= 0x7fffffff;
 }
 

@@ -57,3 +57,22 @@ def test_prune_step_after_the_fp32_precision_kernel(dtype, pairing, d, heads, do
         ref = orc.prune_topk(b["score"][q].cpu().numpy(), st.doc_lens[st.query_docs[q]], list(range(docs)), keep)
         assert a["keep"][q, :keep].tolist() == ref
         assert float(a["mass"][q, :docs + 2].sum()) == pytest.approx(heads * 2, rel=1e-5)
+
+
+# many queries of few rows over few tokens go row by row: the largest list that does, the next one, and one query less than many
+ROUTES = [("f32", HALF, 16, 1, 32, 64, 65, True), ("f32", HALF, 16, 1, 32, 64, 66, False), ("f32", HALF, 16, 2, 32, 64, 10, True),
+          ("f32", HALF, 16, 3, 32, 64, 10, False), ("bf16", INTER, 80, 1, 32, 64, 115, True), ("bf16", INTER, 80, 1, 32, 64, 116, False),
+          ("f16", HALF, 144, 2, 32, 64, 35, True), ("bf16", HALF, 16, 1, 32, 63, 20, False)]
+
+
+@pytest.mark.parametrize("dtype,pairing,d,tq,heads,batch,tokens,by_row", ROUTES)
+def test_many_queries_of_few_rows(dtype, pairing, d, tq, heads, batch, tokens, by_row):
+    print(f"few rows {dtype} d={d} {batch} x {tq} rows, {heads} heads, {tokens} tokens", flush=True)
+    doc = (tokens - tq) // 2
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name=f"few_{dtype}_{tokens}", geometry=wl.Geometry(heads, heads, d, dtype, 1.0e4, 8192),
+                    n_store_docs=2 * batch, docs_per_query=2, batch=batch, doc_len_range=(doc, doc), tq=tq, prefix_len=tokens - tq - 2 * doc,
+                    doc_stored_start=5, n_planted=1)
+    desc = G.desc_of(cfg, pairing)
+    rows_ws = -(-batch * tq * heads * (4 + 1) * 8 // 256) * 256      # prefix, two documents, own block: a pair per row and entry, and one
+    assert (cf.cf_prefill_workspace_bytes(desc, batch, tq, 4, tokens) == rows_ws) == by_row
+    _run_single_layer(cfg, pairing, seed=tokens)
