@@ -79,6 +79,39 @@ def test_moves(lens, longest, hkv, d, dtype, pairing, layout):
     assert pos[rows].cpu().numpy().tolist() == want.tolist()
 
 
+def _median_us(call):
+    times = []
+    for _ in range(9):
+        e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+        e0.record()
+        for _ in range(20):
+            call()
+        e1.record()
+        torch.cuda.synchronize()
+        times.append(e0.elapsed_time(e1) * 50)
+    return sorted(times)[4]
+
+
+def test_a_long_table_is_not_added_up_by_every_piece():
+    """2000 documents of 20 tokens: the blocks of the assembly each add up the table, so they are few; the time stays within a small
+    multiple of the re-positioning's (half the bytes, no table): 4 times, over 9 with as many blocks as pieces."""
+    n_seg, length, hkv, d = 2000, 20, 8, 128
+    n = n_seg * length
+    ts, hs = pl.store_strides(n, hkv, d, "head")
+    desc = cf.make_desc(hkv, hkv, d, "bf16", 1.0e4, 1 << 20, HALF, store_token_stride=ts, store_head_stride=hs)
+    table = cf.segments_to_device(cf.segments_array([(i * length, length, 5, 9 * i, cf.CF_SEG_DOC, i) for i in range(n_seg)]))
+    k = torch.randn(n * hkv * d, device="cuda").to(torch.bfloat16)
+    k_out, v_out, flag = torch.empty_like(k), torch.empty_like(k), torch.zeros(1, **I32)
+    q_off, count, final_off, final_len = torch.zeros(2, **I32), torch.full((1,), n_seg, **I32), torch.zeros(1, dtype=torch.int64, device="cuda"), torch.zeros(1, **I32)
+    moved = _median_us(lambda: cf.cf_reposition_keys(desc, k, k_out, table, n_seg, n, length, flag))
+    assembled = _median_us(lambda: cf.cf_assemble_cache(desc, k, k, n, None, None, q_off, table, count, n_seg, 1, 1, length, final_off, n, ts, hs,
+                                                        k_out, v_out, final_len, None, flag))
+    print(f"long table: re-positioning {moved:.1f} us, assembly {assembled:.1f} us", flush=True)
+    assert flag.item() == 0 and final_len.item() == n
+    assert torch.equal(v_out, k)
+    assert assembled <= 7 * moved
+
+
 def test_a_loose_stated_length_costs_little():
     """The stated longest length only sizes the launch: a bound 200 times too large may not cost a multiple of the call."""
     n_seg, length, hkv, d = 30, 160, 32, 128
@@ -96,20 +129,8 @@ def test_a_loose_stated_length_costs_little():
     def assembled(longest):
         cf.cf_assemble_cache(desc, k, k, n, None, None, q_off, table, count, n_seg, 1, 1, longest, final_off, n, ts, hs, k_out, v_out, final_len, None, flag)
 
-    def us(call, longest):
-        times = []
-        for _ in range(9):
-            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
-            e0.record()
-            for _ in range(20):
-                call(longest)
-            e1.record()
-            torch.cuda.synchronize()
-            times.append(e0.elapsed_time(e1) * 50)
-        return sorted(times)[4]
-
     for call in (moved, assembled):
-        fits, loose = us(call, length), us(call, 200 * length)
+        fits, loose = (_median_us(lambda: call(longest)) for longest in (length, 200 * length))
         print(f"{call.__name__}: {fits:.1f} us, stated 200 times longer {loose:.1f} us", flush=True)
         assert loose <= 3 * fits             # (without a limit on the launch: over 20 times)
     assert flag.item() == 0
