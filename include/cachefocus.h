@@ -123,7 +123,8 @@ typedef struct cf_segment {
  *   segs         device [n_seg]; kind is ignored, all offsets index k_in/k_out.
  *   n_store_tokens  host: number of tokens in k_in/k_out; entries reaching beyond it are
  *                skipped and flagged CF_FLAG_BAD_SEGMENT.
- *   max_seg_len  host: launch-sizing hint (>= 1); longer segments are still processed fully.
+ *   max_seg_len  host: launch-sizing hint (>= 1); longer segments are still processed fully, and a
+ *                value far above the real lengths costs little.
  * A rotation by 0 positions copies bit-exactly.  Rotation arithmetic is fp32 with the angle
  * reduced in fp64; the result is rounded once (RNE) to desc->dtype.
  */
@@ -311,8 +312,11 @@ CF_API cf_status cf_assemble_cache(const cf_layer_desc* desc, const void* k_stor
  * S += s^l into score_accum, which must be given) followed — when `prune` is not NULL — by the
  * prune event of that layer: cf_prune_topk on the accumulated scores, cf_assign_positions for the
  * survivors and cf_gather_segments into the NEXT layer's table.  Results are identical to the
- * four separate calls; on the 16-bit path the mass reduction, ranking, allocation and table rebuild
- * run in one kernel, so a layer costs three launches instead of six.
+ * four separate calls; except where the row-by-row kernel runs (more than 256 table entries, or many
+ * queries of a row or two over a few tokens outside the 16-bit kernels' shapes) the mass reduction,
+ * ranking, allocation and table rebuild run in one kernel, as long as a query's tables fit its LDS, so a
+ * layer costs three launches instead of six — two where the plan has one split and the
+ * fp32-precision kernel serves it.
  * The current table (segs / n_seg / q_new_start) is only read; the prune step writes next_segs,
  * next_n_seg, new_start, q_start, which therefore must not alias the current ones.
  * All pointers in cf_prune_step are device memory with the shapes given at the stand-alone calls
@@ -329,8 +333,9 @@ CF_API cf_status cf_assemble_cache(const cf_layer_desc* desc, const void* k_stor
  * deferred.  Rules: every call passes the number of layers pending before it (0 after a call that did not defer); at
  * most CF_MAX_PENDING layers may be pending; the pending layers and the call that takes them in must use the same
  * workspace, descriptor, batch, max_tq, seg_stride and max_kv_tokens, and the same, unchanged segs / n_seg / q_off /
- * q_new_start (a prune step changes the tables, so scores cannot be pending across one).  Shapes served by the generic
- * kernel do not defer: there a `defer` call accumulates at once and `n_pending` is ignored, with the same results.
+ * q_new_start (a prune step changes the tables, so scores cannot be pending across one).  Only the 16-bit kernels' shapes
+ * (bf16 / fp16, head_dim 128, half-split pairs, at most 256 table entries) defer: elsewhere a `defer` call accumulates at
+ * once and `n_pending` is ignored, with the same results.
  */
 #define CF_MAX_PENDING 15
 typedef struct cf_prune_step {

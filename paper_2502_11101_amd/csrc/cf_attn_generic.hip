@@ -1,8 +1,9 @@
 // Generic prefill attention: any dtype, head_dim (multiple of 16, <= 256) and RoPE pairing.
 // One wavefront per (query, row, q head) walks the query's segments with an online softmax
 // (Eq. 1), rotating each key on the fly by its relative position shift (Eq. 5) in fp32.
-// It serves the tables that do not fit the other kernels (more than 256 segments per query): their tables live in LDS or in
-// registers, this kernel walks the table in memory.
+// It serves the tables that do not fit the other kernels (more than 256 segments per query: their tables live in LDS or in
+// registers, this kernel walks the table in memory), and outside the 16-bit kernels' shapes many queries of a row or two over a few
+// tokens and what cf_prefill_attention_static can only fit this way.
 //
 // Per row it leaves, for every segment, the pair (running max at the end of the segment,
 // sum of exp2(score - that max) over the segment's visible tokens) and the row's final

@@ -15,10 +15,14 @@
 //     in the fp32 accumulators, so the result has fp32 precision at a third of the 16-bit matrix rate: 2048 -> 384 matrix cycles
 //     per 16 rows x 32 tokens x 128 channels and product, against v_mfma_f32_16x16x4f32.
 //
-// Bound by: the memory round trips of a launch at these sizes, and beyond them the matrix pipe (fp32) or the issue of the softmax and
-// the splitting (16-bit).  Measured against the row-by-row kernel of cf_attn_generic.hip, whole layer calls with a prune event:
-// bf16, interleaved pairs, 32 heads, 10 documents of 100-200 tokens, 48 query rows: 909 -> 31 us (attention 871 -> 16 us, 26.7 MB of
-// keys, values, queries and outputs); fp32, head_dim 64, 4 heads, 4 x 32 tokens, 8 rows: 54 -> 18 us.
+// Infinities and NaN: a tile's product multiplies the tokens a row does not see by zero, and parts do not add up to an infinity;
+// rows whose sums are not finite at the end are gone over once more token by token (redo_row).
+//
+// Bound by the latency of a launch's memory round trips at the sizes measured: bf16, interleaved pairs, 32 heads, 10 documents of 100-200
+// tokens, 48 query rows: 17.2 us for 26.7 MB of keys, values, queries and outputs, the wavefronts waiting 56 % of their cycles, matrix
+// pipe busy 13 %, VALU issue 33 %; the merge 8.4 us.  Whole layer calls with a prune event, from the row-by-row kernel of
+// cf_attn_generic.hip to this one: 916 -> 31.8 us (31.0 before non-finite rows were gone over again); fp32, head_dim 64, 4 heads,
+// 4 x 32 tokens, 8 rows: 54 -> 18.2 us (17.9).  fp16 at the first one's shape takes 10 % more than bf16.
 #include "cf_attn_plan.h"
 #include "cf_attn_tile.h"
 

@@ -22,7 +22,7 @@ NEAR_MASS_TOL = {"f32": 1e-5, "bf16": 2e-4, "f16": 2e-4}
 
 def rounds_moved_keys(g, pairing, seg_stride) -> bool:
     """Whether a call of this shape takes the 16-bit MFMA kernels, which round a moved key once to the storage
-    type (the generic kernel moves keys in fp32 on the fly and rounds nothing)."""
+    type (the others turn the query, or the keys on the fly, in fp32 and round nothing)."""
     return g.dtype != "f32" and g.head_dim == 128 and pairing == cf.CF_ROPE_HALF and seg_stride <= 256
 
 

@@ -195,7 +195,7 @@ def test_assign_keep_only_lists_survivors():
     assert q_start.item() == 99 and torch.all(new_start == 5)
 
 
-# ----------------------------------------------------------------------------- generic attention path
+# ----------------------------------------------------------------------------- attention outside the 16-bit kernels' shapes
 def _run_single_layer(cfg, pairing=cf.CF_ROPE_HALF, seed=None, mass_tol=None, layout="token"):
     """Masses are checked twice.  Against the rounded-key reference (the oracle on keys moved by Eq. 5 and
     rounded once to the storage type, as the fused kernels hold them) the bound is always the tight one,
@@ -283,6 +283,7 @@ def test_tiny_fp32_configuration_end_to_end():
                                                     ("f16", cf.CF_ROPE_HALF, 64, 6, 3),
                                                     ("f32", cf.CF_ROPE_HALF, 256, 2, 1)])
 def test_generic_path_shapes(dtype, pairing, d, hq, hkv, layout):
+    """Shapes outside the 16-bit kernels' (the fp32-precision kernel; row by row: test_gpu_plain_prune.py)."""
     base = wl.CONFIGS["tiny_f32"]
     cfg = wl.scaled(base, name=f"generic_{dtype}_{d}", geometry=wl.Geometry(hq, hkv, d, dtype, 1.0e6, 32768),
                     n_store_docs=12, docs_per_query=4, batch=3, doc_len_range=(1, 150), tq=11, prefix_len=5,
@@ -455,7 +456,7 @@ def test_mfma_path_seeded_random_shapes(dtype, layout, hq, hkv, tq, docs, len_ra
 @pytest.mark.parametrize("docs,fused", [(254, False), (300, False), (300, True)])
 def test_more_segments_than_the_16_bit_kernels_hold(docs, fused):
     """254 documents fill the 256-entry segment table of the 16-bit kernels exactly; 300 do not fit and the call
-    takes the generic kernel (and, fused, the stand-alone prune kernels) — same results either way."""
+    takes the row-by-row kernel (and, fused, the stand-alone prune kernels) — same results either way."""
     cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name=f"segs_{docs}", geometry=wl.Geometry(4, 2, 128, "bf16", 1.0e4, 8192),
                     n_store_docs=docs, docs_per_query=docs, batch=1, doc_len_range=(1, 9), tq=3, prefix_len=2,
                     doc_stored_start=2, n_planted=3)

@@ -45,7 +45,7 @@ SHAPES = {
     # more than 64 table entries: the segment table lives in LDS instead of registers
     "few_rows_long_table": (wl.Geometry(4, 4, 128, "bf16", 1.0e6, 32768), 1, 16, 2, 70, (1, 9)),
     "many_rows_long_table": (wl.Geometry(14, 2, 128, "bf16", 1.0e6, 32768), 1, 13, 2, 70, (1, 9)),
-    # fp32, head_dim 64: the generic kernel
+    # fp32, head_dim 64: the fp32-precision kernel
     "f32_generic": (wl.Geometry(4, 2, 64, "f32", 1.0e6, 32768), 2, 8, 4, 4, (20, 40)),
 }
 # fp16 shapes whose plans have several splits (used by the range test at the end)

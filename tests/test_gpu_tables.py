@@ -59,7 +59,7 @@ def _attend(g, t, tables, tq, q_stored, q_pos, n_store, n_docs, score0=None):
 
 
 # geometry, tq, pieces per document: the single-wavefront mass path (at most 64 entries), the block-wide one (more), the
-# kernel for many stacked rows, and the fp32 kernel
+# kernel for many stacked rows, and the fp32-precision kernel
 SPLIT_CASES = {
     "few_rows_small_table": (wl.Geometry(4, 4, 128, "bf16", 1.0e4, 8192), 6, 3),
     "few_rows_long_table": (wl.Geometry(4, 4, 128, "bf16", 1.0e4, 8192), 6, 30),
