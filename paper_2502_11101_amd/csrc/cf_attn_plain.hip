@@ -22,7 +22,7 @@
 // tokens, 48 query rows: 17.2 us for 26.7 MB of keys, values, queries and outputs, the wavefronts waiting 56 % of their cycles, matrix
 // pipe busy 13 %, VALU issue 33 %; the merge 8.4 us.  Whole layer calls with a prune event, from the row-by-row kernel of
 // cf_attn_generic.hip to this one: 916 -> 31.8 us (31.0 before non-finite rows were gone over again); fp32, head_dim 64, 4 heads,
-// 4 x 32 tokens, 8 rows: 54 -> 18.2 us (17.9).  fp16 at the first one's shape takes 10 % more than bf16.
+// 4 x 32 tokens, 8 rows: 54 -> 18.2 us (17.9).  fp16 at the first one's shape takes 5 % more than bf16.
 #include "cf_attn_plan.h"
 #include "cf_attn_tile.h"
 
@@ -378,10 +378,10 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
                 const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(vb + 32 * db + 16 * S::kVRow));
                 const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
                 const uint4 va = make_uint4(l2.x, l2.y, h2.x, h2.y);
-                if constexpr (DT == CF_F16) {                // the scaled parts: their sum joins the first's
-                    f32x4 t = Mma<CF_F16>::run(va, pp[2], f32x4{0.f, 0.f, 0.f, 0.f});
-                    t = Mma<CF_F16>::run(va, pp[1], t * 0x1p-11f);
-                    acc[db] = Mma<CF_F16>::run(va, pp[0], acc[db] + t * 0x1p-11f);
+                if constexpr (DT == CF_F16) {                // the scaled parts' sum joins the first's; three chains (one: up to 6 % slower)
+                    const f32x4 none = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const f32x4 t = Mma<CF_F16>::run(va, pp[1], none), u = Mma<CF_F16>::run(va, pp[2], none);
+                    acc[db] = Mma<CF_F16>::run(va, pp[0], acc[db]) + (t + u * 0x1p-11f) * 0x1p-11f;
                 } else {
 #pragma unroll
                     for (int n = S::kPParts - 1; n >= 0; --n) acc[db] = Mma<CF_BF16>::run(va, pp[n], acc[db]);
