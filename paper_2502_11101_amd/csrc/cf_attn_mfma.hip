@@ -7,11 +7,10 @@
 //   * At most 4 row blocks (MHA, short queries: HBM- and latency-bound): attn_tile_kernel, 32-token tiles,
 //     one row block per wavefront, every wavefront loads, stages and computes; two groups of four wavefronts
 //     per workgroup stream disjoint runs of tiles.
-//   * More (GQA groups, long queries: MFMA-bound): attn_pipe_kernel, 32-token units, two wavefronts load, rotate
-//     and stage while six do the math, two row blocks each (up to 192 rows per workgroup), software-pipelined
-//     over three units.
+//   * More (GQA groups, long queries: bound by instruction issue): attn_wide_kernel, 32-token tiles, two or three row
+//     blocks per wavefront (up to 192 rows per workgroup), one or two groups of four wavefronts.
 // Per tile, in both:
-//   * the tiles two steps ahead are in flight in registers (coalesced 16-byte loads),
+//   * the tiles ahead (two, or one) are in flight in registers (coalesced 16-byte loads),
 //   * the key tile is rotated in registers by its segment's relative position shift (Eq. 5;
 //     cos/sin per 2-D slice from an fp64-reduced angle), rounded once to the storage type and
 //     staged into LDS — rotated keys never return to memory; V is staged as loaded,
@@ -233,221 +232,236 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
 }
 
 // ---------------------------------------------------------------------------------------------
-// The attention kernel for many stacked rows (GQA groups, long queries), where staging costs as much issue time as
-// the math: eight wavefronts, of which the first two only load, rotate (Eq. 5) and stage, and six only do the math,
-// two 16-row blocks each (up to 192 rows per workgroup) — so the rotation and the LDS writes run beside the MFMAs and
-// the softmax instead of before them.  The unit of work is 32 tokens, and a math wavefront keeps three units in flight, so that its MFMAs and its softmax arithmetic — which depend on each other
-// inside a unit — come from different units and run side by side:
-//   iteration i:   S^T(i+1) = K(i+1) Q^T      16 MFMAs  \  interleaved in one basic block
-//                  softmax of S^T(i) -> P(i)   VALU      |  (scheduling groups), no branch inside
-//                  O^T += V^T(i-1) P^T(i-1)    16 MFMAs  /
-//   with the K fragments of unit i+2 and the V^T fragments of unit i requested from LDS inside the block, for the
-//   next iteration.  The softmax reference is the stale maximum of tile_math (kProbLimit); the rare iteration in which
-//   a reference has to move is repaired after the block: maximum, rescale of everything accumulated (which by then
-//   includes unit i-1), probabilities redone.
-// Staging: units are staged in pairs into a ring of eight unit slots; one workgroup barrier per pair.  With the barrier
-// of step s passed, pair s is staged; the math of units 2k and 2k+1 touches pairs k-1 and k (V) and k+1 (K) and runs
-// after the barrier of step k+1, while the producers stage pair k+2 over pair k-2, which no one reads any more.
-constexpr int kPipeUnit = 32;                        // tokens per unit
-constexpr int kPipeSlots = 8;                        // unit slots in LDS: four pairs
-constexpr int kPipeKUnit = kPipeUnit * kKRow;        // bytes
-constexpr int kPipeVUnit = kPipeUnit * kD * 2;
-constexpr int kPipeDesc = 16;                        // unit descriptors kept for the math wavefronts
-constexpr int kPipeCs = 4;                           // cos/sin tables: the pair being staged and the next may use two each
+// The attention kernel for many stacked rows (GQA groups, long queries), where the instructions that a SIMD can issue are the
+// bound: per 32-token tile and 48 rows a wavefront has 48 MFMAs (768 cycles of matrix pipe), about 145 other vector
+// instructions and 24 exponentials.  Four wavefronts own NRB 16-row blocks each — 128 or 192 rows of a workgroup, so that a
+// staged key serves three row blocks per fragment read — and all of them load, rotate (Eq. 5) and stage the tiles they share.
+// A tile passes through two phases of a wavefront:
+//   M (matrix)   O^T += V^T P^T of tile t - 1 (8 * NRB MFMAs), S^T = K Q^T of tile t (8 * NRB MFMAs); between the second half of
+//                the scores tile t + 1 is rotated in registers and staged; the fragments are read from LDS a few MFMAs ahead of use
+//   V (vector)   tile t + 2 requested from memory, softmax of tile t against a stale maximum (kProbLimit)
+// The two wavefronts of a SIMD should be in different phases:
+//   GROUPS == 2: two groups of four wavefronts stream disjoint runs of the workgroup's tiles, the second group one phase behind the
+//                first (a barrier after every phase); their results meet in LDS at the end.  For plans of up to 256 units.
+//   GROUPS == 1: one group per workgroup, two workgroups per CU, one barrier per tile: more units than CUs.  One hides the other's
+//                prologue and tail as well: 30 documents of 160 rows and 192 tokens x 32 heads (960 units) 53 us, two groups 77.
+// Against the kernel before it (two wavefronts that load and stage, six with two row blocks each, software-pipelined): 64 queries,
+// 2 kv heads, 384 rows, 3064 tokens, fp16: 130 -> 111 us (690 TFLOP/s); the 30 documents above 72 -> 53; one query, 4 kv heads, 448
+// rows, 7600 tokens 26 us both (a third of it prologue and merge).  Two tiles in flight instead of one, or the rotation on the
+// matrix cores (diagonal matrices of cosines in three 16-bit parts), no longer fit the 256 registers or cost more than they save.
+constexpr int kWideTile = 32;                        // tokens per tile
+constexpr int kWideK = kWideTile * kKRow;            // bytes
+constexpr int kWideVRow = 288;                       // bytes per token of a staged V tile
+constexpr int kWideV = kWideTile * kWideVRow;
 
-template <int DT, bool REG_TABLE>
-__global__ __launch_bounds__(kPcWaves * kWave, 2) void attn_pipe_kernel(AttnArgs a, RopeFreq freq, Plan p) {
-    constexpr int NRB = kPcNrb;
-    constexpr int kPT = kPcProducers * kWave;        // producer threads: 128
-    constexpr int kKItems = kPipeUnit * 8 / kPT;     // (row, chunk pair) items per producer thread and unit: 2
-    constexpr int kVItems = kPipeUnit * 16 / kPT;    // (row, chunk) items: 4
+// A register table's fields moved to LDS: the kernel has no registers left to carry them through its loop.
+struct LdsSegs {
+    const int4* e;              // two per segment: (first token lo, hi, visible, shift), (first tile, end, own block, -)
+    int n;
+};
+__device__ __forceinline__ FoundSegment find_segment(const LdsSegs& t, int x, int, int prev) {
+    // the walk goes on from `prev`: the next entry that owns a tile (x < total: there is one)
+    int s = prev + 1;
+    int4 u = t.e[2 * s], w = t.e[2 * s + 1];
+    while (__builtin_amdgcn_readfirstlane(w.y) <= x && s + 1 < t.n) {
+        ++s;
+        u = t.e[2 * s];
+        w = t.e[2 * s + 1];
+    }
+    FoundSegment f;
+    f.seg = s;
+    f.tok = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(u.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(u.x));
+    f.vis = __builtin_amdgcn_readfirstlane(u.z);
+    f.delta = __builtin_amdgcn_readfirstlane(u.w);
+    f.first = __builtin_amdgcn_readfirstlane(w.x);
+    f.end = __builtin_amdgcn_readfirstlane(w.y);
+    f.self = __builtin_amdgcn_readfirstlane(w.z);
+    return f;
+}
+
+// The lane's index from the hardware: where it is needed seldom, so that nothing derived from it is kept in registers.
+__device__ __forceinline__ int lane_anew() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
+// x + the other half's x, for lane pairs 16 and then 32 apart: every lane ends with the sum over the four groups of 16 lanes
+__device__ __forceinline__ float add_lane_groups(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+template <int DT, int NRB, int GROUPS, bool REG_TABLE>
+__global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArgs a, RopeFreq freq, Plan p) {
     __shared__ SegTable tbl;
-    __shared__ __attribute__((aligned(16))) unsigned char k_ring[kPipeSlots][kPipeKUnit];
-    __shared__ __attribute__((aligned(16))) unsigned char v_ring[kPipeSlots][kPipeVUnit];
-    __shared__ __attribute__((aligned(16))) float2 cs_lds[kPipeCs][kHalf];
-    __shared__ int4 desc_ring[kPipeDesc];            // (segment, first token, tokens, own block) of unit u in entry u & 15
+    __shared__ double freq_lds[kHalf];
+    __shared__ int4 seg_lds[2 * kWave];
+    constexpr int kGroupBytes = 2 * kWideK + 3 * kWideV;
+    constexpr int kStageBytes = GROUPS * kGroupBytes;
+    constexpr int kMergeBytes = GROUPS == 1 ? 0 : 2 * kWaves * NRB * 4 * kWave * (int)sizeof(f32x4);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kStageBytes > kMergeBytes ? kStageBytes : kMergeBytes];
+    __shared__ __attribute__((aligned(16))) float2 cs_lds[GROUPS][2][kHalf];
+    __shared__ float2 red_ml[GROUPS][kWaves * NRB * 16];
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & (kThreads - 1);
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int grp = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
     const int li = lane & 15, lg = lane >> 4;
+    unsigned char* const k_lds = lds + grp * kGroupBytes;
+    unsigned char* const v_lds = k_lds + 2 * kWideK;
 
-    const int bid = blockIdx.x;
-    const int rg = bid / p.x_count;
-    const int x = bid - rg * p.x_count;
-    const int split = x % p.nsplit;
-    const int hkv = (x / p.nsplit) % a.n_kv_heads;
-    const int b = __builtin_amdgcn_readfirstlane(x / (p.nsplit * a.n_kv_heads));
-    const int unit = (b * a.n_kv_heads + hkv) * p.n_rg + rg;
+    // grid (split * batch + query, kv head * row groups + row group): a (query, kv head)'s row groups, which read the same keys, come to
+    // one XCD where eight divides the first dimension
+    const int split = p.nsplit == 1 ? 0 : (int)div_exact(blockIdx.x, (unsigned)a.batch);
+    const int b = (int)blockIdx.x - split * a.batch;
+    const int hkv = p.n_rg == 1 ? (int)blockIdx.y : (int)div_exact(blockIdx.y, (unsigned)p.n_rg);
+    const int rg = (int)blockIdx.y - hkv * p.n_rg;
+    const int unit = b * p.units_per_b + (int)blockIdx.y;
     const int group = p.group;
-    const QueryHead qh = load_query_head<false>(a, b, REG_TABLE ? lane : (int)threadIdx.x);
+    const QueryHead qh = load_query_head(a, b, REG_TABLE ? lane : (int)threadIdx.x);
+    if (wave == 0 && grp == 0) freq_lds[lane] = freq.rev[lane];
     const int tq = min(qh.tq_raw, a.max_tq);
     const int row_base = rg * p.blocks_rg * 16;
     const int row_limit = min(group * tq, row_base + p.blocks_rg * 16);
-    const int cw = wave - kPcProducers;              // index among the wavefronts that do the math
-    const bool has_rows = cw >= 0 && row_base + cw * NRB * 16 < row_limit;       // wavefront-uniform
+    const bool has_rows = row_base + wave * NRB * 16 < row_limit;        // wavefront-uniform
     uint4 qf[NRB][4];
-    int trow[NRB];
-    if (cw >= 0) load_q_fragments<NRB>(a, qh.q0, tq, hkv, group, cw * NRB, row_base, row_limit, li, lg, qf, trow);
+    {
+        int trow[NRB];
+        load_q_fragments<NRB>(a, qh.q0, tq, hkv, group, wave * NRB, row_base, row_limit, li, lg, qf, trow);
+    }
     RegSegTable rtbl;
     unsigned total;
     if constexpr (REG_TABLE) {
-        rtbl = build_reg_table(a, qh, lane, kPipeUnit);
+        rtbl = build_reg_table(a, qh, lane, kWideTile);
         total = (unsigned)rtbl.total;
+        if (threadIdx.x < kWave) {
+            seg_lds[2 * lane] = make_int4((int)(uint32_t)rtbl.tok, (int)(uint32_t)((uint64_t)rtbl.tok >> 32), rtbl.vis, rtbl.delta);
+            seg_lds[2 * lane + 1] = make_int4(rtbl.t0, rtbl.t1, rtbl.self, 0);
+        }
     } else {
-        build_table(a, qh, &tbl, kPipeUnit);
+        build_table(a, qh, &tbl, kWideTile);
         total = (unsigned)tbl.tile0[tbl.n];
     }
-    const int t_begin = split_begin(total, (unsigned)p.nsplit, split), t_end = split_begin(total, (unsigned)p.nsplit, split + 1);
-    const int n_units = t_end - t_begin;
-    const int n_pairs = (n_units + 1) >> 1;
-    const int n_steps = (n_pairs + 2) & ~1;          // producer steps (pairs 0 .. n_pairs and, to make it even, one more)
+    const unsigned nsub = (unsigned)(p.nsplit * GROUPS);
+    const int ss = split * GROUPS + grp;
 
-    if (wave < kPcProducers) {
-        // ------------------------------------------------------------------ producers
-        const double my_freq = freq.rev[tid & (kHalf - 1)];
-        // K items: row kr + 16*it, chunks kj and kj + 8.  The two rows that the sixteen lanes of one LDS write pass
-        // cover lie eight apart: their 16-byte chunks then fall into disjoint halves of the banks (rows are 272 bytes).
-        const int kr = ((tid >> 3) & 1) * 8 + (tid >> 4), kj = tid & 7;
-        const int vr = tid >> 4, vc = tid & 15;      // V items: row vr + 8*it, chunk vc
-        struct UnitRegs { uint4 ka[kKItems], kb[kKItems], v[kVItems]; };
-        struct Unit { Tile d; int cs; };
-        TileWalk<kPipeUnit> walk(t_begin, t_end);
-        int n_fetched = 0, n_tables = 0, last_seg = -1;
-        // Loads go through buffer descriptors whose base is the unit's first key / value (wavefront-uniform, worked
-        // out on the scalar unit); a thread's offsets inside a unit depend only on the distance between tokens and
-        // are kept: rows past the end of a ragged unit re-read its last row.
-        uint32_t row_bytes = 0, koff[kKItems], voff[kVItems];
-        auto fetch = [&](Unit& u, UnitRegs& r) {     // a fixed number of loads, as in attn_tile_kernel
-            if constexpr (REG_TABLE) u.d = walk.next(rtbl, lane);
-            else u.d = walk.next(tbl, lane);
-            if (tid == kWave) desc_ring[n_fetched & (kPipeDesc - 1)] = make_int4(u.d.seg, u.d.tok0, u.d.ntok, u.d.self);
-            ++n_fetched;
-            const TileSource src = tile_source(a, u.d, walk.c_tok, hkv);
-            if (src.row_bytes != row_bytes && src.last >= 0) {           // the store's and the own block's rows differ
-                row_bytes = src.row_bytes;
-#pragma unroll
-                for (int it = 0; it < kKItems; ++it) koff[it] = (uint32_t)(kr + (kPT / 8) * it) * row_bytes + 16 * kj;
-#pragma unroll
-                for (int it = 0; it < kVItems; ++it) voff[it] = (uint32_t)(vr + (kPT / 16) * it) * row_bytes + 16 * vc;
-            }
-            const int last = src.last;               // -1: no unit left, everything reads the first bytes of the workspace
-            const uint32_t last_row = last < 0 ? 0u : (uint32_t)last * row_bytes;
-            const uint32_t klast = last < 0 ? 0u : last_row + 16 * kj, vlast = last < 0 ? 0u : last_row + 16 * vc;
-            const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src.k), 0, 0x7fffffff, 0x00020000);
-            const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src.v), 0, 0x7fffffff, 0x00020000);
-            const int hi = last < 0 ? 0 : 128;       // the second chunk of a pair sits 64 channels on
-#pragma unroll
-            for (int it = 0; it < kKItems; ++it) {
-                const uint32_t off = kr + (kPT / 8) * it > last ? klast : koff[it];
-                r.ka[it] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, 0, 0));
-                r.kb[it] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off, hi, 0));
-            }
-#pragma unroll
-            for (int it = 0; it < kVItems; ++it) {
-                const uint32_t off = vr + (kPT / 16) * it > last ? vlast : voff[it];
-                r.v[it] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, off, 0, 0));
-            }
-        };
-        // the cos/sin table of a unit that starts a segment with a shift; units of one segment share theirs
-        // (made by the second producer wavefront, which also writes the unit descriptors)
-        auto table_for = [&](Unit& u) {
-            if (u.d.ntok > 0 && u.d.delta != 0 && u.d.seg != last_seg) {
-                ++n_tables;
-                if (tid >= kWave) cs_lds[n_tables & (kPipeCs - 1)][tid - kWave] = rope_cos_sin_fast(u.d.delta, my_freq);
-            }
-            if (u.d.ntok > 0) last_seg = u.d.seg;
-            u.cs = n_tables & (kPipeCs - 1);
-        };
-        auto stage = [&](const Unit& u, const UnitRegs& r, int slot) {
-            if (u.d.ntok <= 0) return;
-            unsigned char* k_lds = k_ring[slot];
-            unsigned char* v_lds = v_ring[slot];
-            ChunkAngles ang;
-            if (u.d.delta != 0) ang = load_chunk_angles(cs_lds[u.cs] + 8 * kj);
-#pragma unroll
-            for (int it = 0; it < kKItems; ++it) {
-                uint4 ra = r.ka[it], rb4 = r.kb[it];
-                if (u.d.delta != 0) rotate_chunk_pair<DT>(ra, rb4, ang);
-                k_tile_write(k_lds, kr + (kPT / 8) * it, kj, ra);
-                k_tile_write(k_lds, kr + (kPT / 8) * it, kj + 8, rb4);
-            }
-#pragma unroll
-            for (int it = 0; it < kVItems; ++it) {
-                const int t = vr + (kPT / 16) * it;
-                *reinterpret_cast<uint4*>(v_lds + t * 256 + 16 * (vc ^ (2 * (t & 7)))) = r.v[it];
-            }
-        };
-        Unit a0, a1, b0, b1;
-        UnitRegs ra0, ra1, rb0, rb1;
-        fetch(a0, ra0); fetch(a1, ra1); fetch(b0, rb0); fetch(b1, rb1);
-        table_for(a0); table_for(a1);
-        __syncthreads();                             // the tables of pair 0 are published
-        int slot = 0;                                // the slot pair s goes to: 2 * (s % 4)
-        // step s: stage pair s, refill its registers with pair s + 2, make the tables of pair s + 1
-        auto step = [&](Unit& x0, Unit& x1, UnitRegs& r0, UnitRegs& r1, Unit& y0, Unit& y1) {
-            stage(x0, r0, slot);
-            stage(x1, r1, slot + 1);
-            slot = (slot + 2) & (kPipeSlots - 1);
-            fetch(x0, r0);
-            fetch(x1, r1);
-            table_for(y0);
-            table_for(y1);
-            __syncthreads();
-        };
-        for (int s = 0; s < n_steps; s += 2) {
-            step(a0, a1, ra0, ra1, b0, b1);
-            step(b0, b1, rb0, rb1, a0, a1);
+    const int kr = tid >> 3, kj = tid & 7;
+    const int vr = tid >> 4, vc = tid & 15;
+    struct StageRegs { uint4 ka, kb, v[2]; };
+    StageRegs regs;
+    // The walk over the sub-split's tiles: next tile, its segment, and where the segment's next tokens start.
+    int w_next = split_begin(total, nsub, ss), w_left = 0;
+    const int w_end = split_begin(total, nsub, ss + 1);
+    Tile w;
+    w.seg = -1; w.tok0 = 0; w.ntok = 0; w.delta = 0; w.self = 0;
+    int w_slot = 0;                                  // the cos/sin table of its segment
+    const char *w_k = static_cast<const char*>(a.workspace), *w_v = w_k;
+    uint32_t row_bytes = 0, koff = 0, voff = 0;
+    const LdsSegs lsegs{seg_lds, rtbl.n};
+    // the next tile's segment, if it starts one, and the segment's cos/sin table
+    auto next_segment = [&](auto in_loop) {
+        if (w_next >= w_end || w_left > 0) return;
+        FoundSegment f;
+        if constexpr (!REG_TABLE) f = find_segment(tbl, w_next, lane_anew(), w.seg);
+        else if constexpr (decltype(in_loop)::value) f = find_segment(lsegs, w_next, lane_anew(), w.seg);
+        else f = find_segment(rtbl, w_next, lane, w.seg);
+        w.seg = f.seg;
+        w.delta = f.delta;
+        w.self = f.self;
+        w.tok0 = (w_next - f.first) * kWideTile;
+        w.ntok = 1;
+        w_left = f.vis - w.tok0;
+        const TileSource src = tile_source(a, w, f.tok, hkv);
+        w_k = src.k;
+        w_v = src.v;
+        if (src.row_bytes != row_bytes) {            // the store's and the own block's rows differ
+            row_bytes = src.row_bytes;
+            const uint32_t t = (uint32_t)(wave * kWave + lane_anew());
+            koff = (t >> 3) * row_bytes + 16 * (t & 7);
+            voff = (t >> 4) * row_bytes + 16 * (t & 15);
         }
-        return;
-    }
+        if (f.delta != 0) {
+            w_slot ^= 1;
+            if (wave == 0) {
+                const int l = lane_anew();
+                cs_lds[grp][w_slot][l] = rope_cos_sin_fast(f.delta, decltype(in_loop)::value ? freq_lds[l] : freq.rev[l]);
+            }
+        }
+    };
+    // requests the next tile (d, its table's slot) into r and steps over it
+    auto fetch = [&](Tile& d, int& slot, StageRegs& r) {
+        d = w;
+        d.ntok = w_next < w_end ? min(w_left, kWideTile) : 0;
+        slot = w_slot;
+        // rows past a ragged tile's end, and everything where no tile is left, lie past the range and read as zero
+        const int range = d.ntok > 0 ? (d.ntok - 1) * (int)row_bytes + 2 * kD : 0;
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(w_k), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(w_v), 0, range, 0x00020000);
+        r.ka = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff, 0, 0));
+        r.kb = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 128, 0, 0));
+        r.v[0] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff, 0, 0));
+        r.v[1] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff + 16 * row_bytes, 0, 0));
+    };
+    auto advance = [&]() {
+        ++w_next;
+        w.tok0 += kWideTile;
+        w_left -= kWideTile;
+        w_k += (int64_t)kWideTile * row_bytes;
+        w_v += (int64_t)kWideTile * row_bytes;
+    };
+    unsigned char* const k_write = k_lds + kr * kKRow + 16 * kj;
+    unsigned char* const v_write = v_lds + vr * kWideVRow + 16 * vc;
+    auto stage = [&](int delta, const StageRegs& r, int slot, int kbuf, int vbuf) {
+        uint4 ra = r.ka, rb4 = r.kb;
+        rotate_chunk_pair<DT>(ra, rb4, load_chunk_angles(cs_lds[grp][slot] + 8 * kj));
+        const bool still = delta == 0;               // bit-exact, and no branch where the matrix instructions run
+        ra = make_uint4(still ? r.ka.x : ra.x, still ? r.ka.y : ra.y, still ? r.ka.z : ra.z, still ? r.ka.w : ra.w);
+        rb4 = make_uint4(still ? r.kb.x : rb4.x, still ? r.kb.y : rb4.y, still ? r.kb.z : rb4.z, still ? r.kb.w : rb4.w);
+        *reinterpret_cast<uint4*>(v_write + vbuf) = r.v[0];
+        *reinterpret_cast<uint4*>(v_write + vbuf + 16 * kWideVRow) = r.v[1];
+        *reinterpret_cast<uint4*>(k_write + kbuf) = ra;
+        *reinterpret_cast<uint4*>(k_write + kbuf + 128) = rb4;
+    };
 
-    // ---------------------------------------------------------------------- the others: math
+    // The first two tiles are requested together, the first into registers of its own.
+    Tile cd, d0;                                     // the tile whose phase M comes next; the tile in `regs` and its table's slot
+    int first_slot, slot0;
+    StageRegs first;
+    next_segment(std::false_type{});
+    fetch(cd, first_slot, first);
+    advance();
+    next_segment(std::false_type{});
+    fetch(d0, slot0, regs);
+    int most_tiles = 0;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        most_tiles = max(most_tiles, split_begin(total, nsub, split * GROUPS + g + 1) - split_begin(total, nsub, split * GROUPS + g));
+
     RowState<NRB> st;
     st.clear();
     float2* massml = reinterpret_cast<float2*>(static_cast<char*>(a.workspace) + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg;
-    const int tr_row = 4 * lg + (li >> 2);
-    const uint32_t tr_base = (uint32_t)tr_row * 256 + 8 * (li & 3);
-    const uint32_t tr_x = (uint32_t)(tr_row & 7) * 32;
+    const unsigned char* const k_read = k_lds + li * kKRow + 16 * lg;
+    const unsigned char* const v_read = v_lds + (4 * lg + (li >> 2)) * kWideVRow + 8 * (li & 3);
     const float scale_log2e = a.scale_log2e;
     int cur_seg = -1;
 
-    // fragments and results in flight (see the head of the kernel)
-    uint4 kf[2][4];                                  // K fragments of the unit whose scores come next
-    short4v vlo[8], vhi[8];                          // V^T fragments of the unit whose O^T update comes next
-    f32x4 sc[NRB][2];                                // S^T of the unit whose softmax comes next
-    uint4 pfrag[NRB];                                // P^T of the unit whose O^T update comes next
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) pfrag[rb] = make_uint4(0, 0, 0, 0);
+    short4v vlo[8], vhi[8];                          // V^T fragments of the tile weighed next
+    f32x4 sc[NRB][2];                                // its scores
+    uint4 pfrag[NRB];                                // its probabilities
 
-    // slot: the unit's index modulo kPipeSlots, kept by the caller (no division inside the scheduled blocks)
-    auto read_k = [&](int slot) {
-        const unsigned char* k_lds = k_ring[slot];
+    auto read_v = [&](int vbuf, int db0, int db1) {
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) kf[tb][kk] = k_tile_fragment(k_lds, 16 * tb + li, 4 * kk + lg);
-    };
-    auto read_v = [&](int slot) {
-        const unsigned char* v_lds = v_ring[slot];
-#pragma unroll
-        for (int db = 0; db < 8; ++db) {
-            const unsigned char* src = v_lds + tr_base + ((uint32_t)(32 * db) ^ tr_x);
+        for (int db = db0; db < db1; ++db) {
+            const unsigned char* src = v_read + vbuf + 32 * db;
             vlo[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src));
-            vhi[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src + 16 * 256));
+            vhi[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src + 16 * kWideVRow));
         }
     };
-    auto scores_into = [&](f32x4 (&out)[NRB][2]) {
-#pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) { out[rb][0] = f32x4{0.f, 0.f, 0.f, 0.f}; out[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb) out[rb][tb] = Mma<DT>::run(kf[tb][kk], qf[rb][kk], out[rb][tb]);
-    };
-    auto weigh_prev = [&]() {                        // O^T += V^T P^T of the previous unit
+    auto weigh = [&]() {
 #pragma unroll
         for (int db = 0; db < 8; ++db) {
             const uint2 l2 = __builtin_bit_cast(uint2, vlo[db]), h2v = __builtin_bit_cast(uint2, vhi[db]);
@@ -456,105 +470,112 @@ __global__ __launch_bounds__(kPcWaves * kWave, 2) void attn_pipe_kernel(AttnArgs
             for (int rb = 0; rb < NRB; ++rb) st.acc[rb][db] = Mma<DT>::run(va, pfrag[rb], st.acc[rb][db]);
         }
     };
-    auto desc_of = [&](int u) {
-        const int4 e = desc_ring[u & (kPipeDesc - 1)];
-        Tile t;
-        t.seg = __builtin_amdgcn_readfirstlane(e.x);
-        t.tok0 = __builtin_amdgcn_readfirstlane(e.y);
-        t.ntok = __builtin_amdgcn_readfirstlane(e.z);
-        t.self = __builtin_amdgcn_readfirstlane(e.w);
-        t.delta = 0;                                 // the staged keys are rotated already
-        return t;
+    uint4 kf[2][4];
+    auto read_k = [&](int kbuf, int kk) {
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) kf[tb][kk] = *reinterpret_cast<const uint4*>(k_read + kbuf + 16 * tb * kKRow + 64 * kk);
     };
-
-    // One iteration (see the head of the kernel).  MASKED: unit i is ragged or the causal own block; FIRST: i == 0,
-    // nothing to weigh yet.  The K and the V^T fragments share their time in registers: the V^T fragments of unit
-    // i - 1 are requested while the scores consume the K fragments of unit i + 1, the K fragments of unit i + 2 while
-    // the O^T update consumes the V^T fragments.
-    int slot_i = 0;                                  // unit i modulo kPipeSlots
-    auto iterate = [&](const Tile& cd, auto masked_tag, auto first_tag) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        constexpr bool FIRST = decltype(first_tag)::value;
-        if (cd.seg != cur_seg) {
-            if (cur_seg >= 0) emit_segment<NRB>(st, massml, cur_seg + split, p.rows_wg, cw * NRB, li, lg);
-            cur_seg = cd.seg;
+    auto scores = [&](int kk) {
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) st.seg_l[rb] = 0.f;
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb)
+                sc[rb][tb] = Mma<DT>::run(kf[tb][kk], qf[rb][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sc[rb][tb]);
+    };
+    // phase M
+    auto matrix_phase = [&](int vprev, int kcur, int knext, int vnext) {
+        __builtin_amdgcn_sched_barrier(0);
+        // channel blocks 0-3 while the V^T fragments of 4-7 come in, those while the first K fragments do
+        read_v(vprev, 4, 8);
+        weigh();
+        read_k(kcur, 0);
+        read_k(kcur, 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
-        const bool causal = cd.self != 0;
-        f32x4 sn[NRB][2];
-        float lsum[NRB];
-        uint4 pnew[NRB];
-        // probabilities of row block rb against the reference as it stands
-        auto probabilities = [&](int rb) {
-            float xv[8], pv[8];
+        __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
+        for (int n = 0; n < 4; ++n) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        scores(0);
+        scores(1);
+        read_k(kcur, 2);
+        read_k(kcur, 3);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) xv[4 * tb + e] = sc[rb][tb][e];
-            if constexpr (MASKED) {
+        for (int n = 0; n < 4; ++n) {
+            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the second half of the scores beside the next tile's rotation
+        scores(2);
+        scores(3);
+        stage(d0.delta, regs, slot0, knext, vnext);
+        advance();
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int tk = 16 * (e >> 2) + 4 * lg + (e & 3);
-                    const bool ok = tk < cd.ntok && (!causal || cd.tok0 + tk <= trow[rb]);
-                    xv[e] = ok ? xv[e] : -INFINITY;
-                    sc[rb][e >> 2][e & 3] = xv[e];   // the repair path works on the masked scores
-                }
+        for (int n = 0; n < 4; ++n) {
+            if (n < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+            for (int i = 0; i < NRB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 16 / NRB, 0);
             }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        next_segment(std::true_type{});
+    };
+    auto softmax = [&](const Tile& cd, int vbuf) {
+        float lsum[NRB];
+        auto probabilities = [&](int rb) {
             const float m_safe = st.m_run[rb] == -INFINITY ? 0.f : st.m_run[rb];
+            float pv[8];
             float s = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                pv[e] = __builtin_amdgcn_exp2f(fmaf(xv[e], scale_log2e, -m_safe));
+                pv[e] = __builtin_amdgcn_exp2f(fmaf(sc[rb][e >> 2][e & 3], scale_log2e, -m_safe));
                 s += pv[e];
             }
             lsum[rb] = s;
-            pnew[rb] = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
-                                  Mma<DT>::pack(pv[6], pv[7]));
+            pfrag[rb] = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
+                                   Mma<DT>::pack(pv[6], pv[7]));
         };
-        const int slot_prev = slot_i == 0 ? kPipeSlots - 1 : slot_i - 1;
-        const int slot_next2 = slot_i + 2 >= kPipeSlots ? slot_i + 2 - kPipeSlots : slot_i + 2;
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- first half: the scores of unit i + 1 beside the softmax of the first row block of unit i
-        scores_into(sn);
-        probabilities(0);
-        if constexpr (!FIRST) read_v(slot_prev);
-        // (a V^T read only once four MFMAs have released the K fragments whose registers it takes over)
+        if (cd.ntok < kWideTile || cd.self != 0) {
+            const int l = lane_anew();
+            int tqs = tq;
+            asm volatile("" : "+v"(tqs));            // nothing of the division below is kept from tile to tile
 #pragma unroll
-        for (int n = 0; n < 16; ++n) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, MASKED ? 3 : 2, 0);       // a few VALU
-            if (!FIRST && (n & 3) == 3) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);     // four LDS reads
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- second half: O^T of unit i - 1 beside the softmax of the second row block of unit i
-        if constexpr (!FIRST) weigh_prev();
-        probabilities(1);
-        read_k(slot_next2);
+            for (int rb = 0; rb < NRB; ++rb) {
+                int lim = cd.ntok;
+                if (cd.self != 0) {                  // causal: row m = g * tq + t sees the own block up to its t
+                    const int m = row_base + (wave * NRB + rb) * 16 + (l & 15);
+                    const int t = m - (int)div_exact((unsigned)m, (unsigned)tqs) * tqs;
+                    lim = min(lim, t - cd.tok0 + 1);
+                }
+                lim -= 4 * (l >> 4);
 #pragma unroll
-        for (int n = 0; n < 16; ++n) {
-            if (!FIRST) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, MASKED ? 3 : 2, 0);
-            if (n & 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                for (int e = 0; e < 8; ++e)
+                    sc[rb][e >> 2][e & 3] = 16 * (e >> 2) + (e & 3) < lim ? sc[rb][e >> 2][e & 3] : -INFINITY;
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- did a reference have to move?  (rare after a row's first units)
-        bool off[NRB];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) probabilities(rb);
         bool any_off = false;
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
-            off[rb] = !(lsum[rb] <= kProbLimit) || st.m_run[rb] == -INFINITY;
-            any_off = any_off || off[rb];
-        }
+        for (int rb = 0; rb < NRB; ++rb) any_off = any_off || !(lsum[rb] <= kProbLimit) || st.m_run[rb] == -INFINITY;
         if (__any(any_off)) {
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb) {
-                if (!__any(off[rb])) continue;
-                float xv[8];
+                float mloc = -INFINITY;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) xv[e] = sc[rb][e >> 2][e & 3];
-                float mloc = fmaxf(fmaxf(fmaxf(xv[0], xv[1]), fmaxf(xv[2], xv[3])), fmaxf(fmaxf(xv[4], xv[5]), fmaxf(xv[6], xv[7])));
-                mloc *= scale_log2e;                     // scale > 0: max commutes with it
+                for (int e = 0; e < 8; ++e) mloc = fmaxf(mloc, sc[rb][e >> 2][e & 3]);
+                mloc *= scale_log2e;
                 mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
                 mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
                 const float m_old = st.m_run[rb];
@@ -563,73 +584,147 @@ __global__ __launch_bounds__(kPcWaves * kWave, 2) void attn_pipe_kernel(AttnArgs
                 st.l_run[rb] *= alpha;
                 st.seg_l[rb] *= alpha;
                 st.m_run[rb] = m_new;
-                if (__any(alpha != 1.f && m_old != -INFINITY)) {     // nothing accumulated yet: nothing to rescale
 #pragma unroll
-                    for (int db = 0; db < 8; ++db) st.acc[rb][db] *= alpha;
-                }
-                const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-                float pv[8];
-                float s = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    pv[e] = __builtin_amdgcn_exp2f(fmaf(xv[e], scale_log2e, -m_safe));
-                    s += pv[e];
-                }
-                lsum[rb] = s;
-                pnew[rb] = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
-                                      Mma<DT>::pack(pv[6], pv[7]));
+                for (int db = 0; db < 8; ++db) st.acc[rb][db] *= alpha;
+                probabilities(rb);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
+        read_v(vbuf, 0, 4);
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) {
-            st.l_run[rb] += lsum[rb];
             st.seg_l[rb] += lsum[rb];
-            pfrag[rb] = pnew[rb];
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) sc[rb][tb] = sn[rb][tb];
         }
-        slot_i = slot_i + 1 == kPipeSlots ? 0 : slot_i + 1;
     };
+    // (reference, segment sum) per row for the segment's slot
+    auto emit = [&](int seg) {
+        float tot[NRB];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) tot[rb] = add_lane_groups(st.seg_l[rb]);
+        const int l = lane_anew();
+        if (l < 16) {
+            float2* dst = massml + (int64_t)(seg + ss) * p.rows_wg + wave * NRB * 16 + l;
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) dst[16 * rb] = make_float2(st.m_run[rb], tot[rb]);
+        }
+    };
+    // phase V
+    auto vector_phase = [&](const Tile& cd, int vbuf) {
+        if (cd.ntok <= 0) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) pfrag[rb] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int db = 0; db < 4; ++db) vlo[db] = vhi[db] = short4v{0, 0, 0, 0};      // (an infinity times zero)
+            return;
+        }
+        if (cd.seg != cur_seg) {
+            if (cur_seg >= 0) {
+                emit(cur_seg);
+            }
+            cur_seg = cd.seg;
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) { st.l_run[rb] += st.seg_l[rb]; st.seg_l[rb] = 0.f; }
+        }
+        softmax(cd, vbuf);
+    };
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) pfrag[rb] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int db = 0; db < 8; ++db) vlo[db] = vhi[db] = short4v{0, 0, 0, 0};
 
-    __syncthreads();                                 // the tables of pair 0
-    __syncthreads();                                 // step 0: pair 0 is staged
-    Tile upcoming = desc_of(0);
-    if (has_rows && n_units > 0) {
-        read_k(0);
-        scores_into(sc);
-        read_k(1);
+    // (the first phase weighs nothing, with probabilities of zero: what it reads of the buffer before must be finite)
+    *reinterpret_cast<uint4*>(v_write + 2 * kWideV) = make_uint4(0, 0, 0, 0);
+    *reinterpret_cast<uint4*>(v_write + 2 * kWideV + 16 * kWideVRow) = make_uint4(0, 0, 0, 0);
+    __syncthreads();                                 // the cos/sin tables of the first two tiles, the segment table in LDS
+    stage(cd.delta, first, first_slot, 0, 0);
+    __syncthreads();                                 // tile 0 is staged
+    if (GROUPS == 2 && grp == 1) __syncthreads();    // the second group runs one phase behind
+    // step t: d0 / regs hold tile t + 1, after it tile t + 2
+    int kcur = 0, vprev = 2 * kWideV, vcur = 0, vnext = kWideV;
+    for (int it = 0; it < most_tiles; ++it) {
+        __builtin_amdgcn_s_setprio(1);
+        matrix_phase(vprev, kcur, kWideK - kcur, vnext);
+        __builtin_amdgcn_s_setprio(0);
+        if (GROUPS == 2) __syncthreads();
+        const Tile cur = cd;
+        cd = d0;
+        fetch(d0, slot0, regs);
+        vector_phase(cur, vcur);
+        kcur = kWideK - kcur;
+        const int v = vprev;
+        vprev = vcur;
+        vcur = vnext;
+        vnext = v;
+        __syncthreads();
     }
-    auto run_unit = [&](int i, auto first_tag) {
-        if (i >= n_units) return;
-        const Tile cd = upcoming;
-        upcoming = desc_of(i + 1);
-        if (cd.ntok < kPipeUnit || cd.self != 0) iterate(cd, std::true_type{}, first_tag);
-        else iterate(cd, std::false_type{}, first_tag);
-    };
-    __syncthreads();                                 // step 1: pair 1 is staged
-    if (has_rows) {
-        run_unit(0, std::true_type{});
-        run_unit(1, std::false_type{});
-    }
-    for (int k = 1; k < n_steps - 1; ++k) {
-        __syncthreads();                             // step k + 1: pair k + 1 is staged; the loads in flight have landed
-        if (!has_rows) continue;
-        run_unit(2 * k, std::false_type{});
-        run_unit(2 * k + 1, std::false_type{});
-    }
-    if (!has_rows) return;
-    if (n_units > 0) {                               // the last unit's O^T update
-        read_v(slot_i == 0 ? kPipeSlots - 1 : slot_i - 1);
-        weigh_prev();
-    }
-    if (cur_seg >= 0) emit_segment<NRB>(st, massml, cur_seg + split, p.rows_wg, cw * NRB, li, lg);
+    if (GROUPS == 2 && grp == 0) __syncthreads();
+    read_v(vprev, 4, 8);
+    weigh();
+    if (has_rows && cur_seg >= 0) emit(cur_seg);
+
     float l_row[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
+        st.l_run[rb] += st.seg_l[rb];
         l_row[rb] = st.l_run[rb] + __shfl_xor(st.l_run[rb], 16);
         l_row[rb] += __shfl_xor(l_row[rb], 32);
     }
-    store_partials<DT, NRB>(a, p, unit, split, cw * NRB, st, l_row, lane, qh.q0, tq, hkv, group, row_base, row_limit);
+    if (GROUPS == 1) {
+        if (has_rows) store_partials<DT, NRB>(a, p, unit, split, wave * NRB, st, l_row, lane, qh.q0, tq, hkv, group, row_base, row_limit);
+        return;
+    }
+    __syncthreads();
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        if (lg == 0) red_ml[grp][(wave * NRB + rb) * 16 + li] = make_float2(st.m_run[rb], l_row[rb]);
+        // the first group keeps channel blocks 0-3, the second 4-7
+        f32x4* dst = red + (((grp * kWaves + wave) * NRB + rb) * 4) * kWave + lane;
+        if (grp == 0) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db) dst[db * kWave] = st.acc[rb][4 + db];
+        } else {
+#pragma unroll
+            for (int db = 0; db < 4; ++db) dst[db * kWave] = st.acc[rb][db];
+#pragma unroll
+            for (int db = 0; db < 4; ++db) st.acc[rb][db] = st.acc[rb][4 + db];
+        }
+    }
+    __syncthreads();
+    if (!has_rows) return;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const float2 o = red_ml[grp ^ 1][(wave * NRB + rb) * 16 + li];
+        const float m = fmaxf(st.m_run[rb], o.x);
+        const float ms = m == -INFINITY ? 0.f : m;
+        const float f0 = __builtin_amdgcn_exp2f(st.m_run[rb] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
+        const f32x4* src = red + ((((grp ^ 1) * kWaves + wave) * NRB + rb) * 4) * kWave + lane;
+        // the sums in the groups' order, so that both come to the same row sum
+        const float l = grp == 0 ? l_row[rb] * f0 + o.y * f1 : o.y * f1 + l_row[rb] * f0;
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        const int blk = wave * NRB + rb;
+        float2* ml = reinterpret_cast<float2*>(static_cast<char*>(a.workspace) + p.off_ml) + ((int64_t)unit * p.nsplit + split) * p.rows_wg;
+        if (grp == 0 && lg == 0) ml[blk * 16 + li] = make_float2(m, l);
+        uint2 w[4];
+#pragma unroll
+        for (int db = 0; db < 4; ++db) {
+            const f32x4 v = (st.acc[rb][db] * f0 + src[db * kWave] * f1) * inv;
+            w[db] = make_uint2(Mma<DT>::pack(v[0], v[1]), Mma<DT>::pack(v[2], v[3]));
+        }
+        if (p.direct_out) {
+            const int mrow = row_base + blk * 16 + li;
+            if (mrow >= row_limit) continue;
+            const int gi = (int)div_exact((unsigned)mrow, (unsigned)tq), t = mrow - gi * tq;
+            uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 4 * lg + 64 * grp;
+#pragma unroll
+            for (int db = 0; db < 4; ++db) *reinterpret_cast<uint2*>(op + 16 * db) = w[db];
+        } else {
+            uint2* opart = reinterpret_cast<uint2*>(static_cast<char*>(a.workspace) + p.off_opart) +
+                           ((((int64_t)unit * p.nsplit + split) * p.rows_wg / 16 + blk) * 8 + 4 * grp) * kWave + lane;
+#pragma unroll
+            for (int db = 0; db < 4; ++db) opart[db * kWave] = w[db];
+        }
+    }
 }
 
 }  // namespace
@@ -654,8 +749,8 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         return st != CF_OK || !prune ? st : launch_prune_step(a, prune, s);
     }
     const Plan p = make_plan(a.n_q_heads, a.n_kv_heads, a.batch, a.max_tq, a.seg_stride, a.max_kv_tokens);
-    const dim3 grid((unsigned)(p.x_count * p.n_rg));
     const dim3 grid3((unsigned)p.nsplit, (unsigned)a.n_kv_heads, (unsigned)a.batch);     // attn_tile_kernel's
+    const dim3 grid2((unsigned)(p.nsplit * a.batch), (unsigned)p.units_per_b);           // attn_wide_kernel's
     // grid dimensions of this path's kernels (the merge kernel's may carry one more row, for pending score parts)
     if (a.batch > 65535 || (int64_t)a.n_kv_heads * p.n_rg + 1 > 65535) {
         set_error("batch must not exceed 65535 and n_kv_heads * row groups 65534 on this path");
@@ -670,17 +765,25 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
         else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
     } while (0)
+#define CF_LAUNCH_WIDE(DT, GROUPS)                                                                                            \
+    if (p.nrb == 2) {                                                                                                         \
+        if (reg_table) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, GROUPS, true>), grid2, dim3(GROUPS * kThreads));              \
+        else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, GROUPS, false>), grid2, dim3(GROUPS * kThreads));                       \
+    } else {                                                                                                                  \
+        if (reg_table) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, GROUPS, true>), grid2, dim3(GROUPS * kThreads));              \
+        else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, GROUPS, false>), grid2, dim3(GROUPS * kThreads));                       \
+    }
 #define CF_LAUNCH_DT(DT)                                                                                                       \
-    if (p.producers == 0) {                                                                                                    \
+    if (!p.wide) {                                                                                                             \
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, true>), grid3, dim3(2 * kThreads));                            \
         else CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, false>), grid3, dim3(2 * kThreads));                                     \
     } else {                                                                                                                   \
-        if (reg_table) CF_LAUNCH_TIMED((attn_pipe_kernel<DT, true>), grid, dim3(kPcWaves * kWave));                                  \
-        else CF_LAUNCH_TIMED((attn_pipe_kernel<DT, false>), grid, dim3(kPcWaves * kWave));                                           \
+        if (p.groups == 2) { CF_LAUNCH_WIDE(DT, 2) } else { CF_LAUNCH_WIDE(DT, 1) }                                             \
     }                                                                                                                          \
     CF_HIP(hipGetLastError());
     if (a.dtype == CF_BF16) { CF_LAUNCH_DT(CF_BF16) } else { CF_LAUNCH_DT(CF_F16) }
 #undef CF_LAUNCH_DT
+#undef CF_LAUNCH_WIDE
 #undef CF_LAUNCH_TIMED
     const bool combine = !(p.direct_out && a.mass == nullptr);            // else nothing left to merge or reduce
     // before a fused epilogue the pending score parts are taken in by one more row of the combine kernel's grid

@@ -714,7 +714,6 @@ Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stri
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
     p.slots = seg_stride + p.nsplit * p.groups;
-    p.x_count = p.units * p.nsplit;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
     p.off_ml = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));

@@ -27,12 +27,12 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 struct Plan {
     int group;          // query heads per kv head
     int row_blocks;     // 16-row blocks of the stacked rows of one kv head
-    int producers;      // 0: attn_tile_kernel (few rows); else attn_pipe_kernel with that many loading wavefronts
+    int wide;           // 0: attn_tile_kernel (few rows), 1: attn_wide_kernel
     int nrb;            // 64-row passes of a workgroup's rows (what the combine kernel handles at a time)
     int rows_wg;        // rows a workgroup has room for: 64 * nrb
     int n_rg;           // row groups per (query, kv head)
     int blocks_rg;      // 16-row blocks per row group
-    int units_per_b, units, nsplit, slots, x_count;
+    int units_per_b, units, nsplit, slots;
     int tile;           // tokens per tile: 32 or 64
     int groups;         // groups of four wavefronts per workgroup (each streams its own run of tiles): 1 or 2
     int direct_out;     // one split: the attention kernel writes the output rows itself, nothing to merge
@@ -40,9 +40,7 @@ struct Plan {
     size_t masspart_bytes;      // one layer's slot partials (the ledger holds kMaxPending + 1 such parts)
 };
 
-constexpr int kPcWaves = 8;         // wavefronts of an attn_pipe_kernel workgroup
-constexpr int kPcProducers = 2;     // of which load and stage
-constexpr int kPcNrb = 2;           // 16-row blocks per math wavefront
+constexpr int kWideNrb = 3;         // 16-row blocks per wavefront of attn_wide_kernel, at most
 
 inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
     Plan p;
@@ -54,24 +52,27 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
         // Few stacked rows (MHA-like, HBM-bound): one row block per wavefront, small tiles, so that ragged
         // segment ends waste little and a split still holds several tiles; two groups of four wavefronts per
         // workgroup run two tiles at a time on one CU and hide each other's LDS and barrier waits.
-        p.producers = 0;
+        p.wide = 0;
         p.n_rg = 1;
         p.nrb = 1;
         p.tile = 32;
         p.groups = 2;
     } else {
-        // Many rows (GQA, long queries): 32-token units, two row blocks per math wavefront.
-        const int blocks_wg = kPcNrb * (kPcWaves - kPcProducers);
-        p.producers = kPcProducers;
-        p.n_rg = (row_blocks + blocks_wg - 1) / blocks_wg;
-        p.nrb = blocks_wg / 4;
+        // Many rows (GQA, long queries): up to three row blocks per wavefront, as few row groups as that allows (each stages the
+        // same keys once more).
+        p.wide = 1;
+        p.n_rg = (row_blocks + kWaves * kWideNrb - 1) / (kWaves * kWideNrb);
+        p.nrb = ((row_blocks + p.n_rg - 1) / p.n_rg + kWaves - 1) / kWaves;
         p.tile = 32;
-        p.groups = 1;
     }
     p.blocks_rg = (row_blocks + p.n_rg - 1) / p.n_rg;
     p.rows_wg = 64 * p.nrb;
     p.units_per_b = n_kv_heads * p.n_rg;
     p.units = batch * p.units_per_b;
+    // attn_wide_kernel: units past the CUs come as one group of wavefronts per workgroup and two workgroups per CU, fewer as two
+    // groups of one workgroup (30 documents x 32 heads, 960 units: 84 us encoded and stored against 108; 64 queries x 2 heads x 2 row
+    // groups, 256 units: 140 against 122, half of the difference the merge of two splits).
+    if (p.wide) p.groups = p.units > 256 ? 1 : 2;
     const int64_t est_tiles = max_kv_tokens / p.tile + seg_stride;
     // One launch wave: a CU holds one workgroup of either kernel at a time (8 wavefronts of about 190 and 250 registers), so a
     // grid a little past the 256 CUs runs two rounds, the second nearly empty, each with its prologue and tail.  Rounded down and
@@ -83,7 +84,7 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     // split against two: up to 4096 tokens, lengths a fifth of that and more: 144 units 78 -> 64 us, 160 78 -> 62, 176 80 -> 74; up to
     // 12000: 198 -> 154, 204 -> 186, 207 -> 175; all of 4096: 82 -> 95, 82 -> 97, 83 -> 100.  At 192 units and more one is the better
     // (50 queries of 1000-5000 tokens, 200 units: 77 against 85), and for shorter lists (1024 tokens, 160 units: 31 against 35 and 39).
-    const bool halves = !p.producers && p.units > 128 && p.units < 192 && est_tiles > 128;
+    const bool halves = !p.wide && p.units > 128 && p.units < 192 && est_tiles > 128;
     int64_t ns = halves ? 2 : 256 / p.units;
     const int64_t cap = est_tiles / (2 * p.groups) > 1 ? est_tiles / (2 * p.groups) : 1;
     if (ns > cap) ns = cap;
@@ -91,16 +92,25 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     if (ns < 1) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
-    p.slots = seg_stride + p.nsplit * p.groups;
-    p.x_count = batch * n_kv_heads * p.nsplit;
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-    p.off_ml = take((size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
-    p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * kD * sizeof(uint16_t));
-    p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
-    p.masspart_bytes = ((size_t)p.units * p.nrb * p.slots * sizeof(float) + 255) & ~(size_t)255;
-    p.off_masspart = take(p.masspart_bytes * (kMaxPending + 1));
-    p.total = off;
+    auto layout = [&](int groups) {
+        p.groups = groups;
+        p.slots = seg_stride + p.nsplit * groups;
+        size_t off = 0;
+        auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
+        p.off_ml = take((size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
+        p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * kD * sizeof(uint16_t));
+        p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
+        p.masspart_bytes = ((size_t)p.units * p.nrb * p.slots * sizeof(float) + 255) & ~(size_t)255;
+        p.off_masspart = take(p.masspart_bytes * (kMaxPending + 1));
+        p.total = off;
+    };
+    layout(p.groups);
+    // A second group costs one slot per split.  Where that alone would take a plan past the buffer of the entry point that brings
+    // its own, the plan stays with one group.
+    if (p.wide && p.groups == 2 && p.total > CF_STATIC_SCRATCH_BYTES) {
+        layout(1);
+        if (p.total > CF_STATIC_SCRATCH_BYTES) layout(2);
+    }
     return p;
 }
 
@@ -126,17 +136,11 @@ struct QueryHead {
 
 // `entry`: which table entry this thread takes (its index in the workgroup for the LDS table, its lane
 // for the register table).
-// kAlways: threads past the stride re-read the last entry instead of skipping the load — a conditional load makes
+// Threads past the stride re-read the last entry instead of skipping the load — a conditional load makes
 // the compiler wait for it inside the branch, before the scalar loads below are even issued (a whole round trip).
-// (The producer/consumer attention kernel keeps the conditional form: it has no register to spare and runs long.)
-template <bool kAlways = true>
 __device__ __forceinline__ QueryHead load_query_head(const AttnArgs& a, int b, int entry) {   // b: wave-uniform
     QueryHead h;
-    if constexpr (kAlways) {
-        h.seg = a.segs[(int64_t)b * a.seg_stride + min(entry, a.seg_stride - 1)];   // seg_stride >= 1; callers test entry < n
-    } else {
-        if (entry < a.seg_stride) h.seg = a.segs[(int64_t)b * a.seg_stride + entry];   // seg_stride <= kMaxSegs
-    }
+    h.seg = a.segs[(int64_t)b * a.seg_stride + min(entry, a.seg_stride - 1)];   // seg_stride >= 1; callers test entry < n
     const int q0 = a.q_off[b], q1 = a.q_off[b + 1], qt = a.q_off[a.batch], n = a.n_seg[b], qn = a.q_new_start[b];
     asm volatile("" ::"s"(q0), "s"(q1), "s"(qt), "s"(n), "s"(qn));    // all five scalar loads are out before any is used
     h.q0 = q0;

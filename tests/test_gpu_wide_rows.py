@@ -1,0 +1,109 @@
+"""GPU parity of the attention kernel for many stacked rows at the edges of its plan: row counts around a wavefront's two and three
+blocks and around the step to another row group, units on both sides of 256 (two groups of wavefronts per workgroup, or one), tile
+lists of one, two and three tiles per group with ragged ends and tables past 64 entries."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_11101_amd import workloads as wl
+from tests import gpu_harness as G
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(geo, batch, tq, lens, docs, prefix, seed, layout="head"):
+    """Every query attends `docs` documents of the given lengths (rotated from query to query); outputs and masses of a few
+    queries against the oracle."""
+    rng = np.random.default_rng(seed)
+    lens = np.asarray(lens, np.int32)
+    off = np.concatenate([[prefix], prefix + np.cumsum(lens)]).astype(np.int64)
+    picks = np.stack([np.roll(np.arange(len(lens)), b)[:docs] for b in range(batch)]).astype(np.int32)
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name=f"wide_{seed}", geometry=geo, n_store_docs=len(lens), docs_per_query=docs, batch=batch,
+                    tq=tq, prefix_len=prefix, doc_stored_start=prefix, n_planted=1)
+    st = wl.Structure(lens, off, int(off[-1]), picks, np.zeros((batch, 1), np.int32), 0)
+    normal = lambda n, h: wl.round_to_dtype(rng.standard_normal((n, h, 128), dtype=np.float32), geo.dtype)
+    t = dict(q=normal(batch * tq, geo.n_q_heads), k_self=normal(batch * tq, geo.n_kv_heads), v_self=normal(batch * tq, geo.n_kv_heads),
+             k_store=normal(st.n_store_tokens, geo.n_kv_heads), v_store=normal(st.n_store_tokens, geo.n_kv_heads))
+    pb = G.make_batch(cfg, st, layout=layout)
+    dev = G.upload_layer(cfg, t, layout=layout)
+    out = torch.empty_like(dev["q"])
+    pb.allocate_initial()
+    pb.workspace.fill_(0xFF)                         # whatever an earlier call left: not read
+    pb.attention(dev["q"], dev["k_self"], dev["v_self"], dev["k_store"], dev["v_store"], out)
+    torch.cuda.synchronize()
+    assert pb.flags() == 0
+    got, mass = out.float().cpu().numpy(), pb.mass.cpu().numpy()
+    for b in sorted({0, batch // 2, batch - 1}):
+        segs, q_start, _ = H.initial_segments(cfg, st, b)
+        ks, vs, table = H.compact_query(segs, t["k_store"], t["v_store"])
+        rows = slice(b * tq, (b + 1) * tq)
+        ref, near = H.rounded_key_reference(geo.dtype, t["q"][rows], 0, q_start, ks, vs, t["k_self"], t["v_self"], table,
+                                            geo.n_kv_heads, geo.rope_base)
+        assert np.isfinite(got[rows]).all()
+        assert G.row_error(got[rows], ref) <= G.OUT_TOL[geo.dtype]
+        assert G.rel_error(mass[b, :len(segs)], near) <= G.NEAR_MASS_TOL[geo.dtype]
+        assert mass[b, :len(segs)].sum() == pytest.approx(geo.n_q_heads * tq, rel=1e-5)
+
+
+# stacked rows of a kv head: 65 (five blocks), 128 | 129 (two | three per wavefront), 192 | 193 (one | two row groups), 385, 577
+@pytest.mark.parametrize("group,tq", [(5, 13), (4, 32), (3, 43), (6, 32), (1, 193), (7, 55), (1, 577)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_row_counts(group, tq, dtype):
+    print(f"rows {group * tq} {dtype}", flush=True)
+    _run(wl.Geometry(2 * group, 2, 128, dtype, 1.0e4, 8192), 2, tq, [33, 95, 64, 1, 160], 4, 32, seed=group * tq)
+
+
+# tiles of a (query, kv head): from a list that leaves the second group without one, to several per group, ragged ends of 1, 31, 32
+@pytest.mark.parametrize("lens", [[1], [31], [32], [33, 1], [63, 32], [65, 31, 2], [200, 1, 129]])
+@pytest.mark.parametrize("batch", [3, 140])          # 6 and 280 units
+@pytest.mark.parametrize("prefix", [0, 17])
+def test_short_tile_lists(lens, batch, prefix):
+    print(f"lens {lens} batch {batch} prefix {prefix}", flush=True)
+    _run(wl.Geometry(10, 2, 128, "bf16", 1.0e4, 4096), batch, 16, lens, len(lens), prefix, seed=sum(lens) + batch)
+
+
+@pytest.mark.parametrize("batch", [128, 129])        # 256 and 258 units
+@pytest.mark.parametrize("layout", ["head", "token"])
+def test_units_around_the_compute_units(batch, layout):
+    print(f"units {2 * batch} {layout}", flush=True)
+    _run(wl.Geometry(12, 2, 128, "f16", 1.0e6, 8192), batch, 30, [70, 130, 100, 41], 3, 8, seed=batch, layout=layout)
+
+
+@pytest.mark.parametrize("docs", [62, 63, 90])       # 64, 65 and 92 table entries
+@pytest.mark.parametrize("batch", [1, 130])
+def test_table_in_lds(docs, batch):
+    print(f"docs {docs} batch {batch}", flush=True)
+    lens = np.random.default_rng(docs).integers(1, 70, size=docs)
+    _run(wl.Geometry(14, 2, 128, "bf16", 1.0e4, 8192), batch, 12, lens, docs, 32, seed=docs)
+
+
+def test_non_finite_values_stay_with_the_rows_that_see_them():
+    """An infinite value in a document turns its channel infinite in every row of its kv head — not into NaN by a phase that weighs
+    nothing — and leaves every other channel and head alone."""
+    geo = wl.Geometry(10, 2, 128, "bf16", 1.0e4, 4096)
+    rng = np.random.default_rng(5)
+    for lens in ([32], [100, 40]):
+        n, tq = int(sum(lens)), 16
+        normal = lambda m, h: torch.from_numpy(rng.standard_normal((m, h, 128), dtype=np.float32)).to(torch.bfloat16).cuda()
+        q, ks, vs = normal(tq, 10), normal(tq, 2), normal(tq, 2)
+        k, v = normal(n, 2), normal(n, 2)
+        cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name="wide_inf", geometry=geo, n_store_docs=len(lens), docs_per_query=len(lens), batch=1,
+                        tq=tq, prefix_len=0, doc_stored_start=0, n_planted=1)
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        st = wl.Structure(np.asarray(lens, np.int32), off, n, np.arange(len(lens), dtype=np.int32)[None], np.zeros((1, 1), np.int32), 0)
+        pb = G.make_batch(cfg, st)
+        pb.allocate_initial()
+        outs = []
+        for bad in (False, True):
+            if bad:
+                v[7, 1, 90] = float("inf")
+            out = torch.empty_like(q)
+            pb.attention(q, ks, vs, k, v, out)
+            torch.cuda.synchronize()
+            outs.append(out.float().cpu().reshape(tq, 2, 5, 128))
+        hit = torch.zeros(outs[0].shape, dtype=torch.bool)
+        hit[:, 1, :, 90] = True
+        assert torch.isposinf(outs[1][hit]).all()
+        assert torch.equal(outs[0][~hit], outs[1][~hit])
