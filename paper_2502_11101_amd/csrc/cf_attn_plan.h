@@ -3,6 +3,8 @@
 // segment table in its two forms (LDS, registers) with the tile walk over it, and the MFMA wrappers.
 #pragma once
 
+#include <algorithm>
+
 #include "cf_common.h"
 #include "cf_select_dev.h"
 
@@ -40,14 +42,21 @@ struct Plan {
     size_t masspart_bytes;      // one layer's slot partials (the ledger holds kMaxPending + 1 such parts)
 };
 
-constexpr int kWideNrb = 3;         // 16-row blocks per wavefront of attn_wide_kernel, at most
-
-inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
+// `small`: the fewest row groups and slots (see make_plan).
+inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens, bool small) {
     Plan p;
     const int group = n_q_heads / n_kv_heads;
     const int row_blocks = (group * max_tq + 15) / 16;
     p.group = group;
     p.row_blocks = row_blocks;
+    const int64_t est_tiles = max_kv_tokens / 32 + seg_stride;           // every plan's tiles are of 32 tokens
+    // splits of a (query, kv head, row group): the CUs are shared out, and a split of attn_tile_kernel has about two tiles for each of
+    // its two groups (four a split are the better for attn_wide_kernel too: one query of 20 rows x 4 heads, ten documents, 23.5 us
+    // against 25.4 with two)
+    auto splits_of = [&](int64_t units) {
+        const int64_t cap = std::max<int64_t>(est_tiles / 4, 1);
+        return std::max<int64_t>(std::min({256 / units, cap, (int64_t)kMaxSplit}), 1);
+    };
     if (row_blocks <= 4) {
         // Few stacked rows (MHA-like, HBM-bound): one row block per wavefront, small tiles, so that ragged
         // segment ends waste little and a split still holds several tiles; two groups of four wavefronts per
@@ -58,22 +67,27 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
         p.tile = 32;
         p.groups = 2;
     } else {
-        // Many rows (GQA, long queries): up to three row blocks per wavefront, as few row groups as that allows (each stages the
-        // same keys once more).
+        // Many rows (GQA, long queries): row groups of up to three blocks per wavefront, or of up to two.  Fewer groups stage the same keys
+        // less often, but three blocks keep every register busy and two do not: a tile's time goes about as 4 * blocks per wavefront
+        // + 2, and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
+        // three of three: one query of 50 documents 37.8 us against 41.7, 8 queries of 20 66 against 76, 32 171 against 197.  384 rows, 64
+        // queries x 2 kv heads, as three of two 168 us, as two of three 127 (384 units against 256); five documents of 100-200 tokens x 7
+        // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).
         p.wide = 1;
-        p.n_rg = (row_blocks + kWaves * kWideNrb - 1) / (kWaves * kWideNrb);
-        p.nrb = ((row_blocks + p.n_rg - 1) / p.n_rg + kWaves - 1) / kWaves;
         p.tile = 32;
+        double best = 0;
+        for (int per_wave = 3; per_wave >= (small ? 3 : 2); --per_wave) {
+            const int n_rg = (row_blocks + kWaves * per_wave - 1) / (kWaves * per_wave);
+            const int nrb = ((row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves;
+            const int64_t units = (int64_t)batch * n_kv_heads * n_rg;
+            const double cost = (4 * nrb + 2) * (units > 256 ? units / 256. : 1. / splits_of(units));
+            if (per_wave == 3 || cost < best) { best = cost; p.n_rg = n_rg; p.nrb = nrb; }
+        }
     }
     p.blocks_rg = (row_blocks + p.n_rg - 1) / p.n_rg;
     p.rows_wg = 64 * p.nrb;
     p.units_per_b = n_kv_heads * p.n_rg;
     p.units = batch * p.units_per_b;
-    // attn_wide_kernel: units past the CUs come as one group of wavefronts per workgroup and two workgroups per CU, fewer as two
-    // groups of one workgroup (30 documents x 32 heads, 960 units: 84 us encoded and stored against 108; 64 queries x 2 heads x 2 row
-    // groups, 256 units: 140 against 122, half of the difference the merge of two splits).
-    if (p.wide) p.groups = p.units > 256 ? 1 : 2;
-    const int64_t est_tiles = max_kv_tokens / p.tile + seg_stride;
     // One launch wave: a CU holds one workgroup of either kernel at a time (8 wavefronts of about 190 and 250 registers), so a
     // grid a little past the 256 CUs runs two rounds, the second nearly empty, each with its prologue and tail.  Rounded down and
     // not up, attn_tile_kernel's calls that 256 does not divide measured: 6 decode queries x 32 heads over 1017-1573 tokens (192
@@ -85,34 +99,36 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     // 12000: 198 -> 154, 204 -> 186, 207 -> 175; all of 4096: 82 -> 95, 82 -> 97, 83 -> 100.  At 192 units and more one is the better
     // (50 queries of 1000-5000 tokens, 200 units: 77 against 85), and for shorter lists (1024 tokens, 160 units: 31 against 35 and 39).
     const bool halves = !p.wide && p.units > 128 && p.units < 192 && est_tiles > 128;
-    int64_t ns = halves ? 2 : 256 / p.units;
-    const int64_t cap = est_tiles / (2 * p.groups) > 1 ? est_tiles / (2 * p.groups) : 1;
-    if (ns > cap) ns = cap;
-    if (ns > kMaxSplit) ns = kMaxSplit;
-    if (ns < 1) ns = 1;
+    const int64_t ns = halves ? 2 : splits_of(p.units);
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
-    auto layout = [&](int groups) {
-        p.groups = groups;
-        p.slots = seg_stride + p.nsplit * groups;
-        size_t off = 0;
-        auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-        p.off_ml = take((size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
-        p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * kD * sizeof(uint16_t));
-        p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
-        p.masspart_bytes = ((size_t)p.units * p.nrb * p.slots * sizeof(float) + 255) & ~(size_t)255;
-        p.off_masspart = take(p.masspart_bytes * (kMaxPending + 1));
-        p.total = off;
-    };
-    layout(p.groups);
-    // A second group costs one slot per split.  Where that alone would take a plan past the buffer of the entry point that brings
-    // its own, the plan stays with one group.
-    if (p.wide && p.groups == 2 && p.total > CF_STATIC_SCRATCH_BYTES) {
-        layout(1);
-        if (p.total > CF_STATIC_SCRATCH_BYTES) layout(2);
-    }
+    // attn_wide_kernel as one group of wavefronts per workgroup: for units past the CUs, two workgroups of which share one (30
+    // documents x 32 heads, 960 units, encoded and stored: 84 us against 108 with two groups), and for splits of few tiles, which the second
+    // group's delay and the merge of the groups cost more than it saves.  Around the line, us with one group against two: one query x 2
+    // kv heads, 384 rows, under four tiles a split 29.0 against 32.0, 4 queries x 4 heads, 140 rows, seven 31.3 against 33.2; 8 queries x
+    // 2 heads, 384 rows, fifteen 42.2 against 41.2, 2 x 32 heads, 130 rows, twelve 40.9 against 38.9.
+    if (p.wide) p.groups = !small && p.units <= 256 && est_tiles >= 10 * ns ? 2 : 1;
+    p.slots = seg_stride + p.nsplit * p.groups;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
+    p.off_ml = take((size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
+    p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * kD * sizeof(uint16_t));
+    p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
+    p.masspart_bytes = ((size_t)p.units * p.nrb * p.slots * sizeof(float) + 255) & ~(size_t)255;
+    p.off_masspart = take(p.masspart_bytes * (kMaxPending + 1));
+    p.total = off;
     return p;
 }
+
+// More row groups and a second group of wavefronts take workspace.  Where that alone would carry a plan past the buffer of the entry
+// point that brings its own, the plan does without.
+inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
+    const Plan p = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, false);
+    if (!p.wide || p.total <= CF_STATIC_SCRATCH_BYTES) return p;
+    const Plan least = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, true);
+    return least.total <= CF_STATIC_SCRATCH_BYTES ? least : p;
+}
+
 
 
 // Per-query segment table in LDS with the tile prefix that defines the partition.

@@ -3,29 +3,27 @@
 from paper_2502_11101_amd import binding as cf
 
 
-def test_two_groups_refuse_no_static_call():
-    """Plans of the workspace sizes around the static entry point's buffer: a second group of wavefronts never takes one past it
-    that a single group keeps within."""
-    limit, seen = cf.CF_STATIC_SCRATCH_BYTES, 0
-    for hq, hkv in ((28, 4), (12, 2), (32, 8)):
+def test_static_calls_of_many_rows_stay_accepted():
+    """Calls of many stacked rows whose plan of at most twelve row blocks a group, one slot per entry and split, fits the static entry
+    point's buffer: the plan in use, which may have a second group of wavefronts (one more slot per split), fits it as well."""
+    up = lambda x: -(-x // 256) * 256
+    limit, near = cf.CF_STATIC_SCRATCH_BYTES, 0
+    for hq, hkv in ((28, 4), (12, 2), (32, 8), (32, 32)):
         d = cf.make_desc(hq, hkv, 128, "bf16", 1.0e4, 32768, cf.CF_ROPE_HALF)
-        for batch in range(1, 40):
-            for tq in (24, 48, 64):
-                for stride in range(20, 257, 4):
-                    need = cf.cf_prefill_workspace_bytes(d, batch, tq, stride, 8000)
-                    group = hq // hkv
-                    blocks = -(-group * tq // 16)
-                    if blocks <= 4 or need <= limit:
-                        continue
-                    rg = -(-blocks // 12)
-                    units = batch * hkv * rg
-                    rows = 64 * -(-(-(-blocks // rg)) // 4)
-                    splits = max(1, min(256 // units if units <= 256 else 1, 32))
-                    # one group: (max, sum) pairs and partial rows, slot statistics, sixteen parts of slot masses
-                    up = lambda x: -(-x // 256) * 256
-                    slots = stride + splits
-                    one = up(units * splits * rows * 8) + (up(units * splits * rows * 256) if splits > 1 else 0) + \
-                        up(units * slots * rows * 8) + 16 * up(units * rows // 64 * slots * 4)
-                    assert one > limit, (hq, hkv, batch, tq, stride)
-                    seen += need < limit + (2 << 20)
-    assert seen > 10
+        for batch in (*range(1, 24), 32, 48, 64, 100, 128, 200):
+            for tq in (24, 48, 64, 100, 180):
+                for stride in (*range(3, 66, 9), *range(70, 257, 6)):
+                    for max_kv in (500, 8000):
+                        blocks = -(-hq // hkv * tq // 16)
+                        if blocks <= 4:
+                            continue
+                        units = batch * hkv * -(-blocks // 12)
+                        splits = max(1, min(256 // units, (max_kv // 32 + stride) // 2, 32))
+                        slots = stride + splits
+                        total = up(units * splits * 1536) + (up(units * splits * 49152) if splits > 1 else 0) + up(units * slots * 1536) + \
+                            16 * up(units * 3 * slots * 4)
+                        if total <= limit:
+                            need = cf.cf_prefill_workspace_bytes(d, batch, tq, stride, max_kv)
+                            assert need <= limit, (hq, hkv, batch, tq, stride, max_kv)
+                            near += total > limit - (1 << 20)
+    assert near > 10
