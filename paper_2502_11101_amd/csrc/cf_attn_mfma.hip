@@ -232,6 +232,203 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
 }
 
 // ---------------------------------------------------------------------------------------------
+// The attention kernel for one 16-row block and outputs only (decode steps: one row per query head of a group), bound by HBM where there are
+// enough tokens.  With one block attn_tile_kernel has one of four wavefronts do a tile's math while the others wait for it: a
+// tile's chain of LDS round trips, ~1 us per 32 KB of a CU.  Here each of a workgroup's eight wavefronts streams tiles of its own
+// without a barrier: key fragments straight from memory into the registers the matrix instructions take them from (a lane's 16-byte
+// chunks 32 kk + 8 lg of token li hold both channels of each 2-D slice), values through a piece of LDS of the wavefront's own for
+// the transposing read.  Two tiles, 256 KB per CU, are in flight.  The eight results meet in LDS at the end.
+constexpr int kSoloWaves = 8;
+constexpr int kSoloVRow = 288;                       // bytes per token of a staged V tile
+constexpr int kSoloV = 32 * kSoloVRow;
+
+template <int DT, bool REG_TABLE>
+__global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnArgs a, RopeFreq freq, Plan p) {
+    __shared__ SegTable tbl;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kSoloWaves * kSoloV];
+    __shared__ __attribute__((aligned(16))) float2 cs_lds[kSoloWaves][kHalf];
+    __shared__ float2 red_ml[kSoloWaves][16];
+    static_assert(kSoloWaves * kSoloV >= kSoloWaves * 8 * kWave * (int)sizeof(f32x4), "the results reuse the V tiles");
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int li = lane & 15, lg = lane >> 4;
+    // grid (split, kv head, query)
+    const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
+    const int unit = b * a.n_kv_heads + hkv;
+    const int group = p.group;
+    const QueryHead qh = load_query_head(a, b, REG_TABLE ? lane : (int)threadIdx.x);
+    const double my_freq = freq.rev[lane];
+    const int tq = min(qh.tq_raw, a.max_tq);
+    const int row_limit = group * tq;                // at most 16
+    uint4 qf[1][4];
+    int trow[1];
+    load_q_fragments<1>(a, qh.q0, tq, hkv, group, 0, 0, row_limit, li, lg, qf, trow);
+    RegSegTable rtbl;
+    unsigned total;
+    if constexpr (REG_TABLE) {
+        rtbl = build_reg_table(a, qh, lane, 32);
+        total = (unsigned)rtbl.total;
+    } else {
+        build_table(a, qh, &tbl, 32);
+        total = (unsigned)tbl.tile0[tbl.n];
+    }
+    // a wavefront's contiguous run of the workgroup's tiles
+    const int t_begin = split_begin(total, (unsigned)p.nsplit, split);
+    const unsigned n_tiles = (unsigned)(split_begin(total, (unsigned)p.nsplit, split + 1) - t_begin);
+    TileWalk<32> walk(t_begin + split_begin(n_tiles, kSoloWaves, wave), t_begin + split_begin(n_tiles, kSoloWaves, wave + 1));
+    const int my_tiles = walk.t_end - walk.next_tile;
+
+    struct Regs { uint4 k[2][4], v[8]; };            // key fragments [16 tokens][32 channels], V row 4 * i + lane / 16, chunk lane % 16
+    auto fetch = [&](Tile& d, Regs& r) {
+        if constexpr (REG_TABLE) d = walk.next(rtbl, lane);
+        else d = walk.next(tbl, lane);
+        const TileSource src = tile_source(a, d, walk.c_tok, hkv);
+        // rows past a ragged tile's end, and everything where no tile is left, lie past the range and read as zero
+        const int range = src.last < 0 ? 0 : src.last * (int)src.row_bytes + 2 * kD;
+        const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src.k), 0, range, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src.v), 0, range, 0x00020000);
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+            const uint32_t off = (uint32_t)(16 * tb + li) * src.row_bytes + 16 * lg;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                r.k[tb][kk] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, off + 64 * kk, 0, 0));
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            r.v[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, (uint32_t)(4 * i + lg) * src.row_bytes + 16 * li, 0, 0));
+    };
+    Tile d0, d1;
+    Regs r0, r1;
+    fetch(d0, r0);
+    fetch(d1, r1);
+
+    f32x4 acc[8];
+#pragma unroll
+    for (int db = 0; db < 8; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    unsigned char* const v_lds = lds + wave * kSoloV;
+    unsigned char* const v_write = v_lds + lg * kSoloVRow + 16 * li;
+    const unsigned char* const v_read = v_lds + (4 * lg + (li >> 2)) * kSoloVRow + 8 * (li & 3);
+    const float scale_log2e = a.scale_log2e;
+    int cs_seg = -1;
+
+    auto step = [&](Tile& d, Regs& r) {
+        const Tile cd = d;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<uint4*>(v_write + 4 * i * kSoloVRow) = r.v[i];
+        if (cd.delta != 0) {
+            if (cd.seg != cs_seg) {
+                cs_seg = cd.seg;
+                cs_lds[wave][lane] = rope_cos_sin_fast(cd.delta, my_freq);
+            }
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const ChunkAngles ang = load_chunk_angles(cs_lds[wave] + 32 * kk + 8 * lg);
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb) rotate_chunk_pair<DT>(r.k[tb][kk], r.k[tb][kk + 2], ang);
+            }
+        }
+        f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int tb = 0; tb < 2; ++tb) sc[tb] = Mma<DT>::run(r.k[tb][kk], qf[0][kk], sc[tb]);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(d, r);                                 // the registers are free again
+        __builtin_amdgcn_sched_barrier(0);
+        if (cd.ntok < 32 || cd.self != 0) {
+            const int last = (cd.self != 0 ? min(cd.ntok - 1, trow[0] - cd.tok0) : cd.ntok - 1) - 4 * lg;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sc[e >> 2][e & 3] = 16 * (e >> 2) + (e & 3) <= last ? sc[e >> 2][e & 3] : -INFINITY;
+        }
+        // online softmax (exp2 domain) against a stale row maximum (see kProbLimit)
+        float pv[8], lsum;
+        auto probabilities = [&]() {
+            const float m_safe = m_run == -INFINITY ? 0.f : m_run;
+            lsum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                pv[e] = __builtin_amdgcn_exp2f(fmaf(sc[e >> 2][e & 3], scale_log2e, -m_safe));
+                lsum += pv[e];
+            }
+        };
+        probabilities();
+        if (__any(!(lsum <= kProbLimit) || m_run == -INFINITY)) {
+            float mloc = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mloc = fmaxf(mloc, sc[e >> 2][e & 3]);
+            mloc *= scale_log2e;                     // scale > 0: max commutes with it
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            const float m_new = fmaxf(m_run, mloc);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+            if (__any(alpha != 1.f && m_run != -INFINITY)) {         // nothing accumulated yet: nothing to rescale
+#pragma unroll
+                for (int db = 0; db < 8; ++db) acc[db] *= alpha;
+            }
+            l_run *= alpha;
+            m_run = m_new;
+            probabilities();
+        }
+        l_run += lsum;
+        const uint4 pfrag = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
+                                       Mma<DT>::pack(pv[6], pv[7]));
+#pragma unroll
+        for (int db = 0; db < 8; ++db) {
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(v_read + 32 * db));
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(v_read + 32 * db + 16 * kSoloVRow));
+            const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+            acc[db] = Mma<DT>::run(make_uint4(l2.x, l2.y, h2.x, h2.y), pfrag, acc[db]);
+        }
+    };
+    // (left from the middle: with a step skipped the wait for one register set would have to cover the other as well)
+    for (int left = my_tiles; left > 0;) {
+        step(d0, r0);
+        if (--left == 0) break;
+        step(d1, r1);
+        --left;
+    }
+
+    // ---- the wavefronts' results: wavefront w merges channel block w
+    float l_row = l_run + __shfl_xor(l_run, 16);
+    l_row += __shfl_xor(l_row, 32);
+    __syncthreads();                                 // every wavefront is done with its V tile
+    f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int db = 0; db < 8; ++db) red[(wave * 8 + db) * kWave + lane] = acc[db];
+    if (lg == 0) red_ml[wave][li] = make_float2(m_run, l_row);
+    __syncthreads();
+    float m = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kSoloWaves; ++w) m = fmaxf(m, red_ml[w][li].x);
+    const float ms = m == -INFINITY ? 0.f : m;
+    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSoloWaves; ++w) {
+        const float2 ml = red_ml[w][li];
+        const float f = __builtin_amdgcn_exp2f(ml.x - ms);
+        l += ml.y * f;
+        o += red[(w * 8 + wave) * kWave + lane] * f;
+    }
+    o *= l > 0.f ? 1.f / l : 0.f;
+    const uint2 packed = make_uint2(Mma<DT>::pack(o[0], o[1]), Mma<DT>::pack(o[2], o[3]));
+    char* ws = static_cast<char*>(a.workspace);
+    if (p.direct_out) {
+        if (li >= row_limit) return;
+        const int gi = (int)div_exact((unsigned)li, (unsigned)tq), t = li - gi * tq;
+        uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 16 * wave + 4 * lg;
+        *reinterpret_cast<uint2*>(op) = packed;
+        return;
+    }
+    const int64_t part = (int64_t)unit * p.nsplit + split;
+    if (wave == 0 && lg == 0) reinterpret_cast<float2*>(ws + p.off_ml)[part * p.rows_wg + li] = make_float2(m, l);
+    reinterpret_cast<uint2*>(ws + p.off_opart)[(part * (p.rows_wg / 16) * 8 + wave) * kWave + lane] = packed;
+}
+
+// ---------------------------------------------------------------------------------------------
 // The attention kernel for many stacked rows (GQA groups, long queries), where the instructions that a SIMD can issue are the
 // bound: per 32-token tile and 48 rows a wavefront has 48 MFMAs (768 cycles of matrix pipe), about 145 other vector
 // instructions and 24 exponentials.  Four wavefronts own NRB 16-row blocks each — 128 or 192 rows of a workgroup, so that a
@@ -757,6 +954,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         return CF_ERR_UNSUPPORTED;
     }
     const bool reg_table = a.seg_stride <= kWave;    // the attention kernels keep a table this small in registers
+    const bool solo = p.row_blocks == 1 && a.mass == nullptr;
     // the attention kernel's launch carries the profiling aid's start/stop events (null when it is off)
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     profile_kernel_pair(&ev_start, &ev_stop);
@@ -774,7 +972,10 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, GROUPS, false>), grid2, dim3(GROUPS * kThreads));                       \
     }
 #define CF_LAUNCH_DT(DT)                                                                                                       \
-    if (!p.wide) {                                                                                                             \
+    if (solo) {                                                                                                                \
+        if (reg_table) CF_LAUNCH_TIMED((attn_solo_kernel<DT, true>), grid3, dim3(kSoloWaves * kWave));                                \
+        else CF_LAUNCH_TIMED((attn_solo_kernel<DT, false>), grid3, dim3(kSoloWaves * kWave));                                         \
+    } else if (!p.wide) {                                                                                                      \
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, true>), grid3, dim3(2 * kThreads));                            \
         else CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, false>), grid3, dim3(2 * kThreads));                                     \
     } else {                                                                                                                   \
