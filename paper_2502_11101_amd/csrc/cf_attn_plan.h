@@ -79,6 +79,7 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
         for (int per_wave = 3; per_wave >= (small ? 3 : 2); --per_wave) {
             const int n_rg = (row_blocks + kWaves * per_wave - 1) / (kWaves * per_wave);
             const int nrb = ((row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves;
+            if (per_wave < 3 && (int64_t)n_kv_heads * n_rg + 1 > 65535) continue;        // past the grid: fewer groups are taken instead
             const int64_t units = (int64_t)batch * n_kv_heads * n_rg;
             const double cost = (4 * nrb + 2) * (units > 256 ? units / 256. : 1. / splits_of(units));
             if (per_wave == 3 || cost < best) { best = cost; p.n_rg = n_rg; p.nrb = nrb; }
@@ -128,8 +129,6 @@ inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     const Plan least = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, true);
     return least.total <= CF_STATIC_SCRATCH_BYTES ? least : p;
 }
-
-
 
 // Per-query segment table in LDS with the tile prefix that defines the partition.
 struct SegTable {

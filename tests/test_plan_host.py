@@ -27,3 +27,13 @@ def test_static_calls_of_many_rows_stay_accepted():
                             assert need <= limit, (hq, hkv, batch, tq, stride, max_kv)
                             near += total > limit - (1 << 20)
     assert near > 10
+
+
+def test_row_groups_stay_within_the_grid():
+    """A call whose (kv heads x row groups) the grid holds only with the larger row groups gets those: 28 row blocks of 20000 kv
+    heads are three groups of three blocks per wavefront (60000), where groups of two would be four (80000)."""
+    up = lambda x: -(-x // 256) * 256
+    d = cf.make_desc(20000, 20000, 128, "bf16", 1.0e4, 32768, cf.CF_ROPE_HALF)
+    units, slots = 20000 * 3, 3 + 1
+    want = up(units * 192 * 8) + up(units * slots * 192 * 8) + 16 * up(units * 3 * slots * 4)
+    assert cf.cf_prefill_workspace_bytes(d, 1, 448, 3, 4000) == want
