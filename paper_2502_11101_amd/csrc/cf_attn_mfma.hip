@@ -232,19 +232,17 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
 }
 
 // ---------------------------------------------------------------------------------------------
-// The attention kernel for one 16-row block and outputs only (decode steps: one row per query head of a group), bound by HBM where there are
-// enough tokens.  With one block attn_tile_kernel has one of four wavefronts do a tile's math while the others wait for it: a
+// The attention kernel for one 16-row block over a short table (decode steps: one row per query head of a group) and up to eight splits,
+// bound by HBM where there are enough tokens.  With one block attn_tile_kernel has one of four wavefronts do a tile's math while the others wait for it: a
 // tile's chain of LDS round trips, ~1 us per 32 KB of a CU.  Here each of a workgroup's eight wavefronts streams tiles of its own
 // without a barrier: key fragments straight from memory into the registers the matrix instructions take them from (a lane's 16-byte
 // chunks 32 kk + 8 lg of token li hold both channels of each 2-D slice), values through a piece of LDS of the wavefront's own for
 // the transposing read.  Two tiles, 256 KB per CU, are in flight.  The eight results meet in LDS at the end.
-constexpr int kSoloWaves = 8;
 constexpr int kSoloVRow = 288;                       // bytes per token of a staged V tile
 constexpr int kSoloV = 32 * kSoloVRow;
 
-template <int DT, bool REG_TABLE>
+template <int DT>
 __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnArgs a, RopeFreq freq, Plan p) {
-    __shared__ SegTable tbl;
     __shared__ __attribute__((aligned(16))) unsigned char lds[kSoloWaves * kSoloV];
     __shared__ __attribute__((aligned(16))) float2 cs_lds[kSoloWaves][kHalf];
     __shared__ float2 red_ml[kSoloWaves][16];
@@ -257,32 +255,24 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int unit = b * a.n_kv_heads + hkv;
     const int group = p.group;
-    const QueryHead qh = load_query_head(a, b, REG_TABLE ? lane : (int)threadIdx.x);
+    const QueryHead qh = load_query_head(a, b, lane);
     const double my_freq = freq.rev[lane];
     const int tq = min(qh.tq_raw, a.max_tq);
     const int row_limit = group * tq;                // at most 16
     uint4 qf[1][4];
     int trow[1];
     load_q_fragments<1>(a, qh.q0, tq, hkv, group, 0, 0, row_limit, li, lg, qf, trow);
-    RegSegTable rtbl;
-    unsigned total;
-    if constexpr (REG_TABLE) {
-        rtbl = build_reg_table(a, qh, lane, 32);
-        total = (unsigned)rtbl.total;
-    } else {
-        build_table(a, qh, &tbl, 32);
-        total = (unsigned)tbl.tile0[tbl.n];
-    }
-    // a wavefront's contiguous run of the workgroup's tiles
-    const int t_begin = split_begin(total, (unsigned)p.nsplit, split);
-    const unsigned n_tiles = (unsigned)(split_begin(total, (unsigned)p.nsplit, split + 1) - t_begin);
-    TileWalk<32> walk(t_begin + split_begin(n_tiles, kSoloWaves, wave), t_begin + split_begin(n_tiles, kSoloWaves, wave + 1));
+    const RegSegTable rtbl = build_reg_table(a, qh, lane, 32);
+    const unsigned total = (unsigned)rtbl.total;
+    // a wavefront's contiguous run of tiles (sub-split `ss`)
+    const unsigned nsub = (unsigned)(p.nsplit * kSoloWaves);
+    const int ss = split * kSoloWaves + wave;
+    TileWalk<32> walk(split_begin(total, nsub, ss), split_begin(total, nsub, ss + 1));
     const int my_tiles = walk.t_end - walk.next_tile;
 
     struct Regs { uint4 k[2][4], v[8]; };            // key fragments [16 tokens][32 channels], V row 4 * i + lane / 16, chunk lane % 16
     auto fetch = [&](Tile& d, Regs& r) {
-        if constexpr (REG_TABLE) d = walk.next(rtbl, lane);
-        else d = walk.next(tbl, lane);
+        d = walk.next(rtbl, lane);
         const TileSource src = tile_source(a, d, walk.c_tok, hkv);
         // rows past a ragged tile's end, and everything where no tile is left, lie past the range and read as zero
         const int range = src.last < 0 ? 0 : src.last * (int)src.row_bytes + 2 * kD;
@@ -307,7 +297,17 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     f32x4 acc[8];
 #pragma unroll
     for (int db = 0; db < 8; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
+    float m_run = -INFINITY, l_run = 0.f, seg_l = 0.f;
+    char* ws = static_cast<char*>(a.workspace);
+    float2* const massml = reinterpret_cast<float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg;
+    const bool want_mass = a.mass != nullptr;
+    int cur_seg = -1;
+    // (reference, sum) per row of the segment that ends here
+    auto emit = [&]() {
+        float tot = seg_l + __shfl_xor(seg_l, 16);
+        tot += __shfl_xor(tot, 32);
+        if (lg == 0) massml[(int64_t)(cur_seg + ss) * p.rows_wg + li] = make_float2(m_run, tot);
+    };
     unsigned char* const v_lds = lds + wave * kSoloV;
     unsigned char* const v_write = v_lds + lg * kSoloVRow + 16 * li;
     const unsigned char* const v_read = v_lds + (4 * lg + (li >> 2)) * kSoloVRow + 8 * (li & 3);
@@ -316,6 +316,11 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
 
     auto step = [&](Tile& d, Regs& r) {
         const Tile cd = d;
+        if (cd.seg != cur_seg) {
+            if (want_mass && cur_seg >= 0) emit();
+            cur_seg = cd.seg;
+            seg_l = 0.f;
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) *reinterpret_cast<uint4*>(v_write + 4 * i * kSoloVRow) = r.v[i];
         if (cd.delta != 0) {
@@ -369,10 +374,12 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
                 for (int db = 0; db < 8; ++db) acc[db] *= alpha;
             }
             l_run *= alpha;
+            seg_l *= alpha;
             m_run = m_new;
             probabilities();
         }
         l_run += lsum;
+        seg_l += lsum;
         const uint4 pfrag = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
                                        Mma<DT>::pack(pv[6], pv[7]));
 #pragma unroll
@@ -390,6 +397,7 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
         step(d1, r1);
         --left;
     }
+    if (want_mass && cur_seg >= 0) emit();
 
     // ---- the wavefronts' results: wavefront w merges channel block w
     float l_row = l_run + __shfl_xor(l_run, 16);
@@ -415,7 +423,8 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     }
     o *= l > 0.f ? 1.f / l : 0.f;
     const uint2 packed = make_uint2(Mma<DT>::pack(o[0], o[1]), Mma<DT>::pack(o[2], o[3]));
-    char* ws = static_cast<char*>(a.workspace);
+    const int64_t part = (int64_t)unit * p.nsplit + split;
+    if (wave == 0 && lg == 0) reinterpret_cast<float2*>(ws + p.off_ml)[part * p.rows_wg + li] = make_float2(m, l);
     if (p.direct_out) {
         if (li >= row_limit) return;
         const int gi = (int)div_exact((unsigned)li, (unsigned)tq), t = li - gi * tq;
@@ -423,8 +432,6 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
         *reinterpret_cast<uint2*>(op) = packed;
         return;
     }
-    const int64_t part = (int64_t)unit * p.nsplit + split;
-    if (wave == 0 && lg == 0) reinterpret_cast<float2*>(ws + p.off_ml)[part * p.rows_wg + li] = make_float2(m, l);
     reinterpret_cast<uint2*>(ws + p.off_opart)[(part * (p.rows_wg / 16) * 8 + wave) * kWave + lane] = packed;
 }
 
@@ -954,7 +961,6 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         return CF_ERR_UNSUPPORTED;
     }
     const bool reg_table = a.seg_stride <= kWave;    // the attention kernels keep a table this small in registers
-    const bool solo = p.row_blocks == 1 && a.mass == nullptr;
     // the attention kernel's launch carries the profiling aid's start/stop events (null when it is off)
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     profile_kernel_pair(&ev_start, &ev_stop);
@@ -972,9 +978,8 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, GROUPS, false>), grid2, dim3(GROUPS * kThreads));                       \
     }
 #define CF_LAUNCH_DT(DT)                                                                                                       \
-    if (solo) {                                                                                                                \
-        if (reg_table) CF_LAUNCH_TIMED((attn_solo_kernel<DT, true>), grid3, dim3(kSoloWaves * kWave));                                \
-        else CF_LAUNCH_TIMED((attn_solo_kernel<DT, false>), grid3, dim3(kSoloWaves * kWave));                                         \
+    if (p.groups == kSoloWaves) {                                                                                                             \
+        CF_LAUNCH_TIMED((attn_solo_kernel<DT>), grid3, dim3(kSoloWaves * kWave));                                              \
     } else if (!p.wide) {                                                                                                      \
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, true>), grid3, dim3(2 * kThreads));                            \
         else CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, false>), grid3, dim3(2 * kThreads));                                     \

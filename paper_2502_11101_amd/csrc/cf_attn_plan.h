@@ -18,6 +18,8 @@ constexpr int kHalf = 64;
 constexpr int kKRow = 272;      // bytes per token of a staged K tile
 constexpr int kMaxSegs = 256;
 constexpr int kMaxSplit = 32;
+constexpr int kSoloWaves = 8;   // wavefronts of attn_solo_kernel's workgroups, each with tiles of its own
+constexpr int kMaxSub = 2 * kMaxSplit;       // runs of tiles of a (query, kv head, row group): splits x groups
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -29,20 +31,20 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 struct Plan {
     int group;          // query heads per kv head
     int row_blocks;     // 16-row blocks of the stacked rows of one kv head
-    int wide;           // 0: attn_tile_kernel (few rows), 1: attn_wide_kernel
+    int wide;           // 0: attn_tile_kernel or attn_solo_kernel (few rows), 1: attn_wide_kernel
     int nrb;            // 64-row passes of a workgroup's rows (what the combine kernel handles at a time)
     int rows_wg;        // rows a workgroup has room for: 64 * nrb
     int n_rg;           // row groups per (query, kv head)
     int blocks_rg;      // 16-row blocks per row group
     int units_per_b, units, nsplit, slots;
     int tile;           // tokens per tile: 32 or 64
-    int groups;         // groups of four wavefronts per workgroup (each streams its own run of tiles): 1 or 2
+    int groups;         // runs of tiles per workgroup: 1 or 2 (groups of four wavefronts), kSoloWaves (attn_solo_kernel)
     int direct_out;     // one split: the attention kernel writes the output rows itself, nothing to merge
     size_t off_ml, off_opart, off_massml, off_masspart, total;
     size_t masspart_bytes;      // one layer's slot partials (the ledger holds kMaxPending + 1 such parts)
 };
 
-// `small`: the fewest row groups and slots (see make_plan).
+// `small`: the fewest row groups and runs (see make_plan).
 inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens, bool small) {
     Plan p;
     const int group = n_q_heads / n_kv_heads;
@@ -100,7 +102,19 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
     // 12000: 198 -> 154, 204 -> 186, 207 -> 175; all of 4096: 82 -> 95, 82 -> 97, 83 -> 100.  At 192 units and more one is the better
     // (50 queries of 1000-5000 tokens, 200 units: 77 against 85), and for shorter lists (1024 tokens, 160 units: 31 against 35 and 39).
     const bool halves = !p.wide && p.units > 128 && p.units < 192 && est_tiles > 128;
-    const int64_t ns = halves ? 2 : splits_of(p.units);
+    int64_t ns = halves ? 2 : splits_of(p.units);
+    // attn_solo_kernel: one row block over at most two table entries (a decode step: the cache and the own block; short documents over
+    // the prefix) and at most eight splits, as many runs of tiles as the reductions have room for.  Longer tables are layer calls, which ask
+    // for masses: eight statistics per segment and split to reduce cost more than the attention saves (10 documents of 160 tokens x 12
+    // rows x 32 heads 24.8 us against 23.2 with attn_tile_kernel, 30 documents x 16 rows 33.9 against 31.3).  More splits are long lists
+    // over few units, which attn_tile_kernel spreads over more CUs (4 units x 2000 tokens 12.7 us as eight splits here, 12.2 as 16 there, x
+    // 14000 30.4 and 20.3).  The line does not ask for masses, so that a call's outputs do not depend on whether it wants them.
+    // Lists of up to two tiles per wavefront, which are all in flight at once, take one split and no merge: one conversation of 200 | 400
+    // tokens x 32 heads 10.6 -> 8.4 | 11.2 -> 10.0 us, 32 of 200 | 400 x 4 heads 15.2 -> 9.2 | 17.3 -> 12.1; of 881 (seven splits) 13.5
+    // would be 16.6.  Where the CUs allow two splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32
+    // heads 21.8 -> 17.8, of 150-880 19.9 -> 16.0; of 3000 40.7 would be 43.4.
+    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves;
+    if (solo && (est_tiles <= 2 * kSoloWaves || (p.units > 85 && est_tiles <= 4 * kSoloWaves))) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
     // attn_wide_kernel as one group of wavefronts per workgroup: for units past the CUs, two workgroups of which share one (30
@@ -109,6 +123,7 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
     // kv heads, 384 rows, under four tiles a split 29.0 against 32.0, 4 queries x 4 heads, 140 rows, seven 31.3 against 33.2; 8 queries x
     // 2 heads, 384 rows, fifteen 42.2 against 41.2, 2 x 32 heads, 130 rows, twelve 40.9 against 38.9.
     if (p.wide) p.groups = !small && p.units <= 256 && est_tiles >= 10 * ns ? 2 : 1;
+    else if (solo) p.groups = kSoloWaves;
     p.slots = seg_stride + p.nsplit * p.groups;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
@@ -121,11 +136,11 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
     return p;
 }
 
-// More row groups and a second group of wavefronts take workspace.  Where that alone would carry a plan past the buffer of the entry
+// More row groups and more runs of tiles per workgroup take workspace.  Where that alone would carry a plan past the buffer of the entry
 // point that brings its own, the plan does without.
 inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
     const Plan p = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, false);
-    if (!p.wide || p.total <= CF_STATIC_SCRATCH_BYTES) return p;
+    if (p.total <= CF_STATIC_SCRATCH_BYTES) return p;
     const Plan least = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, true);
     return least.total <= CF_STATIC_SCRATCH_BYTES ? least : p;
 }

@@ -182,8 +182,8 @@ __device__ __forceinline__ T group_sum(const T* x, int pitch, int n) {
 
 template <class T>
 struct MassScratch {
-    T colsum[kMaxSegs + 2 * kMaxSplit];
-    int32_t sub_begin[2 * kMaxSplit + 1];
+    T colsum[kMaxSegs + kMaxSub];
+    int32_t sub_begin[kMaxSub + 1];
     float seg_mass[kMaxSegs];               // every entry's mass, for the per-document sums
 };
 

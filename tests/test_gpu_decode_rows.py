@@ -1,6 +1,6 @@
-"""GPU parity of the attention kernel for one 16-row block and outputs only (decode steps): every wavefront streams tiles of its own.
+"""GPU parity of the attention kernel for one 16-row block (decode steps): every wavefront streams tiles of its own.
 Tile counts from fewer than the wavefronts to several each, ragged ends, several splits and one, moved and unmoved keys, rows from one
-to sixteen with the causal own block, tables in registers and in LDS."""
+to sixteen with the causal own block, and the longer tables that the other kernel keeps."""
 
 import numpy as np
 import pytest
@@ -43,18 +43,25 @@ def _check(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head"):
     cf.cf_prefill_attention(desc, dev["q"], i32([b * tq for b in range(batch + 1)]), 0, i32([q_pos] * batch), dev["k_store"], dev["v_store"],
                             n_store, dev["k_self"], dev["v_self"], table, i32([len(x) for x in segs]), stride, batch, tq, max_kv, out,
                             None, None, 1, ws, need, flag)
+    # the same call with the segments' masses: the same outputs, bit for bit
+    again, mass = torch.empty_like(out), torch.zeros((batch, stride), dtype=torch.float32, device="cuda")
+    cf.cf_prefill_attention(desc, dev["q"], i32([b * tq for b in range(batch + 1)]), 0, i32([q_pos] * batch), dev["k_store"], dev["v_store"],
+                            n_store, dev["k_self"], dev["v_self"], table, i32([len(x) for x in segs]), stride, batch, tq, max_kv, again,
+                            mass, None, 1, ws, need, flag)
     torch.cuda.synchronize()
-    assert int(flag.item()) == 0
-    got = out.float().cpu().numpy()
+    assert int(flag.item()) == 0 and torch.equal(again, out)
+    got, mass = out.float().cpu().numpy(), mass.cpu().numpy()
     for b in range(batch):
         ks, vs, compact = H.compact_query(segs[b], t["k_store"], t["v_store"])
         part = slice(b * tq, (b + 1) * tq)
-        ref, _ = H.rounded_key_reference(dtype, t["q"][part], 0, q_pos, ks, vs, t["k_self"], t["v_self"], compact, hkv, 1.0e4)
+        ref, near = H.rounded_key_reference(dtype, t["q"][part], 0, q_pos, ks, vs, t["k_self"], t["v_self"], compact, hkv, 1.0e4)
         assert np.isfinite(got[part]).all()
         assert G.row_error(got[part], ref) <= G.OUT_TOL[dtype]
+        assert G.rel_error(mass[b, :len(segs[b])], near) <= G.NEAR_MASS_TOL[dtype]
+        assert mass[b].sum() == pytest.approx(hq * tq, rel=1e-5)
 
 
-@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 545, 1500])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 447, 448, 545, 1500])        # from 448 on more than one split
 @pytest.mark.parametrize("hq,hkv,dtype", [(32, 32, "bf16"), (28, 4, "f16"), (16, 1, "bf16")])
 def test_one_row_over_a_cache(n, hq, hkv, dtype):
     print(f"decode n={n} {hq}/{hkv} {dtype}", flush=True)
@@ -71,7 +78,7 @@ def test_unequal_conversations(batch, hkv, layout):
     _check(2 * hkv, hkv, 1, [[(int(off[b]), int(lens[b]), 0, 0)] for b in range(batch)], int(off[-1]), "bf16", 1000, seed=batch, layout=layout)
 
 
-@pytest.mark.parametrize("docs", [5, 63, 64, 100])   # tables of 6, 64, 65 and 101 entries
+@pytest.mark.parametrize("docs", [1, 2, 63, 64])   # tables of 2 entries (attn_solo_kernel), 3, 64 and 65 (attn_tile_kernel)
 @pytest.mark.parametrize("group,tq", [(1, 16), (2, 8), (5, 3), (7, 2)])
 def test_moved_documents_and_the_causal_own_block(docs, group, tq):
     print(f"decode docs={docs} group={group} tq={tq}", flush=True)
@@ -79,7 +86,7 @@ def test_moved_documents_and_the_causal_own_block(docs, group, tq):
     lens = rng.integers(1, 90, size=docs)
     off = np.concatenate([[0], np.cumsum(lens)])
     # every third document keeps its distance to the query: not moved
-    new = [(16 if i % 3 == 0 else int(rng.integers(0, 6000))) for i in range(docs)]
+    new = [(16 if i % 3 == 1 else int(rng.integers(0, 6000))) for i in range(docs)]
     _check(2 * group, 2, tq, [[(int(off[i]), int(lens[i]), 16, new[i]) for i in range(docs)]] * 2, int(off[-1]), "bf16", 0, seed=docs)
 
 

@@ -37,3 +37,25 @@ def test_row_groups_stay_within_the_grid():
     units, slots = 20000 * 3, 3 + 1
     want = up(units * 192 * 8) + up(units * slots * 192 * 8) + 16 * up(units * 3 * slots * 4)
     assert cf.cf_prefill_workspace_bytes(d, 1, 448, 3, 4000) == want
+
+
+def test_static_calls_of_one_row_block_stay_accepted():
+    """As above for one 16-row block: a plan of two runs of tiles per workgroup that fits the static entry point's buffer; the plan in use
+    may have eight (six more slots per split)."""
+    up = lambda x: -(-x // 256) * 256
+    limit, near = cf.CF_STATIC_SCRATCH_BYTES, 0
+    for hkv in (1, 2, 4, 32):
+        d = cf.make_desc(2 * hkv, hkv, 128, "bf16", 1.0e4, 32768, cf.CF_ROPE_HALF)
+        for batch in (*range(1, 24), 32, 40, 64, 100, 128, 200, 500, 1000, 2000):
+            for stride in (*range(1, 66, 9), *range(70, 257, 6)):
+                for max_kv in (100, 500, 2000, 8000):
+                    units, tiles = batch * hkv, max_kv // 32 + stride
+                    splits = 2 if 128 < units < 192 and tiles > 128 else max(1, min(256 // units, max(tiles // 4, 1), 32))
+                    slots = stride + 2 * splits
+                    total = up(units * splits * 512) + (up(units * splits * 16384) if splits > 1 else 0) + up(units * slots * 512) + \
+                        16 * up(units * slots * 4)
+                    if total <= limit:
+                        need = cf.cf_prefill_workspace_bytes(d, batch, 8, stride, max_kv)
+                        assert need <= limit, (hkv, batch, stride, max_kv)
+                        near += total > limit - (1 << 20)
+    assert near > 10
