@@ -518,7 +518,7 @@ def bench_assemble(args) -> int:
                        "kv_tokens_per_step": tokens + 1, "kv_heads": g.n_kv_heads, "head_dim": g.head_dim, "layer_buffers": n_buf,
                        "step": "cf_prefill_attention (Tq = 1)"},
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                         "traffic": None, "kernel": "whole call: attn_tile_kernel + attn_combine_kernel (no mass asked for)",
+                         "traffic": None, "kernel": "whole call: attn_solo_kernel + attn_combine_kernel (no mass asked for)",
                          "ms_per_launch": call_ms, "algorithmic_bytes_per_launch": (tokens + 1) * bytes_per_token,
                          "attention_kernel_ms": kernel_ms, "attention_kernel_launches_timed": n_bracketed,
                          "attention_kernel_gbs": (tokens + 1) * bytes_per_token / (kernel_ms * 1e-3) / 1e9}}))
@@ -610,7 +610,7 @@ def bench_encode(args) -> int:
                    "step": "cf_prefill_attention (each document over the prefix and causally over itself) + cf_assemble_cache into the store"},
         "roofline": {"bound": "mfma", "achieved": tflops, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": tflops / MFMA_PEAK_TFLOPS, "traffic": None,
-                     "kernel": f"attn_wide_kernel<{g.dtype},2> (first kernel of cf_prefill_attention)",
+                     "kernel": f"attn_wide_kernel<{g.dtype}> (first kernel of cf_prefill_attention)",
                      "ms_per_launch": kernel_ms, "launches_timed": n_bracketed, "algorithmic_flops_per_launch": flops}}))
     return 0
 
