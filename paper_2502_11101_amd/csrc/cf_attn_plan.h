@@ -74,7 +74,10 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
         // + 2, and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
         // three of three: one query of 50 documents 37.8 us against 41.7, 8 queries of 20 66 against 76, 32 171 against 197.  384 rows, 64
         // queries x 2 kv heads, as three of two 168 us, as two of three 127 (384 units against 256); five documents of 100-200 tokens x 7
-        // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).
+        // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).  Past the CUs a share of a round costs most of one: 107 rows x 6, 36
+        // queries x 2 heads, 10 documents, as four of three (288 units) 91 us, as six of two (432) 80; 83 rows x 7, 14 queries x 4 heads, 10
+        // documents, as five of two (280) 95, as four of three (224) 76; 129 rows x 6, 41 queries x 2 heads, as seven of two (574) 91, as
+        // five of three (410) 75.
         p.wide = 1;
         p.tile = 32;
         double best = 0;
@@ -83,7 +86,9 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
             const int nrb = ((row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves;
             if (per_wave < 3 && (int64_t)n_kv_heads * n_rg + 1 > 65535) continue;        // past the grid: fewer groups are taken instead
             const int64_t units = (int64_t)batch * n_kv_heads * n_rg;
-            const double cost = (4 * nrb + 2) * (units > 256 ? units / 256. : 1. / splits_of(units));
+            // past the CUs two workgroups share one, at 1.7 times what one alone takes, and a third begins when they end
+            const double rounds = units > 512 ? std::max(units / 256., 2.7) : 1.7;
+            const double cost = (4 * nrb + 2) * (units > 256 ? rounds : 1. / splits_of(units));
             if (per_wave == 3 || cost < best) { best = cost; p.n_rg = n_rg; p.nrb = nrb; }
         }
     }
@@ -113,8 +118,12 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
     // tokens x 32 heads 10.6 -> 8.4 | 11.2 -> 10.0 us, 32 of 200 | 400 x 4 heads 15.2 -> 9.2 | 17.3 -> 12.1; of 881 (seven splits) 13.5
     // would be 16.6.  Where the CUs allow two splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32
     // heads 21.8 -> 17.8, of 150-880 19.9 -> 16.0; of 3000 40.7 would be 43.4.
-    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves;
-    if (solo && (est_tiles <= 2 * kSoloWaves || (p.units > 85 && est_tiles <= 4 * kSoloWaves))) ns = 1;
+    // With more than two splits of more than four tiles attn_tile_kernel is the faster: 2 conversations of 1500 tokens x 32 heads 18.7 us
+    // against 20.7, 1 14.5 against 15.3, 8 of 1000-2000 x 4 heads 15.2 against 16.0; with two 28.3 against 28.5 (3 of 1972 x 32), 28.6
+    // against 28.2 (24 of 1000-2400 x 4); with one 33.7 against 32.1 (40 of 1000-2000 x 4); with seven of four tiles 12.6 against 11.7.
+    const bool whole = est_tiles <= 2 * kSoloWaves || (p.units > 85 && est_tiles <= 4 * kSoloWaves);
+    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves && (whole || ns <= 2 || est_tiles < 5 * ns);
+    if (solo && whole) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
     // attn_wide_kernel as one group of wavefronts per workgroup: for units past the CUs, two workgroups of which share one (30

@@ -61,7 +61,7 @@ def _check(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head"):
         assert mass[b].sum() == pytest.approx(hq * tq, rel=1e-5)
 
 
-@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 447, 448, 545, 1500])        # from 448 on more than one split
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 479, 480, 545, 1500])        # one split up to 479, the other kernel at 1500
 @pytest.mark.parametrize("hq,hkv,dtype", [(32, 32, "bf16"), (28, 4, "f16"), (16, 1, "bf16")])
 def test_one_row_over_a_cache(n, hq, hkv, dtype):
     print(f"decode n={n} {hq}/{hkv} {dtype}", flush=True)
