@@ -119,10 +119,10 @@ inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int se
     // would be 16.6.  Where the CUs allow two splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32
     // heads 21.8 -> 17.8, of 150-880 19.9 -> 16.0; of 3000 40.7 would be 43.4.
     // With more than two splits of more than four tiles attn_tile_kernel is the faster: 2 conversations of 1500 tokens x 32 heads 18.7 us
-    // against 20.7, 1 14.5 against 15.3, 8 of 1000-2000 x 4 heads 15.2 against 16.0; with two 28.3 against 28.5 (3 of 1972 x 32), 28.6
-    // against 28.2 (24 of 1000-2400 x 4); with one 33.7 against 32.1 (40 of 1000-2000 x 4); with seven of four tiles 12.6 against 11.7.
+    // against 20.7, 1 14.5 against 15.3, 8 of 1000-2000 x 4 heads 15.2 against 16.0; with two up to 112
+    // units 28.3 against 28.5 (3 of 1972 x 32) and 26.7 against 26.9 (28 of 1500 x 4), at 128 54.7 against 53.7 (32 of 1000-5000 x 4); with one 33.7 against 32.1 (40 of 1000-2000 x 4); with seven of four tiles 12.6 against 11.7.
     const bool whole = est_tiles <= 2 * kSoloWaves || (p.units > 85 && est_tiles <= 4 * kSoloWaves);
-    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves && (whole || ns <= 2 || est_tiles < 5 * ns);
+    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves && (whole || ns == 1 || (ns == 2 && p.units > 112) || est_tiles < 5 * ns);
     if (solo && whole) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
