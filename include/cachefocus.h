@@ -133,7 +133,10 @@ CF_API cf_status cf_reposition_keys(const cf_layer_desc* desc, const void* k_in,
                              int32_t max_seg_len, int32_t* dev_flag, void* stream);
 
 /* Bytes of device workspace cf_prefill_attention needs for these bounds (host only, no HIP
- * call).  Returns 0 for an invalid/unsupported descriptor. */
+ * call).  Returns 0 for an invalid/unsupported descriptor.
+ * On the 16-bit kernels' shapes with up to 256 table entries a workspace for some max_kv_tokens and seg_stride serves every
+ * call of that batch and max_tq with smaller ones (a decode loop allocates once, for its longest cache).  A smaller batch or
+ * max_tq may need more: its calls are split further. */
 CF_API size_t cf_prefill_workspace_bytes(const cf_layer_desc* desc, int32_t batch, int32_t max_tq,
                                   int32_t seg_stride, int64_t max_kv_tokens);
 
@@ -190,7 +193,7 @@ CF_API cf_status cf_prefill_attention(const cf_layer_desc* desc,
  * library owns: a file-scope device array of CF_STATIC_SCRATCH_BYTES that every GPU the library runs on
  * holds until the process ends.  The call itself allocates nothing (no hipMalloc / hipFree, no
  * allocating library routine).
- *   - Shapes whose workspace (cf_prefill_workspace_bytes) exceeds CF_STATIC_SCRATCH_BYTES are
+ *   - Shapes whose partial results exceed CF_STATIC_SCRATCH_BYTES (never those whose cf_prefill_workspace_bytes does not) are
  *     rejected with CF_ERR_WORKSPACE before anything is launched.  One exception: shapes outside the 16-bit kernels'
  *     (fp32, head_dim other than 128, interleaved pairs) whose batch * max_tq * n_q_heads * (seg_stride + 1) * 8 bytes
  *     fit are served by the row-by-row kernel, slower and with results that agree to fp32 rounding instead.

@@ -173,6 +173,12 @@ size_t cf_prefill_workspace_bytes(const cf_layer_desc* desc, int32_t batch, int3
     return (n + 255) & ~(size_t)255;
 }
 
+// What a call with a workspace of `given` bytes needs.
+static size_t call_bytes(const cf_layer_desc* desc, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens, size_t given) {
+    return mfma_path_supported(desc) ? mfma_call_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens, given)
+                                     : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+}
+
 static cf_status check_prune_step(const cf_prune_step* pr, int32_t seg_stride, const float* score_accum,
                                   int32_t score_stride, const cf_segment* segs, const int32_t* n_seg,
                                   const int32_t* q_new_start) {
@@ -238,9 +244,10 @@ static cf_status prefill_impl(const cf_layer_desc* desc, const void* q, const in
     CF_REQUIRE(q_stored_start >= 0 && q_stored_start < desc->max_positions, CF_ERR_RANGE,
                "q_stored_start outside [0, max_positions)");
     const size_t need = row_by_row ? generic_workspace_bytes(desc, batch, max_tq, seg_stride)
-                                   : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+                                   : call_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens, workspace_bytes);
     CF_REQUIRE(workspace != nullptr && workspace_bytes >= need, CF_ERR_WORKSPACE,
-               "workspace too small: %zu bytes given, %zu needed", workspace_bytes, need);
+               "workspace too small: %zu bytes given, %zu needed", workspace_bytes,
+               row_by_row ? need : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens));
     CF_REQUIRE((reinterpret_cast<uintptr_t>(workspace) & 255u) == 0, CF_ERR_WORKSPACE,
                "workspace must be 256-byte aligned");
 
@@ -321,7 +328,8 @@ cf_status cf_prefill_attention_static(const cf_layer_desc* desc, const void* q, 
     CF_REQUIRE(batch >= 0 && max_tq >= 1 && seg_stride >= 1 && max_kv_tokens >= 0, CF_ERR_INVALID_ARG,
                "batch, max_tq, seg_stride or max_kv_tokens out of range");
     if (batch == 0) return CF_OK;
-    size_t need = cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+    // the plan that a call with a workspace of its own gets, so that results are the same
+    size_t need = call_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens, SIZE_MAX);
     // Outside the 16-bit kernels' shapes a plan may need more than the row-by-row kernel, which keeps (slots x rows) statistics only:
     // by the partial rows of its splits and the slots' sums.  What that kernel can serve from the buffer is served by it.
     const bool row_by_row = need > CF_STATIC_SCRATCH_BYTES && !mfma_path_supported(desc) &&
@@ -329,7 +337,7 @@ cf_status cf_prefill_attention_static(const cf_layer_desc* desc, const void* q, 
     if (row_by_row) need = generic_workspace_bytes(desc, batch, max_tq, seg_stride);
     CF_REQUIRE(need <= CF_STATIC_SCRATCH_BYTES, CF_ERR_WORKSPACE,
                "this shape needs %zu bytes of scratch, the library-owned buffer holds %zu: use cf_prefill_attention with a workspace",
-               need, (size_t)CF_STATIC_SCRATCH_BYTES);
+               cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens), (size_t)CF_STATIC_SCRATCH_BYTES);
     void* scratch = nullptr;
     st = static_scratch(&scratch);
     if (st != CF_OK) return st;

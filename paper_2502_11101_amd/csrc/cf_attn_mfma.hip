@@ -941,10 +941,13 @@ static bool mfma_shape_ok(int seg_stride) { return seg_stride <= kMaxSegs; }
 
 size_t mfma_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride,
                             int64_t max_kv_tokens) {
-    const size_t gen = generic_workspace_bytes(d, batch, max_tq, seg_stride);
-    if (!mfma_shape_ok(seg_stride)) return gen;
-    const Plan p = make_plan(d->n_q_heads, d->n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
-    return p.total;
+    if (!mfma_shape_ok(seg_stride)) return generic_workspace_bytes(d, batch, max_tq, seg_stride);
+    return workspace_bytes(d->n_q_heads, d->n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
+}
+
+size_t mfma_call_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens, size_t given) {
+    if (!mfma_shape_ok(seg_stride)) return generic_workspace_bytes(d, batch, max_tq, seg_stride);
+    return make_plan(d->n_q_heads, d->n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, given).total;
 }
 
 cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_t s, const cf_prune_step* prune) {
@@ -952,7 +955,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         cf_status st = launch_attention_generic(a, f, s);
         return st != CF_OK || !prune ? st : launch_prune_step(a, prune, s);
     }
-    const Plan p = make_plan(a.n_q_heads, a.n_kv_heads, a.batch, a.max_tq, a.seg_stride, a.max_kv_tokens);
+    const Plan p = make_plan(a.n_q_heads, a.n_kv_heads, a.batch, a.max_tq, a.seg_stride, a.max_kv_tokens, a.workspace_bytes);
     const dim3 grid3((unsigned)p.nsplit, (unsigned)a.n_kv_heads, (unsigned)a.batch);     // attn_tile_kernel's
     const dim3 grid2((unsigned)(p.nsplit * a.batch), (unsigned)p.units_per_b);           // attn_wide_kernel's
     // grid dimensions of this path's kernels (the merge kernel's may carry one more row, for pending score parts)

@@ -1,25 +1,21 @@
-// Shared by the 16-bit attention kernels and the kernels that reduce their partial results: the launch plan
-// (how rows, tokens and splits map to workgroups and where the partials live in the workspace), the per-query
+// Shared by the 16-bit attention kernels and the kernels that reduce their partial results: the launch plan (cf_plan.h), the per-query
 // segment table in its two forms (LDS, registers) with the tile walk over it, and the MFMA wrappers.
 #pragma once
 
-#include <algorithm>
-
 #include "cf_common.h"
+#include "cf_plan.h"
 #include "cf_select_dev.h"
 
 namespace cf {
 namespace attn {
 
 constexpr int kThreads = 256;
-constexpr int kWaves = 4;
-constexpr int kD = 128;
 constexpr int kHalf = 64;
 constexpr int kKRow = 272;      // bytes per token of a staged K tile
 constexpr int kMaxSegs = 256;
-constexpr int kMaxSplit = 32;
-constexpr int kSoloWaves = 8;   // wavefronts of attn_solo_kernel's workgroups, each with tiles of its own
 constexpr int kMaxSub = 2 * kMaxSplit;       // runs of tiles of a (query, kv head, row group): splits x groups
+static_assert(kSoloSplits * kSoloWaves <= kMaxSub, "the reductions have room for that many runs");
+static_assert(kMaxPending == CF_MAX_PENDING, "the plan's ledger");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -27,132 +23,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-struct Plan {
-    int group;          // query heads per kv head
-    int row_blocks;     // 16-row blocks of the stacked rows of one kv head
-    int wide;           // 0: attn_tile_kernel or attn_solo_kernel (few rows), 1: attn_wide_kernel
-    int nrb;            // 64-row passes of a workgroup's rows (what the combine kernel handles at a time)
-    int rows_wg;        // rows a workgroup has room for: 64 * nrb
-    int n_rg;           // row groups per (query, kv head)
-    int blocks_rg;      // 16-row blocks per row group
-    int units_per_b, units, nsplit, slots;
-    int tile;           // tokens per tile: 32 or 64
-    int groups;         // runs of tiles per workgroup: 1 or 2 (groups of four wavefronts), kSoloWaves (attn_solo_kernel)
-    int direct_out;     // one split: the attention kernel writes the output rows itself, nothing to merge
-    size_t off_ml, off_opart, off_massml, off_masspart, total;
-    size_t masspart_bytes;      // one layer's slot partials (the ledger holds kMaxPending + 1 such parts)
-};
-
-// `small`: the fewest row groups and runs (see make_plan).
-inline Plan plan_of(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens, bool small) {
-    Plan p;
-    const int group = n_q_heads / n_kv_heads;
-    const int row_blocks = (group * max_tq + 15) / 16;
-    p.group = group;
-    p.row_blocks = row_blocks;
-    const int64_t est_tiles = max_kv_tokens / 32 + seg_stride;           // every plan's tiles are of 32 tokens
-    // splits of a (query, kv head, row group): the CUs are shared out, and a split of attn_tile_kernel has about two tiles for each of
-    // its two groups (four a split are the better for attn_wide_kernel too: one query of 20 rows x 4 heads, ten documents, 23.5 us
-    // against 25.4 with two)
-    auto splits_of = [&](int64_t units) {
-        const int64_t cap = std::max<int64_t>(est_tiles / 4, 1);
-        return std::max<int64_t>(std::min({256 / units, cap, (int64_t)kMaxSplit}), 1);
-    };
-    if (row_blocks <= 4) {
-        // Few stacked rows (MHA-like, HBM-bound): one row block per wavefront, small tiles, so that ragged
-        // segment ends waste little and a split still holds several tiles; two groups of four wavefronts per
-        // workgroup run two tiles at a time on one CU and hide each other's LDS and barrier waits.
-        p.wide = 0;
-        p.n_rg = 1;
-        p.nrb = 1;
-        p.tile = 32;
-        p.groups = 2;
-    } else {
-        // Many rows (GQA, long queries): row groups of up to three blocks per wavefront, or of up to two.  Fewer groups stage the same keys
-        // less often, but three blocks keep every register busy and two do not: a tile's time goes about as 4 * blocks per wavefront
-        // + 2, and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
-        // three of three: one query of 50 documents 37.8 us against 41.7, 8 queries of 20 66 against 76, 32 171 against 197.  384 rows, 64
-        // queries x 2 kv heads, as three of two 168 us, as two of three 127 (384 units against 256); five documents of 100-200 tokens x 7
-        // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).  Past the CUs a share of a round costs most of one: 107 rows x 6, 36
-        // queries x 2 heads, 10 documents, as four of three (288 units) 91 us, as six of two (432) 80; 83 rows x 7, 14 queries x 4 heads, 10
-        // documents, as five of two (280) 95, as four of three (224) 76; 129 rows x 6, 41 queries x 2 heads, as seven of two (574) 91, as
-        // five of three (410) 75.
-        p.wide = 1;
-        p.tile = 32;
-        double best = 0;
-        for (int per_wave = 3; per_wave >= (small ? 3 : 2); --per_wave) {
-            const int n_rg = (row_blocks + kWaves * per_wave - 1) / (kWaves * per_wave);
-            const int nrb = ((row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves;
-            if (per_wave < 3 && (int64_t)n_kv_heads * n_rg + 1 > 65535) continue;        // past the grid: fewer groups are taken instead
-            const int64_t units = (int64_t)batch * n_kv_heads * n_rg;
-            // past the CUs two workgroups share one, at 1.7 times what one alone takes, and a third begins when they end
-            const double rounds = units > 512 ? std::max(units / 256., 2.7) : 1.7;
-            const double cost = (4 * nrb + 2) * (units > 256 ? rounds : 1. / splits_of(units));
-            if (per_wave == 3 || cost < best) { best = cost; p.n_rg = n_rg; p.nrb = nrb; }
-        }
-    }
-    p.blocks_rg = (row_blocks + p.n_rg - 1) / p.n_rg;
-    p.rows_wg = 64 * p.nrb;
-    p.units_per_b = n_kv_heads * p.n_rg;
-    p.units = batch * p.units_per_b;
-    // One launch wave: a CU holds one workgroup of either kernel at a time (8 wavefronts of about 190 and 250 registers), so a
-    // grid a little past the 256 CUs runs two rounds, the second nearly empty, each with its prologue and tail.  Rounded down and
-    // not up, attn_tile_kernel's calls that 256 does not divide measured: 6 decode queries x 32 heads over 1017-1573 tokens (192
-    // units, two splits against one) 37.6 -> 26.5 us, 17 x 4 heads over 1355-1704 (68 units, four against three) 26.3 -> 19.0,
-    // 28 x 2 heads over 723 (56 units) 18.6 -> 13.1, 3 layer queries x 32 heads, 7 short documents (96 units) 28.0 -> 22.2.
-    // The exception is a long batch that would leave over a quarter of the CUs idle: its halves even out unequal lengths, which the host
-    // does not know, and cost less where the lengths are equal than they save where they are not.  Decode queries x 4 heads, one
-    // split against two: up to 4096 tokens, lengths a fifth of that and more: 144 units 78 -> 64 us, 160 78 -> 62, 176 80 -> 74; up to
-    // 12000: 198 -> 154, 204 -> 186, 207 -> 175; all of 4096: 82 -> 95, 82 -> 97, 83 -> 100.  At 192 units and more one is the better
-    // (50 queries of 1000-5000 tokens, 200 units: 77 against 85), and for shorter lists (1024 tokens, 160 units: 31 against 35 and 39).
-    const bool halves = !p.wide && p.units > 128 && p.units < 192 && est_tiles > 128;
-    int64_t ns = halves ? 2 : splits_of(p.units);
-    // attn_solo_kernel: one row block over at most two table entries (a decode step: the cache and the own block; short documents over
-    // the prefix) and at most eight splits, as many runs of tiles as the reductions have room for.  Longer tables are layer calls, which ask
-    // for masses: eight statistics per segment and split to reduce cost more than the attention saves (10 documents of 160 tokens x 12
-    // rows x 32 heads 24.8 us against 23.2 with attn_tile_kernel, 30 documents x 16 rows 33.9 against 31.3).  More splits are long lists
-    // over few units, which attn_tile_kernel spreads over more CUs (4 units x 2000 tokens 12.7 us as eight splits here, 12.2 as 16 there, x
-    // 14000 30.4 and 20.3).  The line does not ask for masses, so that a call's outputs do not depend on whether it wants them.
-    // Lists of up to two tiles per wavefront, which are all in flight at once, take one split and no merge: one conversation of 200 | 400
-    // tokens x 32 heads 10.6 -> 8.4 | 11.2 -> 10.0 us, 32 of 200 | 400 x 4 heads 15.2 -> 9.2 | 17.3 -> 12.1; of 881 (seven splits) 13.5
-    // would be 16.6.  Where the CUs allow two splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32
-    // heads 21.8 -> 17.8, of 150-880 19.9 -> 16.0; of 3000 40.7 would be 43.4.
-    // With more than two splits of more than four tiles attn_tile_kernel is the faster: 2 conversations of 1500 tokens x 32 heads 18.7 us
-    // against 20.7, 1 14.5 against 15.3, 8 of 1000-2000 x 4 heads 15.2 against 16.0; with two up to 112
-    // units 28.3 against 28.5 (3 of 1972 x 32) and 26.7 against 26.9 (28 of 1500 x 4), at 128 54.7 against 53.7 (32 of 1000-5000 x 4); with one 33.7 against 32.1 (40 of 1000-2000 x 4); with seven of four tiles 12.6 against 11.7.
-    const bool whole = est_tiles <= 2 * kSoloWaves || (p.units > 85 && est_tiles <= 4 * kSoloWaves);
-    const bool solo = !small && row_blocks == 1 && seg_stride <= 2 && ns <= kMaxSub / kSoloWaves && (whole || ns == 1 || (ns == 2 && p.units > 112) || est_tiles < 5 * ns);
-    if (solo && whole) ns = 1;
-    p.nsplit = (int)ns;
-    p.direct_out = p.nsplit == 1;
-    // attn_wide_kernel as one group of wavefronts per workgroup: for units past the CUs, two workgroups of which share one (30
-    // documents x 32 heads, 960 units, encoded and stored: 84 us against 108 with two groups), and for splits of few tiles, which the second
-    // group's delay and the merge of the groups cost more than it saves.  Around the line, us with one group against two: one query x 2
-    // kv heads, 384 rows, under four tiles a split 29.0 against 32.0, 4 queries x 4 heads, 140 rows, seven 31.3 against 33.2; 8 queries x
-    // 2 heads, 384 rows, fifteen 42.2 against 41.2, 2 x 32 heads, 130 rows, twelve 40.9 against 38.9.
-    if (p.wide) p.groups = !small && p.units <= 256 && est_tiles >= 10 * ns ? 2 : 1;
-    else if (solo) p.groups = kSoloWaves;
-    p.slots = seg_stride + p.nsplit * p.groups;
-    size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) & ~(size_t)255; return o; };
-    p.off_ml = take((size_t)p.units * p.nsplit * p.rows_wg * sizeof(float2));
-    p.off_opart = take(p.direct_out ? 0 : (size_t)p.units * p.nsplit * p.rows_wg * kD * sizeof(uint16_t));
-    p.off_massml = take((size_t)p.units * p.slots * p.rows_wg * sizeof(float2));
-    p.masspart_bytes = ((size_t)p.units * p.nrb * p.slots * sizeof(float) + 255) & ~(size_t)255;
-    p.off_masspart = take(p.masspart_bytes * (kMaxPending + 1));
-    p.total = off;
-    return p;
-}
-
-// More row groups and more runs of tiles per workgroup take workspace.  Where that alone would carry a plan past the buffer of the entry
-// point that brings its own, the plan does without.
-inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
-    const Plan p = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, false);
-    if (p.total <= CF_STATIC_SCRATCH_BYTES) return p;
-    const Plan least = plan_of(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens, true);
-    return least.total <= CF_STATIC_SCRATCH_BYTES ? least : p;
-}
 
 // Per-query segment table in LDS with the tile prefix that defines the partition.
 struct SegTable {

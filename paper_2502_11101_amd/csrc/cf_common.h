@@ -205,8 +205,10 @@ size_t plain_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_
 cf_status launch_attention_plain(const cf_layer_desc* d, AttnArgs a, const RopeFreq& f, hipStream_t s, const cf_prune_step* prune);
 
 bool mfma_path_supported(const cf_layer_desc* d);
+// what to allocate for these bounds, and what a call with a workspace of `given` bytes needs (at most as much)
 size_t mfma_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride,
                             int64_t max_kv_tokens);
+size_t mfma_call_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens, size_t given);
 cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_t s, const cf_prune_step* prune);
 // the three stand-alone launches of a prune step (ranking, allocation, table rebuild)
 cf_status launch_prune_step(const AttnArgs& a, const cf_prune_step* prune, hipStream_t s);

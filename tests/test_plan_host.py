@@ -1,6 +1,9 @@
 """Launch plans of the 16-bit attention path, as far as the host sees them."""
 
+import pytest
+
 from paper_2502_11101_amd import binding as cf
+from tests import plan_probe
 
 
 def test_static_calls_of_many_rows_stay_accepted():
@@ -59,3 +62,34 @@ def test_static_calls_of_one_row_block_stay_accepted():
                         assert need <= limit, (hkv, batch, stride, max_kv)
                         near += total > limit - (1 << 20)
     assert near > 10
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 32), (28, 4), (12, 2), (8, 1), (32, 8)])
+def test_a_workspace_for_the_longest_lists_serves_all_shorter_ones(hq, hkv):
+    """The bytes reported never shrink as max_kv_tokens or seg_stride grows, and the plan of a call needs no more than is reported for
+    its own arguments: what was allocated for a decode loop's longest cache serves every step on the way."""
+    d = cf.make_desc(hq, hkv, 128, "bf16", 1.0e4, 32768, cf.CF_ROPE_HALF)
+    tokens = [*range(0, 1600, 32), 2000, 3000, 4096, 8000, 12000, 30000]
+    for batch in (1, 2, 3, 8, 24, 32, 33, 48, 64, 200):
+        for tq in (1, 4, 20, 48, 64, 130):
+            shorter = [0] * len(tokens)                  # the bytes of the table before, per number of tokens
+            for stride in (1, 2, 3, 4, 12, 52, 65, 200):
+                last = 0
+                for i, kv in enumerate(tokens):
+                    need = cf.cf_prefill_workspace_bytes(d, batch, tq, stride, kv)
+                    assert need >= last and need >= shorter[i], (batch, tq, stride, kv)
+                    last = shorter[i] = need
+                    assert plan_probe.plan(hq, hkv, batch, tq, stride, kv, need).total <= need, (batch, tq, stride, kv)
+
+
+def test_a_decode_loop_allocates_once():
+    """One workspace, sized for 4096 tokens: no shorter cache is refused for it.  (The call ends at the next check, of the pointer.)"""
+    fake = 0x1000                                        # never dereferenced
+    for hq, hkv, batch in ((32, 32, 1), (28, 4, 8)):
+        d = cf.make_desc(hq, hkv, 128, "bf16", 1.0e4, 8192, cf.CF_ROPE_HALF)
+        have = cf.cf_prefill_workspace_bytes(d, batch, 1, 2, 4096)
+        for kv in range(1, 4097, 31):
+            with pytest.raises(cf.CacheFocusError) as e:
+                cf.cf_prefill_attention(d, fake, fake, 0, fake, fake, fake, 5000, fake, fake, fake, fake, 2, batch, 1, kv, fake, None, None, 1,
+                                        0x10010, have, None, stream=0)
+            assert "aligned" in e.value.message, (kv, e.value.message)
