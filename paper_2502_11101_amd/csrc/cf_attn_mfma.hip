@@ -323,11 +323,13 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) *reinterpret_cast<uint4*>(v_write + 4 * i * kSoloVRow) = r.v[i];
+        wave_lds_order();                            // what a lane writes here is read by others of the wavefront below
         if (cd.delta != 0) {
             if (cd.seg != cs_seg) {
                 cs_seg = cd.seg;
                 cs_lds[wave][lane] = rope_cos_sin_fast(cd.delta, my_freq);
             }
+            wave_lds_order();
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk) {
                 const ChunkAngles ang = load_chunk_angles(cs_lds[wave] + 32 * kk + 8 * lg);
@@ -389,6 +391,7 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
             const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
             acc[db] = Mma<DT>::run(make_uint4(l2.x, l2.y, h2.x, h2.y), pfrag, acc[db]);
         }
+        wave_lds_order();                            // the next step writes over what others read above
     };
     // (left from the middle: with a step skipped the wait for one register set would have to cover the other as well)
     for (int left = my_tiles; left > 0;) {
