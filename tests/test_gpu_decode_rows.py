@@ -1,71 +1,26 @@
 """GPU parity of the attention kernel for one 16-row block (decode steps): every wavefront streams tiles of its own.
-Tile counts from fewer than the wavefronts to several each, ragged ends, several splits and one, moved and unmoved keys, rows from one
-to sixteen with the causal own block, and the longer tables that the other kernel keeps."""
+Tile counts from fewer than the wavefronts to fourteen each, ragged ends, several splits and one, moved and unmoved keys, references that
+move on the way, rows from one to sixteen with the causal own block, whole layers with their scores and prune events, and the
+longer tables that the other kernel keeps."""
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2502_11101_amd import binding as cf
-from paper_2502_11101_amd import pipeline as pl
 from paper_2502_11101_amd import workloads as wl
+from tests import attn_cases, plan_probe
 from tests import gpu_harness as G
 from tests import helpers as H
-from oracle import cachefocus_oracle as orc
 
 pytestmark = pytest.mark.gpu
 
 
-def _check(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head"):
-    """`tables`: per query the (offset, length, stored, new) of its store segments; the own block of tq rows follows at q_pos."""
-    rng = np.random.default_rng(seed)
-    batch = len(tables)
-    normal = lambda n, h: wl.round_to_dtype(rng.standard_normal((n, h, 128), dtype=np.float32), dtype)
-    t = dict(q=normal(batch * tq, hq), k_self=normal(batch * tq, hkv), v_self=normal(batch * tq, hkv), k_store=normal(n_store, hkv),
-             v_store=normal(n_store, hkv))
-    dev = {k: (pl.store_to_device(v, dtype, layout, 0) if k in ("k_store", "v_store") else pl.to_device(v, dtype)) for k, v in t.items()}
-    ts, hs = (0, 0) if layout == "token" else pl.store_strides(n_store, hkv, 128, layout, 0)
-    desc = cf.make_desc(hq, hkv, 128, dtype, 1.0e4, 8192, cf.CF_ROPE_HALF, store_token_stride=ts, store_head_stride=hs)
-    stride = max(len(x) for x in tables) + 1
-    rows, segs = [], []
-    for b, x in enumerate(tables):
-        own = [orc.Segment(o, n, s, p, orc.KIND_DOC, i) for i, (o, n, s, p) in enumerate(x)] + \
-            [orc.Segment(b * tq, tq, 0, q_pos, orc.KIND_SELF, -1)]
-        segs.append(own)
-        rows += [(g.tok_offset, g.len, g.stored_start, g.new_start, g.kind, g.doc) for g in own]
-        rows += [(0, 0, 0, 0, cf.CF_SEG_DOC, -1)] * (stride - len(own))
-    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
-    table = cf.segments_to_device(cf.segments_array(rows))
-    max_kv = max(sum(n for _, n, _, _ in x) for x in tables) + tq
-    need = cf.cf_prefill_workspace_bytes(desc, batch, tq, stride, max_kv)
-    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
-    flag, out = i32([0]), torch.empty_like(dev["q"])
-    cf.cf_prefill_attention(desc, dev["q"], i32([b * tq for b in range(batch + 1)]), 0, i32([q_pos] * batch), dev["k_store"], dev["v_store"],
-                            n_store, dev["k_self"], dev["v_self"], table, i32([len(x) for x in segs]), stride, batch, tq, max_kv, out,
-                            None, None, 1, ws, need, flag)
-    # the same call with the segments' masses: the same outputs, bit for bit
-    again, mass = torch.empty_like(out), torch.zeros((batch, stride), dtype=torch.float32, device="cuda")
-    cf.cf_prefill_attention(desc, dev["q"], i32([b * tq for b in range(batch + 1)]), 0, i32([q_pos] * batch), dev["k_store"], dev["v_store"],
-                            n_store, dev["k_self"], dev["v_self"], table, i32([len(x) for x in segs]), stride, batch, tq, max_kv, again,
-                            mass, None, 1, ws, need, flag)
-    torch.cuda.synchronize()
-    assert int(flag.item()) == 0 and torch.equal(again, out)
-    got, mass = out.float().cpu().numpy(), mass.cpu().numpy()
-    for b in range(batch):
-        ks, vs, compact = H.compact_query(segs[b], t["k_store"], t["v_store"])
-        part = slice(b * tq, (b + 1) * tq)
-        ref, near = H.rounded_key_reference(dtype, t["q"][part], 0, q_pos, ks, vs, t["k_self"], t["v_self"], compact, hkv, 1.0e4)
-        assert np.isfinite(got[part]).all()
-        assert G.row_error(got[part], ref) <= G.OUT_TOL[dtype]
-        assert G.rel_error(mass[b, :len(segs[b])], near) <= G.NEAR_MASS_TOL[dtype]
-        assert mass[b].sum() == pytest.approx(hq * tq, rel=1e-5)
-
-
-@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 479, 480, 545, 1500])        # one split up to 479, the other kernel at 1500
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 255, 257, 478, 479, 480, 545, 1500])   # 32 heads: one split up to 478, the other kernel at 1500
 @pytest.mark.parametrize("hq,hkv,dtype", [(32, 32, "bf16"), (28, 4, "f16"), (16, 1, "bf16")])
 def test_one_row_over_a_cache(n, hq, hkv, dtype):
     print(f"decode n={n} {hq}/{hkv} {dtype}", flush=True)
-    _check(hq, hkv, 1, [[(0, n, 0, 0)]], n, dtype, n, seed=n)
+    G.check_tables(hq, hkv, 1, [[(0, n, 0, 0)]], n, dtype, n, seed=n)
 
 
 @pytest.mark.parametrize("layout", ["head", "token"])
@@ -75,7 +30,7 @@ def test_unequal_conversations(batch, hkv, layout):
     rng = np.random.default_rng(batch)
     lens = rng.integers(1, 900, size=batch)
     off = np.concatenate([[0], np.cumsum(lens)])
-    _check(2 * hkv, hkv, 1, [[(int(off[b]), int(lens[b]), 0, 0)] for b in range(batch)], int(off[-1]), "bf16", 1000, seed=batch, layout=layout)
+    G.check_tables(2 * hkv, hkv, 1, [[(int(off[b]), int(lens[b]), 0, 0)] for b in range(batch)], int(off[-1]), "bf16", 1000, seed=batch, layout=layout)
 
 
 @pytest.mark.parametrize("docs", [1, 2, 63, 64])   # tables of 2 entries (attn_solo_kernel), 3, 64 and 65 (attn_tile_kernel)
@@ -87,29 +42,95 @@ def test_moved_documents_and_the_causal_own_block(docs, group, tq):
     off = np.concatenate([[0], np.cumsum(lens)])
     # every third document keeps its distance to the query: not moved
     new = [(16 if i % 3 == 1 else int(rng.integers(0, 6000))) for i in range(docs)]
-    _check(2 * group, 2, tq, [[(int(off[i]), int(lens[i]), 16, new[i]) for i in range(docs)]] * 2, int(off[-1]), "bf16", 0, seed=docs)
+    G.check_tables(2 * group, 2, tq, [[(int(off[i]), int(lens[i]), 16, new[i]) for i in range(docs)]] * 2, int(off[-1]), "bf16", 0, seed=docs)
 
 
-def test_scores_that_rise_move_the_reference():
-    """Keys whose scores climb tile after tile: every wavefront's reference moves at almost every tile."""
-    n, hkv = 800, 2
-    rng = np.random.default_rng(3)
-    base = rng.standard_normal((1, hkv, 128)).astype(np.float32)
-    q = wl.round_to_dtype(np.repeat(base, 2, axis=1), "bf16")
-    ramp = np.linspace(0.0, 5.0, n, dtype=np.float32)[:, None, None]
-    k = wl.round_to_dtype(ramp * base + 0.1 * rng.standard_normal((n, hkv, 128)).astype(np.float32), "bf16")
-    v = wl.round_to_dtype(rng.standard_normal((n, hkv, 128)).astype(np.float32), "bf16")
-    own = [wl.round_to_dtype(rng.standard_normal((1, hkv, 128)).astype(np.float32), "bf16") for _ in range(2)]
-    desc = cf.make_desc(2 * hkv, hkv, 128, "bf16", 1.0e4, 8192, cf.CF_ROPE_HALF)
-    segs = [orc.Segment(0, n, 0, 0, orc.KIND_DOC, 0), orc.Segment(0, 1, 0, n, orc.KIND_SELF, -1)]
-    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")
-    table = cf.segments_to_device(cf.segments_array([(g.tok_offset, g.len, g.stored_start, g.new_start, g.kind, g.doc) for g in segs]))
-    need = cf.cf_prefill_workspace_bytes(desc, 1, 1, 2, n + 1)
-    ws, flag = torch.zeros(need, dtype=torch.uint8, device="cuda"), i32([0])
-    dq, dk, dv, dks, dvs = (pl.to_device(x, "bf16") for x in (q, k, v, *own))
-    out = torch.empty_like(dq)
-    cf.cf_prefill_attention(desc, dq, i32([0, 1]), n, i32([n]), dk, dv, n, dks, dvs, table, i32([2]), 2, 1, 1, n + 1, out, None, None, 1, ws,
-                            need, flag)
+@pytest.mark.parametrize("pattern", ["rising", "falling", "saw", "spike", "moved"])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", attn_cases.SOLO, ids=attn_cases.id_of)
+def test_long_runs_of_a_wavefront(case, dtype, pattern):
+    """Conversations of unequal length over one cache, up to fourteen tiles per wavefront.  `rising` and the others: keys with a growing
+    share of the query's direction, so that a wavefront's reference moves again and again and takes what it has summed with it (about ten
+    nats over a run of 400 tokens); `moved`: plain keys that are moved."""
+    print(f"runs {attn_cases.id_of(case)} {dtype} {pattern}", flush=True)
+    rng = np.random.default_rng(case.tokens + case.batch)
+    cached = case.tokens - case.tq
+    lens = [cached, cached // 2, 1] + [int(x) for x in rng.integers(1, cached + 1, size=case.batch - 3)]
+
+    def shape(t, rng):
+        if pattern == "moved":
+            return
+        i = np.arange(cached)
+        share = {"rising": 8.0 * i / cached, "falling": 8.0 - 8.0 * i / cached, "saw": 6.0 * (i % 300) / 300,
+                 "spike": np.where(i % 700 == 350, 6.0, 0.0)}[pattern]
+        base = rng.standard_normal((1, case.hkv, 128)).astype(np.float32)
+        rd = lambda x: wl.round_to_dtype(x.astype(np.float32), dtype)
+        t["q"] = rd(np.repeat(base, case.hq // case.hkv, axis=1) + 0.1 * t["q"])
+        t["k_store"] = rd(share[:, None, None] * base + 0.1 * t["k_store"])
+        t["k_self"] = rd(share.max() * base + 0.1 * t["k_self"])        # as much as the largest, so that no mass vanishes
+
+    new = 900 if pattern == "moved" else 0
+    G.check_tables(case.hq, case.hkv, case.tq, [[(0, n, 0, new)] for n in lens], cached, dtype, 0, seed=case.tokens,
+                   layout="head" if dtype == "bf16" else "token", check=[0, 1, 2, case.batch - 1], shape=shape)
+
+
+def _layers_over_one_document(cfg, st, layers, keeps, deferred):
+    """A stack whose tables have two entries, a document and the own block."""
+    pb = G.make_batch(cfg, st, layout="head")
+    assert pb.seg_stride == 3 and cfg.prefix_len == 0
+    pb.seg_stride = 2
+    pb.segs, pb.next_segs = pb.segs[:, :2].contiguous(), pb.next_segs[:, :2].contiguous()
+    pb.mass = pb.mass[:, :2].contiguous()
+    pb.ws_bytes = cf.cf_prefill_workspace_bytes(pb.desc, pb.batch, pb.tq, 2, pb.max_kv_tokens)
+    pb.workspace = torch.full((pb.ws_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    g = cfg.geometry
+    assert plan_probe.plan(g.n_q_heads, g.n_kv_heads, pb.batch, pb.tq, 2, pb.max_kv_tokens, pb.ws_bytes).groups == 8
+    pb.allocate_initial()
+    outs, tables = [], []
+    for i, dev in enumerate(layers):
+        out, args = torch.empty_like(dev["q"]), (dev["q"], dev["k_self"], dev["v_self"], dev["k_store"], dev["v_store"])
+        if deferred is None:                         # the separate calls
+            pb.attention(*args, out)
+            if i in keeps:
+                pb.prune(1)
+        else:
+            pb.layer(*args, out, keep=1 if i in keeps else None, defer=deferred and i not in keeps and i != len(layers) - 1)
+        outs.append(out)
+        if i in keeps:
+            torch.cuda.synchronize()
+            tables += [pb.score.clone(), pb.keep_idx.clone(), pb.n_keep.clone(), pb.next_segs.clone(), pb.next_q_start.clone()]
+            pb.advance()
     torch.cuda.synchronize()
-    ref, _ = orc.prefill_attention(H.f64(q), n, n, k, v, own[0], own[1], segs, hkv, 1.0e4)
-    assert G.row_error(out.float().cpu().numpy(), ref) <= G.OUT_TOL["bf16"]
+    assert pb.flags() == 0
+    return outs, tables + [pb.score.clone()], pb.mass.clone()
+
+
+@pytest.mark.parametrize("geo,batch,tq,length", [(wl.Geometry(8, 2, 128, "bf16", 1.0e4, 8192), 3, 4, 700),        # eight splits
+                                                 (wl.Geometry(8, 8, 128, "f16", 1.0e4, 8192), 40, 16, 150)])      # one
+def test_layers_over_one_document(geo, batch, tq, length):
+    """cf_prefill_layer, deferred and not, against the separate calls and its scores against the oracle."""
+    print(f"layers over one document, batch {batch}", flush=True)
+    n_layers, keeps = 5, (2,)
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name=f"one_document_{batch}", geometry=geo, n_store_docs=batch, docs_per_query=1, batch=batch,
+                    doc_len_range=(length - 60, length), tq=tq, prefix_len=0, doc_stored_start=8, n_planted=1)
+    st = wl.build_structure(cfg, seed=batch)
+    tensors = [wl.build_layer(cfg, st, layer, seed=batch + layer) for layer in range(n_layers)]
+    layers = [G.upload_layer(cfg, t, "head") for t in tensors]
+    apart, eager, lazy = (_layers_over_one_document(cfg, st, layers, keeps, deferred) for deferred in (None, False, True))
+    assert all(torch.equal(x, y) for x, y in zip(apart[0], eager[0])) and all(torch.equal(x, y) for x, y in zip(eager[0], lazy[0]))
+    assert all(torch.equal(x, y) for x, y in zip(eager[1], lazy[1])) and torch.equal(eager[2], lazy[2])
+    assert all(torch.equal(x, y) for x, y in zip(apart[1][1:5], eager[1][1:5]))
+    assert G.rel_error(eager[1][0].cpu().numpy(), apart[1][0].cpu().numpy()) < 2e-6        # the same parts, added in another order
+    assert G.rel_error(eager[2].cpu().numpy(), apart[2].cpu().numpy()) < 2e-6
+    ref = np.zeros((batch, 1))
+    for layer in range(keeps[0] + 1):
+        t = tensors[layer]
+        for b in range(batch):
+            segs, q_start, _ = H.initial_segments(cfg, st, b)
+            ks, vs, table = H.compact_query(segs, t["k_store"], t["v_store"])
+            part = slice(b * tq, (b + 1) * tq)
+            out, mass = H.rounded_key_reference(geo.dtype, t["q"][part], 0, q_start, ks, vs, t["k_self"], t["v_self"], table, geo.n_kv_heads,
+                                                geo.rope_base)
+            ref[b] += H.doc_scores(table, mass, 1)
+            assert G.row_error(eager[0][layer][part].float().cpu().numpy(), out) <= G.OUT_TOL[geo.dtype]
+    assert G.rel_error(eager[1][0].cpu().numpy(), ref) <= G.NEAR_MASS_TOL[geo.dtype]

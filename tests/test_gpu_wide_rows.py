@@ -1,12 +1,14 @@
-"""GPU parity of the attention kernel for many stacked rows at the edges of its plan: row counts around a wavefront's two and three
-blocks and around the step to another row group, units on both sides of 256 (two groups of wavefronts per workgroup, or one), tile
-lists of one, two and three tiles per group with ragged ends and tables past 64 entries."""
+"""GPU parity of the attention kernel for many stacked rows: every variant (two and three blocks per wavefront, one and two groups of
+wavefronts, table in registers and in LDS, one split and several; attn_cases) over ragged batches whose short queries leave a group
+of wavefronts without a tile; then row counts around the step to another row group, short lists with ragged ends, units
+on both sides of 256 and long tables."""
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2502_11101_amd import workloads as wl
+from tests import attn_cases, plan_probe
 from tests import gpu_harness as G
 from tests import helpers as H
 
@@ -47,7 +49,35 @@ def _run(geo, batch, tq, lens, docs, prefix, seed, layout="head"):
         assert mass[b, :len(segs)].sum() == pytest.approx(geo.n_q_heads * tq, rel=1e-5)
 
 
-# stacked rows of a kv head: 65 (five blocks), 128 | 129 (two | three per wavefront), 192 | 193 (one | two row groups), 385, 577
+# tiles of a (query, kv head) whose own block is one tile: none but that one, then one, two, three and four before it
+SHORT = [[], [1], [31], [32], [33, 1], [63, 32], [65, 31, 2]]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", attn_cases.WIDE, ids=attn_cases.id_of)
+def test_variants(case, dtype):
+    """The first query has the longest table; the others have a few tiles for the same splits and groups, fewer rows now and then, or none."""
+    print(f"variant {attn_cases.id_of(case)} {dtype}", flush=True)
+    c = case
+    rng = np.random.default_rng(c.tokens + c.batch + c.group)
+    docs, total = c.entries - 1, c.tokens - c.tq
+    cuts = np.sort(rng.choice(np.arange(1, total), size=docs - 1, replace=False))
+    full = np.diff(np.concatenate([[0], cuts, [total]]))
+
+    def table(lens):
+        off = np.concatenate([[0], np.cumsum(lens)])
+        # every third document keeps its distance to the query: not moved
+        return [(int(off[i]), int(n), 16, 16 if i % 3 == 1 else int(rng.integers(0, 6000))) for i, n in enumerate(lens)]
+
+    short = [x for x in SHORT if len(x) <= docs]
+    tables = [table(full)] + [table(short[b % len(short)]) for b in range(1, c.batch)]
+    lengths = [c.tq] + [0 if b % 11 == 5 else c.tq // 3 if b % 4 == 3 else c.tq for b in range(1, c.batch)]
+    G.check_tables(c.group * c.hkv, c.hkv, c.tq, tables, total, dtype, 0, seed=c.tokens, layout="head" if dtype == "bf16" else "token",
+                   lengths=lengths, check=sorted({*range(min(c.batch, 13)), c.batch - 1}))
+
+
+# The next three: two blocks per wavefront and one group, unless said otherwise.
+# stacked rows of a kv head: 65 (five blocks), 128, then two row groups or more: 129, 192, 193, 385, 577
 @pytest.mark.parametrize("group,tq", [(5, 13), (4, 32), (3, 43), (6, 32), (1, 193), (7, 55), (1, 577)])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_row_counts(group, tq, dtype):
@@ -55,7 +85,7 @@ def test_row_counts(group, tq, dtype):
     _run(wl.Geometry(2 * group, 2, 128, dtype, 1.0e4, 8192), 2, tq, [33, 95, 64, 1, 160], 4, 32, seed=group * tq)
 
 
-# tiles of a (query, kv head): from a list that leaves the second group without one, to several per group, ragged ends of 1, 31, 32
+# tiles of a (query, kv head): from one to a dozen, ragged ends of 1, 31, 32
 @pytest.mark.parametrize("lens", [[1], [31], [32], [33, 1], [63, 32], [65, 31, 2], [200, 1, 129]])
 @pytest.mark.parametrize("batch", [3, 140])          # 6 and 280 units
 @pytest.mark.parametrize("prefix", [0, 17])
@@ -64,7 +94,7 @@ def test_short_tile_lists(lens, batch, prefix):
     _run(wl.Geometry(10, 2, 128, "bf16", 1.0e4, 4096), batch, 16, lens, len(lens), prefix, seed=sum(lens) + batch)
 
 
-@pytest.mark.parametrize("batch", [128, 129])        # 256 and 258 units
+@pytest.mark.parametrize("batch", [128, 129])        # 256 and 258 units, three blocks per wavefront: two groups, one
 @pytest.mark.parametrize("layout", ["head", "token"])
 def test_units_around_the_compute_units(batch, layout):
     print(f"units {2 * batch} {layout}", flush=True)
@@ -107,3 +137,36 @@ def test_non_finite_values_stay_with_the_rows_that_see_them():
         hit[:, 1, :, 90] = True
         assert torch.isposinf(outs[1][hit]).all()
         assert torch.equal(outs[0][~hit], outs[1][~hit])
+
+
+@pytest.mark.parametrize("batch,nsplit", [(64, 2), (128, 1)])
+def test_non_finite_values_with_two_groups(batch, nsplit):
+    """The same where one long query gives every query two groups of wavefronts and the short ones leave a group with one tile or none."""
+    print(f"infinities, two groups, batch {batch}", flush=True)
+    geo, tq, lens = wl.Geometry(10, 2, 128, "bf16", 1.0e4, 4096), 16, np.array([700, 400, 32, 1, 33], np.int32)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(off[-1])
+    picks = np.array([[0, 1]] + [[2, 3] if b % 2 else [4, 3] for b in range(1, batch)], np.int32)
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name="wide_inf_groups", geometry=geo, n_store_docs=len(lens), docs_per_query=2, batch=batch, tq=tq,
+                    prefix_len=0, doc_stored_start=0, n_planted=1)
+    pb = G.make_batch(cfg, wl.Structure(lens, off, n, picks, np.zeros((batch, 1), np.int32), 0))
+    p = plan_probe.plan(10, 2, batch, tq, pb.seg_stride, pb.max_kv_tokens, pb.ws_bytes)
+    assert (p.groups, p.nsplit) == (2, nsplit)
+    pb.allocate_initial()
+    rng = np.random.default_rng(6)
+    normal = lambda m, h: torch.from_numpy(rng.standard_normal((m, h, 128), dtype=np.float32)).to(torch.bfloat16).cuda()
+    q, ks, vs, k, v = normal(batch * tq, 10), normal(batch * tq, 2), normal(batch * tq, 2), normal(n, 2), normal(n, 2)
+    outs = []
+    for bad in (False, True):
+        if bad:
+            v[350, 0, 5] = float("inf")              # in the middle of the long query's first document
+            v[int(off[2]) + 31, 1, 90] = float("inf")        # the last token of the odd queries' first
+        out = torch.empty_like(q)
+        pb.attention(q, ks, vs, k, v, out)
+        torch.cuda.synchronize()
+        outs.append(out.float().cpu().reshape(batch, tq, 2, 5, 128))
+    hit = torch.zeros(outs[0].shape, dtype=torch.bool)
+    hit[0, :, 0, :, 5] = True
+    hit[1::2, :, 1, :, 90] = True
+    assert torch.isfinite(outs[0]).all() and torch.isposinf(outs[1][hit]).all()
+    assert torch.equal(outs[0][~hit], outs[1][~hit])

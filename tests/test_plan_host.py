@@ -3,7 +3,7 @@
 import pytest
 
 from paper_2502_11101_amd import binding as cf
-from tests import plan_probe
+from tests import attn_cases, plan_probe
 
 
 def test_static_calls_of_many_rows_stay_accepted():
@@ -93,3 +93,16 @@ def test_a_decode_loop_allocates_once():
                 cf.cf_prefill_attention(d, fake, fake, 0, fake, fake, fake, 5000, fake, fake, fake, fake, 2, batch, 1, kv, fake, None, None, 1,
                                         0x10010, have, None, stream=0)
             assert "aligned" in e.value.message, (kv, e.value.message)
+
+
+def test_the_attention_tests_reach_every_variant():
+    """The calls of attn_cases get the plans written beside them; those of many rows take every combination of blocks per wavefront, groups of
+    wavefronts, table form, and one split or several."""
+    for c in attn_cases.WIDE:
+        p = plan_probe.plan(c.group * c.hkv, c.hkv, c.batch, c.tq, c.entries, c.tokens)
+        assert (p.wide, p.nrb, p.groups, p.n_rg, p.nsplit) == (1, c.nrb, c.groups, c.n_rg, c.nsplit), c
+    assert {(c.nrb, c.groups, c.entries <= 64, c.nsplit == 1) for c in attn_cases.WIDE} == \
+        {(n, g, reg, one) for n in (2, 3) for g in (1, 2) for reg in (True, False) for one in (True, False)}
+    for c in attn_cases.SOLO:
+        p = plan_probe.plan(c.hq, c.hkv, c.batch, c.tq, 2, c.tokens)
+        assert (p.groups, p.nsplit, -(-(c.tokens // 32 + 2) // (8 * p.nsplit))) == (8, c.nsplit, c.tiles), c
