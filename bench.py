@@ -219,7 +219,7 @@ def setup_stack(args):
         assert pb.flags() == 0 and int(pb.n_cand[0].item()) == k
 
     info = dict(cfg=cfg, st=st, kv_tokens=kv_tokens, launches_per_step=cfg.n_layers, bound="hbm", check=check,
-                kernel="attn_tile_kernel<bf16,1,32,2,true>, the 32 launches of a step taken together",
+                kernel="attn_tile_kernel<bf16,true>, the 32 launches of a step taken together",
                 config={"workload": "llama2_7b_stack", "layers": cfg.n_layers, "documents_per_layer": alive,
                         "kv_tokens_per_step": kv_tokens, "q_heads": g.n_q_heads, "kv_heads": g.n_kv_heads,
                         "head_dim": g.head_dim, "tq": cfg.tq, "batch": 1, "store_layout": args.store_layout,

@@ -2,23 +2,25 @@
 //
 // Work decomposition.  The query rows that share a kv head (all rows of the G = Hq/Hkv heads of
 // the group, stacked: row m = g*tq + t) are cut into 16-row blocks; a workgroup owns a run of such blocks of one
-// (query, kv head) and a contiguous run of the attended tokens.  Tokens are counted in tiles that never
-// straddle a segment; the tile list of a (query, kv head) is divided evenly over `nsplit` workgroups.
-//   * At most 4 row blocks (MHA, short queries: HBM- and latency-bound): attn_tile_kernel, 32-token tiles,
-//     one row block per wavefront, every wavefront loads, stages and computes; two groups of four wavefronts
-//     per workgroup stream disjoint runs of tiles.
-//   * More (GQA groups, long queries: bound by instruction issue): attn_wide_kernel, 32-token tiles, two or three row
+// (query, kv head) and a contiguous run of the attended tokens.  Tokens are counted in 32-token tiles that never
+// straddle a segment; the tile list of a (query, kv head) is divided evenly over `nsplit` workgroups.  cf_plan.h picks the kernel:
+//   * At most 4 row blocks (MHA, short queries: HBM- and latency-bound): attn_tile_kernel, one row block per
+//     wavefront, every wavefront loads, stages and computes; two groups of four wavefronts per workgroup stream
+//     disjoint runs of tiles.
+//   * One row block over a table of at most two entries (decode steps): attn_solo_kernel, every wavefront streams a run of
+//     tiles of its own.
+//   * More than 4 (GQA groups, long queries): attn_wide_kernel, two or three row
 //     blocks per wavefront (up to 192 rows per workgroup), one or two groups of four wavefronts.
-// Per tile, in both:
+// Per tile, in all three:
 //   * the tiles ahead (two, or one) are in flight in registers (coalesced 16-byte loads),
-//   * the key tile is rotated in registers by its segment's relative position shift (Eq. 5;
-//     cos/sin per 2-D slice from an fp64-reduced angle), rounded once to the storage type and
-//     staged into LDS — rotated keys never return to memory; V is staged as loaded,
+//   * the keys are rotated in registers by their segment's relative position shift (Eq. 5; cos/sin per 2-D slice
+//     from an fp64-reduced angle) and rounded once to the storage type — rotated keys never return to memory; they
+//     go to LDS (attn_solo_kernel: stay in the registers they were loaded to, as matrix operands); V is staged as loaded,
 //   * S^T = K Q^T and O^T += V^T P^T run on v_mfma_f32_16x16x32 with the Q fragments resident
 //     in registers and the V^T fragments read with transposing LDS reads; the transposed forms keep
 //     one query row per lane, so the online softmax (fp32, exp2 domain) needs no cross-lane exchange
 //     except when its reference maximum moves.
-// At the end of each segment a wavefront leaves (reference maximum, sum of exp2) per row.
+// At the end of each segment a wavefront leaves (reference maximum, sum of exp2) per row (attn_solo_kernel: where masses are wanted).
 //
 // A second kernel merges the splits' partial outputs and writes the output rows; a third reduces
 // the (max, sum) pairs to per-segment attention mass (the document-wise score of Alg. 2) in a
@@ -35,8 +37,8 @@ using namespace attn;
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// The attention kernel for few stacked rows: the four wavefronts of a group stream the same TILE-token
-// tiles and own different query rows (wavefront w the 16-row blocks [w*NRB, (w+1)*NRB)), so there is
+// The attention kernel for few stacked rows: the four wavefronts of a group stream the same 32-token
+// tiles and own different query rows (wavefront w the 16-row block w), so there is
 // nothing to merge inside a group.  Per tile:
 //   * every thread's K/V loads for the tile two ahead are in flight in registers (a fixed number of
 //     loads per step, so the wait for one tile never covers a later one);
@@ -44,23 +46,21 @@ namespace {
 //     them [token][channel] to one of two LDS tile buffers; V chunks are copied as loaded, row-major
 //     with a 32-byte XOR swizzle; one workgroup barrier per tile;
 //   * the tile's math (tile_math).
-// With GROUPS == 2 two such groups share a workgroup, stream disjoint runs of tiles and merge at the end.
-template <int DT, int NRB, int TILE, int GROUPS, bool REG_TABLE>
-__global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArgs a, RopeFreq freq, Plan p) {
-    static_assert(GROUPS == 1 || (GROUPS == 2 && NRB == 1), "two groups: one row block per wavefront");
-    constexpr int kKTile = TILE * kKRow;             // bytes
-    constexpr int kVTile = TILE * kD * 2;
-    constexpr int kKItems = TILE / 32;               // (row, chunk pair) items per thread
-    constexpr int kVItems = TILE / 16;               // (row, chunk) items per thread
+// Two such groups share a workgroup, stream disjoint runs of tiles and merge at the end.
+template <int DT, bool REG_TABLE>
+__global__ __launch_bounds__(kThreads * 2, 2) void attn_tile_kernel(AttnArgs a, RopeFreq freq, Plan p) {
+    constexpr int kGroups = 2;
+    constexpr int kKTile = kTile * kKRow;            // bytes
+    constexpr int kVTile = kTile * kD * 2;
     __shared__ SegTable tbl;
-    __shared__ __attribute__((aligned(16))) unsigned char k_buf[GROUPS][2][kKTile];
-    __shared__ __attribute__((aligned(16))) unsigned char v_buf[GROUPS][2][kVTile];
-    __shared__ __attribute__((aligned(16))) float2 cs_lds[GROUPS][2][kHalf];
+    __shared__ __attribute__((aligned(16))) unsigned char k_buf[kGroups][2][kKTile];
+    __shared__ __attribute__((aligned(16))) unsigned char v_buf[kGroups][2][kVTile];
+    __shared__ __attribute__((aligned(16))) float2 cs_lds[kGroups][2][kHalf];
 
     const int tid = threadIdx.x & (kThreads - 1);    // thread, wavefront: inside the group of four wavefronts
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int grp = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
+    const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kThreads);
     const int li = lane & 15, lg = lane >> 4;
     {
         const void *p0 = a.q, *p1 = a.q_off, *p2 = a.q_new_start, *p3 = a.k_store, *p4 = a.v_store, *p5 = a.k_self,
@@ -73,7 +73,6 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
 
     // grid (split, kv head, query): nothing to divide; one row group (at most four row blocks)
     const int split = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
-    constexpr int rg = 0;
     const int unit = b * a.n_kv_heads + hkv;
     const int group = p.group;
     const QueryHead qh = load_query_head(a, b, REG_TABLE ? lane : (int)threadIdx.x);
@@ -81,34 +80,33 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
     const int tq = min(qh.tq_raw, a.max_tq);
 
     // ---- Q fragments first (loads return in order)
-    uint4 qf[NRB][4];
-    int trow[NRB];
-    const int row_base = rg * p.blocks_rg * 16;
-    const int row_limit = min(group * tq, row_base + p.blocks_rg * 16);
-    const bool has_rows = row_base + wave * NRB * 16 < row_limit;        // wavefront-uniform
-    load_q_fragments<NRB>(a, qh.q0, tq, hkv, group, wave * NRB, row_base, row_limit, li, lg, qf, trow);
+    uint4 qf[1][4];
+    int trow[1];
+    const int row_limit = min(group * tq, p.blocks_rg * 16);
+    const bool has_rows = wave * 16 < row_limit;     // wavefront-uniform
+    load_q_fragments<1>(a, qh.q0, tq, hkv, group, wave, 0, row_limit, li, lg, qf, trow);
 
     // at most 64 table entries: every wavefront keeps the table in registers; more: one table in LDS
     RegSegTable rtbl;
     unsigned total;
     if constexpr (REG_TABLE) {
-        rtbl = build_reg_table(a, qh, lane, TILE);
+        rtbl = build_reg_table(a, qh, lane, kTile);
         total = (unsigned)rtbl.total;
     } else {
-        build_table(a, qh, &tbl, TILE);
+        build_table(a, qh, &tbl, kTile);
         total = (unsigned)tbl.tile0[tbl.n];
     }
     // a group streams a contiguous run of the workgroup's tiles of its own (sub-split `ss`)
-    const unsigned nsub = (unsigned)(p.nsplit * GROUPS);
-    const int ss = split * GROUPS + grp;
+    const unsigned nsub = (unsigned)(p.nsplit * kGroups);
+    const int ss = split * kGroups + grp;
 
-    // staging items: K (row kr + 32*it, chunks kj and kj + 8), V (row vr + 16*it, chunk vc)
+    // staging items: K (row kr, chunks kj and kj + 8), V (rows vr and vr + 16, chunk vc)
     const int kr = tid >> 3, kj = tid & 7;
     const int vr = tid >> 4, vc = tid & 15;
-    struct StageRegs { uint4 ka[kKItems], kb[kKItems], v[kVItems]; };
+    struct StageRegs { uint4 ka, kb, v[2]; };
     StageRegs regs0, regs1;
 
-    TileWalk<TILE> walk(split_begin(total, nsub, ss), split_begin(total, nsub, ss + 1));
+    TileWalk<kTile> walk(split_begin(total, nsub, ss), split_begin(total, nsub, ss + 1));
     // Every call issues the same loads whether or not a tile is left, so the number of loads in flight
     // at any point of the loop is fixed.  Rows past the end of a ragged tile re-read its last row (in
     // bounds; their scores are masked).
@@ -116,14 +114,11 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
         if constexpr (REG_TABLE) d = walk.next(rtbl, lane);
         else d = walk.next(tbl, lane);
         const TileSource src = tile_source(a, d, walk.c_tok, hkv);
+        const uint32_t k_off = src.last < 0 ? 0u : (uint32_t)min(kr, src.last) * src.row_bytes + 16 * kj;
+        r.ka = *reinterpret_cast<const uint4*>(src.k + k_off);
+        r.kb = *reinterpret_cast<const uint4*>(src.k + k_off + (src.last < 0 ? 0 : 128));
 #pragma unroll
-        for (int it = 0; it < kKItems; ++it) {
-            const uint32_t off = src.last < 0 ? 0u : (uint32_t)min(kr + 32 * it, src.last) * src.row_bytes + 16 * kj;
-            r.ka[it] = *reinterpret_cast<const uint4*>(src.k + off);
-            r.kb[it] = *reinterpret_cast<const uint4*>(src.k + off + (src.last < 0 ? 0 : 128));
-        }
-#pragma unroll
-        for (int it = 0; it < kVItems; ++it) {
+        for (int it = 0; it < 2; ++it) {
             const uint32_t off = src.last < 0 ? 0u : (uint32_t)min(vr + 16 * it, src.last) * src.row_bytes + 16 * vc;
             r.v[it] = *reinterpret_cast<const uint4*>(src.v + off);
         }
@@ -135,10 +130,10 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
     // first loads are out)
     int most_tiles = 0;
 #pragma unroll
-    for (int g = 0; g < GROUPS; ++g)
-        most_tiles = max(most_tiles, split_begin(total, nsub, split * GROUPS + g + 1) - split_begin(total, nsub, split * GROUPS + g));
+    for (int g = 0; g < kGroups; ++g)
+        most_tiles = max(most_tiles, split_begin(total, nsub, split * kGroups + g + 1) - split_begin(total, nsub, split * kGroups + g));
 
-    RowState<NRB> st;
+    RowState<1> st;
     st.clear();
     char* ws = static_cast<char*>(a.workspace);
     float2* massml = reinterpret_cast<float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg;
@@ -165,15 +160,12 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
         if (live) {
             ChunkAngles ang;
             if (cd.delta != 0) ang = load_chunk_angles(cs_lds[grp][cs_slot] + 8 * kj);
+            uint4 ra = r.ka, rb4 = r.kb;
+            if (cd.delta != 0) rotate_chunk_pair<DT>(ra, rb4, ang);
+            k_tile_write(k_lds, kr, kj, ra);
+            k_tile_write(k_lds, kr, kj + 8, rb4);
 #pragma unroll
-            for (int it = 0; it < kKItems; ++it) {
-                uint4 ra = r.ka[it], rb4 = r.kb[it];
-                if (cd.delta != 0) rotate_chunk_pair<DT>(ra, rb4, ang);
-                k_tile_write(k_lds, kr + 32 * it, kj, ra);
-                k_tile_write(k_lds, kr + 32 * it, kj + 8, rb4);
-            }
-#pragma unroll
-            for (int it = 0; it < kVItems; ++it) *reinterpret_cast<uint4*>(v_lds + it * 16 * 256 + vw_off) = r.v[it];
+            for (int it = 0; it < 2; ++it) *reinterpret_cast<uint4*>(v_lds + it * 16 * 256 + vw_off) = r.v[it];
         }
         fetch(cur, r);                               // the registers are free again
         if (nxt.ntok > 0 && nxt.seg != cd.seg && nxt.delta != 0) {
@@ -183,12 +175,12 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
         __syncthreads();            // tile `cur` is staged; every wavefront is done with the other buffer
         if (!live || !has_rows) return;
         if (cd.seg != cur_seg) {
-            if (cur_seg >= 0) emit_segment<NRB>(st, massml, cur_seg + ss, p.rows_wg, wave * NRB, li, lg);
+            if (cur_seg >= 0) emit_segment<1>(st, massml, cur_seg + ss, p.rows_wg, wave, li, lg);
             cur_seg = cd.seg;
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) st.seg_l[rb] = 0.f;
+            for (float& l : st.seg_l) l = 0.f;
         }
-        tile_math<DT, NRB, TILE>(cd, k_lds, v_lds, qf, trow, st, a.scale_log2e, li, lg, tr_base, tr_x);
+        tile_math<DT>(cd, k_lds, v_lds, qf, trow, st, a.scale_log2e, li, lg, tr_base, tr_x);
     };
     // Steps come in pairs and the trip count is the workgroup's: every path round the loop issues the
     // same loads and meets the same barriers.  A group with fewer tiles runs steps without one.
@@ -196,39 +188,33 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
         step(d0, regs0, d1, 0);
         step(d1, regs1, d0, 1);
     }
-    if (cur_seg >= 0) emit_segment<NRB>(st, massml, cur_seg + ss, p.rows_wg, wave * NRB, li, lg);
+    if (cur_seg >= 0) emit_segment<1>(st, massml, cur_seg + ss, p.rows_wg, wave, li, lg);
 
-    float l_row[NRB];                                // row sums (each lane holds those of its own tokens so far)
+    float l_row[1] = {st.l_run[0] + __shfl_xor(st.l_run[0], 16)};       // row sums (each lane holds those of its own tokens so far)
+    l_row[0] += __shfl_xor(l_row[0], 32);
+    // the second group hands its rows' results (same rows, other tokens) to the first through the tile
+    // buffers, which nobody reads any more
+    f32x4* red = reinterpret_cast<f32x4*>(&k_buf[0][0][0]);                    // 4 wavefronts x 8 x 64 lanes
+    float2* red_ml = reinterpret_cast<float2*>(&v_buf[0][0][0]);               // 4 wavefronts x 16 rows
+    __syncthreads();
+    if (grp == 1) {
 #pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        l_row[rb] = st.l_run[rb] + __shfl_xor(st.l_run[rb], 16);
-        l_row[rb] += __shfl_xor(l_row[rb], 32);
+        for (int db = 0; db < 8; ++db) red[(wave * 8 + db) * kWave + lane] = st.acc[0][db];
+        if (lg == 0) red_ml[wave * 16 + li] = make_float2(st.m_run[0], l_row[0]);
     }
-    if (GROUPS == 2) {
-        // the second group hands its rows' results (same rows, other tokens) to the first through the tile
-        // buffers, which nobody reads any more
-        f32x4* red = reinterpret_cast<f32x4*>(&k_buf[0][0][0]);                    // 4 wavefronts x 8 x 64 lanes
-        float2* red_ml = reinterpret_cast<float2*>(&v_buf[0][0][0]);               // 4 wavefronts x 16 rows
-        __syncthreads();
-        if (grp == 1) {
+    __syncthreads();
+    if (grp == 1) return;
+    const float2 o = red_ml[wave * 16 + li];
+    const float m = fmaxf(st.m_run[0], o.x);
+    const float ms = m == -INFINITY ? 0.f : m;
+    const float f0 = __builtin_amdgcn_exp2f(st.m_run[0] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
 #pragma unroll
-            for (int db = 0; db < 8; ++db) red[(wave * 8 + db) * kWave + lane] = st.acc[0][db];
-            if (lg == 0) red_ml[wave * 16 + li] = make_float2(st.m_run[0], l_row[0]);
-        }
-        __syncthreads();
-        if (grp == 1) return;
-        const float2 o = red_ml[wave * 16 + li];
-        const float m = fmaxf(st.m_run[0], o.x);
-        const float ms = m == -INFINITY ? 0.f : m;
-        const float f0 = __builtin_amdgcn_exp2f(st.m_run[0] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
-#pragma unroll
-        for (int db = 0; db < 8; ++db) st.acc[0][db] = st.acc[0][db] * f0 + red[(wave * 8 + db) * kWave + lane] * f1;
-        l_row[0] = l_row[0] * f0 + o.y * f1;
-        st.m_run[0] = m;
-    }
+    for (int db = 0; db < 8; ++db) st.acc[0][db] = st.acc[0][db] * f0 + red[(wave * 8 + db) * kWave + lane] * f1;
+    l_row[0] = l_row[0] * f0 + o.y * f1;
+    st.m_run[0] = m;
     // a wavefront whose rows are all padding leaves nothing
     if (!has_rows) return;
-    store_partials<DT, NRB>(a, p, unit, split, wave * NRB, st, l_row, lane, qh.q0, tq, hkv, group, row_base, row_limit);
+    store_partials<DT, 1>(a, p, unit, split, wave, st, l_row, lane, qh.q0, tq, hkv, group, 0, row_limit);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -239,7 +225,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_tile_kernel(AttnArg
 // chunks 32 kk + 8 lg of token li hold both channels of each 2-D slice), values through a piece of LDS of the wavefront's own for
 // the transposing read.  Two tiles, 256 KB per CU, are in flight.  The eight results meet in LDS at the end.
 constexpr int kSoloVRow = 288;                       // bytes per token of a staged V tile
-constexpr int kSoloV = 32 * kSoloVRow;
+constexpr int kSoloV = kTile * kSoloVRow;
 
 template <int DT>
 __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnArgs a, RopeFreq freq, Plan p) {
@@ -262,12 +248,12 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     uint4 qf[1][4];
     int trow[1];
     load_q_fragments<1>(a, qh.q0, tq, hkv, group, 0, 0, row_limit, li, lg, qf, trow);
-    const RegSegTable rtbl = build_reg_table(a, qh, lane, 32);
+    const RegSegTable rtbl = build_reg_table(a, qh, lane, kTile);
     const unsigned total = (unsigned)rtbl.total;
     // a wavefront's contiguous run of tiles (sub-split `ss`)
     const unsigned nsub = (unsigned)(p.nsplit * kSoloWaves);
     const int ss = split * kSoloWaves + wave;
-    TileWalk<32> walk(split_begin(total, nsub, ss), split_begin(total, nsub, ss + 1));
+    TileWalk<kTile> walk(split_begin(total, nsub, ss), split_begin(total, nsub, ss + 1));
     const int my_tiles = walk.t_end - walk.next_tile;
 
     struct Regs { uint4 k[2][4], v[8]; };            // key fragments [16 tokens][32 channels], V row 4 * i + lane / 16, chunk lane % 16
@@ -345,7 +331,7 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
         __builtin_amdgcn_sched_barrier(0);
         fetch(d, r);                                 // the registers are free again
         __builtin_amdgcn_sched_barrier(0);
-        if (cd.ntok < 32 || cd.self != 0) {
+        if (cd.ntok < kTile || cd.self != 0) {
             const int last = (cd.self != 0 ? min(cd.ntok - 1, trow[0] - cd.tok0) : cd.ntok - 1) - 4 * lg;
 #pragma unroll
             for (int e = 0; e < 8; ++e) sc[e >> 2][e & 3] = 16 * (e >> 2) + (e & 3) <= last ? sc[e >> 2][e & 3] : -INFINITY;
@@ -449,17 +435,18 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
 //   V (vector)   tile t + 2 requested from memory, softmax of tile t against a stale maximum (kProbLimit)
 // The two wavefronts of a SIMD should be in different phases:
 //   GROUPS == 2: two groups of four wavefronts stream disjoint runs of the workgroup's tiles, the second group one phase behind the
-//                first (a barrier after every phase); their results meet in LDS at the end.  For plans of up to 256 units.
-//   GROUPS == 1: one group per workgroup, two workgroups per CU, one barrier per tile: more units than CUs.  One hides the other's
-//                prologue and tail as well: 30 documents of 160 rows and 192 tokens x 32 heads (960 units) 53 us, two groups 77.
+//                first (a barrier after every phase); their results meet in LDS at the end.  For plans of up to 256 units with ten
+//                tiles a split and more.
+//   GROUPS == 1: one group per workgroup, one barrier per tile.  Past 256 units two workgroups share a CU, and one hides the other's
+//                prologue and tail as well: 30 documents of 160 rows and 192 tokens x 32 heads (960 units) 53 us, two groups 77.  Within
+//                256 units, where splits are short, a wavefront has its SIMD to itself: the second group's delay and the merge cost more.
 // Against the kernel before it (two wavefronts that load and stage, six with two row blocks each, software-pipelined): 64 queries,
 // 2 kv heads, 384 rows, 3064 tokens, fp16: 130 -> 111 us (690 TFLOP/s); the 30 documents above 72 -> 53; one query, 4 kv heads, 448
 // rows, 7600 tokens 26 us both (a third of it prologue and merge).  Two tiles in flight instead of one, or the rotation on the
 // matrix cores (diagonal matrices of cosines in three 16-bit parts), no longer fit the 256 registers or cost more than they save.
-constexpr int kWideTile = 32;                        // tokens per tile
-constexpr int kWideK = kWideTile * kKRow;            // bytes
+constexpr int kWideK = kTile * kKRow;            // bytes
 constexpr int kWideVRow = 288;                       // bytes per token of a staged V tile
-constexpr int kWideV = kWideTile * kWideVRow;
+constexpr int kWideV = kTile * kWideVRow;
 
 // A register table's fields moved to LDS: the kernel has no registers left to carry them through its loop.
 struct LdsSegs {
@@ -543,14 +530,14 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     RegSegTable rtbl;
     unsigned total;
     if constexpr (REG_TABLE) {
-        rtbl = build_reg_table(a, qh, lane, kWideTile);
+        rtbl = build_reg_table(a, qh, lane, kTile);
         total = (unsigned)rtbl.total;
         if (threadIdx.x < kWave) {
             seg_lds[2 * lane] = make_int4((int)(uint32_t)rtbl.tok, (int)(uint32_t)((uint64_t)rtbl.tok >> 32), rtbl.vis, rtbl.delta);
             seg_lds[2 * lane + 1] = make_int4(rtbl.t0, rtbl.t1, rtbl.self, 0);
         }
     } else {
-        build_table(a, qh, &tbl, kWideTile);
+        build_table(a, qh, &tbl, kTile);
         total = (unsigned)tbl.tile0[tbl.n];
     }
     const unsigned nsub = (unsigned)(p.nsplit * GROUPS);
@@ -579,7 +566,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         w.seg = f.seg;
         w.delta = f.delta;
         w.self = f.self;
-        w.tok0 = (w_next - f.first) * kWideTile;
+        w.tok0 = (w_next - f.first) * kTile;
         w.ntok = 1;
         w_left = f.vis - w.tok0;
         const TileSource src = tile_source(a, w, f.tok, hkv);
@@ -602,7 +589,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     // requests the next tile (d, its table's slot) into r and steps over it
     auto fetch = [&](Tile& d, int& slot, StageRegs& r) {
         d = w;
-        d.ntok = w_next < w_end ? min(w_left, kWideTile) : 0;
+        d.ntok = w_next < w_end ? min(w_left, kTile) : 0;
         slot = w_slot;
         // rows past a ragged tile's end, and everything where no tile is left, lie past the range and read as zero
         const int range = d.ntok > 0 ? (d.ntok - 1) * (int)row_bytes + 2 * kD : 0;
@@ -615,10 +602,10 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     };
     auto advance = [&]() {
         ++w_next;
-        w.tok0 += kWideTile;
-        w_left -= kWideTile;
-        w_k += (int64_t)kWideTile * row_bytes;
-        w_v += (int64_t)kWideTile * row_bytes;
+        w.tok0 += kTile;
+        w_left -= kTile;
+        w_k += (int64_t)kTile * row_bytes;
+        w_v += (int64_t)kTile * row_bytes;
     };
     unsigned char* const k_write = k_lds + kr * kKRow + 16 * kj;
     unsigned char* const v_write = v_lds + vr * kWideVRow + 16 * vc;
@@ -753,7 +740,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
             pfrag[rb] = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
                                    Mma<DT>::pack(pv[6], pv[7]));
         };
-        if (cd.ntok < kWideTile || cd.self != 0) {
+        if (cd.ntok < kTile || cd.self != 0) {
             const int l = lane_anew();
             int tqs = tq;
             asm volatile("" : "+v"(tqs));            // nothing of the division below is kept from tile to tile
@@ -959,7 +946,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         return st != CF_OK || !prune ? st : launch_prune_step(a, prune, s);
     }
     const Plan p = make_plan(a.n_q_heads, a.n_kv_heads, a.batch, a.max_tq, a.seg_stride, a.max_kv_tokens, a.workspace_bytes);
-    const dim3 grid3((unsigned)p.nsplit, (unsigned)a.n_kv_heads, (unsigned)a.batch);     // attn_tile_kernel's
+    const dim3 grid3((unsigned)p.nsplit, (unsigned)a.n_kv_heads, (unsigned)a.batch);     // attn_tile_kernel's and attn_solo_kernel's
     const dim3 grid2((unsigned)(p.nsplit * a.batch), (unsigned)p.units_per_b);           // attn_wide_kernel's
     // grid dimensions of this path's kernels (the merge kernel's may carry one more row, for pending score parts)
     if (a.batch > 65535 || (int64_t)a.n_kv_heads * p.n_rg + 1 > 65535) {
@@ -987,8 +974,8 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
     if (p.groups == kSoloWaves) {                                                                                                             \
         CF_LAUNCH_TIMED((attn_solo_kernel<DT>), grid3, dim3(kSoloWaves * kWave));                                              \
     } else if (!p.wide) {                                                                                                      \
-        if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, true>), grid3, dim3(2 * kThreads));                            \
-        else CF_LAUNCH_TIMED((attn_tile_kernel<DT, 1, 32, 2, false>), grid3, dim3(2 * kThreads));                                     \
+        if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, true>), grid3, dim3(2 * kThreads));                            \
+        else CF_LAUNCH_TIMED((attn_tile_kernel<DT, false>), grid3, dim3(2 * kThreads));                                     \
     } else {                                                                                                                   \
         if (p.groups == 2) { CF_LAUNCH_WIDE(DT, 2) } else { CF_LAUNCH_WIDE(DT, 1) }                                             \
     }                                                                                                                          \

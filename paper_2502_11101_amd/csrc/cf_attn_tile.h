@@ -110,125 +110,97 @@ struct RowState {
     }
 };
 
-// The math of one staged tile for one wavefront: S^T = K Q^T from LDS key fragments and the register-resident
-// Q fragments, online softmax against a stale maximum, O^T += V^T P^T with V^T fragments from
+// The math of one staged 32-token tile for one wavefront and its row block: S^T = K Q^T from LDS key fragments and the
+// register-resident Q fragments, online softmax against a stale maximum, O^T += V^T P^T with V^T fragments from
 // transposing LDS reads.  K tile: see k_tile_write; V tile: row-major [token][256 bytes], chunk c of
 // row t at chunk c ^ 2*(t & 7).  `trow`: query position of the lane's row inside the own block
 // (causal mask), `tr_base`/`tr_x`: the lane's transposing-read offsets.
-template <int DT, int NRB, int TILE>
+template <int DT>
 __device__ __forceinline__ void tile_math(const Tile& cd, const unsigned char* k_lds, const unsigned char* v_lds,
-                                          const uint4 (&qf)[NRB][4], const int (&trow)[NRB], RowState<NRB>& st,
+                                          const uint4 (&qf)[1][4], const int (&trow)[1], RowState<1>& st,
                                           float scale_log2e, int li, int lg, uint32_t tr_base, uint32_t tr_x) {
     const bool causal = cd.self != 0;
-    // ---- S^T = K Q^T of 32-token half h2: lane (li, lg) gets, for query row li, tokens 32*h2 + 16*tb + 4*lg + r
-    auto scores = [&](int h2, f32x4 (&sc)[NRB][2]) {
+    // ---- S^T = K Q^T: lane (li, lg) gets, for query row li, tokens 16*tb + 4*lg + r
+    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    uint4 kf[2][4];
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) { sc[rb][0] = f32x4{0.f, 0.f, 0.f, 0.f}; sc[rb][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        uint4 kf[2][4];
+    for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int kk = 0; kk < 4; ++kk) kf[tb][kk] = k_tile_fragment(k_lds, 16 * tb + li, 4 * kk + lg);
+    __builtin_amdgcn_sched_barrier(0);           // all eight reads are out before the first MFMA waits
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                kf[tb][kk] = k_tile_fragment(k_lds, 32 * h2 + 16 * tb + li, 4 * kk + lg);
-        __builtin_amdgcn_sched_barrier(0);       // all eight reads are out before the first MFMA waits
+    for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                for (int rb = 0; rb < NRB; ++rb) sc[rb][tb] = Mma<DT>::run(kf[tb][kk], qf[rb][kk], sc[rb][tb]);
-    };
-    // ---- softmax of half h2 and O^T += V^T P^T
-    auto weigh = [&](int h2, f32x4 (&sc)[NRB][2]) {
-        const int nt = cd.ntok - 32 * h2;      // valid tokens of this half
+        for (int tb = 0; tb < 2; ++tb) sc[tb] = Mma<DT>::run(kf[tb][kk], qf[0][kk], sc[tb]);
+    // softmax and O^T += V^T P^T (written in line, without the lambda, the kernel has 39 instructions more)
+    auto weigh = [&](f32x4 (&sc)[2]) {
         // V^T fragments, requested before the softmax arithmetic that hides their latency
         short4v vlo[8], vhi[8];
 #pragma unroll
         for (int db = 0; db < 8; ++db) {
-            const unsigned char* src = v_lds + h2 * 32 * 256 + tr_base + ((uint32_t)(32 * db) ^ tr_x);
+            const unsigned char* src = v_lds + tr_base + ((uint32_t)(32 * db) ^ tr_x);
             vlo[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src));
             vhi[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src + 16 * 256));
         }
         __builtin_amdgcn_sched_barrier(0);
         // ---- online softmax (exp2 domain), fp32, against a stale row maximum (see kProbLimit)
-        const bool need_mask = causal || nt < 32;
-        uint4 pfrag[NRB];
+        float xv[8];
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
-            float xv[8];
+        for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
+            for (int e = 0; e < 4; ++e) xv[4 * tb + e] = sc[tb][e];
+        if (causal || cd.ntok < kTile) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) xv[4 * tb + e] = sc[rb][tb][e];
-            if (need_mask) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int tk = 16 * (e >> 2) + 4 * lg + (e & 3);
-                    const bool ok = tk < nt && (!causal || cd.tok0 + 32 * h2 + tk <= trow[rb]);
-                    xv[e] = ok ? xv[e] : -INFINITY;
-                }
+            for (int e = 0; e < 8; ++e) {
+                const int tk = 16 * (e >> 2) + 4 * lg + (e & 3);
+                const bool ok = tk < cd.ntok && (!causal || cd.tok0 + tk <= trow[0]);
+                xv[e] = ok ? xv[e] : -INFINITY;
             }
-            // Probabilities against the reference as it stands; their sum tells whether one of them left the
-            // range the reference allows (or no reference exists yet) — only then is the maximum worked out,
-            // the reference moved, everything accumulated so far rescaled, and the probabilities redone.
-            float pv[8];
-            float lsum = 0.f;
-            auto probabilities = [&](float m_ref) {
-                const float m_safe = m_ref == -INFINITY ? 0.f : m_ref;
-                lsum = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    pv[e] = __builtin_amdgcn_exp2f(fmaf(xv[e], scale_log2e, -m_safe));
-                    lsum += pv[e];
-                }
-            };
-            probabilities(st.m_run[rb]);
-            if (__any(!(lsum <= kProbLimit) || st.m_run[rb] == -INFINITY)) {
-                float mloc = fmaxf(fmaxf(fmaxf(xv[0], xv[1]), fmaxf(xv[2], xv[3])), fmaxf(fmaxf(xv[4], xv[5]), fmaxf(xv[6], xv[7])));
-                mloc *= scale_log2e;                     // scale > 0: max commutes with it
-                mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-                mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-                const float m_old = st.m_run[rb];
-                const float m_new = fmaxf(m_old, mloc);
-                const float alpha = __builtin_amdgcn_exp2f(m_old - (m_new == -INFINITY ? 0.f : m_new));
-                st.l_run[rb] *= alpha;
-                st.seg_l[rb] *= alpha;
-                st.m_run[rb] = m_new;
-                if (__any(alpha != 1.f && m_old != -INFINITY)) {     // nothing accumulated yet: nothing to rescale
-#pragma unroll
-                    for (int db = 0; db < 8; ++db) st.acc[rb][db] *= alpha;
-                }
-                probabilities(m_new);
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) xv[e] = pv[e];
-            st.l_run[rb] += lsum;
-            st.seg_l[rb] += lsum;
-            pfrag[rb] = make_uint4(Mma<DT>::pack(xv[0], xv[1]), Mma<DT>::pack(xv[2], xv[3]),
-                                   Mma<DT>::pack(xv[4], xv[5]), Mma<DT>::pack(xv[6], xv[7]));
         }
+        // Probabilities against the reference as it stands; their sum tells whether one of them left the
+        // range the reference allows (or no reference exists yet) — only then is the maximum worked out,
+        // the reference moved, everything accumulated so far rescaled, and the probabilities redone.
+        float pv[8];
+        float lsum = 0.f;
+        auto probabilities = [&](float m_ref) {
+            const float m_safe = m_ref == -INFINITY ? 0.f : m_ref;
+            lsum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                pv[e] = __builtin_amdgcn_exp2f(fmaf(xv[e], scale_log2e, -m_safe));
+                lsum += pv[e];
+            }
+        };
+        probabilities(st.m_run[0]);
+        if (__any(!(lsum <= kProbLimit) || st.m_run[0] == -INFINITY)) {
+            float mloc = fmaxf(fmaxf(fmaxf(xv[0], xv[1]), fmaxf(xv[2], xv[3])), fmaxf(fmaxf(xv[4], xv[5]), fmaxf(xv[6], xv[7])));
+            mloc *= scale_log2e;                     // scale > 0: max commutes with it
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            const float m_old = st.m_run[0];
+            const float m_new = fmaxf(m_old, mloc);
+            const float alpha = __builtin_amdgcn_exp2f(m_old - (m_new == -INFINITY ? 0.f : m_new));
+            st.l_run[0] *= alpha;
+            st.seg_l[0] *= alpha;
+            st.m_run[0] = m_new;
+            if (__any(alpha != 1.f && m_old != -INFINITY)) {     // nothing accumulated yet: nothing to rescale
+#pragma unroll
+                for (int db = 0; db < 8; ++db) st.acc[0][db] *= alpha;
+            }
+            probabilities(m_new);
+        }
+        st.l_run[0] += lsum;
+        st.seg_l[0] += lsum;
+        const uint4 pfrag = make_uint4(Mma<DT>::pack(pv[0], pv[1]), Mma<DT>::pack(pv[2], pv[3]), Mma<DT>::pack(pv[4], pv[5]),
+                                       Mma<DT>::pack(pv[6], pv[7]));
         // ---- O^T += V^T P^T
 #pragma unroll
         for (int db = 0; db < 8; ++db) {
             const uint2 l2 = __builtin_bit_cast(uint2, vlo[db]), h2v = __builtin_bit_cast(uint2, vhi[db]);
-            const uint4 va = make_uint4(l2.x, l2.y, h2v.x, h2v.y);
-#pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) st.acc[rb][db] = Mma<DT>::run(va, pfrag[rb], st.acc[rb][db]);
+            st.acc[0][db] = Mma<DT>::run(make_uint4(l2.x, l2.y, h2v.x, h2v.y), pfrag, st.acc[0][db]);
         }
     };
-    // The scores of the second half are requested before the first half is weighed: their MFMAs run
-    // beside the first half's softmax arithmetic.  A ragged tile of at most 32 tokens has no second half.
-    f32x4 sc0[NRB][2];
-    scores(0, sc0);
-    if (TILE == 64) {
-        f32x4 sc1[NRB][2];
-        const bool two = cd.ntok > 32;
-        if (two) scores(1, sc1);
-        weigh(0, sc0);
-        if (two) weigh(1, sc1);
-    } else {
-        weigh(0, sc0);
-    }
+    weigh(sc);
 }
 
 // Q fragments of a wavefront's row blocks [first_blk, first_blk + NRB) of the stacked rows of kv head

@@ -14,6 +14,7 @@ namespace attn {
 
 constexpr int kWaves = 4;       // wavefronts of a group
 constexpr int kD = 128;
+constexpr int kTile = 32;       // tokens per tile
 constexpr int kMaxSplit = 32;
 constexpr int kSoloWaves = 8;   // wavefronts of attn_solo_kernel's workgroups, each with tiles of its own
 
@@ -34,7 +35,7 @@ struct Plan {
 };
 
 // Tiles of a (query, kv head): every segment may end in a ragged one.
-inline int64_t plan_tiles(int seg_stride, int64_t max_kv_tokens) { return max_kv_tokens / 32 + seg_stride; }
+inline int64_t plan_tiles(int seg_stride, int64_t max_kv_tokens) { return max_kv_tokens / kTile + seg_stride; }
 
 // Splits of a (query, kv head, row group): the CUs are shared out, each split has at least `least` tiles.
 inline int plan_splits(int64_t units, int64_t tiles, int least) {
@@ -121,7 +122,7 @@ inline Plan plan_shape(int n_q_heads, int n_kv_heads, int max_tq) {
     p.group = n_q_heads / n_kv_heads;
     p.row_blocks = (p.group * max_tq + 15) / 16;
     p.wide = p.row_blocks > 4;
-    p.tile = 32;
+    p.tile = kTile;
     return p;
 }
 
