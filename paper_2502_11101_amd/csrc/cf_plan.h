@@ -109,9 +109,10 @@ inline Plan wide_plan(Plan p, int batch, int n_kv_heads, int seg_stride, int64_t
     // One group of wavefronts per workgroup for units past the CUs, two workgroups of which share one (30 documents x 32 heads, 960
     // units, encoded and stored: 84 us against 108 with two groups), and for splits of few tiles, which
     // the second group's delay and the merge of the groups cost more than it saves.  Around the line, us with one group
-    // against two: one query x 2 kv heads, 384 rows, under four tiles a split 29.0 against 32.0, 4 queries x 4 heads, 140 rows, seven
-    // 31.3 against 33.2; 8 queries x 2 heads, 384 rows, fifteen 42.2 against 41.2, 2 x 32 heads, 130 rows, twelve 40.9 against 38.9.
-    p.groups = groups == 2 && p.units <= 256 && tiles >= 10 * p.nsplit ? 2 : 1;
+    // against two: layers of 64 queries x 2 heads, 384 rows, ten tiles a split 34.8 against 35.6, twelve 37.6 and 37.5, fourteen 39.5 and
+    // 39.0; 16 x 4 heads, 336 rows, eleven 42.7 and 44.0, 13.5 46.2 and 45.8; 8 x 4, 448 rows, 11.5 34.3 and 34.5, 13.5 37.0 and 36.0.
+    // Documents x 2 heads, encoded: 12 of 228 tokens (ten) 28.6 and 30.3, of 300 (twelve) 33.3 and 34.7, 6 of 340 (thirteen) 28.1 and 27.1.
+    p.groups = groups == 2 && p.units <= 256 && tiles >= 13 * p.nsplit ? 2 : 1;
     plan_layout(p, seg_stride);
     return p;
 }
@@ -139,19 +140,22 @@ inline Plan best_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     if (p.wide) {
         // Many rows (GQA, long queries): row groups of up to three blocks per wavefront, or of up to two.  Fewer groups stage the same keys
         // less often, but three blocks keep every register busy and two do not: a tile's time goes about as 4 * blocks per wavefront
-        // + 2, and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
+        // + 2 (each about 0.09 us), and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
         // three of three: one query of 50 documents 37.8 us against 41.7, 8 queries of 20 66 against 76, 32 171 against 197.  384 rows, 64
         // queries x 2 kv heads, as three of two 168 us, as two of three 127 (384 units against 256); five documents of 100-200 tokens x 7
         // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).  Past the CUs a share of a round costs most of one: 107 rows x 6, 36
         // queries x 2 heads, 10 documents, as four of three (288 units) 91 us, as six of two (432) 80; 83 rows x 7, 14 queries x 4 heads, 10
         // documents, as five of two (280) 95, as four of three (224) 76; 129 rows x 6, 41 queries x 2 heads, as seven of two (574) 91, as
-        // five of three (410) 75.
+        // five of three (410) 75.  Splits pay for their partial rows, written and read, and for the merge: about 30 of those parts per 64
+        // rows of every CU (8 us for three blocks).  12 documents of 160 tokens x 2 heads, encoded, as five of three in two splits 32.9
+        // us, as eight of two in one 20.5; 8 of 228 35.9 and 23.8; 15 queries x 4 heads, 336 rows, 7 documents of 67 46.4 and 40.5.
         const Plan three = wide_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens, 3, 2);
         const Plan two = wide_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens, 2, 2);
         // past the CUs two workgroups share one, at 1.7 times what one alone takes, and a third begins when they end
-        auto cost = [](const Plan& c) {
+        auto cost = [tiles](const Plan& c) {
             const double rounds = c.units > 512 ? std::max(c.units / 256., 2.7) : 1.7;
-            return (4 * c.nrb + 2) * (c.units > 256 ? rounds : 1. / c.nsplit);
+            const double merge = c.nsplit > 1 ? 30. * c.nrb * c.units * c.nsplit / 256 : 0;
+            return (4 * c.nrb + 2) * tiles * (c.units > 256 ? rounds : 1. / c.nsplit) + merge;
         };
         return wide_grid_ok(two) && cost(two) < cost(three) ? two : three;
     }

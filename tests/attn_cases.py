@@ -11,20 +11,20 @@ WIDE = [
     # table in registers
     Wide(4, 2, 3, 32, 3, 200, 2, 1, 1, 2),           # 128 rows: eight blocks
     Wide(7, 2, 22, 55, 3, 200, 2, 1, 4, 1),          # 385
-    Wide(1, 3, 9, 193, 3, 1200, 2, 2, 2, 4),
+    Wide(1, 3, 9, 193, 3, 1700, 2, 2, 2, 4),
     Wide(7, 2, 22, 55, 3, 1200, 2, 2, 4, 1),
-    Wide(3, 3, 22, 43, 3, 200, 3, 1, 1, 2),          # 129: nine blocks, the last with one row
+    Wide(3, 3, 22, 43, 3, 900, 3, 1, 1, 3),          # 129: nine blocks, the last with one row
     Wide(6, 3, 43, 32, 3, 200, 3, 1, 1, 1),          # 192: all twelve blocks
-    Wide(6, 3, 15, 32, 3, 1900, 3, 2, 1, 5),
+    Wide(6, 3, 15, 32, 3, 2300, 3, 2, 1, 5),
     Wide(3, 3, 43, 43, 3, 1200, 3, 2, 1, 1),
     # table in LDS
     Wide(1, 2, 1, 193, 66, 900, 2, 1, 2, 23),        # 193
     Wide(7, 2, 43, 55, 66, 900, 2, 1, 4, 1),
     Wide(7, 1, 9, 55, 66, 900, 2, 2, 4, 7),
     Wide(7, 2, 22, 55, 80, 900, 2, 2, 4, 1),
-    Wide(3, 1, 9, 43, 66, 900, 3, 1, 1, 23),
+    Wide(3, 1, 22, 43, 66, 900, 3, 1, 1, 11),
     Wide(6, 3, 90, 32, 66, 900, 3, 1, 1, 1),
-    Wide(7, 1, 11, 55, 66, 900, 3, 2, 3, 7),
+    Wide(6, 1, 47, 32, 66, 900, 3, 2, 1, 5),
     Wide(6, 3, 43, 32, 66, 900, 3, 2, 1, 1),
 ]
 

@@ -19,7 +19,7 @@ def test_one_workspace_for_a_growing_cache(hq, hkv, batch, n):
 
 
 # a decode step of eight runs per split; four row groups of two blocks; two groups of wavefronts
-@pytest.mark.parametrize("hq,hkv,batch,tq,lens", [(32, 32, 1, 1, [1000]), (28, 4, 1, 20, [3000]), (12, 2, 64, 32, [700, 90])])
+@pytest.mark.parametrize("hq,hkv,batch,tq,lens", [(32, 32, 1, 1, [1000]), (28, 4, 1, 20, [3000]), (12, 2, 64, 32, [1000, 90])])
 def test_the_least_workspace(hq, hkv, batch, tq, lens):
     print(f"least workspace {hq}/{hkv} {batch} x {tq}", flush=True)
     args = (hq, hkv, batch, tq, len(lens) + 1, sum(lens) + tq)

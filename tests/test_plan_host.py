@@ -106,3 +106,13 @@ def test_the_attention_tests_reach_every_variant():
     for c in attn_cases.SOLO:
         p = plan_probe.plan(c.hq, c.hkv, c.batch, c.tq, 2, c.tokens)
         assert (p.groups, p.nsplit, -(-(c.tokens // 32 + 2) // (8 * p.nsplit))) == (8, c.nsplit, c.tiles), c
+
+
+def test_a_split_pays_for_its_merge():
+    """Documents encoded over a 32-token prefix: eight row groups in one split, not five in two that save three tiles; one group of wavefronts
+    where a split has ten tiles, two from thirteen on.  Long lists are split as before."""
+    shape = lambda *a: plan_probe.plan(*a)[1:5]          # blocks per wavefront, groups, row groups, splits
+    assert shape(12, 2, 12, 160, 2, 192) == (2, 1, 8, 1)
+    assert shape(12, 2, 16, 228, 2, 260) == (3, 1, 8, 1)
+    assert shape(12, 2, 6, 340, 2, 372) == (2, 2, 16, 1)
+    assert shape(28, 4, 1, 64, 52, 7446) == (2, 2, 4, 16)
