@@ -161,22 +161,32 @@ inline Plan best_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     }
     p = tile_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens);
     // attn_solo_kernel: one row block over at most two table entries (a decode step: the cache and the own block; short documents over
-    // the prefix) and at most eight splits.  Longer tables are layer calls, which ask
-    // for masses: statistics of eight wavefronts per segment to reduce cost more than the attention saves (10 documents of 160 tokens x 12
-    // rows x 32 heads 24.8 us against 23.2 with attn_tile_kernel, 30 documents x 16 rows 33.9 against 31.3).  More splits are long lists
-    // over few units, which attn_tile_kernel spreads over more CUs (4 units x 2000 tokens 12.7 us as eight splits here, 12.2 as 16 there, x
-    // 14000 30.4 and 20.3).  The line does not ask for masses, so that a call's outputs do not depend on whether it wants them.
-    // Lists of up to two tiles per wavefront, which are all in flight at once, take one split and no merge: one conversation of 200 | 400
-    // tokens x 32 heads 10.6 -> 8.4 | 11.2 -> 10.0 us, 32 of 200 | 400 x 4 heads 15.2 -> 9.2 | 17.3 -> 12.1; of 881 (seven splits) 13.5
-    // would be 16.6.  Where the CUs allow two splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32
-    // heads 21.8 -> 17.8, of 150-880 19.9 -> 16.0; of 3000 40.7 would be 43.4.
-    // With more than two splits of more than four tiles attn_tile_kernel is the faster: 2 conversations of 1500 tokens x 32 heads 18.7 us
-    // against 20.7, 1 14.5 against 15.3, 8 of 1000-2000 x 4 heads 15.2 against 16.0; with two up to 112
-    // units 28.3 against 28.5 (3 of 1972 x 32) and 26.7 against 26.9 (28 of 1500 x 4), at 128 54.7 against 53.7 (32 of 1000-5000 x 4); with one 33.7 against 32.1 (40 of 1000-2000 x 4); with seven of four tiles 12.6 against 11.7.
+    // the prefix) and at most eight splits.  Longer tables are layer calls, which ask for masses: statistics of eight wavefronts per
+    // segment to reduce cost more than the attention saves (10 documents of 160 tokens x 12 rows x 32 heads 24.8 us against 23.2 with
+    // attn_tile_kernel, 30 documents x 16 rows 33.9 against 31.3).  The line does not ask for masses, so that a call's outputs do not
+    // depend on whether it wants them.
     const int ns = p.nsplit;
-    const bool whole = tiles <= 2 * kSoloWaves || (p.units > 85 && tiles <= 4 * kSoloWaves);
-    const bool solo = p.row_blocks == 1 && seg_stride <= kSoloStride && ns <= kSoloSplits && (whole || ns == 1 || (ns == 2 && p.units > 112) || tiles < 5 * ns);
-    return solo ? solo_plan(p, seg_stride, whole ? 1 : ns) : p;
+    if (p.row_blocks > 1 || seg_stride > kSoloStride || ns > kSoloSplits) return p;
+    // Past four rounds of the CUs the merge of eight wavefronts per workgroup costs what their streams save: 2048 units of ten tiles 84.0
+    // us against 78.8 with attn_tile_kernel, of 22 135.0 and 134.1; 1024 of ten 43.9 and 43.2, of 48 136.5 and 136.7.
+    if (p.units > 1024) return p;
+    // Lists of up to two tiles per wavefront, which are all in flight at once, take one split and no merge: one conversation of 200 | 400
+    // tokens x 32 heads 10.6 -> 8.4 | 11.2 -> 10.0 us, 32 of 200 | 400 x 4 heads 15.2 -> 9.2 | 17.3 -> 12.1.  Where the CUs allow two
+    // splits at most, lists of up to four tiles per wavefront do: 4 conversations of 881 tokens x 32 heads 21.8 -> 17.8, of 150-880 19.9
+    // -> 16.0; of 3000 40.7 would be 43.4.
+    if (tiles <= 2 * kSoloWaves || (p.units > 85 && tiles <= 4 * kSoloWaves)) return solo_plan(p, seg_stride, 1);
+    // One split: 40 conversations of 1000-2000 tokens x 4 heads 32.1 us against 33.7, 28 of 850-2100 x 8 39.0 against 40.0.  (Equal lists
+    // just past two tiles per wavefront are up to 4.5 % slower, unequal ones faster; the host does not know.)
+    if (ns == 1) return solo_plan(p, seg_stride, 1);
+    // Two: from 112 units on, equal lists within 2 % either way and unequal ones faster, below, equal ones are slower.  x 4 heads, us
+    // against attn_tile_kernel, 1972 tokens | 2500 | 1000-4000: 22 conversations 27.9 and 26.9 | 31.9 and 30.5 | 38.0 and 39.4; 25 30.1 and
+    // 29.5 | 34.3 and 33.8 | 40.5 and 41.1; 28 32.1 and 31.8 | 36.3 and 36.3 | 42.5 and 43.1; 32 34.7 and 34.3 | 39.5 and 40.1 | 45.9 and 47.0.
+    if (ns == 2) return p.units > 112 ? solo_plan(p, seg_stride, 2) : p;
+    // More: of up to four tiles (one conversation of 881 tokens x 32 heads in seven 11.9 us, with attn_tile_kernel 12.6; in one, two, three
+    // and four splits 14.6, 13.9, 13.2 and 12.4); longer ones are the better there (1500 tokens 15.3 and 14.5, two of them
+    // 20.7 and 18.7, 8 of 1000-2000 x 4 heads 16.0 and 15.2), as are those of more than eight splits, which it spreads over more CUs (4
+    // units x 2000 tokens 12.7 us as eight splits here, 12.2 as 16 there, x 14000 30.4 and 20.3).
+    return tiles < 5 * ns ? solo_plan(p, seg_stride, ns) : p;
 }
 
 // What cf_prefill_workspace_bytes reports: no plan of these arguments takes more, nor one of a smaller max_kv_tokens or seg_stride, so that

@@ -116,3 +116,10 @@ def test_a_split_pays_for_its_merge():
     assert shape(12, 2, 16, 228, 2, 260) == (3, 1, 8, 1)
     assert shape(12, 2, 6, 340, 2, 372) == (2, 2, 16, 1)
     assert shape(28, 4, 1, 64, 52, 7446) == (2, 2, 4, 16)
+
+
+def test_decode_calls_of_many_rounds_keep_the_tile_kernel():
+    """attn_solo_kernel (eight runs of tiles per workgroup) up to 1024 units."""
+    for tokens in (300, 600, 2000):
+        assert plan_probe.plan(32, 32, 32, 1, 2, tokens).groups == 8
+        assert plan_probe.plan(32, 32, 33, 1, 2, tokens).groups == 2
