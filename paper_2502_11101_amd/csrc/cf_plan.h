@@ -102,17 +102,21 @@ constexpr int kSoloStride = 2, kSoloSplits = 8;      // the longest table and th
 // attn_wide_kernel's, with row groups of up to `per_wave` blocks per wavefront and at most `groups` groups of wavefronts.
 inline Plan wide_plan(Plan p, int batch, int n_kv_heads, int seg_stride, int64_t max_kv_tokens, int per_wave, int groups) {
     const int n_rg = (p.row_blocks + kWaves * per_wave - 1) / (kWaves * per_wave);
-    plan_rows(p, batch, n_kv_heads, n_rg, ((p.row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves);
+    const int nrb = ((p.row_blocks + n_rg - 1) / n_rg + kWaves - 1) / kWaves;
+    plan_rows(p, batch, n_kv_heads, n_rg, nrb);
     const int64_t tiles = plan_tiles(seg_stride, max_kv_tokens);
     // four tiles a split are better than two: one query of 20 rows x 4 heads, ten documents, 23.5 us against 25.4
     p.nsplit = plan_splits(p.units, tiles, 4);
     // One group of wavefronts per workgroup for units past the CUs, two workgroups of which share one (30 documents x 32 heads, 960
-    // units, encoded and stored: 84 us against 108 with two groups), and for splits of few tiles, which
-    // the second group's delay and the merge of the groups cost more than it saves.  Around the line, us with one group
-    // against two: layers of 64 queries x 2 heads, 384 rows, ten tiles a split 34.8 against 35.6, twelve 37.6 and 37.5, fourteen 39.5 and
-    // 39.0; 16 x 4 heads, 336 rows, eleven 42.7 and 44.0, 13.5 46.2 and 45.8; 8 x 4, 448 rows, 11.5 34.3 and 34.5, 13.5 37.0 and 36.0.
-    // Documents x 2 heads, encoded: 12 of 228 tokens (ten) 28.6 and 30.3, of 300 (twelve) 33.3 and 34.7, 6 of 340 (thirteen) 28.1 and 27.1.
-    p.groups = groups == 2 && p.units <= 256 && tiles >= 13 * p.nsplit ? 2 : 1;
+    // units, encoded and stored: 84 us against 108 with two groups), and for splits of few tiles, which the second group's delay and the
+    // merge of the groups cost more than it saves, the more the more blocks a wavefront has.  Around the lines, us with one group against
+    // two, tiles a split in brackets.  Three blocks: layers of 64 queries x 2 heads, 384 rows, (10) 34.8 and 35.6, (12) 37.6 and 37.5,
+    // (14) 39.5 and 39.0; 16 x 4, 336 rows, (11) 42.7 and 44.0, (13.5) 46.2 and 45.8; documents encoded x 2 heads, 12 of 228 tokens (10)
+    // 28.6 and 30.3, of 300 (12) 33.3 and 34.7.  Two: 8 queries x 16 heads, 120 rows, (10.5) 37.3 and 37.7, 3 (11.4) 35.0 and 34.4; 4
+    // documents x 32 heads of 228 (10) 28.6 and 30.0, x 4 heads of 260 (11) 26.1 and 25.5.  Five blocks, which leave one of the four
+    // wavefronts idle and one half: 8 queries x 16 heads, 80 rows, (8) 29.3 and 30.4, (10) 36.1 and 35.7, 3 x 32 (10.5) 34.0 and 32.8.
+    const int pays = p.blocks_rg <= 5 ? 10 : nrb == 2 ? 11 : 13;
+    p.groups = groups == 2 && p.units <= 256 && tiles >= pays * p.nsplit ? 2 : 1;
     plan_layout(p, seg_stride);
     return p;
 }
@@ -127,7 +131,8 @@ inline Plan plan_shape(int n_q_heads, int n_kv_heads, int max_tq) {
     return p;
 }
 
-// The plan that takes the least workspace: no run of tiles beyond what fills the CUs, no row group beyond the fewest.
+// The plan to fall back on for its workspace: no run of tiles beyond what fills the CUs, no row group beyond the fewest.  (Where more row
+// groups do without splits, they take less still.)
 inline Plan least_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
     const Plan p = plan_shape(n_q_heads, n_kv_heads, max_tq);
     return p.wide ? wide_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens, 3, 1) : tile_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens);
@@ -140,10 +145,10 @@ inline Plan best_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
     if (p.wide) {
         // Many rows (GQA, long queries): row groups of up to three blocks per wavefront, or of up to two.  Fewer groups stage the same keys
         // less often, but three blocks keep every register busy and two do not: a tile's time goes about as 4 * blocks per wavefront
-        // + 2 (each about 0.09 us), and what it adds up to depends on how the units fill the CUs.  448 rows, 4 kv heads, as four groups of two blocks against
-        // three of three: one query of 50 documents 37.8 us against 41.7, 8 queries of 20 66 against 76, 32 171 against 197.  384 rows, 64
-        // queries x 2 kv heads, as three of two 168 us, as two of three 127 (384 units against 256); five documents of 100-200 tokens x 7
-        // rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).  Past the CUs a share of a round costs most of one: 107 rows x 6, 36
+        // + 2 (each about 0.09 us for one group of wavefronts), and what it adds up to depends on how the units fill the CUs.  448
+        // rows, 4 kv heads, as four groups of two blocks against three of three: one query of 50 documents 37.8 us against 41.7, 8 queries
+        // of 20 66 against 76, 32 171 against 197.  384 rows, 64 queries x 2 kv heads, as three of two 168 us, as two of three 127 (384
+        // units against 256); five documents of 100-200 tokens x 7 rows, 4 kv heads, 22.7 against 24.8 (220 units against 140).  Past the CUs a share of a round costs most of one: 107 rows x 6, 36
         // queries x 2 heads, 10 documents, as four of three (288 units) 91 us, as six of two (432) 80; 83 rows x 7, 14 queries x 4 heads, 10
         // documents, as five of two (280) 95, as four of three (224) 76; 129 rows x 6, 41 queries x 2 heads, as seven of two (574) 91, as
         // five of three (410) 75.  Splits pay for their partial rows, written and read, and for the merge: about 30 of those parts per 64

@@ -110,11 +110,12 @@ def test_the_attention_tests_reach_every_variant():
 
 def test_a_split_pays_for_its_merge():
     """Documents encoded over a 32-token prefix: eight row groups in one split, not five in two that save three tiles; one group of wavefronts
-    where a split has ten tiles, two from thirteen on.  Long lists are split as before."""
+    where a split has ten tiles of three blocks each, two from thirteen on, and from ten on with five blocks in all.  Long lists are split as before."""
     shape = lambda *a: plan_probe.plan(*a)[1:5]          # blocks per wavefront, groups, row groups, splits
     assert shape(12, 2, 12, 160, 2, 192) == (2, 1, 8, 1)
     assert shape(12, 2, 16, 228, 2, 260) == (3, 1, 8, 1)
     assert shape(12, 2, 6, 340, 2, 372) == (2, 2, 16, 1)
+    assert shape(32, 16, 8, 40, 5, 492) == (2, 2, 1, 2)
     assert shape(28, 4, 1, 64, 52, 7446) == (2, 2, 4, 16)
 
 
