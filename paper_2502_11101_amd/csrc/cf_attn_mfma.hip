@@ -436,14 +436,15 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
 // The two wavefronts of a SIMD should be in different phases:
 //   GROUPS == 2: two groups of four wavefronts stream disjoint runs of the workgroup's tiles, the second group one phase behind the
 //                first (a barrier after every phase); their results meet in LDS at the end.  For plans of up to 256 units with ten
-//                tiles a split and more.
+//                to thirteen tiles a split and more.
 //   GROUPS == 1: one group per workgroup, one barrier per tile.  Past 256 units two workgroups share a CU, and one hides the other's
 //                prologue and tail as well: 30 documents of 160 rows and 192 tokens x 32 heads (960 units) 53 us, two groups 77.  Within
 //                256 units, where splits are short, a wavefront has its SIMD to itself: the second group's delay and the merge cost more.
 // Against the kernel before it (two wavefronts that load and stage, six with two row blocks each, software-pipelined): 64 queries,
 // 2 kv heads, 384 rows, 3064 tokens, fp16: 130 -> 111 us (690 TFLOP/s); the 30 documents above 72 -> 53; one query, 4 kv heads, 448
-// rows, 7600 tokens 26 us both (a third of it prologue and merge).  Two tiles in flight instead of one, or the rotation on the
-// matrix cores (diagonal matrices of cosines in three 16-bit parts), no longer fit the 256 registers or cost more than they save.
+// rows, 7600 tokens 26 us both (more than half of it prologue, merge of the groups and partial store: 13 us + 0.6 per tile).  Two
+// tiles in flight instead of one, or the rotation on the matrix cores (diagonal matrices of cosines in three 16-bit parts), no longer
+// fit the 256 registers or cost more than they save.
 constexpr int kWideK = kTile * kKRow;            // bytes
 constexpr int kWideVRow = 288;                       // bytes per token of a staged V tile
 constexpr int kWideV = kTile * kWideVRow;
