@@ -24,7 +24,7 @@ def test_one_row_over_a_cache(n, hq, hkv, dtype):
 
 
 @pytest.mark.parametrize("layout", ["head", "token"])
-@pytest.mark.parametrize("batch,hkv", [(3, 4), (40, 8), (70, 4)])        # 12, 320 and 280 units: several splits, one
+@pytest.mark.parametrize("batch,hkv", [(3, 4), (40, 8), (70, 4), (64, 16), (65, 16)])      # 12 units: several splits; 320, 280, 1024: one; 1040: the other kernel
 def test_unequal_conversations(batch, hkv, layout):
     print(f"decode batch={batch} hkv={hkv} {layout}", flush=True)
     rng = np.random.default_rng(batch)
