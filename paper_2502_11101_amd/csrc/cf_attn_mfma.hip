@@ -20,11 +20,11 @@
 //     in registers and the V^T fragments read with transposing LDS reads; the transposed forms keep
 //     one query row per lane, so the online softmax (fp32, exp2 domain) needs no cross-lane exchange
 //     except when its reference maximum moves.
-// At the end of each segment a wavefront leaves (reference maximum, sum of exp2) per row (attn_solo_kernel: where masses are wanted).
+// Where masses are wanted a wavefront leaves (reference maximum, sum of exp2) per row at the end of each segment.
 //
-// A second kernel merges the splits' partial outputs and writes the output rows; a third reduces
-// the (max, sum) pairs to per-segment attention mass (the document-wise score of Alg. 2) in a
-// fixed order and adds it to the accumulated scores.  Results cross between the kernels at the
+// Where there are several splits a second kernel merges their partial outputs, writes the output rows and reduces the (max, sum) pairs
+// over the rows; with one split the attention kernel does.  A last one adds those up to
+// per-segment attention mass (the document-wise score of Alg. 2) in a fixed order and adds it to the accumulated scores.  Results cross between the kernels at the
 // kernel boundaries: no fences, no atomics on the data path, bit-identical reruns.
 #include <type_traits>
 
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreads * 2, 2) void attn_tile_kernel(AttnArgs a, 
         asm volatile("" ::"s"(p0), "s"(p1), "s"(p2), "s"(p3), "s"(p4), "s"(p5), "s"(p6), "s"(p7), "s"(p8), "s"(p9),
                      "s"(a.n_store_tokens), "s"(a.seg_stride), "s"(a.batch), "s"(a.max_tq), "s"(a.n_q_heads),
                      "s"(a.n_kv_heads), "s"(a.scale_log2e), "s"(a.q_stored_start), "s"(p.nsplit), "s"(p.slots),
-                     "s"(p.off_ml), "s"(p.off_opart), "s"(p.off_massml));
+                     "s"(p.off_massml));
     }
 
     // grid (split, kv head, query): nothing to divide; one row group (at most four row blocks)
@@ -138,6 +138,7 @@ __global__ __launch_bounds__(kThreads * 2, 2) void attn_tile_kernel(AttnArgs a, 
     char* ws = static_cast<char*>(a.workspace);
     float2* massml = reinterpret_cast<float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg;
 
+
     // V staging offsets and the transposing reads: lane 16*lg + s addresses row 4*lg + s/4 (+16), 8 bytes at
     // channel 16*db + 4*(s&3)
     const uint32_t vw_off = (uint32_t)vr * 256 + 16 * (vc ^ (2 * (vr & 7)));    // rows vr + 16*it keep (t & 7)
@@ -190,6 +191,7 @@ __global__ __launch_bounds__(kThreads * 2, 2) void attn_tile_kernel(AttnArgs a, 
     }
     if (cur_seg >= 0) emit_segment<1>(st, massml, cur_seg + ss, p.rows_wg, wave, li, lg);
 
+    const StoreArgs ta = store_args(late_args());
     float l_row[1] = {st.l_run[0] + __shfl_xor(st.l_run[0], 16)};       // row sums (each lane holds those of its own tokens so far)
     l_row[0] += __shfl_xor(l_row[0], 32);
     // the second group hands its rows' results (same rows, other tokens) to the first through the tile
@@ -203,18 +205,24 @@ __global__ __launch_bounds__(kThreads * 2, 2) void attn_tile_kernel(AttnArgs a, 
         if (lg == 0) red_ml[wave * 16 + li] = make_float2(st.m_run[0], l_row[0]);
     }
     __syncthreads();
-    if (grp == 1) return;
-    const float2 o = red_ml[wave * 16 + li];
-    const float m = fmaxf(st.m_run[0], o.x);
-    const float ms = m == -INFINITY ? 0.f : m;
-    const float f0 = __builtin_amdgcn_exp2f(st.m_run[0] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
+    if (grp == 1 && !ta.slots_here) return;
+    float2* const row_ml = red_ml + kWaves * 16;
+    if (grp == 0) {
+        const float2 o = red_ml[wave * 16 + li];
+        const float m = fmaxf(st.m_run[0], o.x);
+        const float ms = m == -INFINITY ? 0.f : m;
+        const float f0 = __builtin_amdgcn_exp2f(st.m_run[0] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
 #pragma unroll
-    for (int db = 0; db < 8; ++db) st.acc[0][db] = st.acc[0][db] * f0 + red[(wave * 8 + db) * kWave + lane] * f1;
-    l_row[0] = l_row[0] * f0 + o.y * f1;
-    st.m_run[0] = m;
-    // a wavefront whose rows are all padding leaves nothing
-    if (!has_rows) return;
-    store_partials<DT, 1>(a, p, unit, split, wave, st, l_row, lane, qh.q0, tq, hkv, group, 0, row_limit);
+        for (int db = 0; db < 8; ++db) st.acc[0][db] = st.acc[0][db] * f0 + red[(wave * 8 + db) * kWave + lane] * f1;
+        l_row[0] = l_row[0] * f0 + o.y * f1;
+        st.m_run[0] = m;
+        if (ta.slots_here && lg == 0) row_ml[wave * 16 + li] = make_float2(m, wave * 16 + li < row_limit ? l_row[0] : 0.f);
+        // a wavefront whose rows are all padding leaves nothing
+        if (has_rows) store_partials<DT, 1>(ta, unit, split, wave, st, l_row, lane, qh.q0, tq, hkv, group, 0, row_limit);
+    }
+    if (!ta.slots_here) return;
+    __syncthreads();
+    reduce_slots<2 * kWaves>(late_args(), unit, row_ml, (int)threadIdx.x / kWave, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -231,7 +239,7 @@ template <int DT>
 __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnArgs a, RopeFreq freq, Plan p) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kSoloWaves * kSoloV];
     __shared__ __attribute__((aligned(16))) float2 cs_lds[kSoloWaves][kHalf];
-    __shared__ float2 red_ml[kSoloWaves][16];
+    __shared__ float2 red_ml[kSoloWaves][16], row_ml[64];
     static_assert(kSoloWaves * kSoloV >= kSoloWaves * 8 * kWave * (int)sizeof(f32x4), "the results reuse the V tiles");
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -389,6 +397,7 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     if (want_mass && cur_seg >= 0) emit();
 
     // ---- the wavefronts' results: wavefront w merges channel block w
+    const StoreArgs ta = store_args(late_args());
     float l_row = l_run + __shfl_xor(l_run, 16);
     l_row += __shfl_xor(l_row, 32);
     __syncthreads();                                 // every wavefront is done with its V tile
@@ -412,16 +421,21 @@ __global__ __launch_bounds__(kSoloWaves * kWave, 2) void attn_solo_kernel(AttnAr
     }
     o *= l > 0.f ? 1.f / l : 0.f;
     const uint2 packed = make_uint2(Mma<DT>::pack(o[0], o[1]), Mma<DT>::pack(o[2], o[3]));
-    const int64_t part = (int64_t)unit * p.nsplit + split;
-    if (wave == 0 && lg == 0) reinterpret_cast<float2*>(ws + p.off_ml)[part * p.rows_wg + li] = make_float2(m, l);
-    if (p.direct_out) {
+    if (ta.direct_out) {
+        if (want_mass) {
+            if (wave == 0) row_ml[lane] = make_float2(m, lane < row_limit ? l : 0.f);
+            __syncthreads();
+            reduce_slots<kSoloWaves>(late_args(), unit, row_ml, wave, lane);
+        }
         if (li >= row_limit) return;
         const int gi = (int)div_exact((unsigned)li, (unsigned)tq), t = li - gi * tq;
-        uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 16 * wave + 4 * lg;
+        uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)qh.q0 + t) * ta.n_q_heads + hkv * group + gi) * kD + 16 * wave + 4 * lg;
         *reinterpret_cast<uint2*>(op) = packed;
         return;
     }
-    reinterpret_cast<uint2*>(ws + p.off_opart)[(part * (p.rows_wg / 16) * 8 + wave) * kWave + lane] = packed;
+    const int64_t part = (int64_t)unit * ta.nsplit + split;
+    if (wave == 0 && lg == 0) reinterpret_cast<float2*>(ta.ws + ta.off_ml)[part * ta.rows_wg + li] = make_float2(m, l);
+    reinterpret_cast<uint2*>(ta.ws + ta.off_opart)[(part * (ta.rows_wg / 16) * 8 + wave) * kWave + lane] = packed;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -813,9 +827,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
             return;
         }
         if (cd.seg != cur_seg) {
-            if (cur_seg >= 0) {
-                emit(cur_seg);
-            }
+            if (cur_seg >= 0) emit(cur_seg);
             cur_seg = cd.seg;
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb) { st.l_run[rb] += st.seg_l[rb]; st.seg_l[rb] = 0.f; }
@@ -857,6 +869,8 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     weigh();
     if (has_rows && cur_seg >= 0) emit(cur_seg);
 
+    const StoreArgs ta = store_args(late_args());
+    const int lane_t = lane_anew(), li_t = lane_t & 15, lg_t = lane_t >> 4;      // (not kept through the loop)
     float l_row[NRB];
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
@@ -865,16 +879,26 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         l_row[rb] += __shfl_xor(l_row[rb], 32);
     }
     if (GROUPS == 1) {
-        if (has_rows) store_partials<DT, NRB>(a, p, unit, split, wave * NRB, st, l_row, lane, qh.q0, tq, hkv, group, row_base, row_limit);
+        if (ta.slots_here && lg_t == 0) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) {
+                const int row = (wave * NRB + rb) * 16 + li_t;
+                red_ml[0][row] = make_float2(st.m_run[rb], row_base + row < row_limit ? l_row[rb] : 0.f);
+            }
+        }
+        if (has_rows) store_partials<DT, NRB>(ta, unit, split, wave * NRB, st, l_row, lane_t, qh.q0, tq, hkv, group, row_base, row_limit);
+        if (!ta.slots_here) return;
+        __syncthreads();
+        reduce_slots<kWaves>(late_args(), unit, red_ml[0], wave, lane_t);
         return;
     }
     __syncthreads();
     f32x4* red = reinterpret_cast<f32x4*>(lds);
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-        if (lg == 0) red_ml[grp][(wave * NRB + rb) * 16 + li] = make_float2(st.m_run[rb], l_row[rb]);
+        if (lg_t == 0) red_ml[grp][(wave * NRB + rb) * 16 + li_t] = make_float2(st.m_run[rb], l_row[rb]);
         // the first group keeps channel blocks 0-3, the second 4-7
-        f32x4* dst = red + (((grp * kWaves + wave) * NRB + rb) * 4) * kWave + lane;
+        f32x4* dst = red + (((grp * kWaves + wave) * NRB + rb) * 4) * kWave + lane_t;
         if (grp == 0) {
 #pragma unroll
             for (int db = 0; db < 4; ++db) dst[db * kWave] = st.acc[rb][4 + db];
@@ -886,40 +910,51 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         }
     }
     __syncthreads();
-    if (!has_rows) return;
+    if (!has_rows && !ta.slots_here) return;
+    const int64_t part = (int64_t)unit * ta.nsplit + split;
+    float2* const row_ml = reinterpret_cast<float2*>(&cs_lds[0][0][0]);          // nobody reads the angles any more
+    static_assert(sizeof(cs_lds) >= kWaves * NRB * 16 * sizeof(float2) || GROUPS == 1, "room for the rows");
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
-        const float2 o = red_ml[grp ^ 1][(wave * NRB + rb) * 16 + li];
+        if (!has_rows) continue;
+        const float2 o = red_ml[grp ^ 1][(wave * NRB + rb) * 16 + li_t];
         const float m = fmaxf(st.m_run[rb], o.x);
         const float ms = m == -INFINITY ? 0.f : m;
         const float f0 = __builtin_amdgcn_exp2f(st.m_run[rb] - ms), f1 = __builtin_amdgcn_exp2f(o.x - ms);
-        const f32x4* src = red + ((((grp ^ 1) * kWaves + wave) * NRB + rb) * 4) * kWave + lane;
+        const f32x4* src = red + ((((grp ^ 1) * kWaves + wave) * NRB + rb) * 4) * kWave + lane_t;
         // the sums in the groups' order, so that both come to the same row sum
         const float l = grp == 0 ? l_row[rb] * f0 + o.y * f1 : o.y * f1 + l_row[rb] * f0;
         const float inv = l > 0.f ? 1.f / l : 0.f;
         const int blk = wave * NRB + rb;
-        float2* ml = reinterpret_cast<float2*>(static_cast<char*>(a.workspace) + p.off_ml) + ((int64_t)unit * p.nsplit + split) * p.rows_wg;
-        if (grp == 0 && lg == 0) ml[blk * 16 + li] = make_float2(m, l);
         uint2 w[4];
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
             const f32x4 v = (st.acc[rb][db] * f0 + src[db * kWave] * f1) * inv;
             w[db] = make_uint2(Mma<DT>::pack(v[0], v[1]), Mma<DT>::pack(v[2], v[3]));
         }
-        if (p.direct_out) {
-            const int mrow = row_base + blk * 16 + li;
+        if (ta.direct_out) {
+            const int mrow = row_base + blk * 16 + li_t;
+            if (ta.slots_here && grp == 0 && lg_t == 0) row_ml[blk * 16 + li_t] = make_float2(m, mrow < row_limit ? l : 0.f);
             if (mrow >= row_limit) continue;
             const int gi = (int)div_exact((unsigned)mrow, (unsigned)tq), t = mrow - gi * tq;
-            uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 4 * lg + 64 * grp;
+            uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)qh.q0 + t) * ta.n_q_heads + hkv * group + gi) * kD + 4 * lg_t + 64 * grp;
 #pragma unroll
             for (int db = 0; db < 4; ++db) *reinterpret_cast<uint2*>(op + 16 * db) = w[db];
         } else {
-            uint2* opart = reinterpret_cast<uint2*>(static_cast<char*>(a.workspace) + p.off_opart) +
-                           ((((int64_t)unit * p.nsplit + split) * p.rows_wg / 16 + blk) * 8 + 4 * grp) * kWave + lane;
+            float2* ml = reinterpret_cast<float2*>(ta.ws + ta.off_ml) + part * ta.rows_wg;
+            if (grp == 0 && lg_t == 0) ml[blk * 16 + li_t] = make_float2(m, l);
+            uint2* opart = reinterpret_cast<uint2*>(ta.ws + ta.off_opart) + ((part * ta.rows_wg / 16 + blk) * 8 + 4 * grp) * kWave + lane_t;
 #pragma unroll
             for (int db = 0; db < 4; ++db) opart[db * kWave] = w[db];
         }
     }
+    if (!ta.slots_here) return;
+    if (!has_rows && grp == 0 && lg_t == 0) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) row_ml[(wave * NRB + rb) * 16 + li_t] = make_float2(0.f, 0.f);
+    }
+    __syncthreads();
+    reduce_slots<2 * kWaves>(late_args(), unit, row_ml, (int)threadIdx.x / kWave, lane_t);
 }
 
 }  // namespace
@@ -985,7 +1020,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
 #undef CF_LAUNCH_DT
 #undef CF_LAUNCH_WIDE
 #undef CF_LAUNCH_TIMED
-    const bool combine = !(p.direct_out && a.mass == nullptr);            // else nothing left to merge or reduce
+    const bool combine = !p.direct_out;              // one split: the attention kernel has written the rows and reduced the slots
     // before a fused epilogue the pending score parts are taken in by one more row of the combine kernel's grid
     const bool pending_beside = combine && !a.defer && prune && a.n_pending > 0 && epilogue_fits(p, prune) && pending_fit_combine(a, p);
     if (combine) launch_combine(a, p, pending_beside, s);

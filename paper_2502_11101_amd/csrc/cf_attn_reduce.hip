@@ -7,7 +7,7 @@ namespace cf {
 using namespace attn;
 namespace {
 
-// Second kernel: one workgroup per (unit = (query, kv head, row group), 64-row pass, eighth of the output channels) merges the
+// Second kernel, where there are several splits: one workgroup per (unit = (query, kv head, row group), 64-row pass, eighth of the output channels) merges the
 // splits' partial outputs and writes its output rows; the eight workgroups of a (unit, pass) also share
 // the reduction, over the pass's 64 rows, of every (segment, split) slot's (max, sum) pairs to
 // sum * exp2(max - row max) / row sum, which the mass kernel then only has to add up.
@@ -34,11 +34,10 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
     const int wave = tid / kWave;
     const int li = lane & 15, lg = lane >> 4;
     char* ws = static_cast<char*>(a.workspace);
-    // grid (channel block + 8 * pass — or just the pass when there is nothing to merge —, kv head * row groups + row group, query)
+    // grid (channel block + 8 * pass, kv head * row groups + row group, query)
     const int hq = a.n_q_heads, group = p.group;
-    const int x_shift = p.direct_out ? 0 : 3;        // nothing to merge: one workgroup per (unit, pass) reduces every slot
-    const int dbq = blockIdx.x & ((1 << x_shift) - 1);
-    const int pass = (int)(blockIdx.x >> x_shift);
+    const int dbq = blockIdx.x & 7;
+    const int pass = (int)(blockIdx.x >> 3);
     const int b = blockIdx.z;
     const int hkv = p.n_rg == 1 ? (int)blockIdx.y : (int)div_exact(blockIdx.y, (unsigned)p.n_rg);
     const int rg = (int)blockIdx.y - hkv * p.n_rg;
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
     auto widen = [](uint2 w) { return f32x4{Mma<DT>::lo(w.x), Mma<DT>::hi(w.x), Mma<DT>::lo(w.y), Mma<DT>::hi(w.y)}; };
     const int64_t split_stride = (int64_t)p.rows_wg / 16 * 8 * kWave;
     const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg + pass * 64 + lane;
-    const int k_first = dbq * kWaves + wave, k_step = kWaves << x_shift;
+    const int k_first = dbq * kWaves + wave, k_step = kWaves * 8;
     constexpr int kSv = 8;                           // slot statistics fetched up front per wavefront
 
     // Everything this workgroup reads is requested up front — row statistics, partial outputs of the first splits,
@@ -59,9 +58,7 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
     // in-bounds address; what lies past the end is dropped afterwards): a load inside a branch makes the compiler
     // wait for it before the branch ends, which would put the round trips one behind the other.
     // (A wavefront whose 16 rows are all padding reads what an earlier call left there: never stored; not waiting for
-    // the query's length here saves a round trip.  With one split the attention kernel wrote the output rows itself:
-    // nothing to merge, the partial outputs' area does not exist and a harmless address is read instead.)
-    const bool merge = !p.direct_out;
+    // the query's length here saves a round trip.)
     constexpr int kMl = kMaxSplit * 64 / kThreads;   // (m, l) pairs per thread
     const int n_ml = p.nsplit * 64;
     float2 ml_regs[kMl];
@@ -70,11 +67,9 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
         const int idx = min(tid + i * kThreads, n_ml - 1);
         ml_regs[i] = ml[(idx >> 6) * p.rows_wg + (idx & 63)];
     }
-    const uint2* src_safe = merge ? src : reinterpret_cast<const uint2*>(ws + p.off_ml) + (lane & 31);
-    const int64_t stride_safe = merge ? split_stride : 0;
     uint2 pre[kPre];
 #pragma unroll
-    for (int s = 0; s < kPre; ++s) pre[s] = src_safe[min(s, p.nsplit - 1) * stride_safe];
+    for (int s = 0; s < kPre; ++s) pre[s] = src[min(s, p.nsplit - 1) * split_stride];
     float2 sv[kSv];
 #pragma unroll
     for (int j = 0; j < kSv; ++j) sv[j] = massml[(int64_t)min(k_first + j * k_step, p.slots - 1) * p.rows_wg];
@@ -120,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
 #pragma unroll
     for (int s = 0; s < kPre; ++s)
         if (s < p.nsplit) o += widen(pre[s]) * mlw[s * 64 + wave * 16 + li].x;
-    if (merge && blk_has_rows)
+    if (blk_has_rows)
         for (int s0 = kPre; s0 < p.nsplit; s0 += kPre) {         // further splits, eight loads at a time
             uint2 more[kPre];
 #pragma unroll
@@ -131,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
         }
     const int lrow = pass * 64 + wave * 16 + li;
     o *= row_inv_sum(wave * 16 + li);
-    if (merge && lrow < rows_here) {
+    if (lrow < rows_here) {
         const int m2 = row_base + lrow;
         const int gi = (int)div_exact((unsigned)m2, (unsigned)tq), t = m2 - gi * tq;
         uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)q0 + t) * hq + hkv * group + gi) * kD + 16 * dbq + 4 * lg;
@@ -619,7 +614,7 @@ bool pending_fit_combine(const AttnArgs& a, const Plan& p) { return p.slots <= 2
 
 void launch_combine(const AttnArgs& a, const Plan& p, bool take_pending, hipStream_t s) {
     const int extra = take_pending ? 1 : 0;
-    const dim3 grid((unsigned)((p.direct_out ? 1 : 8) * p.nrb), (unsigned)(a.n_kv_heads * p.n_rg + extra), (unsigned)a.batch), block(kThreads);
+    const dim3 grid((unsigned)(8 * p.nrb), (unsigned)(a.n_kv_heads * p.n_rg + extra), (unsigned)a.batch), block(kThreads);
     if (a.dtype == CF_BF16) hipLaunchKernelGGL((attn_combine_kernel<CF_BF16>), grid, block, 0, s, a, p, extra);
     else hipLaunchKernelGGL((attn_combine_kernel<CF_F16>), grid, block, 0, s, a, p, extra);
 }

@@ -236,26 +236,87 @@ __device__ __forceinline__ void emit_segment(const RowState<NRB>& st, float2* ma
     }
 }
 
+// The arguments of the attention kernels as they lie in memory, read anew: what only a kernel's end needs would otherwise be kept in
+// scalar registers through its loop, or spilled to vector lanes and back (an eight-split layer call 21.8 -> 22.2 us).
+struct KernelArgs { AttnArgs a; RopeFreq freq; Plan p; };
+typedef const __attribute__((address_space(4))) KernelArgs* LateArgs;
+__device__ __forceinline__ LateArgs late_args() {
+    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+#ifdef __OPTIMIZE__                                   // (unoptimised, nothing is held in scalar registers)
+    asm volatile("" : "+s"(at));
+#endif
+    return reinterpret_cast<LateArgs>(at);
+}
+// What storing a workgroup's results needs of them, requested together and ahead of the barriers of the kernel's end.
+struct StoreArgs {
+    char *ws, *out;
+    size_t off_ml, off_opart;
+    int n_q_heads, nsplit, rows_wg;
+    bool direct_out, slots_here;
+};
+__device__ __forceinline__ StoreArgs store_args(LateArgs args) {
+    void *ws = args->a.workspace, *out = args->a.out, *mass = args->a.mass;
+    StoreArgs t;
+    t.off_ml = args->p.off_ml;
+    t.off_opart = args->p.off_opart;
+    t.n_q_heads = args->a.n_q_heads;
+    t.nsplit = args->p.nsplit;
+    t.rows_wg = args->p.rows_wg;
+    const int direct_out = args->p.direct_out;
+#ifdef __OPTIMIZE__
+    asm volatile("" ::"s"(ws), "s"(out), "s"(mass), "s"(t.off_ml), "s"(t.off_opart), "s"(t.n_q_heads), "s"(t.nsplit), "s"(t.rows_wg), "s"(direct_out));
+#endif
+    t.ws = static_cast<char*>(ws);
+    t.out = static_cast<char*>(out);
+    t.direct_out = direct_out != 0;
+    t.slots_here = t.direct_out && mass != nullptr;
+    return t;
+}
+
+// One split: the rows' statistics are final where the attention kernel ends, so the workgroup reduces its slots itself, as the
+// merge kernel does where there are several (same terms, same order): per (segment, run) slot and 64-row pass
+// sum over the rows of sum * exp2(max - row max) / row sum.  `row_ml`: (row max, row sum) of the workgroup's rows in LDS, row sums of
+// padding rows 0; every wavefront is past a barrier after its last slot store.  A launch of its own for this took 5 us of an
+// eight-query layer's 58 and 6.5 of a 64-query layer's 125; here it is about 1 us.
+template <int WAVES>
+__device__ __forceinline__ void reduce_slots(LateArgs args, int unit, const float2* row_ml, int wave, int lane) {
+    char* ws = static_cast<char*>(args->a.workspace);
+    const int slots = args->p.slots, nrb = args->p.nrb, rows_wg = args->p.rows_wg;
+    const float2* massml = reinterpret_cast<const float2*>(ws + args->p.off_massml) + (int64_t)unit * slots * rows_wg;
+    float* masspart = reinterpret_cast<float*>(ws + args->p.off_masspart + (size_t)args->a.n_pending * args->p.masspart_bytes) + (int64_t)unit * nrb * slots;
+    constexpr int kBatch = 4;                        // slots whose statistics are requested before the first is added up
+    for (int pass = 0; pass < nrb; ++pass) {
+        const float2 r = row_ml[pass * 64 + lane];
+        const float m = r.x == -INFINITY ? 0.f : r.x, inv = r.y > 0.f ? 1.f / r.y : 0.f;
+        for (int k0 = wave; k0 < slots; k0 += WAVES * kBatch) {
+            float2 v[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) v[i] = massml[(int64_t)min(k0 + WAVES * i, slots - 1) * rows_wg + pass * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const float c = wave_sum_dpp(inv > 0.f ? v[i].y * exp2f(v[i].x - m) * inv : 0.f);
+                if (lane == 0 && k0 + WAVES * i < slots) masspart[pass * slots + k0 + WAVES * i] = c;
+            }
+        }
+    }
+}
+
 // Results of a split.  Several splits: partial O^T in MFMA layout (four 16-bit values per lane, row block and
-// channel block, each row divided by the split's own row sum) for the merge kernel.  One split: nothing to merge, the rows are normalised and written to
-// `out` here (row m = g*tq + t of the stacked rows is out[q0 + t][hkv*group + g]).  Either way (reference,
-// row sum) per row, which the mass reduction needs.
+// channel block, each row divided by the split's own row sum) and (reference, row sum) per row for the merge kernel.  One split: nothing to merge, the rows are normalised and written to
+// `out` here (row m = g*tq + t of the stacked rows is out[q0 + t][hkv*group + g]).
 template <int DT, int NRB>
-__device__ __forceinline__ void store_partials(const AttnArgs& a, const Plan& p, int unit, int split, int first_blk,
+__device__ __forceinline__ void store_partials(const StoreArgs& ta, int unit, int split, int first_blk,
                                                const RowState<NRB>& st, const float (&l_row)[NRB], int lane, int q0, int tq,
                                                int hkv, int group, int row_base, int row_limit) {
-    char* ws = static_cast<char*>(a.workspace);
-    float2* ml = reinterpret_cast<float2*>(ws + p.off_ml) + ((int64_t)unit * p.nsplit + split) * p.rows_wg;
-    if (p.direct_out) {
+    if (ta.direct_out) {
         const int li = lane & 15, lg = lane >> 4;
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) {
             const int m = row_base + (first_blk + rb) * 16 + li;
-            if (lg == 0) ml[(first_blk + rb) * 16 + li] = make_float2(st.m_run[rb], l_row[rb]);
             if (m >= row_limit) continue;
             const int gi = (int)div_exact((unsigned)m, (unsigned)tq), t = m - gi * tq;
             const float inv = l_row[rb] > 0.f ? 1.f / l_row[rb] : 0.f;
-            uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 4 * lg;
+            uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)q0 + t) * ta.n_q_heads + hkv * group + gi) * kD + 4 * lg;
 #pragma unroll
             for (int db = 0; db < 8; ++db) {
                 const f32x4 o = st.acc[rb][db] * inv;
@@ -269,8 +330,10 @@ __device__ __forceinline__ void store_partials(const AttnArgs& a, const Plan& p,
     }
     // the split's rows leave normalised by their own sums, in the tensors' 16-bit type: bounded by the values
     // themselves whatever the sums are, and half the bytes of the accumulators
-    uint2* opart = reinterpret_cast<uint2*>(ws + p.off_opart) +
-                   (((int64_t)unit * p.nsplit + split) * p.rows_wg / 16 + first_blk) * 8 * kWave + lane;
+    const int64_t part = (int64_t)unit * ta.nsplit + split;
+    float2* ml = reinterpret_cast<float2*>(ta.ws + ta.off_ml) + part * ta.rows_wg;
+    uint2* opart = reinterpret_cast<uint2*>(ta.ws + ta.off_opart) +
+                   (part * ta.rows_wg / 16 + first_blk) * 8 * kWave + lane;
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const float inv = l_row[rb] > 0.f ? 1.f / l_row[rb] : 0.f;
