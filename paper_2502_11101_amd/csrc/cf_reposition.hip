@@ -18,8 +18,10 @@ template <int DT> struct Chunk8 {
     __device__ __forceinline__ void load(const void* base, int64_t idx) {
         r = *reinterpret_cast<const U4*>(static_cast<const uint16_t*>(base) + idx);
     }
-    __device__ __forceinline__ void store(void* base, int64_t idx) const {
-        *reinterpret_cast<U4*>(static_cast<uint16_t*>(base) + idx) = r;
+    template <bool STREAM> __device__ __forceinline__ void store(void* base, int64_t idx) const {
+        U4* p = reinterpret_cast<U4*>(static_cast<uint16_t*>(base) + idx);
+        if constexpr (STREAM) __builtin_nontemporal_store(r, p);
+        else *p = r;
     }
     __device__ __forceinline__ void to_float(float (&v)[8]) const {
         const uint32_t w[4] = {r.x, r.y, r.z, r.w};
@@ -53,7 +55,7 @@ template <> struct Chunk8<CF_F32> {
         a = p[0];
         b = p[1];
     }
-    __device__ __forceinline__ void store(void* base, int64_t idx) const {
+    template <bool STREAM> __device__ __forceinline__ void store(void* base, int64_t idx) const {
         F4* p = reinterpret_cast<F4*>(static_cast<float*>(base) + idx);
         p[0] = a;
         p[1] = b;
@@ -122,6 +124,13 @@ __device__ __forceinline__ void rotate(Chunk8<DT>& c0, Chunk8<DT>& c1, const flo
     c1.from_float(b);
 }
 
+// What is moved is not read again soon, so 16-bit types are written past the caches.  30 documents x 160 tokens of 32 heads, bf16:
+// assembly 36.0 -> 31.3 us (5.0 TB/s read and written, the rate of a large copy), re-positioning 13.65 -> 13.4; 2 x 18 documents of 66-121
+// tokens, 32 heads, token-major: 28.7 -> 21.1; interleaved pairs 7.3 -> 6.6 and 11.1 -> 10.0.  Not fp32, whose store instructions leave
+// every other 16 bytes to the next one (re-positioning 84 documents of 53 tokens, 4 heads: 6.8 and 8.4 us).  Loads past the caches:
+// re-positioning 13.4 -> 15.3, assembly the same.
+template <int DT> constexpr bool kStream = DT != CF_F32;
+
 // Where a block works in a segment of `len` tokens: panels of whole tokens, in each the block's chunk of U * kThreads
 // items, then those a grid further on.  Every block of a segment visits the same panels.
 template <int U> struct Walk {
@@ -187,8 +196,8 @@ __global__ __launch_bounds__(kThreads) void reposition_kernel(
         }
         if (it >= n_items) continue;
         rotate<DT, PAIRING>(a, b, cs, i.j);
-        a.store(k_out, o0);
-        b.store(k_out, o1);
+        a.template store<kStream<DT>>(k_out, o0);
+        b.template store<kStream<DT>>(k_out, o1);
     }
 }
 
@@ -328,10 +337,10 @@ __global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs a, Rope
             const int64_t dst = (out0 + tok[u]) * a.final_ts + (int64_t)head[u] * a.final_hs;
             const int o0 = first_of<PAIRING>(j[u]), o1 = second_of<PAIRING>(j[u], half);
             if (delta != 0) rotate<DT, PAIRING>(x[u], y[u], cs, j[u]);
-            x[u].store(a.k_final, dst + o0);
-            y[u].store(a.k_final, dst + o1);
-            va[u].store(a.v_final, dst + o0);
-            vb[u].store(a.v_final, dst + o1);
+            x[u].template store<kStream<DT>>(a.k_final, dst + o0);
+            y[u].template store<kStream<DT>>(a.k_final, dst + o1);
+            va[u].template store<kStream<DT>>(a.v_final, dst + o0);
+            vb[u].template store<kStream<DT>>(a.v_final, dst + o1);
             if (a.final_pos && j[u] == 0 && head[u] == 0) a.final_pos[out0 + tok[u]] = seg.new_start + tok[u];
         }
     }
