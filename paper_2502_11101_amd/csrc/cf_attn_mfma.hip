@@ -926,26 +926,22 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         const float l = grp == 0 ? l_row[rb] * f0 + o.y * f1 : o.y * f1 + l_row[rb] * f0;
         const float inv = l > 0.f ? 1.f / l : 0.f;
         const int blk = wave * NRB + rb;
-        uint2 w[4];
+        f32x4 o4[4];
 #pragma unroll
-        for (int db = 0; db < 4; ++db) {
-            const f32x4 v = (st.acc[rb][db] * f0 + src[db * kWave] * f1) * inv;
-            w[db] = make_uint2(Mma<DT>::pack(v[0], v[1]), Mma<DT>::pack(v[2], v[3]));
-        }
+        for (int db = 0; db < 4; ++db) o4[db] = (st.acc[rb][db] * f0 + src[db * kWave] * f1) * inv;
         if (ta.direct_out) {
-            const int mrow = row_base + blk * 16 + li_t;
-            if (ta.slots_here && grp == 0 && lg_t == 0) row_ml[blk * 16 + li_t] = make_float2(m, mrow < row_limit ? l : 0.f);
-            if (mrow >= row_limit) continue;
+            const int row = row_base + blk * 16 + li_t, mrow = min(row, row_limit - 1);
+            if (ta.slots_here && grp == 0 && lg_t == 0) row_ml[blk * 16 + li_t] = make_float2(m, row < row_limit ? l : 0.f);
             const int gi = (int)div_exact((unsigned)mrow, (unsigned)tq), t = mrow - gi * tq;
-            uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)qh.q0 + t) * ta.n_q_heads + hkv * group + gi) * kD + 4 * lg_t + 64 * grp;
+            uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)qh.q0 + t) * ta.n_q_heads + hkv * group + gi) * kD + 64 * grp;
 #pragma unroll
-            for (int db = 0; db < 4; ++db) *reinterpret_cast<uint2*>(op + 16 * db) = w[db];
+            for (int db = 0; db < 4; db += 2) store_row_pair<DT>(op, db, o4[db], o4[db + 1], lg_t, row < row_limit);
         } else {
             float2* ml = reinterpret_cast<float2*>(ta.ws + ta.off_ml) + part * ta.rows_wg;
             if (grp == 0 && lg_t == 0) ml[blk * 16 + li_t] = make_float2(m, l);
             uint2* opart = reinterpret_cast<uint2*>(ta.ws + ta.off_opart) + ((part * ta.rows_wg / 16 + blk) * 8 + 4 * grp) * kWave + lane_t;
 #pragma unroll
-            for (int db = 0; db < 4; ++db) opart[db * kWave] = w[db];
+            for (int db = 0; db < 4; ++db) opart[db * kWave] = make_uint2(Mma<DT>::pack(o4[db][0], o4[db][1]), Mma<DT>::pack(o4[db][2], o4[db][3]));
         }
     }
     if (!ta.slots_here) return;
