@@ -14,15 +14,14 @@ namespace {
 __device__ __forceinline__ void pending_masses_block(const AttnArgs& a, const Plan& p, int b, int n_parts, int write_mass,
                                                      float (*m_all)[kWave]);
 
-// With take_pending the grid has one more row of workgroups (the last blockIdx.x); the first of them, per query, takes
-// the ledger's pending score parts in beside the merge (pending_masses_block), the others leave at once.
+// With take_pending the grid has one more row of workgroups, the first: its first workgroup, per query, takes the ledger's pending
+// score parts in beside the merge (pending_masses_block), which takes longer than a merge, the others leave at once.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan p, int take_pending) {
     __shared__ float2 mlw[kMaxSplit * 64];       // (m, l) per split and row, then the split's weight l * exp2(m - row maximum) in .x
     static_assert(sizeof(float2) * kMaxSplit * 64 >= sizeof(float) * (kMaxPending + 1) * kWave, "the parts' masses reuse mlw");
-    const int units_x = (int)gridDim.x - take_pending;
-    if (take_pending && (int)blockIdx.x == units_x) {
-        if (blockIdx.y == 0)
+    if (take_pending && blockIdx.y == 0) {
+        if (blockIdx.x == 0)
             pending_masses_block(a, p, __builtin_amdgcn_readfirstlane(blockIdx.z), a.n_pending, 0, reinterpret_cast<float (*)[kWave]>(mlw));
         return;
     }
@@ -37,12 +36,11 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
     // grid (kv head * row groups + row group, channel block + 8 * pass, query): where eight divides the first dimension a unit's workgroups
     // come to one XCD, which reads its statistics once and puts its output lines together (16 units 7.3 -> 6.6 us, 32 units 4.4 -> 4.3)
     const int hq = a.n_q_heads, group = p.group;
-    const int dbq = blockIdx.y & 7;
-    const int pass = (int)(blockIdx.y >> 3);
+    const int y = (int)blockIdx.y - take_pending, dbq = y & 7, pass = y >> 3;
     const int b = blockIdx.z;
     const int hkv = p.n_rg == 1 ? (int)blockIdx.x : (int)div_exact(blockIdx.x, (unsigned)p.n_rg);
     const int rg = (int)blockIdx.x - hkv * p.n_rg;
-    const int unit = b * units_x + (int)blockIdx.x;
+    const int unit = b * p.units_per_b + (int)blockIdx.x;
     const int q0 = a.q_off[b], q1 = a.q_off[b + 1];
     const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * p.rows_wg + pass * 64;
     const uint2* opart = reinterpret_cast<const uint2*>(ws + p.off_opart) + (int64_t)unit * p.nsplit * p.rows_wg * (kD / 4);
@@ -615,7 +613,7 @@ bool pending_fit_combine(const AttnArgs& a, const Plan& p) { return p.slots <= 2
 
 void launch_combine(const AttnArgs& a, const Plan& p, bool take_pending, hipStream_t s) {
     const int extra = take_pending ? 1 : 0;
-    const dim3 grid((unsigned)(a.n_kv_heads * p.n_rg + extra), (unsigned)(8 * p.nrb), (unsigned)a.batch), block(kThreads);
+    const dim3 grid((unsigned)p.units_per_b, (unsigned)(8 * p.nrb + extra), (unsigned)a.batch), block(kThreads);
     if (a.dtype == CF_BF16) hipLaunchKernelGGL((attn_combine_kernel<CF_BF16>), grid, block, 0, s, a, p, extra);
     else hipLaunchKernelGGL((attn_combine_kernel<CF_F16>), grid, block, 0, s, a, p, extra);
 }
