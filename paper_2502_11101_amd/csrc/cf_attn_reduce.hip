@@ -1,134 +1,122 @@
 // What follows the attention kernel of a call on the 16-bit path: the merge of the splits' partial outputs
 // (with the slot partial masses as a by-product), the per-segment mass reduction, and the fused layer epilogue
 // (masses, S += mass, ranking, allocation, next segment table).
+#include <type_traits>
+
 #include "cf_attn_plan.h"
 
 namespace cf {
 using namespace attn;
 namespace {
 
-// Second kernel, where there are several splits: one workgroup per (unit = (query, kv head, row group), 64-row pass, eighth of the output channels) merges the
-// splits' partial outputs and writes its output rows; the eight workgroups of a (unit, pass) also share
-// the reduction, over the pass's 64 rows, of every (segment, split) slot's (max, sum) pairs to
-// sum * exp2(max - row max) / row sum, which the mass kernel then only has to add up.
 __device__ __forceinline__ void pending_masses_block(const AttnArgs& a, const Plan& p, int b, int n_parts, int write_mass,
                                                      float (*m_all)[kWave]);
 
+// Second kernel, where there are several splits: merges the splits' partial outputs, writes the output rows and, with MASS, reduces every
+// (segment, split) slot's (max, sum) pairs over a pass's 64 rows to sum * exp2(max - row max) / row sum, which the mass kernel then only
+// has to add up.  A wavefront owns one (16-row block, 16 channels) of a unit = (query, kv head, row group); the wavefronts of a (unit, pass)
+// share its slots.  At these sizes it is bound by its two dependent round trips (arguments, then one batch of loads), so a wavefront works
+// out the statistics of its rows for itself, from loads of that batch, and there is neither LDS nor a barrier behind them.  With the statistics
+// shared through LDS by a workgroup and three barriers: 32 units x 7 splits x 1 row 4.2 -> 3.3 us (the decode step 11.5 -> 10.6), 32 x 8 x 48
+// rows 4.2 -> 3.5 (32 such layers 674 -> 643), 16 x 16 x 112 rows 6.2 -> 4.9, 128 x 2 x 7 rows 5.6 -> 4.7.
+// NS: splits whose statistics are held in registers.  spread: log2 of the channel blocks of a workgroup (0 for more than two row blocks,
+// 1 for two, 2 for one, as in a decode step), so that no wavefront is left without rows.
 // With take_pending the grid has one more row of workgroups, the first: its first workgroup, per query, takes the ledger's pending
 // score parts in beside the merge (pending_masses_block), which takes longer than a merge, the others leave at once.
-template <int DT>
-__global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan p, int take_pending) {
-    __shared__ float2 mlw[kMaxSplit * 64];       // (m, l) per split and row, then the split's weight l * exp2(m - row maximum) in .x
-    static_assert(sizeof(float2) * kMaxSplit * 64 >= sizeof(float) * (kMaxPending + 1) * kWave, "the parts' masses reuse mlw");
-    if (take_pending && blockIdx.y == 0) {
-        if (blockIdx.x == 0)
-            pending_masses_block(a, p, __builtin_amdgcn_readfirstlane(blockIdx.z), a.n_pending, 0, reinterpret_cast<float (*)[kWave]>(mlw));
-        return;
+template <int DT, int NS, bool MASS>
+__global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan p, int take_pending, int spread) {
+    if constexpr (MASS) {
+        __shared__ float m_all[kMaxPending + 1][kWave];
+        if (take_pending && blockIdx.y == 0) {
+            if (blockIdx.x == 0) pending_masses_block(a, p, __builtin_amdgcn_readfirstlane(blockIdx.z), a.n_pending, 0, m_all);
+            return;
+        }
     }
-    __shared__ float part_stat[kWaves][64], part_sum[kWaves][64];   // per wavefront: its splits' maximum and sum, per row
     constexpr int kPre = 8;                      // splits whose partial outputs are fetched before the statistics are ready
+    constexpr int kSv = 8;                       // slot statistics fetched up front per wavefront
 
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int li = lane & 15, lg = lane >> 4;
     char* ws = static_cast<char*>(a.workspace);
-    // grid (kv head * row groups + row group, channel block + 8 * pass, query): where eight divides the first dimension a unit's workgroups
-    // come to one XCD, which reads its statistics once and puts its output lines together (16 units 7.3 -> 6.6 us, 32 units 4.4 -> 4.3)
-    const int hq = a.n_q_heads, group = p.group;
-    const int y = (int)blockIdx.y - take_pending, dbq = y & 7, pass = y >> 3;
+    // grid (kv head * row groups + row group, channel blocks + their number * pass, query): where eight divides the first dimension a unit's
+    // workgroups come to one XCD, which reads its statistics once and puts its output lines together (16 units 7.3 -> 6.6 us, 32 units 4.4 -> 4.3 before the above)
+    const int y = (int)blockIdx.y - (MASS ? take_pending : 0);
+    const int blk_in = wave & (kWaves - 1) >> spread;                              // row block inside the pass
+    const int dbq = (y & 7 >> spread) << spread | wave >> (2 - spread), pass = y >> (3 - spread);
     const int b = blockIdx.z;
     const int hkv = p.n_rg == 1 ? (int)blockIdx.x : (int)div_exact(blockIdx.x, (unsigned)p.n_rg);
     const int rg = (int)blockIdx.x - hkv * p.n_rg;
     const int unit = b * p.units_per_b + (int)blockIdx.x;
     const int q0 = a.q_off[b], q1 = a.q_off[b + 1];
-    const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * p.rows_wg + pass * 64;
+    // with MASS lane r holds row r of the pass, which the slots are reduced over, else the row of the lane's partial outputs
+    const int row = MASS ? lane : blk_in * 16 + li;
+    const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * p.rows_wg + pass * 64 + row;
     const uint2* opart = reinterpret_cast<const uint2*>(ws + p.off_opart) + (int64_t)unit * p.nsplit * p.rows_wg * (kD / 4);
-    const int blk = pass * kWaves + wave;                      // row block inside the workgroup tile
-    const uint2* src = opart + ((int64_t)blk * 8 + dbq) * kWave + lane;
+    const uint2* src = opart + ((int64_t)(pass * kWaves + blk_in) * 8 + dbq) * kWave + lane;
     auto widen = [](uint2 w) { return f32x4{Mma<DT>::lo(w.x), Mma<DT>::hi(w.x), Mma<DT>::lo(w.y), Mma<DT>::hi(w.y)}; };
     const int64_t split_stride = (int64_t)p.rows_wg / 16 * 8 * kWave;
     const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + (int64_t)unit * p.slots * p.rows_wg + pass * 64 + lane;
-    const int k_first = dbq * kWaves + wave, k_step = kWaves * 8;
-    constexpr int kSv = 8;                           // slot statistics fetched up front per wavefront
+    const int k_first = dbq * (kWaves >> spread) + blk_in, k_step = 8 * kWaves >> spread;
 
-    // Everything this workgroup reads is requested up front — row statistics, partial outputs of the first splits,
+    // Everything this wavefront reads is requested up front — row statistics, partial outputs of the first splits,
     // the first slot statistics — so the round trips to memory overlap.  Every load is unconditional (a clamped,
     // in-bounds address; what lies past the end is dropped afterwards): a load inside a branch makes the compiler
     // wait for it before the branch ends, which would put the round trips one behind the other.
     // (A wavefront whose 16 rows are all padding reads what an earlier call left there: never stored; not waiting for
     // the query's length here saves a round trip.)
-    constexpr int kMl = kMaxSplit * 64 / kThreads;   // (m, l) pairs per thread
-    const int n_ml = p.nsplit * 64;
-    float2 ml_regs[kMl];
+    float2 st[NS];
 #pragma unroll
-    for (int i = 0; i < kMl; ++i) {
-        const int idx = min(tid + i * kThreads, n_ml - 1);
-        ml_regs[i] = ml[(idx >> 6) * p.rows_wg + (idx & 63)];
-    }
+    for (int s = 0; s < NS; ++s) st[s] = ml[(int64_t)min(s, p.nsplit - 1) * p.rows_wg];
     uint2 pre[kPre];
 #pragma unroll
     for (int s = 0; s < kPre; ++s) pre[s] = src[min(s, p.nsplit - 1) * split_stride];
     float2 sv[kSv];
+    if constexpr (MASS) {
 #pragma unroll
-    for (int j = 0; j < kSv; ++j) sv[j] = massml[(int64_t)min(k_first + j * k_step, p.slots - 1) * p.rows_wg];
-#pragma unroll
-    for (int i = 0; i < kMl; ++i)
-        if (tid + i * kThreads < n_ml) mlw[tid + i * kThreads] = ml_regs[i];
+        for (int j = 0; j < kSv; ++j) sv[j] = massml[(int64_t)min(k_first + j * k_step, p.slots - 1) * p.rows_wg];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const int tq = min(q1 - q0, a.max_tq);
-    const int n_rows = group * tq;
+    const int n_rows = p.group * tq;
     const int row_base = rg * p.blocks_rg * 16;
     const int rows_here = min(p.blocks_rg * 16, n_rows - row_base);
-    const bool blk_has_rows = pass * 64 + wave * 16 < rows_here;
-    __syncthreads();
-    // Row statistics by the whole workgroup: wavefront w takes the splits w, w + 4, ... of every row, the four
-    // partial maxima and then the four partial sums (added in a fixed order) meet in LDS.  A split's weight stays
-    // unnormalised in LDS; the rows are divided by their sum once at the end.
-    {
-        float m = -INFINITY;
-        for (int s = wave; s < p.nsplit; s += kWaves) m = fmaxf(m, mlw[s * 64 + lane].x);
-        part_stat[wave][lane] = m;
+    // A row's maximum, and its sum in four interleaved parts; a split's weight stays unnormalised (its rows arrive divided by their own
+    // sum), the rows are divided by their sum once at the end.
+    float m = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) m = fmaxf(m, st[s].x);
+    m = m == -INFINITY ? 0.f : m;
+    float z4[4] = {0.f, 0.f, 0.f, 0.f}, weight[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        weight[s] = s < p.nsplit ? st[s].y * exp2f(st[s].x - m) : 0.f;
+        z4[s & 3] += weight[s];
     }
-    __syncthreads();
-    auto row_max = [&](int row) {
-        const float m = fmaxf(fmaxf(part_stat[0][row], part_stat[1][row]), fmaxf(part_stat[2][row], part_stat[3][row]));
-        return m == -INFINITY ? 0.f : m;
-    };
-    {
-        const float ms = row_max(lane);
-        float z = 0.f;
-        for (int s = wave; s < p.nsplit; s += kWaves) {
-            const float2 v = mlw[s * 64 + lane];
-            const float e = exp2f(v.x - ms);
-            z += v.y * e;
-            mlw[s * 64 + lane].x = v.y * e;          // the split's rows arrive divided by their own sum
-        }
-        part_sum[wave][lane] = z;
-    }
-    __syncthreads();
-    auto row_inv_sum = [&](int row) {
-        const float z = ((part_sum[0][row] + part_sum[1][row]) + part_sum[2][row]) + part_sum[3][row];
-        return z > 0.f ? 1.f / z : 0.f;
-    };
+    const float z = ((z4[0] + z4[1]) + z4[2]) + z4[3];
+    const float inv = z > 0.f ? 1.f / z : 0.f;
+    auto of_block = [&](float x) { return MASS ? __shfl(x, blk_in * 16 + li) : x; };
     f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < kPre; ++s)
-        if (s < p.nsplit) o += widen(pre[s]) * mlw[s * 64 + wave * 16 + li].x;
-    if (blk_has_rows)
-        for (int s0 = kPre; s0 < p.nsplit; s0 += kPre) {         // further splits, eight loads at a time
-            uint2 more[kPre];
+    for (int s0 = 0; s0 < NS; s0 += kPre) {
+        if (s0 >= p.nsplit) break;
+        if (s0 > 0) {                                // further splits, eight loads at a time (unconditional, as above)
 #pragma unroll
-            for (int i = 0; i < kPre; ++i) more[i] = src[min(s0 + i, p.nsplit - 1) * split_stride];      // unconditional, as above
-#pragma unroll
-            for (int i = 0; i < kPre; ++i)
-                if (s0 + i < p.nsplit) o += widen(more[i]) * mlw[(s0 + i) * 64 + wave * 16 + li].x;
+            for (int i = 0; i < kPre; ++i) pre[i] = src[min(s0 + i, p.nsplit - 1) * split_stride];
         }
-    const int lrow = pass * 64 + wave * 16 + li;
-    o *= row_inv_sum(wave * 16 + li);
+        float w[kPre];
+#pragma unroll
+        for (int i = 0; i < kPre; ++i) w[i] = of_block(weight[s0 + i]);
+#pragma unroll
+        for (int i = 0; i < kPre; ++i)
+            if (s0 + i < p.nsplit) o += widen(pre[i]) * w[i];
+    }
+    o *= of_block(inv);
+    const int lrow = pass * 64 + blk_in * 16 + li;
     if (lrow < rows_here) {
         const int m2 = row_base + lrow;
         const int gi = (int)div_exact((unsigned)m2, (unsigned)tq), t = m2 - gi * tq;
-        uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)q0 + t) * hq + hkv * group + gi) * kD + 16 * dbq + 4 * lg;
+        uint16_t* op = static_cast<uint16_t*>(a.out) + (((int64_t)q0 + t) * a.n_q_heads + hkv * p.group + gi) * kD + 16 * dbq + 4 * lg;
         uint2 pk;
         pk.x = Mma<DT>::pack(o[0], o[1]);
         pk.y = Mma<DT>::pack(o[2], o[3]);
@@ -136,11 +124,11 @@ __global__ __launch_bounds__(kThreads) void attn_combine_kernel(AttnArgs a, Plan
     }
     // slot partials: slot k = segment + split; slots no split wrote this call hold stale pairs and
     // give meaningless numbers that the mass kernel never reads
-    if (a.mass != nullptr) {
+    if constexpr (MASS) {
         float* masspart = reinterpret_cast<float*>(ws + p.off_masspart + (size_t)a.n_pending * p.masspart_bytes) + ((int64_t)unit * p.nrb + pass) * p.slots;
-        const float2 st = make_float2(row_max(lane), pass * 64 + lane < rows_here ? row_inv_sum(lane) : 0.f);   // padding rows carry no mass
+        const float2 stat = make_float2(m, pass * 64 + lane < rows_here ? inv : 0.f);   // padding rows carry no mass
         auto reduce = [&](int k, float2 v) {
-            const float c = wave_sum_dpp(st.y > 0.f ? v.y * exp2f(v.x - st.x) * st.y : 0.f);
+            const float c = wave_sum_dpp(stat.y > 0.f ? v.y * exp2f(v.x - stat.x) * stat.y : 0.f);
             if (lane == 0 && k < p.slots) masspart[k] = c;
         };
 #pragma unroll
@@ -611,11 +599,24 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
 
 bool pending_fit_combine(const AttnArgs& a, const Plan& p) { return p.slots <= 2 * kWave && a.seg_stride <= kWave; }
 
+template <int DT, int NS>
+static void launch_combine_ns(const AttnArgs& a, const Plan& p, int extra, hipStream_t s) {
+    const int spread = p.nrb > 1 || p.blocks_rg > 2 ? 0 : p.blocks_rg == 2 ? 1 : 2;
+    const dim3 grid((unsigned)p.units_per_b, (unsigned)((8 >> spread) * p.nrb + extra), (unsigned)a.batch), block(kThreads);
+    if (a.mass != nullptr) hipLaunchKernelGGL((attn_combine_kernel<DT, NS, true>), grid, block, 0, s, a, p, extra, spread);
+    else hipLaunchKernelGGL((attn_combine_kernel<DT, NS, false>), grid, block, 0, s, a, p, extra, spread);
+}
+
 void launch_combine(const AttnArgs& a, const Plan& p, bool take_pending, hipStream_t s) {
     const int extra = take_pending ? 1 : 0;
-    const dim3 grid((unsigned)p.units_per_b, (unsigned)(8 * p.nrb + extra), (unsigned)a.batch), block(kThreads);
-    if (a.dtype == CF_BF16) hipLaunchKernelGGL((attn_combine_kernel<CF_BF16>), grid, block, 0, s, a, p, extra);
-    else hipLaunchKernelGGL((attn_combine_kernel<CF_F16>), grid, block, 0, s, a, p, extra);
+    auto by_splits = [&](auto dt) {
+        constexpr int DT = decltype(dt)::value;
+        if (p.nsplit <= 8) launch_combine_ns<DT, 8>(a, p, extra, s);
+        else if (p.nsplit <= 16) launch_combine_ns<DT, 16>(a, p, extra, s);
+        else launch_combine_ns<DT, kMaxSplit>(a, p, extra, s);
+    };
+    if (a.dtype == CF_BF16) by_splits(std::integral_constant<int, CF_BF16>{});
+    else by_splits(std::integral_constant<int, CF_F16>{});
 }
 
 // several parts of a small query: one wavefront per part (see pending_masses_kernel); else one part after the other

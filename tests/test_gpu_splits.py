@@ -8,6 +8,7 @@ import torch
 from paper_2502_11101_amd import workloads as wl
 from tests import gpu_harness as G
 from tests import helpers as H
+from tests import plan_probe
 from tests.test_gpu_parity import _run_single_layer
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +56,12 @@ def test_two_halves_of_a_long_batch(batch, hkv, even):
         assert G.row_error(out_np[b:b + 1], ref) <= G.OUT_TOL["bf16"]
         assert G.rel_error(mass[b, :len(segs)], near) <= G.NEAR_MASS_TOL["bf16"]
         assert mass[b, :len(segs)].sum() == pytest.approx(hkv, rel=1e-5)
+
+
+@pytest.mark.parametrize("tokens,nsplit", [(1000, 8), (1120, 9), (2016, 16), (2130, 17), (4200, 32)])
+@pytest.mark.parametrize("rows", [16, 17, 32, 33, 64])     # one, two, three and four row blocks: 4, 2 and 1 channel blocks a merging workgroup
+def test_merge_of_splits(rows, tokens, nsplit):
+    """Every split count on either side of what the merge kernel holds at a time, with masses and without."""
+    print(f"merge rows={rows} splits={nsplit}", flush=True)
+    assert plan_probe.plan(1, 1, 1, rows, 2, tokens + rows).nsplit == nsplit
+    G.check_tables(1, 1, rows, [[(0, tokens, 0, 300)]], tokens, "bf16" if rows & 1 else "f16", 500, seed=rows + nsplit)
