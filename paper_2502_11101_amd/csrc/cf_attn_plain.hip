@@ -20,7 +20,7 @@
 //
 // Bound by the latency of a launch's memory round trips at the sizes measured: bf16, interleaved pairs, 32 heads, 10 documents of 100-200
 // tokens, 48 query rows: 17.2 us for 26.7 MB of keys, values, queries and outputs, the wavefronts waiting 56 % of their cycles, matrix
-// pipe busy 13 %, VALU issue 33 %; the merge 8.4 us.  Whole layer calls with a prune event, from the row-by-row kernel of
+// pipe busy 13 %, VALU issue 33 %; the merge 5.7 us.  Whole layer calls with a prune event, from the row-by-row kernel of
 // cf_attn_generic.hip to this one: 916 -> 31.8 us (31.0 before non-finite rows were gone over again); fp32, head_dim 64, 4 heads,
 // 4 x 32 tokens, 8 rows: 54 -> 18.2 us (17.9).  fp16 at the first one's shape takes 5 % more than bf16.
 #include "cf_attn_plan.h"
@@ -143,6 +143,10 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
     const int n_pairs = d / (2 * S::kPerChunk);              // chunk pairs of a row: chunks j and j + n_pairs
     const bool reg_table = a.seg_stride <= kWave;
     const QueryHead qh = load_query_head(a, b, reg_table ? lane : (int)threadIdx.x);
+    // requested with the table: read where a segment begins, each segment waited a round trip more for it (4 x 32 tokens x 4 heads in
+    // fp32 12.8 -> 12.2 us, 10 documents x 32 heads 18.1 -> 17.1)
+    static_assert(DP / 2 <= kGroupThreads, "a thread has at most one slice");
+    const double my_freq = freq.rev[min(tid, DP / 2 - 1)];
     const int tq = min(qh.tq_raw, a.max_tq);
     const int row_base = rg * p.blocks_rg * 16;
     const int row_limit = min(group * tq, row_base + p.blocks_rg * 16);
@@ -214,7 +218,7 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
         }
     };
     auto make_angles = [&](const Tile& t, int slot) __attribute__((always_inline)) {
-        for (int m = tid; m < d / 2; m += kGroupThreads) cs_lds[grp][slot][m] = rope_cos_sin(t.delta, freq.rev[m]);
+        if (tid < d / 2) cs_lds[grp][slot][tid] = rope_cos_sin(t.delta, my_freq);
     };
 
     // running state: O^T (channel 16*db + 4*lg + r of row li), softmax reference, sums over the lane's own tokens
@@ -605,84 +609,106 @@ __global__ __launch_bounds__(kThreads, plain_per_cu(DT == CF_F32, DP, RB)) void 
     }
 }
 
-// Merges the splits' partial rows and writes the output rows; reduces the slots to the unit's partial masses.  One wavefront per
-// (row block, 16 channels) of a unit; grid (sets of four, unit of the query, query).  Latency-bound.
-template <int DT>
+// Merges the splits' partial rows and writes the output rows; with MASS reduces the slots to the unit's partial masses.  One wavefront per
+// (row block, 16 channels) of a unit; grid (unit of the query, sets of four wavefronts, query), so that a unit's workgroups share an XCD where
+// eight divides the units.  Bound by its two dependent round trips (arguments, one batch of loads): each wavefront works its rows' statistics
+// out for itself and shares nothing.  NS: splits whose statistics are held in registers.  blocks: log2 of the channel blocks.
+// With the statistics worked out by one thread per row out of LDS behind two barriers: 32 units x 16 splits x 48 rows 8.3 -> 5.7 us.
+template <int DT, int NS, bool MASS>
 __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Plan p, int blocks) {
-    __shared__ float2 mlw[kMaxSplit * 64];                   // (m, l) per split and row, then the split's weight in .x
-    __shared__ float2 stat[64];                              // row maximum, row sum (0: no such row)
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int li = lane & 15, lg = lane >> 4;
-    const int b = blockIdx.z, unit = b * p.units_per_b + (int)blockIdx.y;
-    const int hkv = p.n_rg == 1 ? (int)blockIdx.y : (int)div_exact(blockIdx.y, (unsigned)p.n_rg);
-    const int rg = (int)blockIdx.y - hkv * p.n_rg;
+    const int b = blockIdx.z, unit = b * p.units_per_b + (int)blockIdx.x;
+    const int hkv = p.n_rg == 1 ? (int)blockIdx.x : (int)div_exact(blockIdx.x, (unsigned)p.n_rg);
+    const int rg = (int)blockIdx.x - hkv * p.n_rg;
     const int rows = p.rows_wg, rbs = rows / 16;
+    const int item = blockIdx.y * kWaves + wave;             // row block, channel block (at least four channel blocks: no wavefront is left over)
+    const int rb = item >> blocks, db = item - (rb << blocks);
     char* ws = static_cast<char*>(a.workspace);
-    const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * rows;
-    const f32x4* opart = reinterpret_cast<const f32x4*>(ws + p.off_opart) + (int64_t)unit * p.nsplit * rbs * blocks * kWave;
-
-    const int item = blockIdx.x * kWaves + wave;             // row block, channel block
-    const bool item_ok = item < rbs * blocks;
-    const int rb = item_ok ? item / blocks : 0, db = item_ok ? item - rb * blocks : 0;
+    // with MASS lane r holds row r of the unit, which the slots are reduced over, else the row of the lane's partial outputs
+    const int row = MASS ? min(lane, rows - 1) : rb * 16 + li;
+    const float2* ml = reinterpret_cast<const float2*>(ws + p.off_ml) + (int64_t)unit * p.nsplit * rows + row;
+    const f32x4* src = reinterpret_cast<const f32x4*>(ws + p.off_opart) + ((((int64_t)unit * p.nsplit * rbs + rb) << blocks) + db) * kWave + lane;
+    const int64_t stride = (int64_t)(rbs << blocks) * kWave;
     const int q0 = a.q_off[b], q1 = a.q_off[b + 1];
-    // rows of idle wavefronts are read (what an earlier call left there) and dropped
-    constexpr int kPre = 16;
+    const int row_base = rg * p.blocks_rg * 16;
+    const int rows_kv = p.group * a.max_tq;
+    const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + ((int64_t)b * a.n_kv_heads + hkv) * p.slots * rows_kv + row_base +
+                           min(lane, rows_kv - row_base - 1);
+    const int k_step = (int)gridDim.y * kWaves;
+    // one batch of unconditional loads: rows without a query are read (what an earlier call left there) and dropped
+    float2 st[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) st[s] = ml[(int64_t)min(s, p.nsplit - 1) * rows];
+    constexpr int kPre = NS == 16 ? 16 : 8;
     f32x4 pre[kPre];
-    const f32x4* src = opart + ((int64_t)rb * blocks + db) * kWave + lane;
-    const int64_t stride = (int64_t)rbs * blocks * kWave;
 #pragma unroll
     for (int s = 0; s < kPre; ++s) pre[s] = src[min(s, p.nsplit - 1) * stride];
-    for (int i = tid; i < p.nsplit * rows; i += kThreads) mlw[i] = ml[i];
-    const int tq = min(q1 - q0, a.max_tq);
-    const int row_base = rg * p.blocks_rg * 16;
-    const int rows_here = min(p.blocks_rg * 16, p.group * tq - row_base);
-    __syncthreads();
-    if (tid < rows) {
-        float m = -INFINITY;
-        for (int s = 0; s < p.nsplit; ++s) m = fmaxf(m, mlw[s * rows + tid].x);
-        m = m == -INFINITY ? 0.f : m;
-        float z = 0.f;
-        for (int s = 0; s < p.nsplit; ++s) {
-            const float2 v = mlw[s * rows + tid];
-            const float w = v.y * exp2f(v.x - m);
-            mlw[s * rows + tid].x = w;
-            z += w;
-        }
-        stat[tid] = make_float2(m, tid < rows_here ? z : 0.f);
-    }
-    __syncthreads();
-    if (item_ok) {
-        const int row = rb * 16 + li;
-        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int kSv = 4;
+    float2 sv[kSv];
+    if constexpr (MASS) {
 #pragma unroll
-        for (int s = 0; s < kPre; ++s)
-            if (s < p.nsplit) o += pre[s] * mlw[s * rows + row].x;
-        for (int s = kPre; s < p.nsplit; ++s) o += src[s * stride] * mlw[s * rows + row].x;
-        const float z = stat[row].y;
-        o *= z > 0.f ? 1.f / z : 0.f;
-        if (row < rows_here && 16 * db < a.head_dim) {
-            const int m2 = row_base + row;
-            const int gi = (int)div_exact((unsigned)m2, (unsigned)tq), t = m2 - gi * tq;
-            using E = Elem<DT>;
-            typename E::type* op = static_cast<typename E::type*>(a.out) +
-                                   (((int64_t)q0 + t) * a.n_q_heads + hkv * p.group + gi) * a.head_dim + 16 * db + 4 * lg;
-            if constexpr (DT == CF_F32) {
-                *reinterpret_cast<f32x4*>(op) = o;
-            } else {
-                *reinterpret_cast<uint2*>(op) = make_uint2(Mma<DT>::pack(o[0], o[1]), Mma<DT>::pack(o[2], o[3]));
-            }
+        for (int j = 0; j < kSv; ++j) sv[j] = massml[(int64_t)min(item + j * k_step, p.slots - 1) * rows_kv];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int tq = min(q1 - q0, a.max_tq);
+    const int rows_here = min(p.blocks_rg * 16, p.group * tq - row_base);
+    float m = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) m = fmaxf(m, st[s].x);
+    m = m == -INFINITY ? 0.f : m;
+    float z = 0.f, weight[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        weight[s] = s < p.nsplit ? st[s].y * exp2f(st[s].x - m) : 0.f;
+        z += weight[s];
+    }
+    auto of_block = [&](float x) { return MASS ? __shfl(x, (rb * 16 + li) & (kWave - 1)) : x; };
+    f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+    int n_splits = p.nsplit;
+#ifdef __OPTIMIZE__
+    asm volatile("" : "+s"(n_splits));                       // (the comparisons above are not kept for those below: 32 pairs of scalar registers)
+#endif
+#pragma unroll
+    for (int s0 = 0; s0 < NS; s0 += kPre) {
+        if (s0 >= n_splits) break;
+        if (s0 > 0) {
+#pragma unroll
+            for (int i = 0; i < kPre; ++i) pre[i] = src[min(s0 + i, p.nsplit - 1) * stride];
+        }
+        float w[kPre];
+#pragma unroll
+        for (int i = 0; i < kPre; ++i) w[i] = of_block(weight[s0 + i]);
+#pragma unroll
+        for (int i = 0; i < kPre; ++i)
+            if (s0 + i < n_splits) o += pre[i] * w[i];
+    }
+    const float z_row = of_block(z);
+    o *= z_row > 0.f ? 1.f / z_row : 0.f;
+    const int lrow = rb * 16 + li;
+    if (lrow < rows_here && 16 * db < a.head_dim) {
+        const int m2 = row_base + lrow;
+        const int gi = (int)div_exact((unsigned)m2, (unsigned)tq), t = m2 - gi * tq;
+        using E = Elem<DT>;
+        typename E::type* op = static_cast<typename E::type*>(a.out) +
+                               (((int64_t)q0 + t) * a.n_q_heads + hkv * p.group + gi) * a.head_dim + 16 * db + 4 * lg;
+        if constexpr (DT == CF_F32) {
+            *reinterpret_cast<f32x4*>(op) = o;
+        } else {
+            *reinterpret_cast<uint2*>(op) = make_uint2(Mma<DT>::pack(o[0], o[1]), Mma<DT>::pack(o[2], o[3]));
         }
     }
-    if (a.mass != nullptr) {
+    if constexpr (MASS) {
         double* part = reinterpret_cast<double*>(ws + p.off_masspart) + (int64_t)unit * p.slots;
-        const int rows_kv = p.group * a.max_tq;
-        const float2* massml = reinterpret_cast<const float2*>(ws + p.off_massml) + ((int64_t)b * a.n_kv_heads + hkv) * p.slots * rows_kv + row_base;
-        const float2 st = lane < rows ? stat[lane] : make_float2(0.f, 0.f);
-        for (int k = item; k < p.slots; k += (int)gridDim.x * kWaves) {
-            const float2 v = lane < rows_here ? massml[(int64_t)k * rows_kv + lane] : make_float2(0.f, 0.f);
-            const double c = wave_sum_f64(slot_share(v, st));
-            if (lane == 0) part[k] = c;
-        }
+        const float2 stat = make_float2(m, lane < rows_here ? z : 0.f);      // (slot_share: a row sum of 0 is no such row)
+        auto reduce = [&](int k, float2 v) {
+            const double c = wave_sum_f64(slot_share(v, stat));
+            if (lane == 0 && k < p.slots) part[k] = c;
+        };
+#pragma unroll
+        for (int j = 0; j < kSv; ++j)
+            if (item + j * k_step < p.slots) reduce(item + j * k_step, sv[j]);
+        for (int k = item + kSv * k_step; k < p.slots; k += k_step) reduce(k, massml[(int64_t)k * rows_kv]);
     }
 }
 
@@ -744,9 +770,15 @@ void launch_plain(const AttnArgs& a, const RopeFreq& f, const Plan& p, hipStream
 #undef CF_PLAIN_D
 #undef CF_PLAIN
     if (p.direct_out) return;
-    const int blocks = padded_dim(a.head_dim) / 16, items = p.rows_wg / 16 * blocks;
-    const dim3 cgrid((unsigned)((items + kWaves - 1) / kWaves), (unsigned)p.units_per_b, (unsigned)a.batch);
-    hipLaunchKernelGGL((plain_combine_kernel<DT>), cgrid, block, 0, s, a, p, blocks);
+    const int blocks = padded_dim(a.head_dim) / 16;
+    const dim3 cgrid((unsigned)p.units_per_b, (unsigned)(p.rows_wg / 16 * blocks / kWaves), (unsigned)a.batch);
+#define CF_COMBINE(NS)                                                                                                          \
+    if (a.mass != nullptr) hipLaunchKernelGGL((plain_combine_kernel<DT, NS, true>), cgrid, block, 0, s, a, p, __builtin_ctz(blocks)); \
+    else hipLaunchKernelGGL((plain_combine_kernel<DT, NS, false>), cgrid, block, 0, s, a, p, __builtin_ctz(blocks))
+    if (p.nsplit <= 8) { CF_COMBINE(8); }
+    else if (p.nsplit <= 16) { CF_COMBINE(16); }
+    else { CF_COMBINE(kMaxSplit); }
+#undef CF_COMBINE
 }
 
 }  // namespace

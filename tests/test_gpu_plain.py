@@ -60,3 +60,23 @@ def test_plain_path_query_at_the_top_of_the_fp16_range():
     assert pb.flags() == 0
     assert G.row_error(out.float().cpu().numpy(), ref_out) <= 2e-3
     assert G.rel_error(pb.mass.cpu().numpy()[0, :len(segs)], ref_mass) <= 1e-4
+
+
+@pytest.mark.parametrize("tokens", [700, 2000])
+@pytest.mark.parametrize("tq", [16, 20, 40])           # one, two and four row blocks: up to 8, 16 and 32 splits to merge
+@pytest.mark.parametrize("dtype,pairing,d", [("f32", HALF, 64), ("f32", HALF, 80), ("bf16", INTER, 128), ("f16", HALF, 144)])
+def test_merge_of_splits(dtype, pairing, d, tq, tokens):
+    """The merge with masses against the oracle, and without them: the same outputs, bit for bit."""
+    cfg = _cfg(f"plain_merge_{d}_{tq}_{tokens}", wl.Geometry(2, 2, d, dtype, 1.0e4, 8192), 3, (tokens // 3 - 9, tokens // 3), 1, tq, 5)
+    _run_single_layer(cfg, pairing, seed=d + tq, layout="head")
+    st = wl.build_structure(cfg, seed=d)
+    pb, dev = G.make_batch(cfg, st, pairing), G.upload_layer(cfg, wl.build_layer(cfg, st, seed=tq))
+    pb.allocate_initial()
+    out, again = torch.empty_like(dev["q"]), torch.empty_like(dev["q"])
+    pb.attention(dev["q"], dev["k_self"], dev["v_self"], dev["k_store"], dev["v_store"], out)
+    pb.workspace.fill_(0xFF)
+    cf.cf_prefill_attention(pb.desc, dev["q"], pb.q_off, pb.q_stored_start, pb.q_start, dev["k_store"], dev["v_store"], st.n_store_tokens,
+                            dev["k_self"], dev["v_self"], pb.segs, pb.n_seg, pb.seg_stride, 1, tq, pb.max_kv_tokens, again, None, None, 1,
+                            pb.workspace, pb.ws_bytes, pb.dev_flag)
+    torch.cuda.synchronize()
+    assert pb.flags() == 0 and torch.isfinite(again).all() and torch.equal(out, again)
