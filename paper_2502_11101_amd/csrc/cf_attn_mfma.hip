@@ -503,8 +503,18 @@ __device__ __forceinline__ float add_lane_groups(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-template <int DT, int NRB, int GROUPS, bool REG_TABLE>
+// CAUSAL: for calls whose own block is most of the list (documents encoded offline), in one split: half of the block's scores are masked.
+// The stacked rows are numbered t * group + head, so that a 16-row block sees the own block up to its own last token; a row group ends its
+// list there, and a wavefront leaves out the row blocks that see nothing more of it.  Its blocks are every fourth one of the row group (in the
+// order of the rows, the missing ones of a group that is not full ahead of all), so that the blocks left out are its first `r0` and the wavefronts
+// have equal shares.  The loop exists once for every r0.
+// Documents encoded and stored, us without and with it (in brackets: row groups in the order of their rows, not the longest lists first): 30 of
+// 160 tokens x 32 heads 76.1 and 73.9, 12 of 300 72.1 and 59.8 (67.1); 28 heads over 4, 30 of 160-250 70.6 and 49.8 (56.1), 100 of 100-200 157
+// and 120 (128); 12 over 2, 200 of 150-300 215 and 147 (156).  At 160 tokens a workgroup's prologue and the 4 * 39 MB it reads and writes are
+// most of its time.
+template <int DT, int NRB, int GROUPS, bool REG_TABLE, bool CAUSAL = false>
 __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArgs a, RopeFreq freq, Plan p) {
+    static_assert(!CAUSAL || (GROUPS == 1 && REG_TABLE), "one split, one group");
     __shared__ SegTable tbl;
     __shared__ double freq_lds[kHalf];
     __shared__ int4 seg_lds[2 * kWave];
@@ -527,18 +537,36 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     // one XCD where eight divides the first dimension
     const int split = p.nsplit == 1 ? 0 : (int)div_exact(blockIdx.x, (unsigned)a.batch);
     const int b = (int)blockIdx.x - split * a.batch;
-    const int hkv = p.n_rg == 1 ? (int)blockIdx.y : (int)div_exact(blockIdx.y, (unsigned)p.n_rg);
-    const int rg = (int)blockIdx.y - hkv * p.n_rg;
-    const int unit = b * p.units_per_b + (int)blockIdx.y;
+    // (CAUSAL: the last row groups, which have the longest lists, first)
+    const int by_rg = CAUSAL && p.n_rg > 1 ? (int)div_exact(blockIdx.y, (unsigned)a.n_kv_heads) : 0;
+    const int hkv = p.n_rg == 1 ? (int)blockIdx.y : CAUSAL ? (int)blockIdx.y - by_rg * a.n_kv_heads : (int)div_exact(blockIdx.y, (unsigned)p.n_rg);
+    const int rg = CAUSAL ? p.n_rg - 1 - by_rg : (int)blockIdx.y - hkv * p.n_rg;
+    const int unit = b * p.units_per_b + hkv * p.n_rg + rg;
     const int group = p.group;
     const QueryHead qh = load_query_head(a, b, REG_TABLE ? lane : (int)threadIdx.x);
     if (wave == 0 && grp == 0) freq_lds[lane] = freq.rev[lane];
     const int tq = min(qh.tq_raw, a.max_tq);
     const int row_base = rg * p.blocks_rg * 16;
     const int row_limit = min(group * tq, row_base + p.blocks_rg * 16);
-    const bool has_rows = row_base + wave * NRB * 16 < row_limit;        // wavefront-uniform
+    // the wavefront's block rb: number blk(rb) of the workgroup's, rows row_base + 16 * (blk(rb) - missing) ...
+    auto blk = [&](int rb) { return CAUSAL ? rb * kWaves + wave : wave * NRB + rb; };
+    const int missing = CAUSAL ? kWaves * NRB - max(0, (row_limit - row_base + 15) / 16) : 0;
+    const bool has_rows = CAUSAL ? blk(NRB - 1) >= missing : row_base + wave * NRB * 16 < row_limit;        // wavefront-uniform
+    int t_last[NRB];                                 // CAUSAL: the block's last row's place in the own block, -1 without rows
     uint4 qf[NRB][4];
-    {
+    if constexpr (CAUSAL) {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            const int m = row_base + (blk(rb) - missing) * 16 + li;
+            const bool valid = blk(rb) >= missing && m < row_limit;
+            const int t = valid ? (int)div_exact((unsigned)m, (unsigned)group) : 0, gi = valid ? m - t * group : 0;
+            const uint16_t* qp = static_cast<const uint16_t*>(a.q) + (((int64_t)qh.q0 + t) * a.n_q_heads + hkv * group + gi) * kD + 8 * lg;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) qf[rb][kk] = valid ? *reinterpret_cast<const uint4*>(qp + 32 * kk) : make_uint4(0, 0, 0, 0);
+            t_last[rb] = __builtin_amdgcn_readfirstlane(
+                blk(rb) < missing ? -1 : (int)div_exact((unsigned)min(row_base + (blk(rb) - missing) * 16 + 15, row_limit - 1), (unsigned)group));
+        }
+    } else {
         int trow[NRB];
         load_q_fragments<NRB>(a, qh.q0, tq, hkv, group, wave * NRB, row_base, row_limit, li, lg, qf, trow);
     }
@@ -554,6 +582,18 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     } else {
         build_table(a, qh, &tbl, kTile);
         total = (unsigned)tbl.tile0[tbl.n];
+    }
+    int own_seg = -1;                                // CAUSAL: the own block, if the list ends with it
+    if constexpr (CAUSAL) {
+        if (row_limit <= row_base) {
+            total = 0;
+        } else if (total > 0) {
+            const FoundSegment f = find_segment(rtbl, (int)total - 1, lane, -1);
+            if (f.self) {
+                own_seg = f.seg;
+                total = min(total, (unsigned)f.first + div_exact((unsigned)(row_limit - 1), (unsigned)group) / kTile + 1);
+            }
+        }
     }
     const unsigned nsub = (unsigned)(p.nsplit * GROUPS);
     const int ss = split * GROUPS + grp;
@@ -572,7 +612,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     uint32_t row_bytes = 0, koff = 0, voff = 0;
     const LdsSegs lsegs{seg_lds, rtbl.n};
     // the next tile's segment, if it starts one, and the segment's cos/sin table
-    auto next_segment = [&](auto in_loop) {
+    auto next_segment = [&](auto in_loop) __attribute__((always_inline)) {
         if (w_next >= w_end || w_left > 0) return;
         FoundSegment f;
         if constexpr (!REG_TABLE) f = find_segment(tbl, w_next, lane_anew(), w.seg);
@@ -602,7 +642,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         }
     };
     // requests the next tile (d, its table's slot) into r and steps over it
-    auto fetch = [&](Tile& d, int& slot, StageRegs& r) {
+    auto fetch = [&](Tile& d, int& slot, StageRegs& r) __attribute__((always_inline)) {
         d = w;
         d.ntok = w_next < w_end ? min(w_left, kTile) : 0;
         slot = w_slot;
@@ -615,7 +655,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         r.v[0] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff, 0, 0));
         r.v[1] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff + 16 * row_bytes, 0, 0));
     };
-    auto advance = [&]() {
+    auto advance = [&]() __attribute__((always_inline)) {
         ++w_next;
         w.tok0 += kTile;
         w_left -= kTile;
@@ -624,7 +664,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     };
     unsigned char* const k_write = k_lds + kr * kKRow + 16 * kj;
     unsigned char* const v_write = v_lds + vr * kWideVRow + 16 * vc;
-    auto stage = [&](int delta, const StageRegs& r, int slot, int kbuf, int vbuf) {
+    auto stage = [&](int delta, const StageRegs& r, int slot, int kbuf, int vbuf) __attribute__((always_inline)) {
         uint4 ra = r.ka, rb4 = r.kb;
         rotate_chunk_pair<DT>(ra, rb4, load_chunk_angles(cs_lds[grp][slot] + 8 * kj));
         const bool still = delta == 0;               // bit-exact, and no branch where the matrix instructions run
@@ -662,7 +702,7 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     f32x4 sc[NRB][2];                                // its scores
     uint4 pfrag[NRB];                                // its probabilities
 
-    auto read_v = [&](int vbuf, int db0, int db1) {
+    auto read_v = [&](int vbuf, int db0, int db1) __attribute__((always_inline)) {
 #pragma unroll
         for (int db = db0; db < db1; ++db) {
             const unsigned char* src = v_read + vbuf + 32 * db;
@@ -670,61 +710,68 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
             vhi[db] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)(src + 16 * kWideVRow));
         }
     };
-    auto weigh = [&]() {
+    auto weigh = [&](auto first) __attribute__((always_inline)) {
 #pragma unroll
         for (int db = 0; db < 8; ++db) {
             const uint2 l2 = __builtin_bit_cast(uint2, vlo[db]), h2v = __builtin_bit_cast(uint2, vhi[db]);
             const uint4 va = make_uint4(l2.x, l2.y, h2v.x, h2v.y);
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) st.acc[rb][db] = Mma<DT>::run(va, pfrag[rb], st.acc[rb][db]);
+            for (int rb = decltype(first)::value; rb < NRB; ++rb) st.acc[rb][db] = Mma<DT>::run(va, pfrag[rb], st.acc[rb][db]);
         }
     };
     uint4 kf[2][4];
-    auto read_k = [&](int kbuf, int kk) {
+    auto read_k = [&](int kbuf, int kk) __attribute__((always_inline)) {
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb) kf[tb][kk] = *reinterpret_cast<const uint4*>(k_read + kbuf + 16 * tb * kKRow + 64 * kk);
     };
-    auto scores = [&](int kk) {
+    auto scores = [&](auto first, int kk) __attribute__((always_inline)) {
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb)
+            for (int rb = decltype(first)::value; rb < NRB; ++rb)
                 sc[rb][tb] = Mma<DT>::run(kf[tb][kk], qf[rb][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sc[rb][tb]);
     };
-    // phase M
-    auto matrix_phase = [&](int vprev, int kcur, int knext, int vnext) {
+    // phase M, for the blocks from `first` on
+    auto matrix_phase = [&](auto first, int vprev, int kcur, int knext, int vnext) __attribute__((always_inline)) {
+        constexpr int kBlocks = NRB - decltype(first)::value;
+        if constexpr (kBlocks == 0) {
+            stage(d0.delta, regs, slot0, knext, vnext);
+            advance();
+            next_segment(std::true_type{});
+            return;
+        } else {
         __builtin_amdgcn_sched_barrier(0);
         // channel blocks 0-3 while the V^T fragments of 4-7 come in, those while the first K fragments do
         read_v(vprev, 4, 8);
-        weigh();
+        weigh(first);
         read_k(kcur, 0);
         read_k(kcur, 1);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
         for (int n = 0; n < 3; ++n) {
-            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, kBlocks, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, kBlocks, 0);
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, kBlocks, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        scores(0);
-        scores(1);
+        scores(first, 0);
+        scores(first, 1);
         read_k(kcur, 2);
         read_k(kcur, 3);
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
-            __builtin_amdgcn_sched_group_barrier(0x008, NRB, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, kBlocks, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         // the second half of the scores beside the next tile's rotation
-        scores(2);
-        scores(3);
+        scores(first, 2);
+        scores(first, 3);
         stage(d0.delta, regs, slot0, knext, vnext);
         advance();
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
@@ -732,17 +779,20 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         for (int n = 0; n < 4; ++n) {
             if (n < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
 #pragma unroll
-            for (int i = 0; i < NRB; ++i) {
+            for (int i = 0; i < kBlocks; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 16 / NRB, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 16 / kBlocks, 0);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
         next_segment(std::true_type{});
+        }
     };
-    auto softmax = [&](const Tile& cd, int vbuf) {
+    auto softmax = [&](auto first, const Tile& cd, int vbuf) __attribute__((always_inline)) {
+        constexpr int kFirst = decltype(first)::value;
+        if constexpr (kFirst == NRB) return;
         float lsum[NRB];
-        auto probabilities = [&](int rb) {
+        auto probabilities = [&](int rb) __attribute__((always_inline)) {
             const float m_safe = st.m_run[rb] == -INFINITY ? 0.f : st.m_run[rb];
             float pv[8];
             float s = 0.f;
@@ -757,14 +807,14 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         };
         if (cd.ntok < kTile || cd.self != 0) {
             const int l = lane_anew();
-            int tqs = tq;
+            int tqs = CAUSAL ? group : tq;
             asm volatile("" : "+v"(tqs));            // nothing of the division below is kept from tile to tile
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) {
+            for (int rb = kFirst; rb < NRB; ++rb) {
                 int lim = cd.ntok;
-                if (cd.self != 0) {                  // causal: row m = g * tq + t sees the own block up to its t
-                    const int m = row_base + (wave * NRB + rb) * 16 + (l & 15);
-                    const int t = m - (int)div_exact((unsigned)m, (unsigned)tqs) * tqs;
+                if (cd.self != 0) {                  // causal: row m = g * tq + t (CAUSAL: t * group + g) sees the own block up to its t
+                    const int m = row_base + (blk(rb) - missing) * 16 + (l & 15);
+                    const int t = CAUSAL ? (int)div_exact((unsigned)max(m, 0), (unsigned)tqs) : m - (int)div_exact((unsigned)m, (unsigned)tqs) * tqs;
                     lim = min(lim, t - cd.tok0 + 1);
                 }
                 lim -= 4 * (l >> 4);
@@ -774,13 +824,13 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
             }
         }
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) probabilities(rb);
+        for (int rb = kFirst; rb < NRB; ++rb) probabilities(rb);
         bool any_off = false;
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) any_off = any_off || !(lsum[rb] <= kProbLimit) || st.m_run[rb] == -INFINITY;
+        for (int rb = kFirst; rb < NRB; ++rb) any_off = any_off || !(lsum[rb] <= kProbLimit) || st.m_run[rb] == -INFINITY;
         if (__any(any_off)) {
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) {
+            for (int rb = kFirst; rb < NRB; ++rb) {
                 float mloc = -INFINITY;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) mloc = fmaxf(mloc, sc[rb][e >> 2][e & 3]);
@@ -801,24 +851,24 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         __builtin_amdgcn_sched_barrier(0);
         read_v(vbuf, 0, 4);
 #pragma unroll
-        for (int rb = 0; rb < NRB; ++rb) {
+        for (int rb = kFirst; rb < NRB; ++rb) {
             st.seg_l[rb] += lsum[rb];
         }
     };
     // (reference, segment sum) per row for the segment's slot
-    auto emit = [&](int seg) {
+    auto emit = [&](int seg) __attribute__((always_inline)) {
         float tot[NRB];
 #pragma unroll
         for (int rb = 0; rb < NRB; ++rb) tot[rb] = add_lane_groups(st.seg_l[rb]);
         const int l = lane_anew();
         if (l < 16) {
-            float2* dst = massml + (int64_t)(seg + ss) * p.rows_wg + wave * NRB * 16 + l;
+            float2* dst = massml + (int64_t)(seg + ss) * p.rows_wg + blk(0) * 16 + l;
 #pragma unroll
-            for (int rb = 0; rb < NRB; ++rb) dst[16 * rb] = make_float2(st.m_run[rb], tot[rb]);
+            for (int rb = 0; rb < NRB; ++rb) dst[16 * (blk(rb) - blk(0))] = make_float2(st.m_run[rb], tot[rb]);
         }
     };
-    // phase V
-    auto vector_phase = [&](const Tile& cd, int vbuf) {
+    // phase V, for the blocks from `first` on
+    auto vector_phase = [&](auto first, const Tile& cd, int vbuf) __attribute__((always_inline)) {
         if (cd.ntok <= 0) {
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb) pfrag[rb] = make_uint4(0, 0, 0, 0);
@@ -832,7 +882,14 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb) { st.l_run[rb] += st.seg_l[rb]; st.seg_l[rb] = 0.f; }
         }
-        softmax(cd, vbuf);
+        softmax(first, cd, vbuf);
+    };
+    // the first of the wavefront's blocks that sees anything of a tile (all after it do); it only grows along the list
+    auto first_block = [&](const Tile& d) __attribute__((always_inline)) {
+        int r0 = 0;
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) r0 += t_last[rb] < (d.seg == own_seg ? d.tok0 : 0) ? 1 : 0;
+        return r0;
     };
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) pfrag[rb] = make_uint4(0, 0, 0, 0);
@@ -848,25 +905,36 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     if (GROUPS == 2 && grp == 1) __syncthreads();    // the second group runs one phase behind
     // step t: d0 / regs hold tile t + 1, after it tile t + 2
     int kcur = 0, vprev = 2 * kWideV, vcur = 0, vnext = kWideV;
-    for (int it = 0; it < most_tiles; ++it) {
-        __builtin_amdgcn_s_setprio(1);
-        matrix_phase(vprev, kcur, kWideK - kcur, vnext);
-        __builtin_amdgcn_s_setprio(0);
-        if (GROUPS == 2) __syncthreads();
-        const Tile cur = cd;
-        cd = d0;
-        fetch(d0, slot0, regs);
-        vector_phase(cur, vcur);
-        kcur = kWideK - kcur;
-        const int v = vprev;
-        vprev = vcur;
-        vcur = vnext;
-        vnext = v;
-        __syncthreads();
+    int it = 0, r_prev = CAUSAL ? first_block(cd) : 0;       // the first block of the tile before
+    auto steps = [&](auto first) __attribute__((always_inline)) {
+        constexpr int kFirst = decltype(first)::value;       // (the probabilities of the blocks before it are zero since their last tile)
+        for (; it < most_tiles && (!CAUSAL || r_prev <= kFirst); ++it) {
+            __builtin_amdgcn_s_setprio(1);
+            matrix_phase(first, vprev, kcur, kWideK - kcur, vnext);
+            __builtin_amdgcn_s_setprio(0);
+            if (GROUPS == 2) __syncthreads();
+            const Tile cur = cd;
+            cd = d0;
+            fetch(d0, slot0, regs);
+            vector_phase(first, cur, vcur);
+            if constexpr (CAUSAL) r_prev = first_block(cur);
+            kcur = kWideK - kcur;
+            const int v = vprev;
+            vprev = vcur;
+            vcur = vnext;
+            vnext = v;
+            __syncthreads();
+        }
+    };
+    steps(std::integral_constant<int, 0>{});
+    if constexpr (CAUSAL) {
+        steps(std::integral_constant<int, 1>{});
+        steps(std::integral_constant<int, 2>{});
+        if constexpr (NRB == 3) steps(std::integral_constant<int, 3>{});
     }
     if (GROUPS == 2 && grp == 0) __syncthreads();
     read_v(vprev, 4, 8);
-    weigh();
+    weigh(std::integral_constant<int, 0>{});
     if (has_rows && cur_seg >= 0) emit(cur_seg);
 
     const StoreArgs ta = store_args(late_args());
@@ -882,11 +950,22 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         if (ta.slots_here && lg_t == 0) {
 #pragma unroll
             for (int rb = 0; rb < NRB; ++rb) {
-                const int row = (wave * NRB + rb) * 16 + li_t;
-                red_ml[0][row] = make_float2(st.m_run[rb], row_base + row < row_limit ? l_row[rb] : 0.f);
+                const int row = blk(rb) * 16 + li_t;
+                red_ml[0][row] = make_float2(st.m_run[rb], blk(rb) >= missing && row_base + row - 16 * missing < row_limit ? l_row[rb] : 0.f);
             }
         }
-        if (has_rows) store_partials<DT, NRB>(ta, unit, split, wave * NRB, st, l_row, lane_t, qh.q0, tq, hkv, group, row_base, row_limit);
+        if constexpr (CAUSAL) {
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) {
+                if (blk(rb) < missing) continue;
+                const int m = row_base + (blk(rb) - missing) * 16 + li_t, mc = min(m, row_limit - 1);      // (every lane takes part in the exchange)
+                const int t = (int)div_exact((unsigned)mc, (unsigned)group), gi = mc - t * group;
+                const float inv = l_row[rb] > 0.f ? 1.f / l_row[rb] : 0.f;
+                uint16_t* op = reinterpret_cast<uint16_t*>(ta.out) + (((int64_t)qh.q0 + t) * ta.n_q_heads + hkv * group + gi) * kD;
+#pragma unroll
+                for (int db = 0; db < 8; db += 2) store_row_pair<DT>(op, db, st.acc[rb][db] * inv, st.acc[rb][db + 1] * inv, lg_t, m < row_limit);
+            }
+        } else if (has_rows) store_partials<DT, NRB>(ta, unit, split, wave * NRB, st, l_row, lane_t, qh.q0, tq, hkv, group, row_base, row_limit);
         if (!ta.slots_here) return;
         __syncthreads();
         reduce_slots<kWaves>(late_args(), unit, red_ml[0], wave, lane_t);
@@ -994,6 +1073,9 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
         else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
     } while (0)
+    // CAUSAL: own blocks of half the list and more (a document's encoding over the prefix).  A shorter one masks a few tiles at most, for which
+    // the rows' other order is not worth a second set of kernels' time to load.
+    const bool causal = p.nsplit == 1 && p.groups == 1 && reg_table && 2 * (int64_t)a.max_tq >= a.max_kv_tokens;
 #define CF_LAUNCH_WIDE(DT, GROUPS)                                                                                            \
     if (p.nrb == 2) {                                                                                                         \
         if (reg_table) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, GROUPS, true>), grid2, dim3(GROUPS * kThreads));              \
@@ -1009,7 +1091,10 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, true>), grid3, dim3(2 * kThreads));                            \
         else CF_LAUNCH_TIMED((attn_tile_kernel<DT, false>), grid3, dim3(2 * kThreads));                                     \
     } else {                                                                                                                   \
-        if (p.groups == 2) { CF_LAUNCH_WIDE(DT, 2) } else { CF_LAUNCH_WIDE(DT, 1) }                                             \
+        if (causal) {                                                                                                          \
+            if (p.nrb == 2) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, 1, true, true>), grid2, dim3(kThreads));                   \
+            else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, 1, true, true>), grid2, dim3(kThreads));                              \
+        } else if (p.groups == 2) { CF_LAUNCH_WIDE(DT, 2) } else { CF_LAUNCH_WIDE(DT, 1) }                                             \
     }                                                                                                                          \
     CF_HIP(hipGetLastError());
     if (a.dtype == CF_BF16) { CF_LAUNCH_DT(CF_BF16) } else { CF_LAUNCH_DT(CF_F16) }

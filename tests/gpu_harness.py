@@ -86,9 +86,10 @@ def oracle_on_device_segments(cfg: wl.Config, tensors: dict, pb: pl.PrefillBatch
     return segs, out, mass
 
 
-def check_tables(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head", lengths=None, check=None, shape=None, given=None):
+def check_tables(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head", lengths=None, check=None, shape=None, given=None, own_first=False):
     """cf_prefill_attention on hand-written tables against the oracle, with masses and without (the same outputs, bit for bit).
-    `tables`: per query the (offset, length, stored, new) of its store segments; the own block of the query's rows follows at q_pos.
+    `tables`: per query the (offset, length, stored, new) of its store segments; the own block of the query's rows follows (own_first:
+    comes before them) at q_pos.
     `lengths`: rows per query where they are not all tq; `check`: the queries compared (default: all); `shape(tensors, rng)` may
     replace what was drawn; `given`: the workspace's bytes where they are not those reported for the call."""
     rng = np.random.default_rng(seed)
@@ -109,6 +110,7 @@ def check_tables(hq, hkv, tq, tables, n_store, dtype, q_pos, seed, layout="head"
     for b, x in enumerate(tables):
         own = [orc.Segment(o, n, s, p, orc.KIND_DOC, i) for i, (o, n, s, p) in enumerate(x)] + \
             [orc.Segment(int(q_off[b]), lengths[b], 0, q_pos, orc.KIND_SELF, -1)]
+        own = own[-1:] + own[:-1] if own_first else own
         segs.append(own)
         rows += [(g.tok_offset, g.len, g.stored_start, g.new_start, g.kind, g.doc) for g in own]
         rows += [(0, 0, 0, 0, cf.CF_SEG_DOC, -1)] * (stride - len(own))
