@@ -111,6 +111,14 @@ __device__ __forceinline__ void build_table(const AttnArgs& a, const QueryHead& 
     __syncthreads();
 }
 
+// Between LDS accesses of one wavefront by which its lanes hand data to each other: the hardware runs them in program order,
+// this holds the compiler to it.  No instruction, no wait.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // split i of a list of `total` tiles owns [total*i/nsplit, total*(i+1)/nsplit)
 __device__ __forceinline__ int split_begin(unsigned total, unsigned nsplit, unsigned i) { return (int)div_exact(total * i, nsplit); }
 // the split that owns tile x

@@ -198,19 +198,22 @@ __device__ __forceinline__ uint32_t wave_or_u32(uint32_t x) {
     v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane(v, 63);
 }
-// Wavefront form: lane s < n holds entry s's slot and mass.  With at most 64 document slots a bit mask tells whether
+// Wavefront form: lane s < n holds entry s's slot (doc) and mass.  With at most 64 document slots a bit mask tells whether
 // every slot is fed by one entry only — the usual table — and then every entry adds its own mass (the same single
 // addend as below); otherwise the loop runs once per table entry.
-__device__ __forceinline__ void add_doc_scores_wave(int doc, float m, int n, int lane, float* score, int stride) {
+__device__ __forceinline__ bool one_entry_per_slot(int doc, int n, int lane, int stride) {
+    if (stride > kWave) return false;
+    const bool valid = lane < n && doc >= 0 && doc < stride;
+    const unsigned long long bit = valid ? 1ull << doc : 0ull;
+    const int slots_fed = __builtin_popcount(wave_or_u32((uint32_t)bit)) + __builtin_popcount(wave_or_u32((uint32_t)(bit >> 32)));
+    return slots_fed == __builtin_popcountll(__ballot(valid));
+}
+__device__ __forceinline__ void add_doc_scores_wave(int doc, float m, int n, int lane, float* score, int stride, bool one_entry) {
     const bool valid = lane < n && doc >= 0 && doc < stride;
     const int d = valid ? doc : -1;
-    if (stride <= kWave) {
-        const unsigned long long bit = valid ? 1ull << d : 0ull;
-        const int slots_fed = __builtin_popcount(wave_or_u32((uint32_t)bit)) + __builtin_popcount(wave_or_u32((uint32_t)(bit >> 32)));
-        if (slots_fed == __builtin_popcountll(__ballot(valid))) {
-            if (valid) score[d] += m;
-            return;
-        }
+    if (one_entry) {
+        if (valid) score[d] += m;
+        return;
     }
     bool first = valid;
     float sum = m;
@@ -280,6 +283,20 @@ __device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTab
     }
 }
 
+// The runs of tiles that segment `lane` has tiles in: s0 .. s1 (none: s1 < s0), of those the ones in owns_mask (a split between a segment's first
+// and last may own no tile at all).  span: the largest s1 - s0.
+struct SegmentRuns { int s0, s1, span; unsigned long long owns_mask; };
+__device__ __forceinline__ SegmentRuns segment_runs(const RegSegTable& t, unsigned nsub, int lane) {
+    const unsigned total = (unsigned)t.total;
+    SegmentRuns r;
+    r.owns_mask = __ballot(lane < (int)nsub && split_begin(total, nsub, lane) < split_begin(total, nsub, lane + 1));
+    r.s0 = 0;
+    r.s1 = -1;
+    if (lane < t.n && t.t1 > t.t0) { r.s0 = split_of(total, nsub, t.t0); r.s1 = split_of(total, nsub, t.t1 - 1); }
+    r.span = wave_max_i32(r.s1 - r.s0);
+    return r;
+}
+
 // The same for one wavefront on its own, for a query with at most 128 slots and a register table: lane k adds
 // up columns k and k + 64, lane s then collects segment s's slots — the same sums in the same order, no barrier.
 // Returns lane s's segment mass (0 for lanes past the table).
@@ -287,7 +304,6 @@ __device__ __forceinline__ void segment_masses_block(const Plan& p, const SegTab
 // add, instead of a round trip — to memory or to LDS — per group of eight.
 template <bool BATCHED = false, class T = float>
 __device__ __forceinline__ float segment_masses_wave(const Plan& p, const RegSegTable& t, const T* parts, int lane) {
-    const unsigned total = (unsigned)t.total;
     const unsigned nsub = (unsigned)(p.nsplit * p.groups);
     const int nparts = p.units_per_b * p.nrb;
     constexpr int kGroup = 8;
@@ -317,13 +333,10 @@ __device__ __forceinline__ float segment_masses_wave(const Plan& p, const RegSeg
         if (lane + 64 * j < p.slots)
             for (int g0 = 0; g0 < nparts; g0 += kGroup)
                 c[j] += group_sum(parts + g0 * p.slots + lane + 64 * j, p.slots, min(kGroup, nparts - g0));
-    // sub-splits that own at least one tile (a split between a segment's first and last may own none)
-    const bool owns = lane < (int)nsub && split_begin(total, nsub, lane) < split_begin(total, nsub, lane + 1);
-    const unsigned long long owns_mask = __ballot(owns);
-    const bool has_tiles = lane < t.n && t.t1 > t.t0;
-    int s0 = 0, s1 = -1;
-    if (has_tiles) { s0 = split_of(total, nsub, t.t0); s1 = split_of(total, nsub, t.t1 - 1); }
-    const int span = wave_max_i32(s1 - s0);
+    const SegmentRuns r = segment_runs(t, nsub, lane);
+    const unsigned long long owns_mask = r.owns_mask;
+    const bool has_tiles = r.s1 >= r.s0;
+    const int s0 = r.s0, s1 = r.s1, span = r.span;
     T m = 0;
     for (int d = 0; d <= span; ++d) {
         const int sp = s0 + d;
@@ -374,7 +387,8 @@ __global__ __launch_bounds__(kThreads) void attn_mass_kernel(AttnArgs a, Plan p,
                 const float m = segment_masses_wave<false>(p, rtbl, stage, tid);
                 if (write_mass && j == n_parts - 1 && tid < rtbl.n) a.mass[(int64_t)b * a.seg_stride + tid] = m;
                 if (a.score_accum)                   // qh.seg is this lane's entry
-                    add_doc_scores_wave(qh.seg.doc, m, rtbl.n, tid, a.score_accum + (int64_t)b * a.score_stride, a.score_stride);
+                    add_doc_scores_wave(qh.seg.doc, m, rtbl.n, tid, a.score_accum + (int64_t)b * a.score_stride, a.score_stride,
+                                        one_entry_per_slot(qh.seg.doc, rtbl.n, tid, a.score_stride));
             }
         }
         return;
@@ -476,15 +490,19 @@ struct PruneArgs {
 // table rebuild then run out of LDS with workgroup barriers between them instead of a round trip
 // through memory per stage, and the results are written back at the end.
 // Dynamic LDS: 44*stride + sizeof(T)*parts*slots bytes; larger problems take the stand-alone kernels.
+// Bound by one wavefront's chain of instructions behind two round trips; what does not belong to the chain is the other wavefronts' (the slot
+// partials' groups, each summed by the thread that read them, the look over the document slots, the ranking, the scores' way back).  One query, ten
+// documents x 32 heads 13300 -> 10800 cycles, 50 documents x 4 heads 17700 -> 13100 (whole layers 20.5 -> 19.7 us and 34.0 -> 32.5).
 template <class T>
 __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a, Plan p, PruneArgs pr) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
     __shared__ SegTable tbl;
     __shared__ MassScratch<T> ms;
-    __shared__ int s_int[6];
-    __shared__ uint4 s_bcast[kWave];
+    __shared__ int s_int[7];
+    __shared__ int32_t s_rank[kWave];
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int stride = pr.stride;
     int64_t* l_tok = reinterpret_cast<int64_t*>(dyn_smem);
     unsigned char* scratch = dyn_smem + (size_t)8 * stride;            // 3*stride words for ranking / allocation
@@ -512,15 +530,22 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     const int32_t r_len = pr.doc_len[off + row_i], r_cand = pr.cand[off + row_i];
     const float r_score = a.score_accum[off + row_i];
     const int32_t r_start = pr.new_start[off + row_i], r_order = pr.order[off + row_i];
-    constexpr int kPartRegs = 4;                     // slot partials per thread fetched with the first batch
+    // Slot partials, eight per thread.  Small queries: thread g * slots + k adds up group g of column k in its registers (the groups of
+    // segment_masses_block).  Others: one after the other, to LDS.
+    constexpr int kPartRegs = 8;
     const int n_part_floats = nparts * p.slots;
+    const int ngroups = (nparts + kPartRegs - 1) / kPartRegs;
+    const bool grouped = p.slots <= 2 * kWave && a.seg_stride <= kWave && ngroups * p.slots <= kEpiThreads;
+    const int part_g = grouped ? (int)div_exact((unsigned)tid, (unsigned)p.slots) : 0, part_k = tid - part_g * p.slots;
     T r_part[kPartRegs];
 #pragma unroll
-    for (int i = 0; i < kPartRegs; ++i) r_part[i] = mp_b[min(tid + i * kEpiThreads, n_part_floats - 1)];
+    for (int i = 0; i < kPartRegs; ++i)
+        r_part[i] = mp_b[grouped ? min(part_g * kPartRegs + i, nparts - 1) * p.slots + part_k : min(tid + i * kEpiThreads, n_part_floats - 1)];
     const int n_cand = pr.n_cand[b];
     const int r_q_start = pr.q_start[b], r_n_reuse = pr.n_reuse[b];
-    const QueryHead qh = load_query_head(a, b, (int)threadIdx.x);
+    const QueryHead qh = load_query_head(a, b, grouped ? lane : tid);
     if (tid == 0) { s_int[4] = r_q_start; s_int[5] = r_n_reuse; }
+    if (tid < kWave) s_rank[tid] = 0;
     if (row0) {
         l_tok[tid] = r_tok; l_len[tid] = r_len; l_cand[tid] = r_cand; l_score[tid] = r_score; l_start[tid] = r_start;
         l_order[tid] = r_order;
@@ -536,21 +561,66 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     // With few candidates one wavefront finishes alone: the others leave, and the barriers of the stages
     // below (which only wait for wavefronts that are still running) cost nothing.
     const int nthr = n_cand <= 2 * kWave ? kWave : kEpiThreads;
-    const bool small = nthr == kWave && p.slots <= 2 * kWave && a.seg_stride <= kWave;
-#pragma unroll
-    for (int i = 0; i < kPartRegs; ++i)
-        if (tid + i * kEpiThreads < n_part_floats) l_part[tid + i * kEpiThreads] = r_part[i];
-    for (int i = tid + kPartRegs * kEpiThreads; i < n_part_floats; i += kEpiThreads) l_part[i] = mp_b[i];
+    const bool small = nthr == kWave && grouped;
     if (small) {
-        // small query: the first wavefront also does the masses, from a table in its registers
-        __syncthreads();                             // publishes the rows above
-        if (tid >= kWave) return;
-        const RegSegTable rtbl = build_reg_table(a, qh, tid, p.tile);
-        const float m = segment_masses_wave<false>(p, rtbl, l_part, tid);
-        if (tid < rtbl.n) a.mass[(int64_t)b * a.seg_stride + tid] = m;
-        add_doc_scores_wave(qh.seg.doc, m, rtbl.n, tid, l_score, stride);       // qh.seg is this lane's entry
+        // Small query: the first wavefront does the masses, from a table in its registers, the second one looks the document slots over.
+        T gs = 0;
+#pragma unroll
+        for (int i = 0; i < kPartRegs; ++i)
+            if (part_g * kPartRegs + i < nparts) gs += r_part[i];
+        if (tid < ngroups * p.slots) l_part[tid] = gs;
+        RegSegTable rtbl;
+        SegmentRuns runs;
+        if (wave == 0) {
+            rtbl = build_reg_table(a, qh, lane, p.tile);
+            runs = segment_runs(rtbl, (unsigned)(p.nsplit * p.groups), lane);
+        } else if (wave == 1) {
+            const bool one = one_entry_per_slot(qh.seg.doc, qh.n_seg < 0 ? 0 : min(qh.n_seg, a.seg_stride), lane, stride);
+            if (lane == 0) s_int[6] = one;
+        }
+        __syncthreads();                             // publishes the rows and the groups' sums
+        if (wave == 0) {
+            // the sums of segment_masses_wave in the same order; columns to LDS, a segment's come from there
+            T c[2] = {0, 0};
+            for (int g0 = 0; g0 < ngroups; g0 += 4) {
+                T v[2][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int at = min(g0 + i, ngroups - 1) * p.slots;
+                    v[0][i] = l_part[at + min(lane, p.slots - 1)];
+                    v[1][i] = l_part[at + min(lane + kWave, p.slots - 1)];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (g0 + i < ngroups) { c[0] += v[0][i]; c[1] += v[1][i]; }
+            }
+            ms.colsum[lane] = c[0];
+            ms.colsum[lane + kWave] = c[1];
+            wave_lds_order();
+            T m = 0;
+            for (int d0 = 0; d0 <= runs.span; d0 += 4) {
+                T v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = ms.colsum[min(lane + runs.s0 + d0 + i, 2 * kWave - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int sp = runs.s0 + d0 + i;
+                    if (sp <= runs.s1 && ((runs.owns_mask >> sp) & 1)) m += v[i];
+                }
+            }
+            if (lane < rtbl.n) a.mass[(int64_t)b * a.seg_stride + lane] = (float)m;
+            add_doc_scores_wave(qh.seg.doc, lane < rtbl.n ? (float)m : 0.f, rtbl.n, lane, l_score, stride, s_int[6] != 0);      // qh.seg is this lane's entry
+        }
         __syncthreads();
     } else {
+        if (grouped) {
+            for (int i = tid; i < n_part_floats; i += kEpiThreads) l_part[i] = mp_b[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < kPartRegs; ++i)
+                if (tid + i * kEpiThreads < n_part_floats) l_part[tid + i * kEpiThreads] = r_part[i];
+            for (int i = tid + kPartRegs * kEpiThreads; i < n_part_floats; i += kEpiThreads) l_part[i] = mp_b[i];
+        }
         build_table(a, qh, &tbl, p.tile);            // its barriers also publish the rows above
         segment_masses_block<T>(p, tbl, l_part, nullptr, &ms, [&](int s, float m) {
             a.mass[(int64_t)b * a.seg_stride + s] = m;
@@ -560,33 +630,35 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
         add_doc_scores_block(tbl.doc, ms.seg_mass, tbl.n, l_score, stride);
         __syncthreads();
     }
-    if (tid >= nthr) return;
-    for (int i = tid; i < stride; i += nthr) a.score_accum[off + i] = l_score[i];
-    int k = min(pr.keep, n_cand);
-    bool done = false;
-    if (n_cand <= kWave) {                               // the usual case: everything in one wavefront's registers
-        SelectWaveArgs sw;
-        sw.score = l_score; sw.len = l_len; sw.cand = l_cand; sw.tok = l_tok; sw.keep_idx = l_keep; sw.new_start = l_start;
-        sw.order = l_order; sw.bcast = s_bcast; sw.n = n_cand; sw.keep = pr.keep; sw.stride = stride; sw.normalise_by_len = pr.normalise_by_len;
+    SelectWaveArgs sw;
+    Candidate cand;
+    if (n_cand <= kWave) {                               // the usual case: everything in registers
+        sw.score = l_score; sw.len = l_len; sw.cand = l_cand; sw.tok = l_tok; sw.start = l_start;
+        sw.keep_idx = pr.keep_idx + off; sw.new_start = pr.new_start + off; sw.order = pr.order + off;
+        sw.n = n_cand; sw.keep = pr.keep; sw.stride = stride; sw.normalise_by_len = pr.normalise_by_len;
         sw.strategy = pr.strategy; sw.force_n_reuse = pr.force_n_reuse; sw.pos_begin = pr.pos_begin; sw.pos_end = pr.pos_end;
         sw.prefix_len = pr.prefix_len; sw.doc_stored_start = pr.doc_stored_start; sw.q_stored_start = a.q_stored_start;
-        sw.q_lo = qh.q0; sw.q_hi = qh.q0 + qh.tq_raw; sw.seg_stride = a.seg_stride;
-        done = select_wave64(sw, pr.n_keep + b, &s_int[4], &s_int[5], pr.next_segs + (int64_t)b * a.seg_stride,
-                             pr.next_n_seg + b);
-        __builtin_amdgcn_wave_barrier();
-    }
-    if (!done) {
-        k = prune_topk_block(l_score, pr.normalise_by_len ? l_len : nullptr, l_cand, n_cand, pr.keep, stride, l_keep,
-                             a.dev_flag, scratch, &s_int[3], nthr);
-        if (tid == 0) pr.n_keep[b] = k;
+        sw.q_lo = qh.q0; sw.q_hi = qh.q0 + qh.tq_raw; sw.seg_stride = a.seg_stride; sw.q_start = r_q_start; sw.n_reuse = r_n_reuse;
+        cand = rank_wave(sw, wave, kEpiThreads / kWave, s_rank);
         __syncthreads();
-        assign_positions_block(l_len, l_keep, k, stride, pr.pos_begin, pr.pos_end, pr.strategy, pr.force_n_reuse, l_start,
-                               &s_int[4], &s_int[5], l_order, a.dev_flag, scratch, s_int, nthr);
-        __syncthreads();
-        gather_segments_block(l_tok, l_len, l_order, k, l_start, s_int[4], qh.q0, qh.q0 + qh.tq_raw, stride, pr.prefix_len,
-                              pr.doc_stored_start, a.q_stored_start, pr.next_segs + (int64_t)b * a.seg_stride,
-                              pr.next_n_seg + b, a.seg_stride, a.dev_flag, nthr);
     }
+    // (by the others, where the first wavefront goes on alone)
+    const int first_writer = nthr == kWave ? kWave : 0;
+    if (tid >= first_writer)
+        for (int i = tid - first_writer; i < stride; i += kEpiThreads - first_writer) a.score_accum[off + i] = l_score[i];
+    if (tid >= nthr) return;
+    if (n_cand <= kWave &&
+        select_wave64(sw, cand, s_rank[lane], pr.n_keep + b, pr.q_start + b, pr.n_reuse + b, pr.next_segs + (int64_t)b * a.seg_stride, pr.next_n_seg + b))
+        return;
+    const int k = prune_topk_block(l_score, pr.normalise_by_len ? l_len : nullptr, l_cand, n_cand, pr.keep, stride, l_keep, a.dev_flag, scratch, &s_int[3],
+                                   nthr);
+    if (tid == 0) pr.n_keep[b] = k;
+    __syncthreads();
+    assign_positions_block(l_len, l_keep, k, stride, pr.pos_begin, pr.pos_end, pr.strategy, pr.force_n_reuse, l_start, &s_int[4], &s_int[5], l_order,
+                           a.dev_flag, scratch, s_int, nthr);
+    __syncthreads();
+    gather_segments_block(l_tok, l_len, l_order, k, l_start, s_int[4], qh.q0, qh.q0 + qh.tq_raw, stride, pr.prefix_len, pr.doc_stored_start,
+                          a.q_stored_start, pr.next_segs + (int64_t)b * a.seg_stride, pr.next_n_seg + b, a.seg_stride, a.dev_flag, nthr);
     for (int i = tid; i < stride; i += nthr) {
         if (i < k) pr.keep_idx[off + i] = l_keep[i];
         pr.new_start[off + i] = l_start[i];

@@ -15,14 +15,6 @@ constexpr float kProbLimit = 256.f;
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 
-// Between LDS accesses of one wavefront by which its lanes hand data to each other: the hardware runs them in program order,
-// this holds the compiler to it.  No instruction, no wait.
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // cos/sin of delta*theta from the hardware sine/cosine (argument in revolutions, reduced in fp64):
 // their absolute error is far below the rounding step of the 16-bit keys this feeds.
 __device__ __forceinline__ float2 rope_cos_sin_fast(int delta, double theta_rev) {

@@ -206,21 +206,61 @@ __device__ inline void gather_segments_block(const int64_t* doc_tok_offset, cons
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same three stages for at most 64 candidates, executed by one wavefront with every list in
-// registers (lane i = list position i): ranks by comparing against broadcast lanes, lists turned
-// into one another through small LDS scatters, sums and maxima by wavefront scans.  No barriers, no
+// The same three stages for at most 64 candidates, every list in registers (lane i = list position i).  A lane issues one instruction at a time
+// and each of a chain waits for the one before, so what can be is spread over the workgroup: the ranking, which is most of it, over all
+// wavefronts (rank_wave), the rest — permutes, sums and maxima across the lanes — by one (select_wave64), without barriers or
 // atomics.  Results are those of the block functions; on any condition they would flag (bad
 // index, non-finite score, bad length, document too long, overflow, table too small) nothing is
 // written and false is returned, so that the caller runs the block functions, which raise the flag.
-// All pointers are this query's rows and may live in LDS; keep_idx also serves as scratch (entries
-// below the candidate count); *q_start / *n_reuse are written like the block function does.
+// On one wavefront alone, with its lists handed over through LDS, this took 3000 cycles for ten candidates and 6200 for fifty; now 2600 and 3700.
 struct SelectWaveArgs {
-    const float* score; const int32_t* len; const int32_t* cand; const int64_t* tok;
-    int32_t* keep_idx; int32_t* new_start; int32_t* order;
-    uint4* bcast;                                   // LDS, 64 entries: the ranking keys, read back as broadcasts
+    const float* score; const int32_t* len; const int32_t* cand; const int64_t* tok; const int32_t* start;      // the query's rows, in LDS
+    int32_t* keep_idx; int32_t* new_start; int32_t* order;                                                      // its rows in memory
     int n, keep, stride, normalise_by_len, strategy, force_n_reuse, pos_begin, pos_end;
     int prefix_len, doc_stored_start, q_stored_start, q_lo, q_hi, seg_stride;
+    int q_start, n_reuse;                           // as they stand ("keep" leaves them)
 };
+
+// list position `lane`'s candidate; `bad` (any of the list's): the block functions' business
+struct Candidate { int c, len; bool have, bad; };
+
+__device__ __forceinline__ int lane_int(int v, int from) { return __builtin_amdgcn_readlane(v, from); }
+__device__ __forceinline__ double lane_double(double v, int from) {
+    const uint64_t bits = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)(uint32_t)lane_int((int)(uint32_t)(bits >> 32), from) << 32 | (uint32_t)lane_int((int)(uint32_t)bits, from));
+}
+
+// Ranking (Alg. 2: argsort of the accumulated scores): wavefront `wave` of n_waves adds to rank[i] (LDS, cleared) how many of its share of the
+// candidates rank before candidate i.
+// The quotient score/len in fp64 orders exactly as the cross products of ranks_before do —
+// two different cross products (a 24-bit significand times an integer below 2^24 each) make quotients
+// that differ by more than 2^-48 of their size, far above the quotient's rounding, and equal ones give
+// the same quotient — so every lane divides once and the loop compares, without branches.
+__device__ inline Candidate rank_wave(const SelectWaveArgs& s, int wave, int n_waves, int32_t* rank) {
+    const int lane = threadIdx.x & 63;
+    const int n = s.n;
+    Candidate d;
+    d.have = lane < min(n, s.stride);
+    d.c = d.have ? s.cand[lane] : 0;
+    const bool c_ok = d.c >= 0 && d.c < s.stride;
+    const int at = d.have && c_ok ? d.c : 0;
+    const float sc = s.score[at];
+    d.len = s.len[at];
+    const int ln = s.normalise_by_len ? d.len : 1;
+    d.bad = __any(d.have && (!c_ok || !isfinite(sc) || ln <= 0 || ln >= (1 << 24))) || n < 0 || n > 64 || n > s.stride;
+    if (d.bad || wave >= n) return d;
+    const double q = (double)sc / (double)ln;
+    int before = 0;
+    for (int j = wave; j < n; j += n_waves) {
+        const double qj = lane_double(q, j);
+        const int cj = lane_int(d.c, j);
+        const int tie = cj != d.c ? cj < d.c : j < lane;     // lower slot, then earlier list position
+        const int eq = qj == q ? tie : 0;
+        before += qj > q ? 1 : eq;
+    }
+    if (d.have) atomicAdd(rank + lane, before);
+    return d;
+}
 
 // In-register reductions over the 64 lanes of a wavefront with DPP (row shifts, then the two row broadcasts,
 // lane 63 ends up with the result): an inclusive prefix sum, and a maximum handed to every lane.
@@ -244,106 +284,40 @@ __device__ __forceinline__ int wave_max_i32(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-__device__ inline bool select_wave64(const SelectWaveArgs& s, int* n_keep_out, int* q_start, int* n_reuse, cf_segment* out,
-                                     int32_t* n_seg_out) {
+// The cut, the allocation and the next table, by one wavefront with all its lanes; `rank`: of the lane's candidate.
+__device__ inline bool select_wave64(const SelectWaveArgs& s, const Candidate& cd, int rank, int32_t* n_keep_out, int32_t* q_start_out,
+                                     int32_t* n_reuse_out, cf_segment* out, int32_t* n_seg_out) {
     const int lane = threadIdx.x & 63;
     const int n = s.n;
-    if (n < 0 || n > 64 || n > s.stride) return false;
-    // ---- ranking (Alg. 2: argsort of the accumulated scores, then the cut)
-    const bool have = lane < n;
-    const int c = have ? s.cand[lane] : 0;
-    const bool c_ok = c >= 0 && c < s.stride;
-    const float sc = have && c_ok ? s.score[c] : 0.f;
-    const int ln_rank = have && c_ok && s.normalise_by_len ? s.len[c] : 1;
-    const bool bad = have && (!c_ok || !isfinite(sc) || ln_rank <= 0 || ln_rank >= (1 << 24));
-    if (__any(bad)) return false;
-    int rank = 0;
-    if (s.stride <= (1 << 26) && __all(!have || ln_rank == __builtin_amdgcn_readlane(ln_rank, 0))) {
-        // equal lengths (the paper's regime, or no normalisation): the products of ranks_before compare as the
-        // scores themselves do
-        // as one unsigned key per lane: score (order-preserving bits, -0 as +0), then lower slot, then earlier position
-        uint32_t u = __float_as_uint(sc + 0.f);
-        u ^= (u >> 31) ? 0xffffffffu : 0x80000000u;
-        const uint32_t low = ((uint32_t)(s.stride - 1 - c) << 6) | (uint32_t)(63 - lane);     // stride <= 2^26
-        const uint64_t key = ((uint64_t)u << 32) | low;
-        // every lane's key goes to LDS once; candidate j's key is then one broadcast read (the same address in every
-        // lane), eight requested at a time
-        // (lanes past n publish the smallest key: read, never counted)
-        s.bcast[lane] = have ? make_uint4(low, u, 0u, 0u) : make_uint4(0u, 0u, 0u, 0u);
-        __builtin_amdgcn_wave_barrier();
-        for (int j0 = 0; j0 < n; j0 += 8) {
-            uint2 e[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) e[i] = *reinterpret_cast<const uint2*>(&s.bcast[(j0 + i) & 63]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) rank += ((((uint64_t)e[i].y << 32) | e[i].x) > key) ? 1 : 0;
-        }
-    } else {
-        // Unequal lengths: the quotient score/len in fp64 orders exactly as the cross products of ranks_before do —
-        // two different cross products (a 24-bit significand times an integer below 2^24 each) make quotients
-        // that differ by more than 2^-48 of their size, far above the quotient's rounding, and equal ones give
-        // the same quotient — so every lane divides once and the loop compares, without branches.
-        const double q = (double)sc / (double)ln_rank;
-        const int q_lo = (int)(uint32_t)__builtin_bit_cast(uint64_t, q), q_hi = (int)(uint32_t)(__builtin_bit_cast(uint64_t, q) >> 32);
-        const uint32_t low = ((uint32_t)(s.stride - 1 - c) << 6) | (uint32_t)(63 - lane);   // lower slot, then earlier position
-        auto lane_quotient = [&](int j) {
-            const uint64_t bits = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(q_hi, j) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane(q_lo, j);
-            return __builtin_bit_cast(double, bits);
-        };
-        if (s.stride <= (1 << 26)) {
-            // as above: (quotient, tie-break word) of every lane in LDS, broadcast reads, eight at a time
-            // (lanes past n publish minus infinity: read, never counted; the selects keep the predicate in vector
-            // registers instead of wavefront masks worked on by the scalar unit)
-            const uint64_t never = __builtin_bit_cast(uint64_t, -__builtin_inf());
-            s.bcast[lane] = have ? make_uint4((uint32_t)q_lo, (uint32_t)q_hi, low, 0u) : make_uint4((uint32_t)never, (uint32_t)(never >> 32), 0u, 0u);
-            __builtin_amdgcn_wave_barrier();
-            for (int j0 = 0; j0 < n; j0 += 8) {
-                uint4 e[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) e[i] = s.bcast[(j0 + i) & 63];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const double qj = __builtin_bit_cast(double, ((uint64_t)e[i].y << 32) | e[i].x);
-                    const int tie = e[i].z > low ? 1 : 0;
-                    const int eq = qj == q ? tie : 0;
-                    rank += qj > q ? 1 : eq;
-                }
-            }
-        } else {                                     // `low` would not hold the slot
-            for (int j = 0; j < n; ++j) {
-                const double qj = lane_quotient(j);
-                const int cj = __builtin_amdgcn_readlane(c, j);
-                rank += (int)((qj > q) | ((qj == q) & (cj != c ? cj < c : j < lane)));
-            }
-        }
-    }
+    if (cd.bad) return false;
     const int k = min(s.keep, n);
     const int has_prefix = s.prefix_len > 0 ? 1 : 0;
     if (k + has_prefix + 1 > s.seg_stride) return false;
-    // ranked list: lane r gets the candidate of rank r
-    if (have && rank < k) s.keep_idx[rank] = c;
-    __builtin_amdgcn_wave_barrier();
     const bool in = lane < k;
-    const int rc = in ? s.keep_idx[lane] : 0x7fffffff;
-    __builtin_amdgcn_wave_barrier();
+    // ranked list: lane r gets the candidate of rank r (the ranks of the n lanes are 0 .. n - 1; the others keep their places)
+    auto move = [](int to, int v) { return __builtin_amdgcn_ds_permute(to << 2, v); };
+    const int64_t tok = s.tok[cd.c];
+    const int to = cd.have ? rank : lane;
+    const int rc = move(to, cd.c);
+    int oc = rc, pl = move(to, cd.len), my_start = move(to, s.start[cd.c]);
+    int tok_lo = move(to, (int)(uint32_t)tok), tok_hi = move(to, (int)(uint32_t)((uint64_t)tok >> 32));
     // ---- placement order (Sec. 2.5): as ranked ("sort") or by ascending slot ("align"; listing order of "keep")
-    int place = lane;
     if (s.strategy != CF_ALLOC_SORT) {
-        place = 0;
+        int place = 0;
         for (int j = 0; j < k; ++j) {
-            const int cj = __builtin_amdgcn_readlane(rc, j);
+            const int cj = lane_int(rc, j);
             place += (cj < rc) || (cj == rc && j < lane);
         }
+        place = in ? place : lane;
+        oc = move(place, rc);
+        pl = move(place, pl);
+        my_start = move(place, my_start);
+        tok_lo = move(place, tok_lo);
+        tok_hi = move(place, tok_hi);
     }
-    if (in) s.keep_idx[place] = rc;                       // scratch use; the ranked list is written back below
-    __builtin_amdgcn_wave_barrier();
-    const int oc = in ? s.keep_idx[lane] : 0;             // slot at placement rank `lane`
-    __builtin_amdgcn_wave_barrier();
-    const int pl = in ? s.len[oc] : 0;
     if (__any(in && pl <= 0)) return false;
-    int qs = *q_start, groups = *n_reuse;
-    int my_start = in ? s.new_start[oc] : 0;
+    pl = in ? pl : 0;
+    int qs = s.q_start, groups = s.n_reuse;
     bool write_pos = false;
     if (s.strategy != CF_ALLOC_KEEP && k > 0) {
         // ---- allocation (Eq. 6): capacity by the longest survivor, balanced contiguous groups, every group
@@ -354,13 +328,16 @@ __device__ inline bool select_wave64(const SelectWaveArgs& s, int* n_keep_out, i
         if (cap <= 0) return false;
         groups = s.force_n_reuse > 0 ? s.force_n_reuse : (cap >= k ? 1 : (int)div_exact((unsigned)(k + cap - 1), (unsigned)cap));
         groups = min(groups, k);
-        const int per_group = (int)div_exact((unsigned)(k + groups - 1), (unsigned)groups);
-        const int incl = wave_inclusive_scan(pl);         // inclusive prefix over placement ranks
-        const int first = (int)div_exact((unsigned)lane, (unsigned)per_group) * per_group;
-        const int before = __shfl(incl, max(first - 1, 0));
-        const int cum = incl - (first > 0 ? before : 0);
-        const bool last = in && ((lane == k - 1) || (lane + 1 == first + per_group));
-        const int span_max = wave_max_i32(last ? cum : 0);
+        int cum = wave_inclusive_scan(pl);                // inclusive prefix over placement ranks
+        int span_max = lane_int(cum, 63);                 // (one group: all of it)
+        if (groups > 1) {
+            const int per_group = (int)div_exact((unsigned)(k + groups - 1), (unsigned)groups);
+            const int first = (int)div_exact((unsigned)lane, (unsigned)per_group) * per_group;
+            const int before = __shfl(cum, max(first - 1, 0));
+            cum -= first > 0 ? before : 0;
+            const bool last = in && ((lane == k - 1) || (lane + 1 == first + per_group));
+            span_max = wave_max_i32(last ? cum : 0);
+        }
         if (span_max > avail) return false;
         qs = s.pos_begin + span_max;
         my_start = qs - cum;
@@ -371,13 +348,18 @@ __device__ inline bool select_wave64(const SelectWaveArgs& s, int* n_keep_out, i
     }
     // ---- everything checked: write the lists and the next segment table (Alg. 2, the logical concat)
     if (in) {
+        cf_segment sg;
+        sg.tok_offset = (int64_t)((uint64_t)(uint32_t)tok_hi << 32 | (uint32_t)tok_lo);
+        sg.len = pl; sg.stored_start = s.doc_stored_start; sg.new_start = my_start;
+        sg.kind = CF_SEG_DOC; sg.doc = oc; sg.reserved = 0;
+        out[has_prefix + lane] = sg;
         s.keep_idx[lane] = rc;
         s.order[lane] = oc;
         if (write_pos) s.new_start[oc] = my_start;
     }
     if (lane == 0) {
         *n_keep_out = k;
-        if (s.strategy != CF_ALLOC_KEEP) { *q_start = qs; *n_reuse = groups; }
+        if (s.strategy != CF_ALLOC_KEEP) { *q_start_out = qs; *n_reuse_out = groups; }
         if (has_prefix) {
             cf_segment p;
             p.tok_offset = 0; p.len = s.prefix_len; p.stored_start = 0; p.new_start = 0;
@@ -389,12 +371,6 @@ __device__ inline bool select_wave64(const SelectWaveArgs& s, int* n_keep_out, i
         q.new_start = qs; q.kind = CF_SEG_SELF; q.doc = -1; q.reserved = 0;
         out[has_prefix + k] = q;
         *n_seg_out = has_prefix + k + 1;
-    }
-    if (in) {
-        cf_segment sg;
-        sg.tok_offset = s.tok[oc]; sg.len = pl; sg.stored_start = s.doc_stored_start; sg.new_start = my_start;
-        sg.kind = CF_SEG_DOC; sg.doc = oc; sg.reserved = 0;
-        out[has_prefix + lane] = sg;
     }
     return true;
 }
