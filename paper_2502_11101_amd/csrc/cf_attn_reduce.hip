@@ -289,10 +289,21 @@ struct SegmentRuns { int s0, s1, span; unsigned long long owns_mask; };
 __device__ __forceinline__ SegmentRuns segment_runs(const RegSegTable& t, unsigned nsub, int lane) {
     const unsigned total = (unsigned)t.total;
     SegmentRuns r;
-    r.owns_mask = __ballot(lane < (int)nsub && split_begin(total, nsub, lane) < split_begin(total, nsub, lane + 1));
     r.s0 = 0;
     r.s1 = -1;
-    if (lane < t.n && t.t1 > t.t0) { r.s0 = split_of(total, nsub, t.t0); r.s1 = split_of(total, nsub, t.t1 - 1); }
+    const bool has_tiles = lane < t.n && t.t1 > t.t0;
+    bool owns;
+    if (total < (1u << 14)) {                        // (nsub <= 64: every product below 2^21) the divisions side by side, their reciprocals shared
+        const float per_total = __builtin_amdgcn_rcpf((float)total), per_nsub = __builtin_amdgcn_rcpf((float)nsub);
+        const unsigned first = div_small(total * lane, nsub, per_nsub), next = div_small(total * (lane + 1), nsub, per_nsub);
+        const unsigned s0 = div_small((t.t0 + 1) * nsub - 1, total, per_total), s1 = div_small(max(t.t1 * (int)nsub, 1) - 1, total, per_total);
+        owns = lane < (int)nsub && first < next;
+        if (has_tiles) { r.s0 = (int)s0; r.s1 = (int)s1; }
+    } else {
+        owns = lane < (int)nsub && split_begin(total, nsub, lane) < split_begin(total, nsub, lane + 1);
+        if (has_tiles) { r.s0 = split_of(total, nsub, t.t0); r.s1 = split_of(total, nsub, t.t1 - 1); }
+    }
+    r.owns_mask = __ballot(owns);
     r.span = wave_max_i32(r.s1 - r.s0);
     return r;
 }
@@ -537,10 +548,11 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     const int ngroups = (nparts + kPartRegs - 1) / kPartRegs;
     const bool grouped = p.slots <= 2 * kWave && a.seg_stride <= kWave && ngroups * p.slots <= kEpiThreads;
     const int part_g = grouped ? (int)div_exact((unsigned)tid, (unsigned)p.slots) : 0, part_k = tid - part_g * p.slots;
+    const int part_first = grouped ? part_g * kPartRegs * p.slots + part_k : tid, part_step = grouped ? p.slots : kEpiThreads;
+    const int part_last = grouped ? (nparts - 1) * p.slots + part_k : n_part_floats - 1;
     T r_part[kPartRegs];
 #pragma unroll
-    for (int i = 0; i < kPartRegs; ++i)
-        r_part[i] = mp_b[grouped ? min(part_g * kPartRegs + i, nparts - 1) * p.slots + part_k : min(tid + i * kEpiThreads, n_part_floats - 1)];
+    for (int i = 0; i < kPartRegs; ++i) r_part[i] = mp_b[min(part_first + i * part_step, part_last)];
     const int n_cand = pr.n_cand[b];
     const int r_q_start = pr.q_start[b], r_n_reuse = pr.n_reuse[b];
     const QueryHead qh = load_query_head(a, b, grouped ? lane : tid);
@@ -562,6 +574,14 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     // below (which only wait for wavefronts that are still running) cost nothing.
     const int nthr = n_cand <= 2 * kWave ? kWave : kEpiThreads;
     const bool small = nthr == kWave && grouped;
+    SelectWaveArgs sw;
+    sw.score = l_score; sw.len = l_len; sw.cand = l_cand; sw.tok = l_tok; sw.start = l_start;
+    sw.keep_idx = pr.keep_idx + off; sw.new_start = pr.new_start + off; sw.order = pr.order + off;
+    sw.n = n_cand; sw.keep = pr.keep; sw.stride = stride; sw.normalise_by_len = pr.normalise_by_len;
+    sw.strategy = pr.strategy; sw.force_n_reuse = pr.force_n_reuse; sw.pos_begin = pr.pos_begin; sw.pos_end = pr.pos_end;
+    sw.prefix_len = pr.prefix_len; sw.doc_stored_start = pr.doc_stored_start; sw.q_stored_start = a.q_stored_start;
+    sw.q_lo = qh.q0; sw.q_hi = qh.q0 + qh.tq_raw; sw.seg_stride = a.seg_stride; sw.q_start = r_q_start; sw.n_reuse = r_n_reuse;
+    RankShare share;
     if (small) {
         // Small query: the first wavefront does the masses, from a table in its registers, the second one looks the document slots over.
         T gs = 0;
@@ -571,14 +591,17 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
         if (tid < ngroups * p.slots) l_part[tid] = gs;
         RegSegTable rtbl;
         SegmentRuns runs;
+        unsigned long long mine = 0;                 // bit i: run s0 + i is the segment's
         if (wave == 0) {
             rtbl = build_reg_table(a, qh, lane, p.tile);
             runs = segment_runs(rtbl, (unsigned)(p.nsplit * p.groups), lane);
+            if (runs.s1 >= runs.s0) mine = (runs.owns_mask >> runs.s0) & (~0ull >> (63 - (runs.s1 - runs.s0)));
         } else if (wave == 1) {
             const bool one = one_entry_per_slot(qh.seg.doc, qh.n_seg < 0 ? 0 : min(qh.n_seg, a.seg_stride), lane, stride);
             if (lane == 0) s_int[6] = one;
         }
         __syncthreads();                             // publishes the rows and the groups' sums
+        if (wave > 0 && n_cand <= kWave) share = rank_prepare(sw, wave - 1, kEpiThreads / kWave - 1);
         if (wave == 0) {
             // the sums of segment_masses_wave in the same order; columns to LDS, a segment's come from there
             T c[2] = {0, 0};
@@ -603,10 +626,9 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = ms.colsum[min(lane + runs.s0 + d0 + i, 2 * kWave - 1)];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int sp = runs.s0 + d0 + i;
-                    if (sp <= runs.s1 && ((runs.owns_mask >> sp) & 1)) m += v[i];
-                }
+                for (int i = 0; i < 4; ++i)
+                    if ((uint32_t)mine >> i & 1) m += v[i];
+                mine >>= 4;
             }
             if (lane < rtbl.n) a.mass[(int64_t)b * a.seg_stride + lane] = (float)m;
             add_doc_scores_wave(qh.seg.doc, lane < rtbl.n ? (float)m : 0.f, rtbl.n, lane, l_score, stride, s_int[6] != 0);      // qh.seg is this lane's entry
@@ -630,16 +652,14 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
         add_doc_scores_block(tbl.doc, ms.seg_mass, tbl.n, l_score, stride);
         __syncthreads();
     }
-    SelectWaveArgs sw;
     Candidate cand;
     if (n_cand <= kWave) {                               // the usual case: everything in registers
-        sw.score = l_score; sw.len = l_len; sw.cand = l_cand; sw.tok = l_tok; sw.start = l_start;
-        sw.keep_idx = pr.keep_idx + off; sw.new_start = pr.new_start + off; sw.order = pr.order + off;
-        sw.n = n_cand; sw.keep = pr.keep; sw.stride = stride; sw.normalise_by_len = pr.normalise_by_len;
-        sw.strategy = pr.strategy; sw.force_n_reuse = pr.force_n_reuse; sw.pos_begin = pr.pos_begin; sw.pos_end = pr.pos_end;
-        sw.prefix_len = pr.prefix_len; sw.doc_stored_start = pr.doc_stored_start; sw.q_stored_start = a.q_stored_start;
-        sw.q_lo = qh.q0; sw.q_hi = qh.q0 + qh.tq_raw; sw.seg_stride = a.seg_stride; sw.q_start = r_q_start; sw.n_reuse = r_n_reuse;
-        cand = rank_wave(sw, wave, kEpiThreads / kWave, s_rank);
+        if (wave > 0) {
+            if (!small) share = rank_prepare(sw, wave - 1, kEpiThreads / kWave - 1);
+            rank_share(sw, share, s_rank);
+        } else {
+            cand = load_candidate(sw);
+        }
         __syncthreads();
     }
     // (by the others, where the first wavefront goes on alone)

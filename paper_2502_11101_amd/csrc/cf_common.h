@@ -22,6 +22,11 @@ __device__ __forceinline__ unsigned div_exact(unsigned a, unsigned b) {
     if (r >= (int)b) ++q;
     return (unsigned)q;
 }
+// a / b for a and b below 2^21, given about 1 / b
+__device__ __forceinline__ unsigned div_small(unsigned a, unsigned b, float per_b) {
+    const int q = (int)((float)a * per_b), r = (int)a - __mul24(q, (int)b);
+    return (unsigned)(q + (r >= (int)b ? 1 : 0) - (r < 0 ? 1 : 0));
+}
 constexpr int kMaxHeadDim = 256;
 constexpr int kMaxHalf = kMaxHeadDim / 2;
 

@@ -208,7 +208,7 @@ __device__ inline void gather_segments_block(const int64_t* doc_tok_offset, cons
 // ---------------------------------------------------------------------------------------------
 // The same three stages for at most 64 candidates, every list in registers (lane i = list position i).  A lane issues one instruction at a time
 // and each of a chain waits for the one before, so what can be is spread over the workgroup: the ranking, which is most of it, over all
-// wavefronts (rank_wave), the rest — permutes, sums and maxima across the lanes — by one (select_wave64), without barriers or
+// wavefronts but one (rank_share), the rest — permutes, sums and maxima across the lanes — by one (select_wave64), without barriers or
 // atomics.  Results are those of the block functions; on any condition they would flag (bad
 // index, non-finite score, bad length, document too long, overflow, table too small) nothing is
 // written and false is returned, so that the caller runs the block functions, which raise the flag.
@@ -221,45 +221,62 @@ struct SelectWaveArgs {
     int q_start, n_reuse;                           // as they stand ("keep" leaves them)
 };
 
-// list position `lane`'s candidate; `bad` (any of the list's): the block functions' business
-struct Candidate { int c, len; bool have, bad; };
-
 __device__ __forceinline__ int lane_int(int v, int from) { return __builtin_amdgcn_readlane(v, from); }
-__device__ __forceinline__ double lane_double(double v, int from) {
-    const uint64_t bits = __builtin_bit_cast(uint64_t, v);
-    return __builtin_bit_cast(double, (uint64_t)(uint32_t)lane_int((int)(uint32_t)(bits >> 32), from) << 32 | (uint32_t)lane_int((int)(uint32_t)bits, from));
-}
 
-// Ranking (Alg. 2: argsort of the accumulated scores): wavefront `wave` of n_waves adds to rank[i] (LDS, cleared) how many of its share of the
-// candidates rank before candidate i.
-// The quotient score/len in fp64 orders exactly as the cross products of ranks_before do —
-// two different cross products (a 24-bit significand times an integer below 2^24 each) make quotients
-// that differ by more than 2^-48 of their size, far above the quotient's rounding, and equal ones give
-// the same quotient — so every lane divides once and the loop compares, without branches.
-__device__ inline Candidate rank_wave(const SelectWaveArgs& s, int wave, int n_waves, int32_t* rank) {
+// list position `lane`'s candidate; `bad` (any of the list's): the block functions' business.  tok and start: of the candidate.
+struct Candidate { int c, len, start; int64_t tok; bool have, bad; };
+__device__ inline Candidate load_candidate(const SelectWaveArgs& s) {
     const int lane = threadIdx.x & 63;
-    const int n = s.n;
     Candidate d;
-    d.have = lane < min(n, s.stride);
+    d.have = lane < min(s.n, s.stride);
     d.c = d.have ? s.cand[lane] : 0;
     const bool c_ok = d.c >= 0 && d.c < s.stride;
-    const int at = d.have && c_ok ? d.c : 0;
+    const int at = c_ok ? d.c : 0;
     const float sc = s.score[at];
     d.len = s.len[at];
+    d.start = s.start[at];
+    d.tok = s.tok[at];
     const int ln = s.normalise_by_len ? d.len : 1;
-    d.bad = __any(d.have && (!c_ok || !isfinite(sc) || ln <= 0 || ln >= (1 << 24))) || n < 0 || n > 64 || n > s.stride;
-    if (d.bad || wave >= n) return d;
-    const double q = (double)sc / (double)ln;
-    int before = 0;
-    for (int j = wave; j < n; j += n_waves) {
-        const double qj = lane_double(q, j);
-        const int cj = lane_int(d.c, j);
-        const int tie = cj != d.c ? cj < d.c : j < lane;     // lower slot, then earlier list position
-        const int eq = qj == q ? tie : 0;
-        before += qj > q ? 1 : eq;
-    }
-    if (d.have) atomicAdd(rank + lane, before);
+    d.bad = __any(d.have && (!c_ok || !isfinite(sc) || ln <= 0 || ln >= (1 << 24))) || s.n < 0 || s.n > 64 || s.n > s.stride;
     return d;
+}
+
+// Ranking (Alg. 2: argsort of the accumulated scores).  A wavefront compares every candidate (lane i = list position i) with its share of
+// them, as ranks_before does, and adds to rank[i] (LDS, cleared) how many of those rank before it.  What does not wait for the scores, before
+// they are there.  (Of lists that load_candidate calls bad the ranks mean nothing.)
+constexpr int kRankShare = 5;                       // at most 64 candidates, at least 13 wavefronts
+struct RankShare { int at, j[kRankShare]; double len, len_j[kRankShare]; bool have, tie[kRankShare]; };
+__device__ inline RankShare rank_prepare(const SelectWaveArgs& s, int wave, int n_waves) {
+    const int lane = threadIdx.x & 63;
+    RankShare r;
+    r.have = lane < min(s.n, s.stride);
+    const int c = r.have ? s.cand[lane] : 0;
+    r.at = c >= 0 && c < s.stride ? c : 0;
+    const int ln = s.normalise_by_len ? s.len[r.at] : 1;
+    r.len = (double)ln;
+#pragma unroll
+    for (int i = 0; i < kRankShare; ++i) {
+        const int j = wave + i * n_waves;
+        r.j[i] = j < min(s.n, 64) ? j : -1;
+        if (r.j[i] < 0) continue;
+        const int cj = lane_int(c, j);
+        r.len_j[i] = (double)lane_int(ln, j);
+        r.tie[i] = cj != c ? cj < c : j < lane;         // lower slot, then earlier list position
+    }
+    return r;
+}
+__device__ inline void rank_share(const SelectWaveArgs& s, const RankShare& r, int32_t* rank) {
+    if (r.j[0] < 0) return;
+    const float score = s.score[r.at];
+    const double sc = (double)score;
+    int before = 0;
+#pragma unroll
+    for (int i = 0; i < kRankShare; ++i) {
+        if (r.j[i] < 0) continue;
+        const double x = (double)__int_as_float(lane_int(__float_as_int(score), r.j[i])) * r.len, y = sc * r.len_j[i];
+        before += x > y || (x == y && r.tie[i]) ? 1 : 0;
+    }
+    if (r.have) atomicAdd(rank + (threadIdx.x & 63), before);
 }
 
 // In-register reductions over the 64 lanes of a wavefront with DPP (row shifts, then the two row broadcasts,
@@ -296,10 +313,10 @@ __device__ inline bool select_wave64(const SelectWaveArgs& s, const Candidate& c
     const bool in = lane < k;
     // ranked list: lane r gets the candidate of rank r (the ranks of the n lanes are 0 .. n - 1; the others keep their places)
     auto move = [](int to, int v) { return __builtin_amdgcn_ds_permute(to << 2, v); };
-    const int64_t tok = s.tok[cd.c];
+    const int64_t tok = cd.tok;
     const int to = cd.have ? rank : lane;
     const int rc = move(to, cd.c);
-    int oc = rc, pl = move(to, cd.len), my_start = move(to, s.start[cd.c]);
+    int oc = rc, pl = move(to, cd.len), my_start = move(to, cd.start);
     int tok_lo = move(to, (int)(uint32_t)tok), tok_hi = move(to, (int)(uint32_t)((uint64_t)tok >> 32));
     // ---- placement order (Sec. 2.5): as ranked ("sort") or by ascending slot ("align"; listing order of "keep")
     if (s.strategy != CF_ALLOC_SORT) {
@@ -324,9 +341,15 @@ __device__ inline bool select_wave64(const SelectWaveArgs& s, const Candidate& c
         // ends at the query
         const int lmax = wave_max_i32(pl);
         const int avail = s.pos_end - s.pos_begin;
-        const int cap = (int)div_exact((unsigned)max(avail, 0), (unsigned)lmax);      // lmax >= 1: every kept length is positive
-        if (cap <= 0) return false;
-        groups = s.force_n_reuse > 0 ? s.force_n_reuse : (cap >= k ? 1 : (int)div_exact((unsigned)(k + cap - 1), (unsigned)cap));
+        if (lmax > avail) return false;                   // (capacity avail / lmax; lmax >= 1: every kept length is positive)
+        groups = s.force_n_reuse;
+        if (groups <= 0) {
+            groups = 1;
+            if ((int64_t)lmax * k > avail) {              // the capacity is less than all
+                const int cap = (int)div_exact((unsigned)avail, (unsigned)lmax);
+                groups = (int)div_exact((unsigned)(k + cap - 1), (unsigned)cap);
+            }
+        }
         groups = min(groups, k);
         int cum = wave_inclusive_scan(pl);                // inclusive prefix over placement ranks
         int span_max = lane_int(cum, 63);                 // (one group: all of it)
