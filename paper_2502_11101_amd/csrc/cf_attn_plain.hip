@@ -736,6 +736,11 @@ Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stri
     const int64_t cap = est_tiles / (2 * p.groups);
     if (ns > cap) ns = cap;
     if (ns * p.groups > kMaxSplit) ns = kMaxSplit / p.groups;
+    // More than eight splits of fewer than four tiles a group: the merge costs more than two workgroups to a CU save, where eight fill the CUs
+    // once.  us with up to sixteen and with eight, tiles in brackets: bf16, 5 documents x 32 heads (2.1) 23.0 and 20.8, 10 (3.5) 27.0 and 26.7,
+    // 16 queries x 2 heads (2.1) 22.3 and 21.0; fp32, 10 documents x 32 heads (3.2) 25.7 and 24.6, 7 (2.8) 30.0 and 28.9; but (5.6) 36.8 and
+    // 39.7, (12.7) 39.3 and 46.5, bf16 (6.8) 26.7 and 28.3.  fp16, whose tiles take longer: (2.3) 27.7 and 28.1, (3.5) 28.4 and 29.6.
+    if (d.dtype != CF_F16 && ns > 8 && p.units >= 32 && est_tiles < 4 * p.groups * ns) ns = 8;
     if (ns < 1 || est_tiles <= 4 * p.groups) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;

@@ -80,3 +80,10 @@ def test_merge_of_splits(dtype, pairing, d, tq, tokens):
                             pb.workspace, pb.ws_bytes, pb.dev_flag)
     torch.cuda.synchronize()
     assert pb.flags() == 0 and torch.isfinite(again).all() and torch.equal(out, again)
+
+
+@pytest.mark.parametrize("dtype,pairing,d,docs", [("bf16", INTER, 128, 5), ("f32", HALF, 64, 4), ("f32", HALF, 64, 14), ("f16", INTER, 128, 5)])
+def test_eight_splits_or_more(dtype, pairing, d, docs):
+    """32 units on both sides of four tiles a group, where all but fp16 keep to eight splits."""
+    cfg = _cfg(f"plain_eight_{dtype}_{docs}", wl.Geometry(32, 32, d, dtype, 1.0e4, 8192), docs, (80, 100), 1, 40, 9)
+    _run_single_layer(cfg, pairing, seed=d + docs, layout="head")
