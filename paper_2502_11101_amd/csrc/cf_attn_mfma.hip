@@ -503,7 +503,8 @@ __device__ __forceinline__ float add_lane_groups(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// CAUSAL: for calls whose own block is most of the list (documents encoded offline), in one split: half of the block's scores are masked.
+// CAUSAL: for calls in one split with several row groups, or whose own block is most of the list (documents encoded offline): half of the
+// block's scores are masked.
 // The stacked rows are numbered t * group + head, so that a 16-row block sees the own block up to its own last token; a row group ends its
 // list there, and a wavefront leaves out the row blocks that see nothing more of it.  Its blocks are every fourth one of the row group (in the
 // order of the rows, the missing ones of a group that is not full ahead of all), so that the blocks left out are its first `r0` and the wavefronts
@@ -1073,9 +1074,11 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
         else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
     } while (0)
-    // CAUSAL: own blocks of half the list and more (a document's encoding over the prefix).  A shorter one masks a few tiles at most, for which
-    // the rows' other order is not worth a second set of kernels' time to load.
-    const bool causal = p.nsplit == 1 && p.groups == 1 && reg_table && 2 * (int64_t)a.max_tq >= a.max_kv_tokens;
+    // CAUSAL: wherever there are several row groups, whose lists then end at different tokens of the own block, and for own blocks of half the
+    // list and more (a document's encoding over the prefix).  28 heads over 4, us without and with it: 40 queries of 130 tokens over 182 | 272 |
+    // 532 others 74.8 and 68.4 | 80.3 and 73.2 | 116.6 and 108.0; 32 of 64 over 1532 95.6 and 91.6, over 3032 156.6 and 156.4; 32 heads, 6 of 400
+    // over 1632 170.7 and 164.3.  In one row group a shorter own block has few tiles to leave out: 12 queries of 128 over 332 41.6 and 42.4.
+    const bool causal = p.nsplit == 1 && p.groups == 1 && reg_table && (p.n_rg > 1 || 2 * (int64_t)a.max_tq >= a.max_kv_tokens);
 #define CF_LAUNCH_WIDE(DT, GROUPS)                                                                                            \
     if (p.nrb == 2) {                                                                                                         \
         if (reg_table) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, GROUPS, true>), grid2, dim3(GROUPS * kThreads));              \

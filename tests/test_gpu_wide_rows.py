@@ -174,7 +174,8 @@ def test_non_finite_values_with_two_groups(batch, nsplit):
 
 # rows 65 (five blocks) to 300 (two row groups) of one head, and of several heads, whose blocks hold tokens of all of them
 OWN = [(1, 4, 70, 65, 0), (1, 4, 70, 128, 32), (1, 2, 140, 160, 57), (1, 2, 140, 192, 100), (1, 3, 90, 193, 1), (1, 2, 140, 300, 32), (7, 2, 70, 40, 40),
-       (6, 3, 60, 33, 16), (2, 2, 140, 97, 33)]
+       (6, 3, 60, 33, 16), (2, 2, 140, 97, 33),
+       (7, 2, 70, 40, 300), (1, 3, 90, 193, 250)]            # several row groups and a shorter own block
 
 
 @pytest.mark.parametrize("own_first", [False, True])
@@ -184,7 +185,7 @@ def test_own_block_of_half_the_list(group, hkv, batch, tq, prefix, own_first):
     leave out nothing where it does not).  Queries of every length, of none and of one row among them."""
     print(f"own block {group} {hkv} {batch} {tq} {prefix} {own_first}", flush=True)
     p = plan_probe.plan(group * hkv, hkv, batch, tq, 1 + (prefix > 0), prefix + tq)
-    assert p.wide == 1 and (p.groups, p.nsplit) == (1, 1) and 2 * tq >= prefix + tq
+    assert p.wide == 1 and (p.groups, p.nsplit) == (1, 1) and (p.n_rg > 1 or 2 * tq >= prefix + tq)
     lengths = [tq, 1, tq - 1, 17, tq // 2, 0, 33 % tq, 64 % tq] + [int(x) for x in np.random.default_rng(tq).integers(1, tq + 1, size=batch - 8)]
     new = 0 if tq % 2 else 500                       # the prefix as it is, or moved
     G.check_tables(group * hkv, hkv, tq, [[(0, prefix, 0, new)] if prefix else []] * batch, max(prefix, 1), "bf16" if tq % 3 else "f16", 0, seed=tq,
