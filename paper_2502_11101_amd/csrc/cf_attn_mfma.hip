@@ -508,7 +508,8 @@ __device__ __forceinline__ float add_lane_groups(float x) {
 // The stacked rows are numbered t * group + head, so that a 16-row block sees the own block up to its own last token; a row group ends its
 // list there, and a wavefront leaves out the row blocks that see nothing more of it.  Its blocks are every fourth one of the row group (in the
 // order of the rows, the missing ones of a group that is not full ahead of all), so that the blocks left out are its first `r0` and the wavefronts
-// have equal shares.  The loop exists once for every r0.
+// have equal shares.  The loop exists once for every r0.  So a value that is not finite stays with its tile and the rows behind it; only rows
+// ahead of it in a block that sees the tile weigh it by zero.
 // Documents encoded and stored, us without and with it (in brackets: row groups in the order of their rows, not the longest lists first): 30 of
 // 160 tokens x 32 heads 76.1 and 73.9, 12 of 300 72.1 and 59.8 (67.1); 28 heads over 4, 30 of 160-250 70.6 and 49.8 (56.1), 100 of 100-200 157
 // and 120 (128); 12 over 2, 200 of 150-300 215 and 147 (156).  At 160 tokens a workgroup's prologue and the 4 * 39 MB it reads and writes are
@@ -935,7 +936,10 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
     }
     if (GROUPS == 2 && grp == 0) __syncthreads();
     read_v(vprev, 4, 8);
-    weigh(std::integral_constant<int, 0>{});
+    // (CAUSAL: the last tile for the blocks that see any of it, not times zero for the others: it may hold an infinity)
+    if (!CAUSAL || r_prev == 0) weigh(std::integral_constant<int, 0>{});
+    else if (r_prev == 1) weigh(std::integral_constant<int, 1>{});
+    else if (r_prev == 2) weigh(std::integral_constant<int, 2>{});
     if (has_rows && cur_seg >= 0) emit(cur_seg);
 
     const StoreArgs ta = store_args(late_args());
