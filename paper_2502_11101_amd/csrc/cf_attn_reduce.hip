@@ -477,6 +477,7 @@ __global__ __launch_bounds__(kWave * (kMaxPending + 1)) void pending_masses_kern
 // table, i.e. Alg. 2's "S += s; ids_sort = argsort(S); ids = prun(ids_sort)" followed by the
 // allocation of Sec. 2.5, without leaving the GPU.
 constexpr int kEpiThreads = 1024;
+constexpr int kPartRegs = 8;                         // slot partials that a thread adds up
 
 
 struct PruneArgs {
@@ -504,7 +505,10 @@ struct PruneArgs {
 // Bound by one wavefront's chain of instructions behind two round trips; what does not belong to the chain is the other wavefronts' (the slot
 // partials' groups, each summed by the thread that read them, the look over the document slots, the ranking, the scores' way back).  One query, ten
 // documents x 32 heads 13300 -> 10800 cycles, 50 documents x 4 heads 17700 -> 13100 (whole layers 20.5 -> 19.7 us and 34.0 -> 32.5).
-template <class T>
+// MORE: a small query with more group sums than threads, which the third wavefront and those after it take a second one of (a loop that the
+// others' queries do not meet cost them 0.1 us).  32 heads, 300 query rows, 50 | 60 documents, 1440 | 1680 sums: with one wavefront adding them up
+// 11.2 | 14.5 us, by the block functions 13.0 | 14.6, this way 6.3 | 6.4 (whole layers 57.9 | 58.4, 58.6 | 57.9 and 51.7 | 49.3).
+template <class T, bool MORE>
 __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a, Plan p, PruneArgs pr) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
     __shared__ SegTable tbl;
@@ -543,10 +547,10 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
     const int32_t r_start = pr.new_start[off + row_i], r_order = pr.order[off + row_i];
     // Slot partials, eight per thread.  Small queries: thread g * slots + k adds up group g of column k in its registers (the groups of
     // segment_masses_block).  Others: one after the other, to LDS.
-    constexpr int kPartRegs = 8;
     const int n_part_floats = nparts * p.slots;
     const int ngroups = (nparts + kPartRegs - 1) / kPartRegs;
-    const bool grouped = p.slots <= 2 * kWave && a.seg_stride <= kWave && ngroups * p.slots <= kEpiThreads;
+    const int n_sums = ngroups * p.slots;
+    const bool grouped = p.slots <= 2 * kWave && a.seg_stride <= kWave;
     const int part_g = grouped ? (int)div_exact((unsigned)tid, (unsigned)p.slots) : 0, part_k = tid - part_g * p.slots;
     const int part_first = grouped ? part_g * kPartRegs * p.slots + part_k : tid, part_step = grouped ? p.slots : kEpiThreads;
     const int part_last = grouped ? (nparts - 1) * p.slots + part_k : n_part_floats - 1;
@@ -588,7 +592,19 @@ __global__ __launch_bounds__(kEpiThreads) void layer_epilogue_kernel(AttnArgs a,
 #pragma unroll
         for (int i = 0; i < kPartRegs; ++i)
             if (part_g * kPartRegs + i < nparts) gs += r_part[i];
-        if (tid < ngroups * p.slots) l_part[tid] = gs;
+        if (tid < n_sums) l_part[tid] = gs;
+        if constexpr (MORE) {
+            for (int x = kEpiThreads + tid - 2 * kWave; wave >= 2 && x < n_sums; x += kEpiThreads - 2 * kWave) {
+                const int g = (int)div_exact((unsigned)x, (unsigned)p.slots), first = g * kPartRegs, k = x - g * p.slots;
+                T v[kPartRegs], sum = 0;
+#pragma unroll
+                for (int i = 0; i < kPartRegs; ++i) v[i] = mp_b[min(first + i, nparts - 1) * p.slots + k];
+#pragma unroll
+                for (int i = 0; i < kPartRegs; ++i)
+                    if (first + i < nparts) sum += v[i];
+                l_part[x] = sum;
+            }
+        }
         RegSegTable rtbl;
         SegmentRuns runs;
         unsigned long long mine = 0;                 // bit i: run s0 + i is the segment's
@@ -746,14 +762,14 @@ static PruneArgs prune_args(const cf_prune_step* prune) {
     return pr;
 }
 
-void launch_epilogue(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
-    hipLaunchKernelGGL(layer_epilogue_kernel<float>, dim3(a.batch), dim3(kEpiThreads), epilogue_lds_bytes(p, prune, sizeof(float)), s, a, p,
-                       prune_args(prune));
+template <class T>
+static void launch_epilogue_of(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
+    const int sums = (p.units_per_b * p.nrb + kPartRegs - 1) / kPartRegs * p.slots;
+    const size_t lds = epilogue_lds_bytes(p, prune, sizeof(T));
+    if (sums > kEpiThreads) hipLaunchKernelGGL((layer_epilogue_kernel<T, true>), dim3(a.batch), dim3(kEpiThreads), lds, s, a, p, prune_args(prune));
+    else hipLaunchKernelGGL((layer_epilogue_kernel<T, false>), dim3(a.batch), dim3(kEpiThreads), lds, s, a, p, prune_args(prune));
 }
-
-void launch_epilogue_f64(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) {
-    hipLaunchKernelGGL(layer_epilogue_kernel<double>, dim3(a.batch), dim3(kEpiThreads), epilogue_lds_bytes(p, prune, sizeof(double)), s, a,
-                       p, prune_args(prune));
-}
+void launch_epilogue(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) { launch_epilogue_of<float>(a, p, prune, s); }
+void launch_epilogue_f64(const AttnArgs& a, const Plan& p, const cf_prune_step* prune, hipStream_t s) { launch_epilogue_of<double>(a, p, prune, s); }
 
 }  // namespace cf

@@ -13,6 +13,7 @@ from paper_2502_11101_amd import pipeline as pl
 from paper_2502_11101_amd import workloads as wl
 from tests import gpu_harness as G
 from tests import helpers as H
+from tests import plan_probe
 
 pytestmark = pytest.mark.gpu
 
@@ -668,6 +669,21 @@ def test_mass_reduction_forms_add_in_the_same_order():
     assert torch.equal(a["out"], b["out"]) and torch.equal(a["mass"], b["mass"]) and torch.equal(a["score"], b["score"])
     assert torch.equal(a["keep"][:, :20], b["keep"][:, :20]) and torch.equal(a["segs"][:, :22], b["segs"][:, :22])
     assert float(a["mass"][0, :52].sum()) == pytest.approx(80 * 3, rel=1e-5)
+
+
+# sums of eight slot partials in the epilogue, one or two to a thread: 1020, 1056, and 1740 close to the limit of its LDS
+@pytest.mark.parametrize("heads,docs,sums", [(120, 62, 1020), (128, 60, 1056), (232, 56, 1740)])
+def test_epilogue_sums_past_one_a_thread(heads, docs, sums):
+    p = plan_probe.plan(heads, heads, 1, 3, docs + 2, 6 + docs * 30 + 3)
+    assert (heads * p.nrb + 7) // 8 * p.slots == sums
+    cfg = wl.scaled(wl.CONFIGS["tiny_f32"], name="epilogue_sums", geometry=wl.Geometry(heads, heads, 128, "bf16", 1.0e4, 8192),
+                    n_store_docs=docs, docs_per_query=docs, batch=1, doc_len_range=(30, 30), tq=3, prefix_len=6, doc_stored_start=6, n_planted=2)
+    st = wl.build_structure(cfg, seed=heads)
+    a, b = _fused_and_separate(cfg, st, wl.build_layer(cfg, st, seed=34), 20, cf.CF_ALLOC_SORT)
+    assert a["flags"] == 0 and b["flags"] == 0
+    assert torch.equal(a["out"], b["out"]) and torch.equal(a["mass"], b["mass"]) and torch.equal(a["score"], b["score"])
+    assert torch.equal(a["keep"][:, :20], b["keep"][:, :20]) and torch.equal(a["segs"][:, :22], b["segs"][:, :22])
+    assert float(a["mass"][0, :docs + 2].sum()) == pytest.approx(heads * 3, rel=1e-5)
 
 
 def test_fused_layer_too_large_for_the_epilogue_kernel():
