@@ -176,7 +176,9 @@ size_t cf_prefill_workspace_bytes(const cf_layer_desc* desc, int32_t batch, int3
 // What a call with a workspace of `given` bytes needs.
 static size_t call_bytes(const cf_layer_desc* desc, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens, size_t given) {
     return mfma_path_supported(desc) ? mfma_call_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens, given)
-                                     : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
+           : plain_path_supported(desc, batch, max_tq, seg_stride, max_kv_tokens)
+               ? plain_call_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens)
+               : cf_prefill_workspace_bytes(desc, batch, max_tq, seg_stride, max_kv_tokens);
 }
 
 static cf_status check_prune_step(const cf_prune_step* pr, int32_t seg_stride, const float* score_accum,

@@ -714,7 +714,8 @@ __global__ __launch_bounds__(kThreads) void plain_combine_kernel(AttnArgs a, Pla
 
 int padded_dim(int d) { return d <= 64 ? 64 : d <= 128 ? 128 : 256; }
 
-Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens) {
+// most: the plan that the bytes reported are those of, which a call's own never takes more than.
+Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens, bool most = false) {
     Plan p = {};
     const int dp = padded_dim(d.head_dim);
     p.group = d.n_q_heads / d.n_kv_heads;
@@ -740,7 +741,9 @@ Plan make_plain_plan(const cf_layer_desc& d, int batch, int max_tq, int seg_stri
     // once.  us with up to sixteen and with eight, tiles in brackets: bf16, 5 documents x 32 heads (2.1) 23.0 and 20.8, 10 (3.5) 27.0 and 26.7,
     // 16 queries x 2 heads (2.1) 22.3 and 21.0; fp32, 10 documents x 32 heads (3.2) 25.7 and 24.6, 7 (2.8) 30.0 and 28.9; but (5.6) 36.8 and
     // 39.7, (12.7) 39.3 and 46.5, bf16 (6.8) 26.7 and 28.3.  fp16, whose tiles take longer: (2.3) 27.7 and 28.1, (3.5) 28.4 and 29.6.
-    if (d.dtype != CF_F16 && ns > 8 && p.units >= 32 && est_tiles < 4 * p.groups * ns) ns = 8;
+    // Not in the bytes reported: smaller batches and longer lists are split further than that, and a workspace serves them as far as it did
+    // without this rule.
+    if (!most && d.dtype != CF_F16 && ns > 8 && p.units >= 32 && est_tiles < 4 * p.groups * ns) ns = 8;
     if (ns < 1 || est_tiles <= 4 * p.groups) ns = 1;
     p.nsplit = (int)ns;
     p.direct_out = p.nsplit == 1;
@@ -803,6 +806,10 @@ bool plain_path_supported(const cf_layer_desc* d, int32_t batch, int32_t max_tq,
 }
 
 size_t plain_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens) {
+    return make_plain_plan(*d, batch, max_tq, seg_stride, max_kv_tokens, true).total;
+}
+
+size_t plain_call_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens) {
     return make_plain_plan(*d, batch, max_tq, seg_stride, max_kv_tokens).total;
 }
 

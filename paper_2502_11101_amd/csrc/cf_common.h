@@ -207,6 +207,7 @@ cf_status launch_attention_generic(const AttnArgs& a, const RopeFreq& f, hipStre
 
 bool plain_path_supported(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens);
 size_t plain_workspace_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens);
+size_t plain_call_bytes(const cf_layer_desc* d, int32_t batch, int32_t max_tq, int32_t seg_stride, int64_t max_kv_tokens);
 cf_status launch_attention_plain(const cf_layer_desc* d, AttnArgs a, const RopeFreq& f, hipStream_t s, const cf_prune_step* prune);
 
 bool mfma_path_supported(const cf_layer_desc* d);

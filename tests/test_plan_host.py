@@ -124,3 +124,20 @@ def test_decode_calls_of_many_rounds_keep_the_tile_kernel():
     for tokens in (300, 600, 2000):
         assert plan_probe.plan(32, 32, 32, 1, 2, tokens).groups == 8
         assert plan_probe.plan(32, 32, 33, 1, 2, tokens).groups == 2
+
+
+# dtype, pairs, query heads, kv heads, head_dim, rows, table entries, tokens; queries of the workspace and of the call
+@pytest.mark.parametrize("case", [("f32", "half", 12, 2, 128, 100, 7, 536, 2, 1), ("bf16", "interleaved", 32, 8, 128, 20, 32, 1500, 2, 1),
+                                  ("f32", "half", 12, 2, 64, 8, 2, 536, 16, 8), ("bf16", "half", 28, 4, 96, 8, 2, 800, 8, 6)])
+def test_a_workspace_for_more_queries_serves_fewer_on_the_fp32_precision_path(case):
+    """Where a call runs in eight splits though more would fill the device, the bytes of those are reported: a smaller batch, which may have them, is
+    served by the workspace of the larger one.  (The calls end at the next check, of the pointer.)"""
+    dtype, pairs, hq, hkv, dim, tq, stride, kv, many, few = case
+    fake = 0x1000                                        # never dereferenced
+    d = cf.make_desc(hq, hkv, dim, dtype, 1.0e4, 8192, cf.CF_ROPE_INTERLEAVED if pairs == "interleaved" else cf.CF_ROPE_HALF)
+    have = cf.cf_prefill_workspace_bytes(d, many, tq, stride, kv)
+    for batch in (few, many):
+        with pytest.raises(cf.CacheFocusError) as e:
+            cf.cf_prefill_attention(d, fake, fake, 0, fake, fake, fake, 9000, fake, fake, fake, fake, stride, batch, tq, kv, fake, None, None, 1,
+                                    0x10010, have, None, stream=0)
+        assert "aligned" in e.value.message, (batch, e.value.message)
