@@ -1075,6 +1075,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
     profile_kernel_pair(&ev_start, &ev_stop);
 #define CF_LAUNCH_TIMED(KERNEL, GRID, BLOCK)                                                          \
     do {                                                                                              \
+        static_assert(std::is_same_v<decltype(&KERNEL), LateArgsKernel>);                             \
         if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
         else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
     } while (0)

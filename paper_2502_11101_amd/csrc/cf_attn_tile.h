@@ -230,7 +230,9 @@ __device__ __forceinline__ void emit_segment(const RowState<NRB>& st, float2* ma
 
 // The arguments of the attention kernels as they lie in memory, read anew: what only a kernel's end needs would otherwise be kept in
 // scalar registers through its loop, or spilled to vector lanes and back (an eight-split layer call 21.8 -> 22.2 us).
+// A kernel that reads them has these parameters in this order (its launch checks that it is a LateArgsKernel).
 struct KernelArgs { AttnArgs a; RopeFreq freq; Plan p; };
+typedef void (*LateArgsKernel)(AttnArgs, RopeFreq, Plan);
 typedef const __attribute__((address_space(4))) KernelArgs* LateArgs;
 __device__ __forceinline__ LateArgs late_args() {
     uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
