@@ -1064,9 +1064,8 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
     const Plan p = make_plan(a.n_q_heads, a.n_kv_heads, a.batch, a.max_tq, a.seg_stride, a.max_kv_tokens, a.workspace_bytes);
     const dim3 grid3((unsigned)p.nsplit, (unsigned)a.n_kv_heads, (unsigned)a.batch);     // attn_tile_kernel's and attn_solo_kernel's
     const dim3 grid2((unsigned)(p.nsplit * a.batch), (unsigned)p.units_per_b);           // attn_wide_kernel's
-    // grid dimensions of this path's kernels (the merge kernel's may carry one more row, for pending score parts)
-    if (a.batch > 65535 || (int64_t)a.n_kv_heads * p.n_rg + 1 > 65535) {
-        set_error("batch must not exceed 65535 and n_kv_heads * row groups 65534 on this path");
+    if (a.batch > 65535 || !wide_grid_ok(a.n_kv_heads, p)) {
+        set_error("neither batch nor n_kv_heads * row groups may exceed 65535 on this path");
         return CF_ERR_UNSUPPORTED;
     }
     const bool reg_table = a.seg_stride <= kWave;    // the attention kernels keep a table this small in registers

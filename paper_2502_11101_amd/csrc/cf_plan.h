@@ -120,7 +120,8 @@ inline Plan wide_plan(Plan p, int batch, int n_kv_heads, int seg_stride, int64_t
     plan_layout(p, seg_stride);
     return p;
 }
-inline bool wide_grid_ok(const Plan& p) { return (int64_t)p.units_per_b + 1 <= 65535; }
+// (kv heads x row groups) is the second dimension of attn_wide_kernel's grid.
+inline bool wide_grid_ok(int n_kv_heads, const Plan& p) { return (int64_t)n_kv_heads * p.n_rg <= 65535; }
 
 inline Plan plan_shape(int n_q_heads, int n_kv_heads, int max_tq) {
     Plan p;
@@ -162,7 +163,7 @@ inline Plan best_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int 
             const double merge = c.nsplit > 1 ? 30. * c.nrb * c.units * c.nsplit / 256 : 0;
             return (4 * c.nrb + 2) * tiles * (c.units > 256 ? rounds : 1. / c.nsplit) + merge;
         };
-        return wide_grid_ok(two) && cost(two) < cost(three) ? two : three;
+        return wide_grid_ok(n_kv_heads, two) && cost(two) < cost(three) ? two : three;
     }
     p = tile_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens);
     // attn_solo_kernel: one row block over at most two table entries (a decode step: the cache and the own block; short documents over
@@ -206,7 +207,7 @@ inline size_t workspace_bytes(int n_q_heads, int n_kv_heads, int batch, int max_
     if (p.wide) {
         const Plan two = wide_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens, 2, 2);
         most = std::max(most, wide_plan(p, batch, n_kv_heads, seg_stride, max_kv_tokens, 3, 2).total);
-        if (wide_grid_ok(two)) most = std::max(most, two.total);
+        if (wide_grid_ok(n_kv_heads, two)) most = std::max(most, two.total);
         Plan f = least;
         plan_rows(f, batch, n_kv_heads, least.n_rg, 3);
         f.nsplit = plan_splits(f.units, plan_tiles(seg_stride, max_kv_tokens), 2);

@@ -8,7 +8,7 @@ import tempfile
 from collections import namedtuple
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-Plan = namedtuple("Plan", "wide nrb groups n_rg nsplit units slots total")
+Plan = namedtuple("Plan", "wide nrb groups n_rg nsplit units slots total grid_ok")
 
 
 @functools.lru_cache(maxsize=None)
@@ -25,6 +25,6 @@ def _probe():
 
 
 def plan(hq, hkv, batch, tq, stride, max_kv, given=2 ** 63):
-    out = (C.c_int64 * 8)()
+    out = (C.c_int64 * 9)()
     _probe()(hq, hkv, batch, tq, stride, max_kv, given, out)
     return Plan(*out)

@@ -42,6 +42,12 @@ def test_row_groups_stay_within_the_grid():
     assert cf.cf_prefill_workspace_bytes(d, 1, 448, 3, 4000) == want
 
 
+def test_the_grid_holds_what_the_header_says():
+    """n_kv_heads x row groups of up to 192 rows <= 65535: one row block of 65535 heads, and 193 rows (two groups) of 32767; not one more of either."""
+    for hkv, tq, fits in ((65535, 4, 1), (65536, 4, 0), (32767, 193, 1), (32768, 193, 0), (21845, 385, 1)):
+        assert plan_probe.plan(hkv, hkv, 1, tq, 3, 4000).grid_ok == fits, (hkv, tq)
+
+
 def test_static_calls_of_one_row_block_stay_accepted():
     """As above for one 16-row block: a plan of two runs of tiles per workgroup that fits the static entry point's buffer; the plan in use
     may have eight (six more slots per split)."""
