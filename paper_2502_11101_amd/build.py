@@ -26,8 +26,8 @@ FLAGS = [
 RESOURCES = os.path.join(HERE, "kernel_resources.json")
 # kernels on the hot path that must keep everything in registers: a spill to scratch memory there
 # (a few lines of source can tip the register allocator over) costs far more than any tuning gains
-NO_SCRATCH = ("attn_tile_kernel", "attn_plain_kernel", "attn_wide_kernel", "attn_solo_kernel", "attn_combine_kernel", "layer_epilogue_kernel", "reposition_kernel",
-              "assemble_kernel")
+NO_SCRATCH = ("attn_tile_kernel", "attn_plain_kernel", "attn_wide_kernel", "attn_solo_kernel", "attn_combine_kernel", "plain_combine_kernel", "layer_epilogue_kernel",
+              "reposition_kernel", "assemble_kernel")
 
 
 def build(verbose: bool = True, jobs: int = 8) -> str:
