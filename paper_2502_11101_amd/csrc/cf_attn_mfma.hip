@@ -1068,7 +1068,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         set_error("neither batch nor n_kv_heads * row groups may exceed 65535 on this path");
         return CF_ERR_UNSUPPORTED;
     }
-    const bool reg_table = a.seg_stride <= kWave;    // the attention kernels keep a table this small in registers
+    const bool reg_table = a.seg_stride <= kRegEntries;      // the attention kernels keep a table this small in registers
     // the attention kernel's launch carries the profiling aid's start/stop events (null when it is off)
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     profile_kernel_pair(&ev_start, &ev_stop);
@@ -1078,11 +1078,6 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (ev_start) hipExtLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, ev_start, ev_stop, 0, a, f, p); \
         else hipLaunchKernelGGL(KERNEL, GRID, BLOCK, 0, s, a, f, p);                                  \
     } while (0)
-    // CAUSAL: wherever there are several row groups, whose lists then end at different tokens of the own block, and for own blocks of half the
-    // list and more (a document's encoding over the prefix).  28 heads over 4, us without and with it: 40 queries of 130 tokens over 182 | 272 |
-    // 532 others 74.8 and 68.4 | 80.3 and 73.2 | 116.6 and 108.0; 32 of 64 over 1532 95.6 and 91.6, over 3032 156.6 and 156.4; 32 heads, 6 of 400
-    // over 1632 170.7 and 164.3.  In one row group a shorter own block has few tiles to leave out: 12 queries of 128 over 332 41.6 and 42.4.
-    const bool causal = p.nsplit == 1 && p.groups == 1 && reg_table && (p.n_rg > 1 || 2 * (int64_t)a.max_tq >= a.max_kv_tokens);
 #define CF_LAUNCH_WIDE(DT, GROUPS)                                                                                            \
     if (p.nrb == 2) {                                                                                                         \
         if (reg_table) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, GROUPS, true>), grid2, dim3(GROUPS * kThreads));              \
@@ -1098,7 +1093,7 @@ cf_status launch_attention_mfma(const AttnArgs& a, const RopeFreq& f, hipStream_
         if (reg_table) CF_LAUNCH_TIMED((attn_tile_kernel<DT, true>), grid3, dim3(2 * kThreads));                            \
         else CF_LAUNCH_TIMED((attn_tile_kernel<DT, false>), grid3, dim3(2 * kThreads));                                     \
     } else {                                                                                                                   \
-        if (causal) {                                                                                                          \
+        if (p.wide == 2) {                                                                                                     \
             if (p.nrb == 2) CF_LAUNCH_TIMED((attn_wide_kernel<DT, 2, 1, true, true>), grid2, dim3(kThreads));                   \
             else CF_LAUNCH_TIMED((attn_wide_kernel<DT, 3, 1, true, true>), grid2, dim3(kThreads));                              \
         } else if (p.groups == 2) { CF_LAUNCH_WIDE(DT, 2) } else { CF_LAUNCH_WIDE(DT, 1) }                                             \

@@ -15,6 +15,7 @@ constexpr int kKRow = 272;      // bytes per token of a staged K tile
 constexpr int kMaxSegs = 256;
 constexpr int kMaxSub = 2 * kMaxSplit;       // runs of tiles of a (query, kv head, row group): splits x groups
 static_assert(kSoloSplits * kSoloWaves <= kMaxSub, "the reductions have room for that many runs");
+static_assert(kRegEntries == kWave, "a lane holds an entry");
 static_assert(kMaxPending == CF_MAX_PENDING, "the plan's ledger");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

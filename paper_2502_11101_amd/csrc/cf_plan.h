@@ -16,12 +16,13 @@ constexpr int kWaves = 4;       // wavefronts of a group
 constexpr int kD = 128;
 constexpr int kTile = 32;       // tokens per tile
 constexpr int kMaxSplit = 32;
+constexpr int kRegEntries = 64; // the longest table that the attention kernels keep in registers
 constexpr int kSoloWaves = 8;   // wavefronts of attn_solo_kernel's workgroups, each with tiles of its own
 
 struct Plan {
     int group;          // query heads per kv head
     int row_blocks;     // 16-row blocks of the stacked rows of one kv head
-    int wide;           // 0: attn_tile_kernel or attn_solo_kernel (few rows), 1: attn_wide_kernel
+    int wide;           // 0: attn_tile_kernel or attn_solo_kernel (few rows), 1: attn_wide_kernel, 2: its CAUSAL variant
     int nrb;            // 64-row passes of a workgroup's rows (what the combine kernel handles at a time)
     int rows_wg;        // rows a workgroup has room for: 64 * nrb
     int n_rg;           // row groups per (query, kv head)
@@ -221,13 +222,28 @@ inline size_t workspace_bytes(int n_q_heads, int n_kv_heads, int batch, int max_
     return std::max(least.total <= CF_STATIC_SCRATCH_BYTES ? std::min(most, CF_STATIC_SCRATCH_BYTES) : most, full);
 }
 
+// attn_wide_kernel's CAUSAL variant: one split and one group of wavefronts, wherever there are several row groups, whose lists then end at
+// different tokens of the own block, and for own blocks of half the list and more (a document's encoding over the prefix).  28 heads over 4, us
+// without and with it: 40 queries of 130 tokens over 182 | 272 | 532 others 74.8 and 68.4 | 80.3 and 73.2 | 116.6 and 108.0; 32 of 64 over 1532
+// 95.6 and 91.6, over 3032 156.6 and 156.4; 32 heads, 6 of 400 over 1632 170.7 and 164.3.  One row group, 30 documents x 32 heads encoded (the own
+// block's share in brackets): of 160 tokens (0.83) 72.9 and 71.2, of 135 (0.58) 72.1 and 68.4, of 128 (0.57) 62.4 and 62.3, of 96 (0.50) 49.6 and
+// 49.1; 50 x 16 heads over 8 of 70 (0.67) 25.8 and 24.7.  Around the line layers, with masses, differ by up to 2 % either way: 24 queries of 192
+// tokens x 16 heads (0.60) 39.3 and 38.8, (0.52) 43.9 and 44.7, (0.46) 44.8 and 45.7, (0.40) 48.3 and 48.9; of 128 (0.67) 25.7 and 25.9, (0.50)
+// 29.6 and 29.9, (0.36) 32.1 and 32.6.  Far below it there are few tiles to leave out.
+inline bool causal_pays(const Plan& p, int max_tq, int seg_stride, int64_t max_kv_tokens) {
+    return p.wide && p.nsplit == 1 && p.groups == 1 && seg_stride <= kRegEntries && (p.n_rg > 1 || 2 * (int64_t)max_tq >= max_kv_tokens);
+}
+
 // `given`: the bytes of the call's workspace.  With as many as workspace_bytes reports the plan follows from the sizes alone; with fewer
 // (sized for another batch, say) a call goes without the runs and row groups that do not fit.
 inline Plan make_plan(int n_q_heads, int n_kv_heads, int batch, int max_tq, int seg_stride, int64_t max_kv_tokens, size_t given) {
-    const Plan p = best_plan(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
-    if (p.total <= std::min(given, CF_STATIC_SCRATCH_BYTES)) return p;
-    const Plan least = least_plan(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
-    return p.total > given || least.total <= CF_STATIC_SCRATCH_BYTES ? least : p;
+    Plan p = best_plan(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
+    if (p.total > std::min(given, CF_STATIC_SCRATCH_BYTES)) {
+        const Plan least = least_plan(n_q_heads, n_kv_heads, batch, max_tq, seg_stride, max_kv_tokens);
+        if (p.total > given || least.total <= CF_STATIC_SCRATCH_BYTES) p = least;
+    }
+    if (causal_pays(p, max_tq, seg_stride, max_kv_tokens)) p.wide = 2;
+    return p;
 }
 
 }  // namespace attn

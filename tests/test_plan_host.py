@@ -103,12 +103,13 @@ def test_a_decode_loop_allocates_once():
 
 def test_the_attention_tests_reach_every_variant():
     """The calls of attn_cases get the plans written beside them; those of many rows take every combination of blocks per wavefront, groups of
-    wavefronts, table form, and one split or several."""
+    wavefronts, table form, and one split or several, and the CAUSAL variant with either number of blocks."""
     for c in attn_cases.WIDE:
         p = plan_probe.plan(c.group * c.hkv, c.hkv, c.batch, c.tq, c.entries, c.tokens)
-        assert (p.wide, p.nrb, p.groups, p.n_rg, p.nsplit) == (1, c.nrb, c.groups, c.n_rg, c.nsplit), c
-    assert {(c.nrb, c.groups, c.entries <= 64, c.nsplit == 1) for c in attn_cases.WIDE} == \
+        assert (p.wide, p.nrb, p.groups, p.n_rg, p.nsplit) == (1 + c.causal, c.nrb, c.groups, c.n_rg, c.nsplit), c
+    assert {(c.nrb, c.groups, c.entries <= 64, c.nsplit == 1) for c in attn_cases.WIDE if not c.causal} == \
         {(n, g, reg, one) for n in (2, 3) for g in (1, 2) for reg in (True, False) for one in (True, False)}
+    assert {c.nrb for c in attn_cases.WIDE if c.causal} == {2, 3}
     for c in attn_cases.SOLO:
         p = plan_probe.plan(c.hq, c.hkv, c.batch, c.tq, 2, c.tokens)
         assert (p.groups, p.nsplit, -(-(c.tokens // 32 + 2) // (8 * p.nsplit))) == (8, c.nsplit, c.tiles), c
