@@ -15,6 +15,7 @@ from paper_2502_11101_amd import binding as cf
 from paper_2502_11101_amd import workloads as wl
 from tests import gpu_harness as G
 from tests import helpers as H
+from tests import plan_probe
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +26,11 @@ def _say(msg):
 
 def _run_stack(cfg, st, layers, keeps, deferred: bool, layout="head"):
     pb = G.make_batch(cfg, st, layout=layout)
+    if cfg.name in ONE_SPLIT:
+        g = cfg.geometry
+        p = plan_probe.plan(g.n_q_heads, g.n_kv_heads, pb.batch, pb.tq, pb.seg_stride, pb.max_kv_tokens, pb.ws_bytes)
+        assert p.nsplit == 1 and (p.wide, p.groups) == ONE_SPLIT[cfg.name], p
+    pb.workspace.fill_(0xFF)                         # whatever an earlier call left: not read
     pb.allocate_initial()
     outs, snap = [], []
     for layer, dev in enumerate(layers):
@@ -50,7 +56,13 @@ CASES = {
     "gqa_batch": (wl.Geometry(12, 2, 128, "f16", 1.0e6, 32768), 6, (40, 90), 24, 3, 6, {2: 4, 4: 2}),
     "long_table": (wl.Geometry(4, 4, 128, "bf16", 1.0e4, 8192), 80, (1, 9), 5, 1, 5, {3: 30}),      # more than 64 entries: block-wide reductions
     "no_prune_at_all": (wl.Geometry(8, 8, 128, "bf16", 1.0e4, 4096), 5, (30, 60), 16, 2, 18, {}),   # 15 layers pending, then a flush, then more
+    # one split: the attention kernel reduces its slots itself, and a launch of its own takes the pending parts in
+    "one_split_tile": (wl.Geometry(32, 32, 128, "bf16", 1.0e4, 8192), 6, (40, 90), 24, 5, 5, {2: 4}),
+    "one_split_two_groups": (wl.Geometry(64, 32, 128, "f16", 1.0e4, 8192), 8, (60, 70), 40, 5, 5, {2: 5}),
+    "one_split_causal": (wl.Geometry(32, 32, 128, "bf16", 1.0e4, 8192), 4, (15, 25), 200, 5, 4, {2: 3}),
+    "one_split_long_table": (wl.Geometry(48, 48, 128, "f16", 1.0e4, 8192), 80, (1, 9), 5, 3, 4, {2: 30}),
 }
+ONE_SPLIT = {"one_split_tile": (0, 2), "one_split_two_groups": (1, 2), "one_split_causal": (2, 1), "one_split_long_table": (0, 2)}   # kernel, groups
 
 
 @pytest.mark.parametrize("case", list(CASES))
