@@ -297,7 +297,10 @@ __device__ __forceinline__ void reduce_slots(LateArgs args, int unit, const floa
 
 // Channel blocks db and db + 1 of a row block, normalised, to the output rows `op` of the lanes' rows: the four lanes of a row exchange halves so
 // that each stores 16 bytes and a row gets 64 in one instruction, past the caches (8-byte stores, 32 a row: 30 documents of 160
-// rows x 32 heads encoded 80.0 us, 16-byte ones 76.1, past the caches 75.5; without any 69.3).  `op`: channel 0 of the lane's row.
+// rows x 32 heads encoded 80.0 us, 16-byte ones 76.1, past the caches 75.5; without any 69.3).  A kernel that reads the rows right behind them
+// fetches them from memory: with one the two kinds of store are even, us through the caches and past them: 8 layer queries x 32 heads and a
+// 4096 x 4096 product of the rows 88.5 and 88.1, an addition to them 58.3 and 58.1; 64 x 12 heads and the addition 122.9 and 123.7; the encoding
+// and the product 206.9 and 207.2, the addition 92.7 and 93.1.  `op`: channel 0 of the lane's row.
 template <int DT>
 __device__ __forceinline__ void store_row_pair(uint16_t* op, int db, f32x4 o, f32x4 u, int lg, bool row_ok) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -124,9 +124,10 @@ __device__ __forceinline__ void rotate(Chunk8<DT>& c0, Chunk8<DT>& c1, const flo
     c1.from_float(b);
 }
 
-// What is moved is not read again soon, so 16-bit types are written past the caches.  30 documents x 160 tokens of 32 heads, bf16:
-// assembly 36.0 -> 31.3 us (5.0 TB/s read and written, the rate of a large copy), re-positioning 13.65 -> 13.4; 2 x 18 documents of 66-121
-// tokens, 32 heads, token-major: 28.7 -> 21.1; interleaved pairs 7.3 -> 6.6 and 11.1 -> 10.0.  Not fp32, whose store instructions leave
+// 16-bit types are written past the caches.  30 documents x 160 tokens of 32 heads, bf16: assembly 36.2 -> 30.0 us (5.2 TB/s read and written, the
+// rate of a large copy); 2 x 18 documents of 66-121 tokens, 32 heads, token-major: 28.7 -> 21.1; interleaved pairs 7.3 -> 6.6 and 11.1 -> 10.0;
+// re-positioning the same within the noise.  What reads the cache next finds it in memory: the assembly of 30 documents and a decode step over
+// them right behind it 55.8 and 56.2 us, of 5 documents 21.1 and 20.5.  Not fp32, whose store instructions leave
 // every other 16 bytes to the next one (re-positioning 84 documents of 53 tokens, 4 heads: 6.8 and 8.4 us).  Loads past the caches:
 // re-positioning 13.4 -> 15.3, assembly the same.
 template <int DT> constexpr bool kStream = DT != CF_F32;
