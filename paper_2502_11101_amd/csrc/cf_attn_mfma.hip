@@ -935,11 +935,11 @@ __global__ __launch_bounds__(kThreads * GROUPS, 2) void attn_wide_kernel(AttnArg
         if constexpr (NRB == 3) steps(std::integral_constant<int, 3>{});
     }
     if (GROUPS == 2 && grp == 0) __syncthreads();
-    read_v(vprev, 4, 8);
     // (CAUSAL: the last tile for the blocks that see any of it, not times zero for the others: it may hold an infinity)
-    if (!CAUSAL || r_prev == 0) weigh(std::integral_constant<int, 0>{});
-    else if (r_prev == 1) weigh(std::integral_constant<int, 1>{});
-    else if (r_prev == 2) weigh(std::integral_constant<int, 2>{});
+    auto close = [&](auto first) __attribute__((always_inline)) { read_v(vprev, 4, 8); weigh(first); };
+    if (!CAUSAL || r_prev == 0) close(std::integral_constant<int, 0>{});
+    else if (r_prev == 1) close(std::integral_constant<int, 1>{});
+    else if (NRB == 3 && r_prev == 2) close(std::integral_constant<int, 2>{});
     if (has_rows && cur_seg >= 0) emit(cur_seg);
 
     const StoreArgs ta = store_args(late_args());
