@@ -40,10 +40,10 @@ REPEATS = 5
 # scaled by what they read for a copy kernel of known size: FETCH_SIZE reads half the bytes of a 1 GiB copy, hence
 # the factor 2 on it, WRITE_SIZE reads them all; both are in KiB).  None: not measured for the kernels as they stand.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    "llama2_7b_stack": int((2 * 23412.6 + 3534.0) * 1024),      # mean of the stack's 32 launches
-    "llama2_7b_layer": int((2 * 15090.7 + 3432.0) * 1024),
-    "qwen2_7b_layer": int((2 * 9365.4 + 9632.0) * 1024),
-    "qwen2_1p5b_batch": int((2 * 103380.8 + 21030.0) * 1024),
+    "llama2_7b_stack": int((2 * 23413.4 + 3534.0) * 1024),      # mean of the stack's 32 launches
+    "llama2_7b_layer": int((2 * 15091.3 + 3432.0) * 1024),
+    "qwen2_7b_layer": int((2 * 9376.7 + 9632.0) * 1024),
+    "qwen2_1p5b_batch": int((2 * 108006.8 + 26278.9) * 1024),
 }
 
 

@@ -19,10 +19,10 @@
 // rows whose sums are not finite at the end are gone over once more token by token (redo_row).
 //
 // Bound by the latency of a launch's memory round trips at the sizes measured: bf16, interleaved pairs, 32 heads, 10 documents of 100-200
-// tokens, 48 query rows: 17.2 us for 26.7 MB of keys, values, queries and outputs, the wavefronts waiting 56 % of their cycles, matrix
-// pipe busy 13 %, VALU issue 33 %; the merge 5.7 us (in eight splits instead of sixteen 18.7 and 4.7).  Whole layer calls with a prune event, from the row-by-row kernel of
-// cf_attn_generic.hip to this one: 916 -> 31.8 us (31.0 before non-finite rows were gone over again); fp32, head_dim 64, 4 heads,
-// 4 x 32 tokens, 8 rows: 54 -> 18.2 us (17.9).  fp16 at the first one's shape takes 5 % more than bf16.
+// tokens, 48 query rows, eight splits: 17.4 us for 26.7 MB of keys, values, queries and outputs, the wavefronts waiting 51 % of their cycles,
+// matrix pipe busy 11 %, VALU issue 21 %; the merge 4.4 us.  Whole layer calls with a prune event, from the row-by-row kernel of
+// cf_attn_generic.hip to this one: 916 -> 26.8 us; fp32, head_dim 64, 4 heads, 4 x 32 tokens, 8 rows: 54 -> 16.2 us.  fp16 at the first one's
+// shape takes 8 % more than bf16.
 #include "cf_attn_plan.h"
 #include "cf_attn_tile.h"
 
